@@ -9,21 +9,25 @@
 //     10000 * sum q  >=  p * (total of q),      i.e.   sum q >= need := ceil(p * total / 10000).
 // Exact in any summation order, which is what a parallel reduction needs.  Ties: lower channel first.
 //
-// Kernels
-//   spark_topp_select_kernel  one wavefront per tile of 64 tokens; per token a radix selection ON SUMS: the float32
-//                             bit pattern of the smallest kept saliency is fixed level by level, each level
-//                             adding the q of the still undecided keys to 64 LDS bins by their next digit; a wave
-//                             prefix sum over the bins (highest digit first) and one ballot give the digit at
-//                             which the running sum reaches `need`.  The first level takes ten bits (exponent
-//                             and two mantissa bits) over a window of sixteen octaves below the row's largest
-//                             key, the others six bits each; the levels end as soon as one key alone starts
-//                             with the bits fixed so far.  Writes the rows' fixed part (mask, mean
-//                             saliency of the pruned channels, count) and the tile's length in the value stream.
-//   spark_topp_scan_kernel    exclusive prefix sum of the tile lengths of every KV head: the directory.
-//   spark_topp_pack_kernel    one wavefront per row: reads the dense key row with one coalesced load; every lane
-//                             finds the slots of its two channels from popcounts of the row's mask and stores its
-//                             kept entries into the value stream at the place the directory and the counts of
-//                             the tile's lower tokens give.
+// Kernels (one block per tile of 64 tokens, four wavefronts of sixteen rows each, FOUR ROWS AT A TIME: sixteen lanes a
+// row, eight channels a lane, so that a reduction over a row is four lane moves that serve four rows, and nothing of
+// a row has to be wave-uniform)
+//   spark_topp_select_kernel  per row a selection ON SUMS: every lane adds the q of its channels to 128 LDS bins of an
+//                             eighth of an octave each, from the row's largest key down; a prefix sum over the bins
+//                             gives the bin in which the running sum reaches `need`, and the keys of that bin are
+//                             then taken one by one, largest first (1.4 of them on average, 2.0 for the slowest of four rows;
+//                             with four bins an octave 1.7 and 2.8).  A bin of which four keys or more are needed
+//                             is first cut into 64 finer ones, up to three times.  Writes the rows' fixed part
+//                             (mask, mean saliency of the pruned channels, count) and the tile's length in the
+//                             value stream.
+//   spark_topp_scan_kernel    prefix sum of the tile lengths of every KV head: the directory.
+//   spark_topp_pack_kernel    reads the dense key rows again; every lane finds the slots of its eight channels from
+//                             the row's mask bytes, the kept entries of sixteen rows are put together in LDS and
+//                             leave as whole words of the value stream.
+// What bounds them (one sequence of 65536 tokens x 8 KV heads, 51 kept channels a row): the selection is bound by
+// vector issue, 100 instructions a row, 71 us (150 us with one row at a time, two channels a lane, radix levels
+// of 64 bins and a wave-wide scan for each); the pack kernel by memory, 31 us for 134 MB read and 54 MB written
+// (47 us with one row at a time and 16-bit stores to memory); the scan is one load and one store's latency, 5 us.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -35,222 +39,260 @@ namespace spark {
 
 namespace {
 
-constexpr int kWaves = 4;     // wavefronts per block, one tile each
+constexpr int kWaves = 4;            // wavefronts per block, one tile a block, sixteen rows a wavefront
+constexpr int kRowsPerWave = SPARK_TILE_TOKENS / kWaves;
+constexpr int kSteps = kRowsPerWave / 4;      // four rows at a time
 
-// Maximum over the 64 lanes, wave-uniform.  Data-parallel-primitive moves: two quad permutes and two row rotates
-// leave each row of 16 lanes holding its row maximum, two row broadcasts fold the four rows into lane 63.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint32_t dpp_max_u32_step(uint32_t x)
-{
-    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROW_MASK, 0xF, false);
-    return x > y ? x : y;
-}
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v)
-{
-    v = dpp_max_u32_step<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
-    v = dpp_max_u32_step<0x4E, 0xF>(v);    // quad_perm [2,3,0,1]
-    v = dpp_max_u32_step<0x124, 0xF>(v);   // row_ror 4
-    v = dpp_max_u32_step<0x128, 0xF>(v);   // row_ror 8
-    v = dpp_max_u32_step<0x142, 0xA>(v);   // row_bcast 15 into rows 1 and 3
-    v = dpp_max_u32_step<0x143, 0xC>(v);   // row_bcast 31 into rows 2 and 3
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
+// First counting level: eight bins an octave over the sixteen octaves below the top of the largest key's.
+constexpr int kBins = 128;
+constexpr int kBinsPerLane = kBins / 16;
+constexpr int kBinStride = 256;      // words per row: keys further down count past the bins that are read
 
-// a saliency (float32 bits, sign clear) in units of 2^(emax - 150), rounded down; emax >= 1
+// a saliency (float32 bits, sign clear) in units of 2^(emax - 150), rounded down; emax >= 1 and not below its exponent
 __device__ __forceinline__ uint32_t quantise(uint32_t bits, int emax)
 {
-    const int e = (int)(bits >> 23);
-    const uint32_t mant = (bits & 0x7FFFFFu) | (e ? 0x800000u : 0u);
-    const int shift = emax - (e ? e : 1);
-    return shift < 24 ? (mant >> shift) : 0u;
+    const int e = max((int)(bits >> 23), 1);
+    const uint32_t mant = bits - ((uint32_t)(e - 1) << 23);      // (the implied bit is in place; below 2^24)
+    return mant >> min(emax - e, 31);
+}
+
+__device__ __forceinline__ uint32_t min8(const uint32_t (&x)[8])
+{
+    return min(min(min(x[0], x[1]), min(x[2], x[3])), min(min(x[4], x[5]), min(x[6], x[7])));
+}
+
+// Where the running sum over the sixteen lanes' bins (NB a lane, in order) reaches `need`: the number of bins in
+// front of that one, and the sum over them.
+template <int NB>
+__device__ __forceinline__ void find_bin(const uint32_t *bins, uint32_t before, uint32_t need, uint32_t &n, uint32_t &above)
+{
+    uint32_t c = before, cnt = 0, below = 0;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        c += bins[j];
+        const bool low = c < need;
+        cnt += low ? 1u : 0u;
+        below = low ? c : below;
+    }
+    n = row16_sum(cnt);
+    above = row16_max(below);
 }
 
 }  // namespace
 
-template <bool FULL>
-__global__ __launch_bounds__(kWaves * 64) void spark_topp_select_kernel(
+__global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
     const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
     uint8_t *__restrict__ packed, SparkLayout L, int p_bp)
 {
-    __shared__ uint32_t hist_all[kWaves][128];      // per wavefront: 64 bins, then one spare word per lane
+    __shared__ __align__(16) uint32_t hist_all[kWaves][4 * kBinStride];
+    __shared__ uint32_t words_of_wave[kWaves];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t wt = (int64_t)blockIdx.x * kWaves + wave;
-    const int64_t full_tiles = L.total_tokens / SPARK_TILE_TOKENS;
-    if (wt >= (FULL ? full_tiles : 1) * L.n_kv_heads) return;    // the whole wavefront leaves; no block barrier is used
-    const int h = FULL ? (int)(wt / full_tiles) : (int)wt;
-    const int64_t tile = FULL ? wt % full_tiles : full_tiles;
+    const int row = lane >> 4, sub = lane & 15;          // this lane: channels 8 sub .. 8 sub + 7 of row 4 s + row
+    const int h = (int)(blockIdx.x / (uint32_t)L.n_tiles);
+    const int64_t tile = blockIdx.x % (uint32_t)L.n_tiles;
     const int64_t n0 = tile * SPARK_TILE_TOKENS;
-    const int nvalid = FULL ? SPARK_TILE_TOKENS : (int)(L.total_tokens - n0);
-    uint32_t *hist = hist_all[wave];
+    const int64_t left = L.total_tokens - n0;
+    const int nvalid = left < SPARK_TILE_TOKENS ? (int)left : SPARK_TILE_TOKENS;
+    const int t0 = wave * kRowsPerWave;
+    uint8_t *tile_out = packed + L.off_tiles + ((int64_t)h * L.n_tiles + tile) * L.tile_bytes;
+    uint32_t my_mu = 0, my_cnt = 0;      // lane 16 row + s (s < kSteps): mean pruned saliency and count of row t0 + 4 s + row
 
-    // sequence of the first token: largest b with cu[b] <= n0 (skips empty sequences)
-    int b;
-    {
-        int lo = 0, hi = L.batch;     // invariant: cu[lo] <= n0 < cu[hi]
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (cu[mid] <= n0) lo = mid; else hi = mid;
+    if (t0 < nvalid) {
+        // all of the wavefront's rows are requested at once; rows past the last token repeat it
+        uint4 x[kSteps];
+        const uint16_t *kbase = k + n0 * k_tok_stride + (int64_t)h * k_head_stride + 8 * sub;
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+            const int t = t0 + 4 * s + row;
+            x[s] = *reinterpret_cast<const uint4 *>(kbase + (int64_t)(t < nvalid ? t : nvalid - 1) * k_tok_stride);
         }
-        b = lo;
-    }
-    int seq_end_t = (int)((int64_t)cu[b + 1] - n0);
-    const float2 *a_all = reinterpret_cast<const float2 *>(packed + L.off_a);
-    // lane l owns channels 2l (low half of its 32-bit load) and 2l+1 (high half)
-    float2 a01 = a_all[((int64_t)b * L.n_kv_heads + h) * (SPARK_D / 2) + lane];
-    const uint16_t *kbase = k + n0 * k_tok_stride + (int64_t)h * k_head_stride + 2 * lane;
-
-    uint32_t e_lo = 0, e_hi = 0, o_lo = 0, o_hi = 0;     // lane t: ballots of the kept even / odd channels of token t
-    uint32_t mu_bits = 0, cnt_reg = 0;                     // lane t: mean pruned saliency, kept count of token t
-
-    uint32_t xnext = *reinterpret_cast<const uint32_t *>(kbase);
-    for (int t = 0; t < nvalid; ++t) {
-        const uint32_t xx = xnext;
-        if (t + 1 < nvalid) xnext = *reinterpret_cast<const uint32_t *>(kbase + (int64_t)(t + 1) * k_tok_stride);
-        if (t >= seq_end_t) {       // the tile crosses into the next non-empty sequence
-            do {
-                ++b;
-                seq_end_t = (int)((int64_t)cu[b + 1] - n0);
-            } while (t >= seq_end_t);
-            a01 = a_all[((int64_t)b * L.n_kv_heads + h) * (SPARK_D / 2) + lane];
+        // sequence of the first row: largest b with cu[b] <= its token (skips empty sequences)
+        int b = 0, seq_end_t;
+        {
+            int hi = L.batch;     // invariant: cu[b] <= n0 + t0 < cu[hi]
+            while (hi - b > 1) {
+                const int mid = (b + hi) >> 1;
+                if (cu[mid] <= n0 + t0) b = mid; else hi = mid;
+            }
+            seq_end_t = (int)((int64_t)cu[b + 1] - n0);
         }
-        // saliency: one float32 multiply, never fused
-        const float w0 = __fmul_rn(a01.x, fabsf(__uint_as_float(xx << 16)));
-        const float w1 = __fmul_rn(a01.y, fabsf(__uint_as_float(xx & 0xFFFF0000u)));
-        const uint32_t k0 = __float_as_uint(w0), k1 = __float_as_uint(w1);
-        // integer saliencies in units of the last place of the row's largest
-        const uint32_t kmax = wave_max_u32(k0 > k1 ? k0 : k1);
-        int emax = (int)(kmax >> 23);
-        emax = emax < 1 ? 1 : emax;
-        const uint32_t q0 = quantise(k0, emax), q1 = quantise(k1, emax);
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(q0 + q1), 63);
-        // need = ceil(total * p / 10000) without a 64-bit division: total = 10000 A + B, B * p < 2^27
-        const uint32_t tA = total / 10000u, tB = total - tA * 10000u;
-        const uint32_t need = tA * (uint32_t)p_bp + (tB * (uint32_t)p_bp + 9999u) / 10000u;
+        const float *a_all = reinterpret_cast<const float *>(packed + L.off_a) + (int64_t)h * SPARK_D + 8 * sub;
+        float a[8];
+        auto load_a = [&]() __attribute__((always_inline)) {
+            const float4 *src = reinterpret_cast<const float4 *>(a_all + (int64_t)b * L.n_kv_heads * SPARK_D);
+            const float4 lo = src[0], hi = src[1];
+            a[0] = lo.x; a[1] = lo.y; a[2] = lo.z; a[3] = lo.w;
+            a[4] = hi.x; a[5] = hi.y; a[6] = hi.z; a[7] = hi.w;
+        };
+        load_a();
+        uint32_t *const hist = hist_all[wave] + row * kBinStride;
 
-        uint64_t kb0, kb1;
-        if (need == 0) {
-            // an all-zero row: one channel is kept, the first
-            kb0 = 1ull;
-            kb1 = 0ull;
-        } else {
-            // radix selection on sums: theta = the largest bit pattern with sum{q : key >= theta} >= need
-            uint32_t theta = 0;      // the bits fixed so far
-            uint32_t above = 0;      // sum of q over the keys above every pattern that starts with theta's fixed bits
-            auto level = [&](const int sh, const int nbits) __attribute__((always_inline)) -> bool {
-                // undecided keys agree with theta above bit sh + nbits; their next digit is (key >> sh) & (2^nbits - 1).
-                // Bins are laid out highest digit first, so lane l reads the bin of digit top - l.
-                const uint32_t top = (theta >> sh) | ((1u << nbits) - 1u);
-                const uint32_t spare = 64u + (uint32_t)lane;
-                const uint32_t i0 = top - (k0 >> sh), i1 = top - (k1 >> sh);      // < 2^nbits exactly for the undecided keys
-                hist[lane] = 0u;
-                prune_lds_sync();
-                atomicAdd(&hist[i0 < (1u << nbits) ? i0 : spare], q0);
-                atomicAdd(&hist[i1 < (1u << nbits) ? i1 : spare], q1);
-                prune_lds_sync();
-                const uint32_t c = wave_inclusive_sum(hist[lane]);                // q of undecided keys with digit >= top - lane
-                prune_lds_sync();
-                const uint64_t reached = __ballot(above + c >= need);            // never empty: the undecided keys reach `need`
-                const int l2 = __builtin_ctzll(reached);
-                if (l2 > 0) above += (uint32_t)__builtin_amdgcn_readlane((int)c, l2 - 1);
-                theta |= (((1u << nbits) - 1u) - (uint32_t)l2) << sh;
-                // If one key alone starts with the bits fixed so far, it is the smallest kept one: the levels
-                // below would only spell out its remaining bits.  (Usual after two or three levels.)
-                const uint64_t in0 = __ballot((k0 >> sh) == (theta >> sh)), in1 = __ballot((k1 >> sh) == (theta >> sh));
-                if (__popcll(in0) + __popcll(in1) != 1) return false;
-                theta = in0 ? (uint32_t)__builtin_amdgcn_readlane((int)k0, __builtin_ctzll(in0))
-                            : (uint32_t)__builtin_amdgcn_readlane((int)k1, __builtin_ctzll(in1 | (1ull << 63)));
-                return true;
-            };
-            // First level: the exponent and two mantissa bits at once (four bins an octave), over the sixteen
-            // octaves below the row's largest key.  All of a row's keys share their top bits, so a level on the
-            // top six bits alone would drop nearly every key into one or two bins (and serialise the adds);
-            // here they spread over some forty.  The window is that long because the cut of a row whose loud
-            // channels hold nearly all of its saliency lies among the quiet ones, seven to ten octaves below
-            // the largest (an outlier) key.  Keys further down go to the spare words; if the kept sum is not
-            // reached inside the window, the row falls back to plain six-bit levels from the top.
-            bool done;
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) {
+            const int t = t0 + 4 * s + row;
+            if (t >= seq_end_t && t < nvalid) {      // (lanes of a row move on together; b stays behind in rows past the end)
+                do {
+                    ++b;
+                    seq_end_t = (int)((int64_t)cu[b + 1] - n0);
+                } while (t >= seq_end_t);
+                load_a();
+            }
+            // saliency: one float32 multiply, never fused
+            uint32_t key[8];
             {
-                constexpr int kSh = 21;
-                const uint32_t dmax = kmax >> kSh;
-                const uint32_t spare = 64u + (uint32_t)lane;
-                const uint32_t i0 = dmax - (k0 >> kSh), i1 = dmax - (k1 >> kSh);
-                hist[lane] = 0u;
-                prune_lds_sync();
-                atomicAdd(&hist[i0 < 64u ? i0 : spare], q0);
-                atomicAdd(&hist[i1 < 64u ? i1 : spare], q1);
-                prune_lds_sync();
-                const uint32_t c = wave_inclusive_sum(hist[lane]);
-                prune_lds_sync();
-                const uint64_t reached = __ballot(c >= need);
-                if (reached != 0ull) {
-                    const int l2 = __builtin_ctzll(reached);
-                    if (l2 > 0) above = (uint32_t)__builtin_amdgcn_readlane((int)c, l2 - 1);
-                    theta = (dmax - (uint32_t)l2) << kSh;
-                    const uint64_t in0 = __ballot((k0 >> kSh) == (theta >> kSh)), in1 = __ballot((k1 >> kSh) == (theta >> kSh));
-                    done = (__popcll(in0) + __popcll(in1) == 1);
-                    if (done)
-                        theta = in0 ? (uint32_t)__builtin_amdgcn_readlane((int)k0, __builtin_ctzll(in0))
-                                    : (uint32_t)__builtin_amdgcn_readlane((int)k1, __builtin_ctzll(in1 | (1ull << 63)));
-                    else
-                        done = level(15, 6) || level(9, 6) || level(3, 6) || level(0, 3);
-                } else {
-                    done = level(25, 6) || level(19, 6) || level(13, 6) || level(7, 6) || level(1, 6) || level(0, 1);
+                const uint32_t xw[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    key[2 * c] = __float_as_uint(__fmul_rn(a[2 * c], fabsf(__uint_as_float(xw[c] << 16))));
+                    key[2 * c + 1] = __float_as_uint(__fmul_rn(a[2 * c + 1], fabsf(__uint_as_float(xw[c] & 0xFFFF0000u))));
                 }
             }
-            (void)done;
-            // `above` is now the sum over the keys > theta; the keys == theta (each worth q_theta) fill the rest,
-            // lowest channels first
-            const bool eq0 = (k0 == theta), eq1 = (k1 == theta);
-            const uint64_t m0 = __ballot(eq0), m1 = __ballot(eq1);
-            const uint32_t q_theta = quantise(theta, emax);
-            int n_tie = 1;
-            uint32_t acc = above + q_theta;
-            const int n_eq = __popcll(m0) + __popcll(m1);
-            while (acc < need && n_tie < n_eq) {
-                acc += q_theta;
-                ++n_tie;
+            const uint32_t kmax = row16_max(max(max(max(key[0], key[1]), max(key[2], key[3])), max(max(key[4], key[5]), max(key[6], key[7]))));
+            const int emax = max((int)(kmax >> 23), 1);
+            // Bins are laid out from the top of the largest key's octave down: bin (top - key) >> 20 holds an eighth of
+            // an octave, and an eighth of its number is the distance of the exponents, which is what a saliency is
+            // shifted by.
+            const uint32_t top = kmax | 0x7FFFFFu;
+            uint32_t q[8], bin[8], total = 0;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) bin[c] = min(top - key[c], 255u << 20) >> 20;
+            if (__builtin_expect(__ballot(kmax < (24u << 23)) == 0ull, 1)) {
+                // (no subnormal saliency is worth a unit here, so the implied bit needs no test)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) q[c] = ((key[c] & 0x7FFFFFu) | 0x800000u) >> (bin[c] >> 3);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) q[c] = quantise(key[c], emax);
             }
-            // tied channels below 2l: both halves of every lower lane; below 2l+1: plus own even
-            const int r0 = mbcnt64(m0) + mbcnt64(m1);
-            const int r1 = r0 + (eq0 ? 1 : 0);
-            kb0 = __ballot((k0 > theta) || (eq0 && r0 < n_tie));
-            kb1 = __ballot((k1 > theta) || (eq1 && r1 < n_tie));
+            uint4 *const my_bins = reinterpret_cast<uint4 *>(hist + kBinsPerLane * sub);
+            my_bins[0] = my_bins[1] = make_uint4(0u, 0u, 0u, 0u);
+            prune_lds_sync();
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                atomicAdd(&hist[bin[c]], q[c]);
+                total += q[c];
+            }
+            prune_lds_sync();
+            const uint4 b0 = my_bins[0], b1 = my_bins[1];
+            prune_lds_sync();
+            total = row16_sum(total);
+            const uint32_t bins[kBinsPerLane] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            const uint32_t mine = ((b0.x + b0.y) + (b0.z + b0.w)) + ((b1.x + b1.y) + (b1.z + b1.w));
+            // need = ceil(total * p / 10000) without a 64-bit division: total = 10000 A + B (A < 2^18, B * p < 2^27)
+            const uint32_t tA = total / 10000u, tB = total - __umul24(tA, 10000u);
+            const uint32_t need = __umul24(tA, (uint32_t)p_bp) + (__umul24(tB, (uint32_t)p_bp) + 9999u) / 10000u;
+            uint32_t n, above;                       // above: sum over the keys >= hi
+            find_bin<kBinsPerLane>(bins, row16_inclusive_sum(mine) - mine, need, n, above);
+            uint32_t hi = top - (n << 20) + 1u;
+            // Where four or more keys of the bin are needed it is cut into 64 finer ones (at most three times).  (A row
+            // whose sum lies below all the bins comes here with every key below them undecided: a cut then takes
+            // off an eighth of an octave at most, and the rest is done key by key.)
+            const uint32_t four_keys = 3u << 24 >> (n >> 3);       // (a key of the bin is worth less than a third of it)
+#pragma nounroll
+            for (int sh = 14; sh > 0; sh -= 6) {
+                if (__builtin_expect(__ballot(need - above >= four_keys) == 0ull, 1)) break;
+                *reinterpret_cast<uint4 *>(hist + 4 * sub) = make_uint4(0u, 0u, 0u, 0u);
+                prune_lds_sync();
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const uint32_t i = (hi - 1u - key[c]) >> sh;      // (keys >= hi wrap round)
+                    if (i < 64u) atomicAdd(&hist[i], q[c]);
+                }
+                prune_lds_sync();
+                const uint4 v = *reinterpret_cast<const uint4 *>(hist + 4 * sub);
+                prune_lds_sync();
+                const uint32_t fine[4] = {v.x, v.y, v.z, v.w};
+                const uint32_t sum4 = v.x + v.y + v.z + v.w;
+                uint32_t n2, more;
+                find_bin<4>(fine, row16_inclusive_sum(sum4) - sum4, need - above, n2, more);
+                hi -= n2 << sh;
+                above += more;
+            }
+            // The keys below hi, largest first, until `need` is reached: theta is the smallest kept one.
+            uint32_t theta, q_theta;
+            int n_eq;                // keys == theta of the four rows (4: no ties)
+            for (int it = 0;; ++it) {
+                uint32_t dist[8], upper = hi - 1u;
+                asm("" : "+v"(upper));               // (a value of its own: one subtraction per key, nothing kept for it)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) dist[c] = upper - key[c];        // (keys >= hi wrap round)
+                theta = upper - row16_min(min8(dist));
+                q_theta = quantise(theta, emax);
+                n_eq = 0;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) n_eq += __popcll(__ballot(key[c] == theta));
+                const bool open = above + q_theta < need;
+                if (__builtin_expect(__ballot(open) == 0ull || it == SPARK_D, 1)) break;    // (a row has 128 keys)
+                uint32_t all = above + q_theta;
+                if (__builtin_expect(n_eq != 4, 0)) {
+                    uint32_t eq = 0;
+#pragma unroll
+                    for (int c = 0; c < 8; ++c) eq += key[c] == theta ? 1u : 0u;
+                    all = above + row16_sum(eq) * q_theta;
+                    if (__ballot(open && all < need) == 0ull) break;
+                }
+                const bool further = open && all < need;
+                above = further ? all : above;
+                hi = further ? theta : hi;
+            }
+            // kept: keys > theta, and of those == theta as many as it takes, lowest channels first
+            uint64_t kb[8];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) kb[c] = __ballot(key[c] >= theta);
+            if (__builtin_expect(n_eq != 4, 0)) {
+                uint32_t eq = 0;
+#pragma unroll
+                for (int c = 0; c < 8; ++c) eq += key[c] == theta ? 1u : 0u;
+                const uint32_t eq_upto = row16_inclusive_sum(eq), eq_row = row16_last(eq_upto);
+                uint32_t n_tie = 1, acc = above + q_theta, rank = eq_upto - eq;
+                while (acc < need && n_tie < eq_row) {
+                    acc += q_theta;
+                    ++n_tie;
+                }
+#pragma unroll
+                for (int c = 0; c < 8; ++c) {
+                    const bool tied = key[c] == theta;
+                    kb[c] = __ballot(key[c] > theta || (tied && rank < n_tie));
+                    rank += tied ? 1u : 0u;
+                }
+            }
+            const uint32_t m = byte_of_masks(kb);
+            const uint32_t cnt = row16_sum((uint32_t)__popc(m));
+            float psum = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) psum += __builtin_amdgcn_inverse_ballot_w64(kb[c]) ? 0.0f : __uint_as_float(key[c]);
+            psum = row16_sum_f32(psum);
+            // mask bytes in channel order (rows past the last token: empty mask)
+            tile_out[t * 16 + sub] = (uint8_t)(t < nvalid ? m : 0u);
+            if (sub == s) {
+                my_mu = __float_as_uint(psum);
+                my_cnt = cnt;
+            }
         }
-        const bool keep0 = (kb0 >> lane) & 1ull, keep1 = (kb1 >> lane) & 1ull;
-        const int cnt = __popcll(kb0) + __popcll(kb1);
-        const float psum = wave_total_f32((keep0 ? 0.0f : w0) + (keep1 ? 0.0f : w1));
-        const float mu = cnt < SPARK_D ? psum / (float)(SPARK_D - cnt) : 0.0f;
-        write_lane1(e_lo, (uint32_t)kb0, t);
-        write_lane1(e_hi, (uint32_t)(kb0 >> 32), t);
-        write_lane1(o_lo, (uint32_t)kb1, t);
-        write_lane1(o_hi, (uint32_t)(kb1 >> 32), t);
-        write_lane1(mu_bits, (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_int(mu)), t);
-        write_lane1(cnt_reg, (uint32_t)cnt, t);
+    } else {
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) tile_out[(t0 + 4 * s + row) * 16 + sub] = 0;
     }
 
-    // ---- fixed part of the rows, lane = token (rows past the last token: empty mask, count 0)
-    const bool valid = lane < nvalid;
-    uint8_t *tile_out = packed + L.off_tiles + ((int64_t)h * L.n_tiles + tile) * L.tile_bytes;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    u32x4 m;
-    // channel-ordered mask: bit 2l of the row = even ballot bit l, bit 2l+1 = odd ballot bit l
-    m.x = valid ? (spread16(e_lo) | (spread16(o_lo) << 1)) : 0u;
-    m.y = valid ? (spread16(e_lo >> 16) | (spread16(o_lo >> 16) << 1)) : 0u;
-    m.z = valid ? (spread16(e_hi) | (spread16(o_hi) << 1)) : 0u;
-    m.w = valid ? (spread16(e_hi >> 16) | (spread16(o_hi >> 16) << 1)) : 0u;
-    *reinterpret_cast<u32x4 *>(tile_out + lane * 16) = m;
-    u32x2 tail;
-    tail.x = valid ? mu_bits : 0u;
-    tail.y = valid ? cnt_reg : 0u;
-    *reinterpret_cast<u32x2 *>(tile_out + 1024 + lane * 8) = tail;
+    // ---- the rest of the rows' fixed part (rows past the last token: mean 0, count 0)
+    const int t = t0 + 4 * sub + row;
+    const bool valid = sub < kSteps && t < nvalid;
+    if (sub < kSteps) {
+        const float mu = my_cnt < SPARK_D ? __uint_as_float(my_mu) / (float)(SPARK_D - my_cnt) : 0.0f;
+        *reinterpret_cast<uint2 *>(tile_out + 1024 + t * 8) = make_uint2(valid ? __float_as_uint(mu) : 0u, valid ? my_cnt : 0u);
+    }
     // words this tile takes in the head's value stream (every row rounded up to a whole word)
-    const uint32_t words = valid ? (cnt_reg + 1u) / 2u : 0u;
-    const uint32_t tile_words = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(words), 63);
-    if (lane == 0)
-        reinterpret_cast<uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile + 1] = tile_words;
-    if (wt == 0 && (FULL || full_tiles == 0) && lane < 16) {
+    const uint32_t words = wave_inclusive_sum(valid ? (my_cnt + 1u) / 2u : 0u);
+    if (lane == 63) words_of_wave[wave] = words;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint32_t sum = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += words_of_wave[w];
+        reinterpret_cast<uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile + 1] = sum;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < 16) {
         // header (the channel weights are written by the window kernel that runs before)
         uint32_t v = 0;
         if (lane == 0) v = SPARK_MAGIC;
@@ -265,79 +307,110 @@ __global__ __launch_bounds__(kWaves * 64) void spark_topp_select_kernel(
 }
 
 // One block per KV head: dir[h][0] = 0, dir[h][t + 1] = words of tiles 0 .. t (they arrive as per-tile counts).
-__global__ __launch_bounds__(256) void spark_topp_scan_kernel(uint8_t *__restrict__ packed, SparkLayout L)
+constexpr int kScanThreads = 1024;
+__global__ __launch_bounds__(kScanThreads) void spark_topp_scan_kernel(uint8_t *__restrict__ packed, SparkLayout L)
 {
-    __shared__ uint32_t part[256];
+    __shared__ uint32_t wave_sum[kScanThreads / 64];
     uint32_t *dir = reinterpret_cast<uint32_t *>(packed + L.off_dir) + (int64_t)blockIdx.x * (L.n_tiles + 1);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t n = L.n_tiles;
-    const int64_t chunk = (n + 255) / 256;
-    const int64_t i0 = (int64_t)threadIdx.x * chunk, i1 = (i0 + chunk < n) ? i0 + chunk : n;
-    uint32_t s = 0;
-    for (int64_t i = i0; i < i1; ++i) s += dir[i + 1];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t run = 0;
-        for (int i = 0; i < 256; ++i) {
-            const uint32_t v = part[i];
-            part[i] = run;
-            run += v;
+    if (threadIdx.x == 0) dir[0] = 0u;
+    uint32_t run = 0;                                    // words of the tiles in front of this round's
+    for (int64_t i0 = 0; i0 < n; i0 += kScanThreads) {
+        const int64_t i = i0 + threadIdx.x;
+        const uint32_t upto = wave_inclusive_sum(i < n ? dir[i + 1] : 0u);
+        if (lane == 63) wave_sum[wave] = upto;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            const uint32_t v = wave_sum[w];
+            before += w < wave ? v : 0u;
+            all += v;
         }
-        dir[0] = 0u;
-    }
-    __syncthreads();
-    uint32_t run = part[threadIdx.x];
-    for (int64_t i = i0; i < i1; ++i) {
-        run += dir[i + 1];
-        dir[i + 1] = run;
+        if (i < n) dir[i + 1] = run + before + upto;
+        run += all;
+        __syncthreads();
     }
 }
 
-// One wavefront per tile.  Lane = token reads the fixed parts (mask, count) and numbers the rows' places in the
-// stream (a wave prefix sum of their lengths); then token by token the wavefront reads the dense key row as
-// spark_topp_select_kernel did (lane l = channels 2l, 2l+1) and every lane stores its kept entries at the slots
-// the mask gives them, so loads and stores both run over contiguous bytes.
+// The kept ones of a lane's eight channels (x: two channels a word; m: their mask byte) go to the 16-bit places in
+// LDS that end at byte address `end`, in order.  The stores run under the channels' wave masks, taken off the byte
+// from its top bit on; all lanes are active before and after.
+__device__ __forceinline__ void stage_kept(uint32_t m, uint32_t end, const uint4 &x)
+{
+    m <<= 24;
+    asm volatile(
+#define SPARK_STAGE(STORE, X)                  \
+    "v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"   \
+    "s_mov_b64 exec, vcc\n\t"                  \
+    "v_add_u32 %[p], -2, %[p]\n\t"             \
+    STORE " %[p], " X "\n\t"                   \
+    "s_mov_b64 exec, -1\n\t"
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x3]")
+        SPARK_STAGE("ds_write_b16", "%[x3]")
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x2]")
+        SPARK_STAGE("ds_write_b16", "%[x2]")
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x1]")
+        SPARK_STAGE("ds_write_b16", "%[x1]")
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x0]")
+        SPARK_STAGE("ds_write_b16", "%[x0]")
+#undef SPARK_STAGE
+        : [m] "+v"(m), [p] "+v"(end)
+        : [x0] "v"(x.x), [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w)
+        : "memory", "vcc");
+}
+
+// One block per tile, sixteen rows a wavefront, sixteen lanes a row as in spark_topp_select_kernel.  The rows of a
+// wavefront take consecutive words of the head's stream: their kept entries are put together in LDS and leave as
+// whole words.
 __global__ __launch_bounds__(kWaves * 64) void spark_topp_pack_kernel(const uint16_t *__restrict__ k, int64_t k_tok_stride,
                                                                       int64_t k_head_stride, uint8_t *__restrict__ packed,
                                                                       SparkLayout L)
 {
+    __shared__ __align__(16) uint32_t stage_all[kWaves][kRowsPerWave * SPARK_D / 2];
     const int lane = threadIdx.x & 63;
-    const int64_t wt = (int64_t)blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wt >= L.n_tiles * L.n_kv_heads) return;
-    const int h = (int)(wt / L.n_tiles);
-    const int64_t tile = wt % L.n_tiles;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane >> 4, sub = lane & 15;
+    const int h = (int)(blockIdx.x / (uint32_t)L.n_tiles);
+    const int64_t tile = blockIdx.x % (uint32_t)L.n_tiles;
     const int64_t n0 = tile * SPARK_TILE_TOKENS;
     const int64_t left = L.total_tokens - n0;
     const int nvalid = left < SPARK_TILE_TOKENS ? (int)left : SPARK_TILE_TOKENS;
+    const int t0 = wave * kRowsPerWave;
+    if (t0 >= nvalid) return;                            // (no block barrier is used)
     const uint8_t *tp = packed + L.off_tiles + ((int64_t)h * L.n_tiles + tile) * L.tile_bytes;
-    const uint4 mk = *reinterpret_cast<const uint4 *>(tp + lane * 16);
-    const uint32_t cnt = *reinterpret_cast<const uint32_t *>(tp + 1024 + lane * 8 + 4);
-    const uint32_t words = (cnt + 1u) / 2u;
-    const uint32_t before = wave_inclusive_sum(words) - words;       // words of the lower tokens of this tile
-    const uint32_t base = reinterpret_cast<const uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile];
-    uint16_t *dst_tile = reinterpret_cast<uint16_t *>(reinterpret_cast<uint32_t *>(packed + L.off_vals) +
-                                                     (int64_t)h * L.vals_head_words + base);
-    const uint16_t *kbase = k + n0 * k_tok_stride + (int64_t)h * k_head_stride + 2 * lane;
-    // this lane's two channels are bits 2l, 2l+1 of the 128-bit mask: bits sh, sh+1 of its lower or upper half
-    const int sh = (2 * lane) & 63;
-    const uint64_t below = (1ull << sh) - 1ull;
-    uint32_t xnext = *reinterpret_cast<const uint32_t *>(kbase);
-    for (int t = 0; t < nvalid; ++t) {
-        const uint32_t xx = xnext;
-        if (t + 1 < nvalid) xnext = *reinterpret_cast<const uint32_t *>(kbase + (int64_t)(t + 1) * k_tok_stride);
-        const uint64_t lo = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mk.y, t) << 32) |
-                            (uint32_t)__builtin_amdgcn_readlane((int)mk.x, t);
-        const uint64_t hi = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)mk.w, t) << 32) |
-                            (uint32_t)__builtin_amdgcn_readlane((int)mk.z, t);
-        const uint32_t cnt_t = (uint32_t)__builtin_amdgcn_readlane((int)cnt, t);
-        uint16_t *dst = dst_tile + 2 * (size_t)(uint32_t)__builtin_amdgcn_readlane((int)before, t);
-        const uint64_t mine = lane < 32 ? lo : hi;
-        const uint32_t slot0 = (lane < 32 ? 0u : (uint32_t)__popcll(lo)) + (uint32_t)__popcll(mine & below);
-        const bool keep0 = (mine >> sh) & 1ull, keep1 = (mine >> (sh + 1)) & 1ull;
-        if (keep0) dst[slot0] = (uint16_t)xx;
-        if (keep1) dst[slot0 + (keep0 ? 1u : 0u)] = (uint16_t)(xx >> 16);
-        if (lane == 0 && (cnt_t & 1u)) dst[cnt_t] = 0;      // the unused half of the row's last word
+    const uint16_t *kbase = k + n0 * k_tok_stride + (int64_t)h * k_head_stride + 8 * sub;
+    uint4 x[kSteps];
+    uint32_t m[kSteps];
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        const int t = t0 + 4 * s + row;
+        x[s] = *reinterpret_cast<const uint4 *>(kbase + (int64_t)(t < nvalid ? t : nvalid - 1) * k_tok_stride);
+        m[s] = tp[t * 16 + sub];                         // (rows past the last token have an empty mask)
     }
+    const uint32_t cnt = *reinterpret_cast<const uint32_t *>(tp + 1024 + lane * 8 + 4);
+    const uint32_t base = reinterpret_cast<const uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile];
+    const uint32_t upto = wave_inclusive_sum((cnt + 1u) / 2u);       // lane = token: words of the tile's rows 0 .. token
+    const uint32_t first = t0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, t0 - 1) : 0u;
+    const uint32_t nwords = (uint32_t)__builtin_amdgcn_readlane((int)upto, t0 + kRowsPerWave - 1) - first;
+    uint32_t *const stage = stage_all[wave];
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    const uint32_t stage_a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)stage;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        const int t = t0 + 4 * s + row;
+        const uint32_t last = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * t, (int)upto) - first - 1u;    // the row's last word
+        const uint32_t kept = (uint32_t)__popc(m[s]);
+        const uint32_t kept_upto = row16_inclusive_sum(kept), kept_row = row16_last(kept_upto);
+        // (its upper half stays 0 where the count is odd; the entries are stored after it)
+        if (sub == 0 && kept_row != 0u) *(lds_u32 *)(uintptr_t)(stage_a + 4u * last) = 0u;
+        prune_lds_sync();
+        stage_kept(m[s], stage_a + 4u * (last + 1u) - 2u * (kept_row + (kept_row & 1u)) + 2u * kept_upto, x[s]);
+    }
+    prune_lds_sync();
+    uint32_t *dst = reinterpret_cast<uint32_t *>(packed + L.off_vals) + (int64_t)h * L.vals_head_words + base + first;
+    for (uint32_t i = lane; i < nwords; i += 64) dst[i] = stage[i];
 }
 
 // canonical export, one thread per (token, KV head) row
@@ -375,23 +448,13 @@ __global__ void spark_topp_unpack_kernel(const uint8_t *__restrict__ packed, Spa
 hipError_t launch_prune_topp(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *cu,
                              uint8_t *packed, const SparkLayout &L, int p_bp, hipStream_t st)
 {
-    const int64_t full_waves = (L.total_tokens / SPARK_TILE_TOKENS) * L.n_kv_heads;
-    const int64_t tail_waves = (L.total_tokens % SPARK_TILE_TOKENS) ? L.n_kv_heads : 0;
-    if (full_waves) {
-        hipLaunchKernelGGL(spark_topp_select_kernel<true>, dim3((unsigned)((full_waves + kWaves - 1) / kWaves)),
-                           dim3(kWaves * 64), 0, st, k, k_tok_stride, k_head_stride, cu, packed, L, p_bp);
-        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    }
-    if (tail_waves) {
-        hipLaunchKernelGGL(spark_topp_select_kernel<false>, dim3((unsigned)((tail_waves + kWaves - 1) / kWaves)),
-                           dim3(kWaves * 64), 0, st, k, k_tok_stride, k_head_stride, cu, packed, L, p_bp);
-        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    }
     if (L.n_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(spark_topp_scan_kernel, dim3(L.n_kv_heads), dim3(256), 0, st, packed, L);
+    hipLaunchKernelGGL(spark_topp_select_kernel, dim3((unsigned)(L.n_tiles * L.n_kv_heads)), dim3(kWaves * 64), 0, st, k,
+                       k_tok_stride, k_head_stride, cu, packed, L, p_bp);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    const int64_t waves = L.n_tiles * L.n_kv_heads;
-    hipLaunchKernelGGL(spark_topp_pack_kernel, dim3((unsigned)((waves + kWaves - 1) / kWaves)), dim3(kWaves * 64), 0, st, k,
+    hipLaunchKernelGGL(spark_topp_scan_kernel, dim3(L.n_kv_heads), dim3(kScanThreads), 0, st, packed, L);
+    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    hipLaunchKernelGGL(spark_topp_pack_kernel, dim3((unsigned)(L.n_tiles * L.n_kv_heads)), dim3(kWaves * 64), 0, st, k,
                        k_tok_stride, k_head_stride, packed, L);
     return hipGetLastError();
 }

@@ -56,6 +56,75 @@ __device__ __forceinline__ float wave_total_f32(float v)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
+// ---- sixteen lanes (a data-parallel-primitive row) per key row, four key rows per wavefront
+
+// x of another lane of the same sixteen: CTRL 0x121..0x12F rotates by 1..15; 0x111..0x11F shifts up by 1..15 (lanes
+// without a source get 0); 0x150 + l hands out lane l
+template <int CTRL>
+__device__ __forceinline__ uint32_t row16_move(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t row16_max(uint32_t x)
+{
+    x = max(x, row16_move<0x128>(x));
+    x = max(x, row16_move<0x124>(x));
+    x = max(x, row16_move<0x122>(x));
+    return max(x, row16_move<0x121>(x));
+}
+__device__ __forceinline__ uint32_t row16_min(uint32_t x)
+{
+    x = min(x, row16_move<0x128>(x));
+    x = min(x, row16_move<0x124>(x));
+    x = min(x, row16_move<0x122>(x));
+    return min(x, row16_move<0x121>(x));
+}
+__device__ __forceinline__ uint32_t row16_sum(uint32_t x)
+{
+    x += row16_move<0x128>(x);
+    x += row16_move<0x124>(x);
+    x += row16_move<0x122>(x);
+    return x + row16_move<0x121>(x);
+}
+__device__ __forceinline__ float row16_sum_f32(float x)
+{
+    x += __uint_as_float(row16_move<0x128>(__float_as_uint(x)));
+    x += __uint_as_float(row16_move<0x124>(__float_as_uint(x)));
+    x += __uint_as_float(row16_move<0x122>(__float_as_uint(x)));
+    return x + __uint_as_float(row16_move<0x121>(__float_as_uint(x)));
+}
+// lane i of sixteen gets x_0 + ... + x_i
+__device__ __forceinline__ uint32_t row16_inclusive_sum(uint32_t x)
+{
+    x += row16_move<0x111>(x);
+    x += row16_move<0x112>(x);
+    x += row16_move<0x114>(x);
+    return x + row16_move<0x118>(x);
+}
+__device__ __forceinline__ uint32_t row16_last(uint32_t x) { return row16_move<0x15F>(x); }      // lane 15 of the sixteen
+
+// The lane's bits of eight wave masks as one byte, bit c from kb[c].
+__device__ __forceinline__ uint32_t byte_of_masks(const uint64_t (&kb)[8])
+{
+    uint32_t m = 0;
+    // (wait states first: a mask that a vector compare has just written must not be read by a vector instruction at
+    //  once; and last: the byte may be read by a lane move next)
+    asm("s_nop 1\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %8\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %7\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %6\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %5\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %4\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+        "s_nop 1"
+        : "+v"(m)
+        : "s"(kb[0]), "s"(kb[1]), "s"(kb[2]), "s"(kb[3]), "s"(kb[4]), "s"(kb[5]), "s"(kb[6]), "s"(kb[7])
+        : "vcc");
+    return m;
+}
+
 // One wave-uniform value into lane `lane_id` of a register.
 __device__ __forceinline__ void write_lane1(uint32_t &a, uint32_t va, int lane_id)
 {
