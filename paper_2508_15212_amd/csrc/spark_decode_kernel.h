@@ -457,6 +457,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     constexpr int NQ_CT = NDW_CT / 4;
 
     __shared__ __align__(16) float qtab[(WARM ? kDecodeWaves : 1) * SPARK_D * GP];   // (balanced mode: one per wavefront)
+    __shared__ __align__(16) float qa[REC ? SPARK_D * G : 1];      // sampled recovery: q_g[j] * scale * log2e / a[j]
     __shared__ float Rsh[16];
     __shared__ __align__(16) uint16_t Pbuf[kDecodeWaves][2][G][64];
     // per wavefront: the accumulators at the end; with packed values, before that, the parked value rows
@@ -901,42 +902,58 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
         if constexpr (REC != 0) {
             // ---- sampled recovery: every pruned entry j adds q_gj * w~_j / a_j
+            // Bound by vector issue: a Gaussian pair of channels is 43 instructions, eight of them at a quarter of the
+            // rate (four 32-bit products of the generator, logarithm, reciprocal root, sine, cosine), and kept
+            // channels' variates are drawn and masked off.  2 x 16001 tokens, Llama heads, T = 26: 58.7 us with the
+            // library's square root, integer conversions, a branch per channel and four table reads a pair; 43.6 us
+            // like this.
             constexpr uint32_t kGold = 0x9E3779B9u;
             auto mix = [](uint32_t x) {
                 x ^= x >> 16; x *= 0x85EBCA6Bu; x ^= x >> 13; x *= 0xC2B2AE35u; x ^= x >> 16;
                 return x;
             };
             const uint32_t base = mix(mix(mix((uint32_t)n_lane) + P.seed_lo) + (uint32_t)h * kGold + P.seed_hi);
-            auto unif = [&](uint32_t c) {   // ((x >> 9) + 0.5) / 2^23: exact in float32
-                return ((float)(mix(base + c * kGold) >> 9) + 0.5f) * (1.0f / 8388608.0f);
+            auto unif = [&](uint32_t c) {
+                // ((x >> 9) + 0.5) / 2^23, exact in float32: the 23 bits become the mantissa of a number in [1, 2)
+                // (one funnel shift puts the exponent in front), and 1 - 2^-24 comes off it.  No conversion, which
+                // runs at a quarter of the rate.
+                return __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, mix(base + c * kGold), 9)) - 0x1.FFFFFEp-1f;
             };
             // (the statistics follow mu, and the scale where the kept entries are int8 codes)
             const float mu_a = INT8 ? __uint_as_float(*reinterpret_cast<const uint32_t *>(tp + spark_tile_word_offset(L, lane, 6)))
                                     : __uint_as_float(r[5]);
             const float sg = __uint_as_float(*reinterpret_cast<const uint32_t *>(tp + spark_tile_word_offset(L, lane, INT8 ? 7 : 6)));
             constexpr float kLn2 = 0.69314718055994530942f;
+            const float neg_mu_ln2 = -mu_a * kLn2;
 #pragma unroll
             for (int wd = 0; wd < 4; ++wd) {
-                uint32_t mw = r[wd];
-#pragma unroll 2
+                uint32_t pruned = ~r[wd];
+#pragma unroll 4
                 for (int pp = 0; pp < 16; ++pp) {
                     const int j = 32 * wd + 2 * pp;
                     const float u1 = unif((uint32_t)j), u2 = unif((uint32_t)j + 1u);
                     float w0, w1;
                     if (REC == 1) {   // Box-Muller pair for channels j, j + 1
-                        const float rr = __builtin_sqrtf(-2.0f * kLn2 * __builtin_amdgcn_logf(u1));
-                        w0 = fmaf(sg, rr * __builtin_amdgcn_cosf(u2), mu_a);    // v_cos / v_sin take revolutions
-                        w1 = fmaf(sg, rr * __builtin_amdgcn_sinf(u2), mu_a);
+                        // root of x = -2 ln u1 (between 2^-23 and 34): reciprocal root and one Newton step, which ends
+                        // within a hair of the correctly rounded root
+                        const float x = -2.0f * kLn2 * __builtin_amdgcn_logf(u1);
+                        const float y = __builtin_amdgcn_rsqf(x), r0 = x * y;
+                        const float rr = fmaf(fmaf(-r0, r0, x), 0.5f * y, r0) * sg;
+                        w0 = fmaf(rr, __builtin_amdgcn_cosf(u2), mu_a);    // v_cos / v_sin take revolutions
+                        w1 = fmaf(rr, __builtin_amdgcn_sinf(u2), mu_a);
                     } else {          // rate 1 / mu
-                        w0 = -mu_a * kLn2 * __builtin_amdgcn_logf(u1);
-                        w1 = -mu_a * kLn2 * __builtin_amdgcn_logf(u2);
+                        w0 = neg_mu_ln2 * __builtin_amdgcn_logf(u1);
+                        w1 = neg_mu_ln2 * __builtin_amdgcn_logf(u2);
                     }
-                    const float *e0 = &qt[j * GP], *e1 = &qt[(j + 1) * GP];
-                    const float t0 = (mw & 1u) ? 0.0f : e0[G] * w0;
-                    const float t1 = (mw & 2u) ? 0.0f : e1[G] * w1;
-                    mw >>= 2;
+                    // (a one-bit field with its sign: all bits for a pruned channel, none for a kept one; written out
+                    //  because the compiler makes a test, a compare and a selection of it)
+                    uint32_t m0, m1;
+                    asm("v_bfe_i32 %0, %1, 0, 1" : "=v"(m0) : "v"(pruned));
+                    asm("v_bfe_i32 %0, %1, 1, 1" : "=v"(m1) : "v"(pruned));
+                    const float t0 = __uint_as_float(__float_as_uint(w0) & m0), t1 = __uint_as_float(__float_as_uint(w1) & m1);
+                    pruned >>= 2;
 #pragma unroll
-                    for (int g = 0; g < G; ++g) s[g] = fmaf(e1[g], t1, fmaf(e0[g], t0, s[g]));
+                    for (int g = 0; g < G; ++g) s[g] = fmaf(qa[(j + 1) * G + g], t1, fmaf(qa[j * G + g], t0, s[g]));
                 }
             }
         }
@@ -1425,7 +1442,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     if (tid < SPARK_D) {
         const int j = tid;
 #pragma unroll
-        for (int g = 0; g < G; ++g) qt[j * GP + g] = bf16lo(q_r[g]) * P.scale_log2;
+        for (int g = 0; g < G; ++g) {
+            qt[j * GP + g] = bf16lo(q_r[g]) * P.scale_log2;
+            if constexpr (REC != 0) qa[j * G + g] = bf16lo(q_r[g]) * P.scale_log2 * inva_r;
+        }
         qt[j * GP + G] = inva_r;
 #pragma unroll
         for (int g = G + 1; g < GP; ++g) qt[j * GP + g] = 0.0f;
