@@ -302,16 +302,46 @@ __device__ __forceinline__ PairInfo warm_pair(const DecodeParams &P, const WarmS
 // unnormalised output) in the spare partial slot; it then takes part in the arrival count like a sequence
 // split, so whichever block comes last folds it in.  qs [G][128] and Psh [4][G][64] are LDS scratch.
 template <int G>
-__device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h, int part, float *qs, float *Psh,
+__device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h, int part, int len, float *qs, float *Psh,
                                              float (*red_m)[G], float (*red_l)[G], float *red_acc /* [4][G][128] */)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    int len = P.tail_len[b];
     len = len < 0 ? 0 : (len > P.tail_cap ? P.tail_cap : len);
-    // this block's share: rows [256 * part, 256 * part + 256)
-    const int first = part * kDecodeWaves * 64;
-    len = (len < first + kDecodeWaves * 64) ? len : first + kDecodeWaves * 64;
+    // this block's share: rows [256 * part, 256 * part + 256), 64 of them by each wavefront
+    const int c0 = part * kDecodeWaves * 64 + wave * 64;
+    const int nval = (len - c0 < 64) ? (len - c0) : 64;
+    const int64_t row0 = (int64_t)b * P.tail_cap;
+    // All of the wavefront's rows are requested at once, keys first (lane = row, past the last one the last), then values
+    // (lane = channels 2l, 2l+1): the block waits for memory about once.  Fetching four pieces of a key row and eight
+    // value rows at a time, a dozen round trips one after the other, made this block the longest of a short batch: four
+    // sequences of 700 to 3900 tokens with up to 256 appended rows took 21.6 us and take 15.6 us, as without appended
+    // rows.
+    // (Sixteen query heads leave no registers for that and keep the small pieces.)
+    constexpr int NK = (G <= 8) ? SPARK_D / 8 : 4, NV = (G <= 8) ? 64 : 8;
+    uint4 kx[NK];
+    uint32_t vw[NV];
+    auto request_keys = [&](int k0) __attribute__((always_inline)) {
+        const uint16_t *krow = P.tail_k + ((row0 + c0 + (lane < nval ? lane : nval - 1)) * P.Hkv + h) * SPARK_D + 8 * k0;
+#pragma unroll
+        for (int c = 0; c < NK; ++c) kx[c] = *reinterpret_cast<const uint4 *>(krow + 8 * c);
+    };
+    auto request_values = [&](int v0) __attribute__((always_inline)) {
+        const uint16_t *vbase = P.tail_v + ((row0 + c0) * P.Hkv + h) * SPARK_D + 2 * lane;
+        const int64_t vstep = (int64_t)P.Hkv * SPARK_D;
+#pragma unroll
+        for (int t0 = 0; t0 < NV; t0 += 8) {
+            if (v0 + t0 < nval) {                  // (wave-uniform)
+#pragma unroll
+                for (int t = t0; t < t0 + 8; ++t)
+                    vw[t] = *reinterpret_cast<const uint32_t *>(vbase + (v0 + t < nval ? v0 + t : nval - 1) * vstep);
+            }
+        }
+    };
+    if (nval > 0) {
+        request_keys(0);
+        if (NV == 64) request_values(0);
+    }
     for (int idx = tid; idx < G * SPARK_D; idx += kDecodeWaves * 64) {
         const int g = idx / SPARK_D, j = idx % SPARK_D;
         qs[g * SPARK_D + j] = bf16lo(P.q[((int64_t)b * P.Hq + h * G + g) * SPARK_D + j]) * P.scale_log2;
@@ -320,60 +350,52 @@ __device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h
     float m[G], l[G], acc[G][2];
 #pragma unroll
     for (int g = 0; g < G; ++g) { m[g] = -INFINITY; l[g] = 0.0f; acc[g][0] = acc[g][1] = 0.0f; }
-    const int64_t row0 = (int64_t)b * P.tail_cap;
     float *pw = Psh + wave * G * 64;
-    for (int c0 = first + wave * 64; c0 < len; c0 += kDecodeWaves * 64) {   // (one pass)
+    if (nval > 0) {
         // scores, lane = token
-        const int t = c0 + lane;
-        const bool valid = t < len;
-        const uint16_t *krow = P.tail_k + ((row0 + (valid ? t : len - 1)) * P.Hkv + h) * SPARK_D;
         float s[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) s[g] = 0.0f;
-#pragma unroll 4
-        for (int c = 0; c < SPARK_D / 8; ++c) {
-            const uint4 x = *reinterpret_cast<const uint4 *>(krow + 8 * c);
-            const float kf[8] = {bf16lo(x.x), bf16hi(x.x), bf16lo(x.y), bf16hi(x.y),
-                                 bf16lo(x.z), bf16hi(x.z), bf16lo(x.w), bf16hi(x.w)};
+#pragma unroll 1
+        for (int k0 = 0; k0 < SPARK_D / 8; k0 += NK) {
+            if (k0 > 0) request_keys(k0);
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
+            for (int c = 0; c < NK; ++c) {
+                const uint4 x = kx[c];
+                const float kf[8] = {bf16lo(x.x), bf16hi(x.x), bf16lo(x.y), bf16hi(x.y),
+                                     bf16lo(x.z), bf16hi(x.z), bf16lo(x.w), bf16hi(x.w)};
 #pragma unroll
-                for (int g = 0; g < G; ++g) s[g] = fmaf(qs[g * SPARK_D + 8 * c + e], kf[e], s[g]);
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int g = 0; g < G; ++g) s[g] = fmaf(qs[g * SPARK_D + 8 * (k0 + c) + e], kf[e], s[g]);
+            }
         }
-        // online softmax (log2 domain); probabilities to LDS
+        // softmax over the wavefront's rows (log2 domain); probabilities to LDS
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const float sg = valid ? s[g] : -INFINITY;
-            const float mnew = fmaxf(m[g], wave_max(sg));          // finite: lane 0 of the chunk is valid
-            const float alpha = fast_exp2(m[g] - mnew);             // m = -inf -> 0
-            const float p = fast_exp2(sg - mnew);
-            m[g] = mnew;
-            l[g] = fmaf(l[g], alpha, p);
-            acc[g][0] *= alpha;
-            acc[g][1] *= alpha;
-            pw[g * 64 + lane] = p;
+            const float sg = lane < nval ? s[g] : -INFINITY;
+            m[g] = wave_max(sg);                                    // finite: lane 0's row is there
+            l[g] = fast_exp2(sg - m[g]);
+            pw[g * 64 + lane] = l[g];
         }
         wave_lds_sync();
-        // weighted sum, lane = channels 2l, 2l+1; eight value rows in flight
-        const int nval = (len - c0 < 64) ? (len - c0) : 64;
-        const uint16_t *vbase = P.tail_v + ((row0 + c0) * P.Hkv + h) * SPARK_D + 2 * lane;
-        const int64_t vstep = (int64_t)P.Hkv * SPARK_D;
-        for (int t0 = 0; t0 < nval; t0 += 8) {
-            uint32_t vw[8];
+        // weighted sum, lane = channels 2l, 2l+1
+#pragma unroll 1
+        for (int v0 = 0; v0 < nval; v0 += NV) {
+            if (NV < 64) request_values(v0);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int tt = (t0 + u < nval) ? (t0 + u) : (nval - 1);
-                vw[u] = *reinterpret_cast<const uint32_t *>(vbase + tt * vstep);
-            }
+            for (int t0 = 0; t0 < NV; t0 += 8) {
+                if (v0 + t0 < nval) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool on = t0 + u < nval;
-                const float v0 = bf16lo(vw[u]), v1 = bf16hi(vw[u]);
+                    for (int t = t0; t < t0 + 8; ++t) {
+                        const float x0 = bf16lo(vw[t]), x1 = bf16hi(vw[t]);
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float p = on ? pw[g * 64 + ((t0 + u) & 63)] : 0.0f;
-                    acc[g][0] = fmaf(p, v0, acc[g][0]);
-                    acc[g][1] = fmaf(p, v1, acc[g][1]);
+                        for (int g = 0; g < G; ++g) {
+                            const float p = pw[g * 64 + v0 + t];    // (0 past the last row)
+                            acc[g][0] = fmaf(p, x0, acc[g][0]);
+                            acc[g][1] = fmaf(p, x1, acc[g][1]);
+                        }
+                    }
                 }
             }
         }
@@ -493,6 +515,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     const int tb = (int)blockIdx.x - nmain;
     const int gid = is_tail ? -1 : (int)(blockIdx.x / P.Hkv);
     const int h = is_tail ? (tb / P.ntail) % P.Hkv : (int)(blockIdx.x % P.Hkv);
+    // (requested before the sequence table is read: one memory round trip less before the appended rows' own)
+    const int tail_rows = is_tail ? P.tail_len[(tb / P.ntail) / P.Hkv] : 0;
     WarmSeqs W;
     PairInfo pi = {0, 0, 0};
     int s0 = 0, s1 = 0;                                  // token range of the sequence being streamed
@@ -587,7 +611,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     const int nmerge = nsplit + P.ntail;                 // partial states the last arrival folds
     if (is_tail) {
         static_assert(sizeof(qtab) >= G * SPARK_D * 4 && sizeof(Pbuf) >= kDecodeWaves * G * 64 * 4, "LDS reuse");
-        tail_partial<G>(P, b, h, tb % P.ntail, qtab, reinterpret_cast<float *>(&Pbuf[0][0][0][0]), red_m, red_l,
+        tail_partial<G>(P, b, h, tb % P.ntail, tail_rows, qtab, reinterpret_cast<float *>(&Pbuf[0][0][0][0]), red_m, red_l,
                         reinterpret_cast<float *>(&wbuf[0][0]));
     } else {
     float m[G], l[G], R[G];

@@ -98,3 +98,11 @@ def test_tail_together_with_pruned_values():
     err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
     print(f"tail + pruned values: max|err|={err.max():.3e} mean|err|={err.mean():.3e}")
     assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+
+
+@pytest.mark.parametrize("G,Hkv", [(1, 1), (4, 1), (8, 1), (16, 1)])
+@pytest.mark.parametrize("rows", [(1, 7, 8, 9), (63, 64, 65, 72), (255, 256, 257, 0)])
+def test_tail_lengths_around_the_pieces_it_is_read_in(rows, G, Hkv):
+    """Groups of eight value rows, a wavefront's 64 rows, a block's 256."""
+    w = wl.small(name=f"tail_rows{G}", n_q_heads=G * Hkv, n_kv_heads=Hkv, keep=26, seqlens=(70, 1, 64, 33), batch=4, seed=460 + G)
+    _tail_case(w, cap=260, tail_len=rows, seed=460 + sum(rows))
