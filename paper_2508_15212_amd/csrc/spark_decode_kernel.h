@@ -436,6 +436,11 @@ constexpr int decode_min_blocks(int, int) { return 2; }
 // displace each other in the L2 / memory-side cache (measured: 129 us -> 118 us on the 32K workload).
 #define NT_LOAD(p) __builtin_nontemporal_load(p)
 
+// Longest packed value row (words) that TVC = -2 takes: 96 kept value channels, or 72 at eight query heads.
+// (4 x 16000 tokens, Llama heads, 50 kept value channels: 70.7 -> 39.7 us.)
+template <int G>
+constexpr int kShortRow = G <= 4 ? 52 : 44;
+
 // Timeline of a launch (a measurement aid, off unless a buffer has been given through spark_decode_timeline):
 // thread 0 of every block files the 100 MHz wall clock at five points - word 0 entry, 1 start of streaming,
 // 2 end of streaming (wavefront 0), 3 partial stored, 4 exit - and, with word 5, its tile count (in the balanced
@@ -446,7 +451,8 @@ __device__ __forceinline__ void stamp(const DecodeParams &P, int word, unsigned 
     if (P.trace != nullptr && threadIdx.x == 0) P.trace[(size_t)blockIdx.x * 8 + word] = value;
 }
 // TVC: 0 = dense values; > 0 = packed values with that many kept channels per row (row held in registers);
-// -1 = packed values, any count (row words read from memory as they are needed).
+// -1 = packed values, any count (row words read from memory as they are needed); -2 = the same for rows of at most
+// kShortRow<G> words.
 // REC: 0 = degenerate recovery (mu / a, folded into the score sum); 1 / 2 = Gaussian / Exponential recovery:
 // a saliency is drawn for every pruned entry from the row's all-channel statistics with a counter-based
 // generator keyed by (seed, token, head, channel), so the run can be repeated and checked.
@@ -469,7 +475,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     // parities (with an even stride the window offsets, which advance by about two words per group, fell on even
     // banks only: 104 instead of 113 us at 26 kept value channels on the 32K shape, no change at 64).  Rows of any
     // length are read from memory in 16-byte pieces and keep a stride that is 4 mod 8; the longest is 68 words.
-    constexpr int RSV = PV ? (TVC > 0 ? (NVW | 1) : 68) : 1;
+    // With that stride a block takes more than half of a compute unit's LDS, which leaves one block there instead of two:
+    // rows of up to kShortRow words have an instantiation (TVC = -2) with a stride that two blocks fit with.
+    constexpr int RSV = PV ? (TVC > 0 ? (NVW | 1) : (TVC == -1 ? 68 : kShortRow<G>)) : 1;
     // floats per table entry: G queries, 1/a, pad -- a multiple of 4 (16-byte gathers) that is 4 mod 8, so
     // that the entries of different channels start in all eight 16-byte bank groups, not in half of them
     constexpr int GP = 8 * ((G + 1 + 3) / 8) + 4;
@@ -706,7 +714,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
     };
 
-    // A wavefront keeps one tile in flight: the loads of tile i+1 are issued when tile i is done.
+    // A wavefront keeps one tile in flight: the loads of tile i+1 are issued when tile i is done (with packed values, when
+    // both its rows have left their registers).
     // (Requesting further ahead was measured slower: more outstanding requests per wavefront cost
     // more in DRAM efficiency than the extra overlap gained.)
     uint32_t rn[NR];
@@ -722,7 +731,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
     };
     // One tile of sequence [s0, s1) whose rows have been requested by prefetch(): scores, online softmax, P V.
-    auto process = [&](int tile) {
+    auto process = [&](int tile, int tnext) {
         const uint8_t *tp = tiles + (int64_t)tile * L.tile_bytes;
         const int n_lane = tile * SPARK_TILE_TOKENS + lane;
         const bool valid = (n_lane >= s0) && (n_lane < s1);
@@ -1060,6 +1069,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
                 *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8]) = m0;
                 *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8 + 4]) = m1;
             }
+            // both rows' registers are free now: the next tile is in flight through the products (12001 to 18777
+            // tokens, 64 kept value channels: 36.4 -> 35.0 us)
+            if (tnext >= 0) prefetch(tnext);
             wave_lds_sync();
         }
         {
@@ -1320,7 +1332,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
                 WarmSeq nxt = cur;
                 if (newseq) nxt = warm_find(W, item);
                 const int tnext = newseq ? nxt.s0 / SPARK_TILE_TOKENS : tile + 1;
-                process(tile);
+                process(tile, -1);
                 if (!more) break;
                 s0 = nxt.s0;
                 s1 = nxt.s1;
@@ -1491,8 +1503,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         tile = tile_of(kidx);
         const bool more = kidx + kDecodeWaves < nts;            // wave-uniform
         const int tnext = tile_of(more ? kidx + kDecodeWaves : kidx);
-        process(tile);
-        if (more) prefetch(tnext);   // request the next tile; its latency is covered by the other resident wavefronts
+        process(tile, more ? tnext : -1);
+        if (more && !PV) prefetch(tnext);   // request the next tile; its latency is covered by the other resident wavefronts
     }
 
     if (P.trace != nullptr) stamp(P, 2, wall_clock64());
@@ -1593,8 +1605,13 @@ static hipError_t launch_pv(const DecodeParams &P, int nblocks, hipStream_t st)
         case 64: return launch_one<G, TCT, INT8, 64>(P, nblocks, st);
         case 38: return launch_one<G, TCT, INT8, 38>(P, nblocks, st);
         case 26: return launch_one<G, TCT, INT8, 26>(P, nblocks, st);
-        default: return launch_one<G, TCT, INT8, -1>(P, nblocks, st);
+        default: break;
     }
+    // (the stride of a parked row is its length rounded up to 4 mod 8)
+    if constexpr (G <= 8) {          // (sixteen query heads: the rest of the block's LDS is too much for two already)
+        if (8 * ((P.Lv.ndw + 3) / 8) + 4 <= kShortRow<G>) return launch_one<G, TCT, INT8, -2>(P, nblocks, st);
+    }
+    return launch_one<G, TCT, INT8, -1>(P, nblocks, st);
 }
 
 // One instantiation per query-group size G; each lives in its own translation unit (spark_decode_g*.hip) so

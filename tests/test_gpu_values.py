@@ -130,3 +130,11 @@ def test_int8_keys_with_pruned_values(T, Tv):
     if T == 26 and Tv == 64:
         _decode_kv_case(wl.small(name="kv_int8_g8", n_q_heads=16, n_kv_heads=2, keep=26, seqlens=(257, 64), seed=399), 64,
                         int8=True)
+
+
+@pytest.mark.parametrize("G,Hkv", [(1, 2), (4, 2), (8, 1), (16, 1)])
+@pytest.mark.parametrize("Tv", [25, 71, 72, 73, 74, 95, 96, 97, 98])
+def test_decode_over_value_rows_around_the_short_row_limit(Tv, G, Hkv):
+    """Rows of any length are parked in LDS at one of two strides; several tiles a wavefront, a ragged tail."""
+    w = wl.small(name=f"values_rows{Tv}", n_q_heads=G * Hkv, n_kv_heads=Hkv, keep=26, batch=2, seqlens=(1100, 77), seed=260 + Tv)
+    _decode_kv_case(w, Tv, n_splits=1)
