@@ -137,6 +137,17 @@ __device__ __forceinline__ float wave_sum(float x)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
+// x0 .. x3 hold one term per 16-lane row for each of four sums; row t of the wavefront gets the whole of sum t
+// (lane-swap instructions across the halves, then across neighbouring rows, which do the selecting for free).
+__device__ __forceinline__ float reduce_scatter_rows(float x0, float x1, float x2, float x3)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x0), __float_as_uint(x2), false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x1), __float_as_uint(x3), false, false);
+    const float even = __uint_as_float(a[0]) + __uint_as_float(a[1]), odd = __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    const auto c = __builtin_amdgcn_permlane16_swap(__float_as_uint(even), __float_as_uint(odd), false, false);
+    return __uint_as_float(c[0]) + __uint_as_float(c[1]);
+}
+
 // device-scope (all XCDs) relaxed store / load of one float
 __device__ __forceinline__ void st_agent(float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ uint32_t u4c(const uint4 &v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
@@ -469,6 +480,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     static_assert(!VAR || (TCT == 0 && INT8 == 0 && TVC == 0 && REC == 0), "variable-length rows: any-length bf16 path only");
     static_assert(!WARM || (TVC == 0 && REC == 0 && VAR == 0 && G <= 8), "balanced mode: dense values, degenerate recovery");
     constexpr bool PV = (TVC != 0);             // packed value cache
+    constexpr bool MM = VAR && G <= 4;          // scores of rows of varying length on the matrix cores
     constexpr int NVW = PV ? (TVC > 0 ? (((4 + (TVC + 1) / 2) + 1) & ~1) : 4) : 1;   // value-row words in registers
     // LDS row stride (words) of a parked value row.  A row kept whole in registers (NVW words) is parked word by
     // word at an ODD stride: the four tokens whose windows a wavefront reads together then start in banks of both
@@ -492,15 +504,18 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     __shared__ __align__(16) uint16_t Pbuf[kDecodeWaves][2][G][64];
     // per wavefront: the accumulators at the end; with packed values, before that, the parked value rows
     // (+ slack: the candidate window may read 4 words past a row)
-    constexpr int RED_BYTES = G * SPARK_D * 4, RAW_BYTES = (SPARK_TILE_TOKENS * RSV + 8) * 4;
-    constexpr int WBUF = (PV && RAW_BYTES > RED_BYTES) ? RAW_BYTES : RED_BYTES;
+    constexpr int RED_BYTES = G * SPARK_D * 4, RAW_BYTES = MM ? (SPARK_TILE_TOKENS / 2 * SPARK_D / 2 + 8) * 4 : (SPARK_TILE_TOKENS * RSV + 8) * 4;
+    constexpr int WBUF = ((PV || MM) && RAW_BYTES > RED_BYTES) ? RAW_BYTES : RED_BYTES;
     __shared__ __align__(16) uint8_t wbuf[kDecodeWaves][WBUF];
     // packed values: per token 16 x {kept entries before the group, the group's mask byte}; the selector
     // table in two arrays (four words and two words per entry, each read with one aligned access: either array's
     // entries then tile all 32 banks; one array of 12-word entries left half the banks idle on the short read)
-    __shared__ __align__(16) uint32_t vmeta[PV ? kDecodeWaves : 1][PV ? SPARK_TILE_TOKENS * 8 : 1];
-    __shared__ __align__(16) uint32_t vlut[PV ? 256 * 4 : 1];
-    __shared__ __align__(16) uint32_t vlutb[PV ? 256 * 2 : 1];
+    __shared__ __align__(16) uint32_t vmeta[(PV || MM) ? kDecodeWaves : 1][(PV || MM) ? SPARK_TILE_TOKENS * 8 : 1];
+    __shared__ __align__(16) uint32_t vlut[(PV || MM) ? 256 * 4 : 1];
+    __shared__ __align__(16) uint32_t vlutb[(PV || MM) ? 256 * 2 : 1];
+    // rows of varying length: first word of every row of the half tile in LDS; the query as it came
+    __shared__ uint32_t row_at[MM ? kDecodeWaves : 1][MM ? SPARK_TILE_TOKENS : 1];
+    __shared__ __align__(16) uint16_t qraw[MM ? G : 1][MM ? SPARK_D : 8];
     __shared__ float red_m[kDecodeWaves][G], red_l[kDecodeWaves][G];
     __shared__ int last_flag;
 
@@ -730,6 +745,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
             load_v(tile, 1, vr[1]);
         }
     };
+    bf16x8 Aq[MM ? 4 : 1], Aqa[MM ? 4 : 1];     // A operands of the scores, one per 32 channels (see the score phase)
     // One tile of sequence [s0, s1) whose rows have been requested by prefetch(): scores, online softmax, P V.
     auto process = [&](int tile, int tnext) {
         const uint8_t *tp = tiles + (int64_t)tile * L.tile_bytes;
@@ -793,6 +809,115 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
 #pragma unroll
                             for (int g = 0; g < G; ++g) s[g] = fmaf(ev[u][g], d, s[g]);
                         }
+                }
+            } else if constexpr (MM) {
+                // Rows of varying length, scores on the matrix cores.  Entry by entry (mask walk, table gather, multiply-
+                // adds) a wavefront's tile costs 24 instructions for every entry of its LONGEST row; here the rows are
+                // spread to dense bf16 pieces of eight channels, as packed values are, at a cost that does not depend on
+                // what they keep, and two matrix products take the sums:
+                //     q . k over the kept entries       B = the pieces, A = the query (bf16, as it came: exact products)
+                //     sum of q_j / a_j over them        B = the pieces with 1.0 for every kept entry, A = q_j / a_j as
+                //                                       three bf16 parts, which together are its float32 value
+                // B operands: lane (tg, cn) = channels 8 tg .. 8 tg + 7 of a block of 32 of token 16 tau + cn.  A operands:
+                // row 4 p + g = query head g; the first product has it in every p, so that lane row tg finds the
+                // scores of its own sixteen tokens in the result of tau = tg; the second has part p there, and the
+                // parts are added up across the lane rows.
+                // Up to four query heads (three parts of more do not fit sixteen rows).  2 x 32768 tokens, 51 kept entries a
+                // row: 53.2 -> 46.2 us, 64 x 1000 tokens: 53.2 -> 44.6 us, error against 64 bits 6.4e-7 -> 3.3e-7 (80 seeds).
+                // Bound by LDS (windows, selector table) and the memory round trips at a tile's start; requesting the
+                // next tile's entries with its values took 47 us (the registers spill).
+                const uint32_t cnt = r[5] < (uint32_t)SPARK_D ? r[5] : (uint32_t)SPARK_D;     // (bounds it whatever the cache holds)
+                const uint32_t words = (cnt + 1u) >> 1;
+                const uint32_t upto = (uint32_t)wave_inclusive_sum_i32((int)words);
+                const uint32_t half = (uint32_t)__builtin_amdgcn_readlane((int)upto, 31), all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+                const uint32_t *vsrc = reinterpret_cast<const uint32_t *>(P.packed + L.off_vals) + (int64_t)h * L.vals_head_words +
+                                       reinterpret_cast<const uint32_t *>(P.packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile];
+                typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+                // the words of half a tile, 16 bytes a lane; loads that straddle the end read at most three words of
+                // what follows or of the stream's padding
+                constexpr int NLV = 4;
+                auto half_words = [&](uint32_t w0, uint32_t w1, u32x4u (&wv)[NLV]) {
+#pragma unroll
+                    for (int u = 0; u < NLV; ++u) {
+                        const uint32_t w = w0 + 4u * (uint32_t)lane + 256u * u;
+                        wv[u] = w < w1 ? *reinterpret_cast<const u32x4u *>(vsrc + w) : u32x4u{0u, 0u, 0u, 0u};
+                    }
+                };
+                uint32_t *raw = reinterpret_cast<uint32_t *>(wbuf[wave]);
+                u32x4u h0[NLV], h1[NLV];
+                half_words(0u, half, h0);
+                half_words(half, all, h1);
+                {
+                    // per token 16 halfwords: kept entries in lower groups << 8 | mask byte of the group; group 4 kb + tg
+                    // at 4 tg + kb, so that a lane fetches the four it works on at once
+                    uint32_t meta[8], before = 0;
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) {
+                        const uint32_t byte = (r[c >> 2] >> (8 * (c & 3))) & 0xFFu;
+                        const uint32_t hw = (before << 8) | byte;
+                        const int at = 4 * (c & 3) + (c >> 2);
+                        if ((c >> 2) & 1) meta[at >> 1] |= hw << 16; else meta[at >> 1] = hw;
+                        before += __popc(byte);
+                    }
+                    const u32x4 m0 = {meta[0], meta[1], meta[2], meta[3]}, m1 = {meta[4], meta[5], meta[6], meta[7]};
+                    *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8]) = m0;
+                    *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8 + 4]) = m1;
+                    row_at[wave][lane] = upto - words - (lane < 32 ? 0u : half);
+                }
+                f32x4 qk[4], qm[4];
+#pragma unroll
+                for (int tau = 0; tau < 4; ++tau) qk[tau] = qm[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int hs = 0; hs < 2; ++hs) {
+                    const uint32_t w0 = hs ? half : 0u, w1 = hs ? all : half;
+#pragma unroll
+                    for (int u = 0; u < NLV; ++u) *reinterpret_cast<u32x4 *>(&raw[4 * lane + 256 * u]) = hs ? u32x4(h1[u]) : u32x4(h0[u]);
+                    if (w1 - w0 > 256u * NLV) {        // (wave-uniform: more than 64 kept entries a row on average)
+                        u32x4u more[NLV];
+                        half_words(w0 + 256u * NLV, w1, more);
+#pragma unroll
+                        for (int u = 0; u < NLV; ++u) *reinterpret_cast<u32x4 *>(&raw[256 * NLV + 4 * lane + 256 * u]) = u32x4(more[u]);
+                    }
+                    wave_lds_sync();
+#pragma unroll
+                    for (int t2 = 0; t2 < 2; ++t2) {
+                        const int tau = 2 * hs + t2, t = 16 * tau + cn;
+                        const uint32_t at = row_at[wave][t];
+                        const uint2 mt = *reinterpret_cast<const uint2 *>(&vmeta[wave][t * 8 + 2 * tg]);
+#pragma unroll
+                        for (int kb = 0; kb < 4; ++kb) {
+                            const uint32_t hw = ((kb & 2) ? mt.y : mt.x) >> (16 * (kb & 1));
+                            const uint32_t byte = hw & 0xFFu, before = (hw >> 8) & 0xFFu;
+                            const uint32_t *win = &raw[at + (before >> 1)];                // 8 candidates start here ...
+                            const uint32_t sh = (before & 1u) << 4;                         // ... or one halfword further
+                            const uint32_t d0 = win[0], d1 = win[1], d2 = win[2], d3 = win[3], d4 = win[4];
+                            const uint32_t q0 = __builtin_amdgcn_alignbit(d1, d0, sh);
+                            const uint32_t q1 = __builtin_amdgcn_alignbit(d2, d1, sh);
+                            const uint32_t q2 = __builtin_amdgcn_alignbit(d3, d2, sh);
+                            const uint32_t q3 = __builtin_amdgcn_alignbit(d4, d3, sh);
+                            const u32x4 sa = *reinterpret_cast<const u32x4 *>(&vlut[byte * 4]);
+                            const uint2 sb = *reinterpret_cast<const uint2 *>(&vlutb[byte * 2]);
+                            u32x4 piece, ones;
+                            piece.x = __builtin_amdgcn_perm(q1, q0, sa.x);
+                            piece.y = __builtin_amdgcn_perm(q1, q0, sa.y);
+                            piece.z = __builtin_amdgcn_perm(q1, q0, sa.z) | __builtin_amdgcn_perm(q3, q2, sa.w);
+                            piece.w = __builtin_amdgcn_perm(q1, q0, sb.x) | __builtin_amdgcn_perm(q3, q2, sb.y);
+                            constexpr uint32_t kOnes = 0x3F803F80u;      // two bf16 ones: any candidate is 1.0
+                            ones.x = __builtin_amdgcn_perm(kOnes, kOnes, sa.x);
+                            ones.y = __builtin_amdgcn_perm(kOnes, kOnes, sa.y);
+                            ones.z = __builtin_amdgcn_perm(kOnes, kOnes, sa.z) | __builtin_amdgcn_perm(kOnes, kOnes, sa.w);
+                            ones.w = __builtin_amdgcn_perm(kOnes, kOnes, sb.x) | __builtin_amdgcn_perm(kOnes, kOnes, sb.y);
+                            qk[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aq[kb], __builtin_bit_cast(bf16x8, piece), qk[tau], 0, 0, 0);
+                            qm[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aqa[kb], __builtin_bit_cast(bf16x8, ones), qm[tau], 0, 0, 0);
+                        }
+                    }
+                    wave_lds_sync();
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const float kept = reduce_scatter_rows(qm[0][g], qm[1][g], qm[2][g], qm[3][g]);
+                    const float dot = tg == 0 ? qk[0][g] : (tg == 1 ? qk[1][g] : (tg == 2 ? qk[2][g] : qk[3][g]));
+                    s[g] = fmaf(dot, P.scale_log2, mu * (R[g] - kept));
                 }
             } else if constexpr (VAR) {
                 // this row's kept entries: words [before, before + (count + 1) / 2) of the tile's part of the stream
@@ -992,7 +1117,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            s[g] = fmaf(mu, R[g], s[g]);
+            if (!MM) s[g] = fmaf(mu, R[g], s[g]);
             s[g] = valid ? s[g] : -INFINITY;
         }
 
@@ -1443,7 +1568,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         for (int g = 0; g < G; ++g) q_r[g] = P.q[((int64_t)b * P.Hq + h * G + g) * SPARK_D + tid];
     }
     if (kidx < nts) prefetch(tile);
-    if constexpr (PV) {
+    if constexpr (PV || MM) {
         // Selector table, entry b = mask byte of a group of 8 channels.  The group's kept entries are the
         // first popcount(b) of a window of 8 candidates = 16 bytes Q0..Q3; output word o holds channels
         // 2o, 2o+1.  A byte-permute picks from two words (selector 0-3: second operand, 4-7: first, 0x0C:
@@ -1480,6 +1605,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             qt[j * GP + g] = bf16lo(q_r[g]) * P.scale_log2;
+            if constexpr (MM) qraw[g][j] = q_r[g];
             if constexpr (REC != 0) qa[j * G + g] = bf16lo(q_r[g]) * P.scale_log2 * inva_r;
         }
         qt[j * GP + G] = inva_r;
@@ -1496,7 +1622,25 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     __syncthreads();
 #pragma unroll
     for (int g = 0; g < G; ++g) R[g] = Rsh[g];
-
+    if constexpr (MM) {
+        const int g = cn & 3, part = cn >> 2;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            uint4 qw = {0u, 0u, 0u, 0u};
+            if (g < G) qw = *reinterpret_cast<const uint4 *>(&qraw[g][32 * kb + 8 * tg]);
+            Aq[kb] = __builtin_bit_cast(bf16x8, qw);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int j = 32 * kb + 8 * tg + i;
+                const float x = g < G ? qt[j * GP + g] * qt[j * GP + G] : 0.0f;
+                const __bf16 hi = (__bf16)x;
+                const float x1 = x - (float)hi;
+                const __bf16 mid = (__bf16)x1;
+                const __bf16 lo = (__bf16)(x1 - (float)mid);
+                Aqa[kb][i] = part == 0 ? hi : (part == 1 ? mid : (part == 2 ? lo : (__bf16)0.0f));
+            }
+        }
+    }
 
     if (P.trace != nullptr) { stamp(P, 1, wall_clock64()); stamp(P, 5, (unsigned long long)nts); }
     for (; kidx < nts; kidx += kDecodeWaves) {
