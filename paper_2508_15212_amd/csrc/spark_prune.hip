@@ -22,9 +22,9 @@
 //        a bounded bisection of the bit pattern.
 //     4. the lane's kept entries go to the row's place in LDS with 16-bit stores under the channels' masks, and sixteen
 //        rows leave together in the tile's 16-byte sections.
-//   What bounds it: vector issue.  46 vector and 17 scalar instructions a row (with one row at a time, two channels a lane,
-//   41 and 37, and both units were at their limit).  One sequence of 131072 tokens x 8 KV heads, T = 26: 101 -> 86 us
-//   (4.0 TB/s); 64 ragged sequences, T = 64: 66 -> 60 us; 40003 tokens, int8 codes: 46 -> 40 us; values, T_v = 38:
+//   What bounds it: vector issue.  45 vector and 19 scalar instructions a row (with one row at a time, two channels a lane,
+//   41 and 37, and both units were at their limit).  One sequence of 131072 tokens x 8 KV heads, T = 26: 101 -> 87 us
+//   (4.0 TB/s); 64 ragged sequences, T = 64: 66 -> 61 us; 40003 tokens, int8 codes: 46 -> 40 us; values, T_v = 38:
 //   36 -> 34 us; 1024 tokens (one wavefront took a whole tile): 23 -> 10 us.  Four steps a group (fewer instructions,
 //   43, but registers for four wavefronts per SIMD only) took 93 us instead of 86.
 #include <hip/hip_runtime.h>
@@ -145,39 +145,41 @@ __host__ inline size_t spark_prune_lds_bytes(const SparkLayout &L)
 template <bool SUM>
 __device__ __forceinline__ float stage_row(uint32_t slot, const uint4 &x, const uint64_t (&kb)[8], const uint32_t (&key)[8])
 {
-    float sum = 0.0f;
+    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;      // (sums by pairs: smaller rounding errors than one running sum's)
 #define SPARK_STAGE(STORE, X, C)             \
     "s_mov_b64 exec, %[k" C "]\n\t"          \
     STORE " %[p], %[" X "]\n\t"              \
     "v_add_u32 %[p], 2, %[p]\n\t"
-#define SPARK_STAGE_SUM(STORE, X, C)         \
+#define SPARK_STAGE_SUM(STORE, X, C, S)      \
     SPARK_STAGE(STORE, X, C)                 \
     "s_not_b64 exec, exec\n\t"               \
-    "v_add_f32 %[s], %[s], %[w" C "]\n\t"
-#define SPARK_STAGE_ALL(M)                                                                                      \
-    M("ds_write_b16", "x0", "0") M("ds_write_b16_d16_hi", "x0", "1") M("ds_write_b16", "x1", "2")               \
-    M("ds_write_b16_d16_hi", "x1", "3") M("ds_write_b16", "x2", "4") M("ds_write_b16_d16_hi", "x2", "5")        \
-    M("ds_write_b16", "x3", "6") M("ds_write_b16_d16_hi", "x3", "7")
+    "v_add_f32 %[" S "], %[" S "], %[w" C "]\n\t"
+#define SPARK_STAGE_ONLY(STORE, X, C, S) SPARK_STAGE(STORE, X, C)
+#define SPARK_STAGE_ALL(M)                                                                                         \
+    M("ds_write_b16", "x0", "0", "s0") M("ds_write_b16_d16_hi", "x0", "1", "s1") M("ds_write_b16", "x1", "2", "s2") \
+    M("ds_write_b16_d16_hi", "x1", "3", "s3") M("ds_write_b16", "x2", "4", "s0")                                   \
+    M("ds_write_b16_d16_hi", "x2", "5", "s1") M("ds_write_b16", "x3", "6", "s2")                                   \
+    M("ds_write_b16_d16_hi", "x3", "7", "s3")
     if constexpr (SUM) {
-        asm volatile(SPARK_STAGE_ALL(SPARK_STAGE_SUM) "s_mov_b64 exec, -1\n\t"
-                     "s_nop 1"               // (the sum goes into a lane move next)
-                     : [p] "+v"(slot), [s] "+v"(sum)
+        asm volatile(SPARK_STAGE_ALL(SPARK_STAGE_SUM) "s_mov_b64 exec, -1"
+                     : [p] "+v"(slot), [s0] "+v"(s0), [s1] "+v"(s1), [s2] "+v"(s2), [s3] "+v"(s3)
                      : [x0] "v"(x.x), [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w), [k0] "s"(kb[0]), [k1] "s"(kb[1]),
                        [k2] "s"(kb[2]), [k3] "s"(kb[3]), [k4] "s"(kb[4]), [k5] "s"(kb[5]), [k6] "s"(kb[6]), [k7] "s"(kb[7]),
                        [w0] "v"(key[0]), [w1] "v"(key[1]), [w2] "v"(key[2]), [w3] "v"(key[3]), [w4] "v"(key[4]),
                        [w5] "v"(key[5]), [w6] "v"(key[6]), [w7] "v"(key[7])
                      : "memory", "scc");
     } else {
-        asm volatile(SPARK_STAGE_ALL(SPARK_STAGE) "s_mov_b64 exec, -1"
+        asm volatile(SPARK_STAGE_ALL(SPARK_STAGE_ONLY) "s_mov_b64 exec, -1"
                      : [p] "+v"(slot)
                      : [x0] "v"(x.x), [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w), [k0] "s"(kb[0]), [k1] "s"(kb[1]),
                        [k2] "s"(kb[2]), [k3] "s"(kb[3]), [k4] "s"(kb[4]), [k5] "s"(kb[5]), [k6] "s"(kb[6]), [k7] "s"(kb[7])
                      : "memory");
     }
 #undef SPARK_STAGE_ALL
+#undef SPARK_STAGE_ONLY
 #undef SPARK_STAGE_SUM
 #undef SPARK_STAGE
-    return sum;
+    return (s0 + s1) + (s2 + s3);
 }
 
 __device__ __forceinline__ uint32_t min8(const uint32_t (&x)[8])
@@ -508,15 +510,15 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
                     mu_reg = sub == g0 / 4 + s ? sum : mu_reg;
                 }
                 if constexpr (STATS) {
-                    float w = 0.0f, q = 0.0f;
+                    // (sums by pairs, for the same reason)
+                    float v[8], d[8];
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) w += __uint_as_float(ks[c]);
-                    w = row16_sum_f32(w) * (1.0f / (float)SPARK_D);
+                    for (int c = 0; c < 8; ++c) v[c] = __uint_as_float(ks[c]);
+                    const float w = row16_sum_f32(((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]))) * (1.0f / (float)SPARK_D);
 #pragma unroll
-                    for (int c = 0; c < 8; ++c) {
-                        const float d = __uint_as_float(ks[c]) - w;
-                        q = fmaf(d, d, q);
-                    }
+                    for (int c = 0; c < 8; ++c) d[c] = v[c] - w;
+                    const float q = (fmaf(d[0], d[0], d[1] * d[1]) + fmaf(d[2], d[2], d[3] * d[3])) +
+                                    (fmaf(d[4], d[4], d[5] * d[5]) + fmaf(d[6], d[6], d[7] * d[7]));
                     const uint32_t sq = __float_as_uint(row16_sum_f32(q));
                     all_reg = sub == g0 / 4 + s ? __float_as_uint(w) : all_reg;
                     sq_reg = sub == g0 / 4 + s ? sq : sq_reg;

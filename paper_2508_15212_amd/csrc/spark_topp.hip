@@ -259,10 +259,10 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
             }
             const uint32_t m = byte_of_masks(kb);
             const uint32_t cnt = row16_sum((uint32_t)__popc(m));
-            float psum = 0.0f;
+            float gone[8];           // (summed by pairs: smaller rounding errors than one running sum's)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) psum += __builtin_amdgcn_inverse_ballot_w64(kb[c]) ? 0.0f : __uint_as_float(key[c]);
-            psum = row16_sum_f32(psum);
+            for (int c = 0; c < 8; ++c) gone[c] = __builtin_amdgcn_inverse_ballot_w64(kb[c]) ? 0.0f : __uint_as_float(key[c]);
+            const float psum = row16_sum_f32(((gone[0] + gone[1]) + (gone[2] + gone[3])) + ((gone[4] + gone[5]) + (gone[6] + gone[7])));
             // mask bytes in channel order (rows past the last token: empty mask)
             tile_out[t * 16 + sub] = (uint8_t)(t < nvalid ? m : 0u);
             if (sub == s) {
