@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kScanThreads) void spark_topp_scan_kernel(uint8_t *
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t n = L.n_tiles;
     if (threadIdx.x == 0) dir[0] = 0u;
-    uint32_t run = 0;                                    // words of the tiles in front of this round's
+    uint32_t run = 0;                                    // words of the tiles in front of this pass's
     for (int64_t i0 = 0; i0 < n; i0 += kScanThreads) {
         const int64_t i = i0 + threadIdx.x;
         const uint32_t upto = wave_inclusive_sum(i < n ? dir[i + 1] : 0u);
