@@ -452,6 +452,24 @@ constexpr int decode_min_blocks(int, int) { return 2; }
 template <int G>
 constexpr int kShortRow = G <= 4 ? 52 : 44;
 
+// Top-p rows, up to four query heads per KV head: a tile whose longest row keeps this many entries at most is walked entry
+// by entry, another one's scores are taken on the matrix cores (see the score phase).  The walk's cost follows the longest
+// row, the other form's does not, and it needs operands prepared and more memory round trips a tile, so the line also
+// depends on the tiles a block has.  Measured, walk / matrix cores (us, every row keeping about the stated number):
+//   G = 4, four tiles a wavefront (64 x 300..1700 tokens):  24: 45.2 / 54.2   31: 49.3 / 54.0   38: 55.1 / 54.6   60: 68.4 / 55.9
+//          two tiles (3 x 8000):    31: 22.3 / 24.9   38: 25.3 / 25.1   60: 28.0 / 25.7
+//          one tile (8 x 500..1500):  31: 13.9 / 16.4   53: 16.0 / 16.2   60: 16.9 / 16.1   68: 17.4 / 18.8   75: 18.2 / 16.9
+//   G = 2, four tiles: 46: 54.3 / 54.5   53: 58.5 / 53.8   two: 60: 25.9 / 26.7   75: 29.0 / 27.1   one: 68: 16.0 / 17.6   75: 16.5 / 15.9
+//   G = 1, four tiles: 46: 52.6 / 51.3   53: 54.9 / 51.3   two: 60: 25.0 / 25.1   68: 26.0 / 25.2   one: 75: 15.3 / 16.2   89: 16.4 / 15.7
+// (Rows of nearly 64 entries each, 68 above, start in few banks; rows whose lengths vary more do not.)
+template <int G>
+__device__ __forceinline__ uint32_t walk_limit_of(int tiles_of_block)
+{
+    if (tiles_of_block <= kDecodeWaves) return G == 1 ? 80u : (G == 2 ? 72u : 56u);
+    if (tiles_of_block <= 2 * kDecodeWaves) return G == 1 ? 64u : (G == 2 ? 72u : 32u);
+    return G == 4 ? 32u : 48u;
+}
+
 // Timeline of a launch (a measurement aid, off unless a buffer has been given through spark_decode_timeline):
 // thread 0 of every block files the 100 MHz wall clock at five points - word 0 entry, 1 start of streaming,
 // 2 end of streaming (wavefront 0), 3 partial stored, 4 exit - and, with word 5, its tile count (in the balanced
@@ -480,7 +498,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     static_assert(!VAR || (TCT == 0 && INT8 == 0 && TVC == 0 && REC == 0), "variable-length rows: any-length bf16 path only");
     static_assert(!WARM || (TVC == 0 && REC == 0 && VAR == 0 && G <= 8), "balanced mode: dense values, degenerate recovery");
     constexpr bool PV = (TVC != 0);             // packed value cache
-    constexpr bool MM = VAR && G <= 4;          // scores of rows of varying length on the matrix cores
+    constexpr bool MM = VAR && G <= 4;          // scores of rows of varying length may go to the matrix cores
     constexpr int NVW = PV ? (TVC > 0 ? (((4 + (TVC + 1) / 2) + 1) & ~1) : 4) : 1;   // value-row words in registers
     // LDS row stride (words) of a parked value row.  A row kept whole in registers (NVW words) is parked word by
     // word at an ODD stride: the four tokens whose windows a wavefront reads together then start in banks of both
@@ -530,6 +548,15 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     }
     const SparkLayout &L = P.L;
     const int T = TCT ? TCT : L.T;
+    // The query table holds q times this: the softmax scale (times log2 e), or only its power of two where the scores can be
+    // multiplied by the rest (rows of varying length, up to four query heads: exact table entries).
+    float q_scale = P.scale_log2, s_scale = 1.0f;
+    if constexpr (MM) {
+        const uint32_t bits = __float_as_uint(P.scale_log2);
+        const bool normal = (bits & 0x7F800000u) != 0u;
+        q_scale = normal ? __uint_as_float(bits & 0x7F800000u) : 1.0f;
+        s_scale = normal ? __uint_as_float((bits & 0x807FFFFFu) | 0x3F800000u) : P.scale_log2;
+    }
     // blocks [0, nmain) stream the cache: (global chunk, KV head) pairs, or in the balanced mode (group of four
     // wavefronts, KV head); when rows have been appended after prefill, B * Hkv * ntail more blocks follow, each
     // taking 256 of a (batch, KV head)'s appended rows
@@ -746,8 +773,28 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
     };
     bf16x8 Aq[MM ? 4 : 1], Aqa[MM ? 4 : 1];     // A operands of the scores, one per 32 channels (see the score phase)
+    uint32_t walk_limit = 0;                    // (see walk_limit_of; SPARK_D: all tiles are walked)
+    auto make_operands = [&]() __attribute__((always_inline)) {
+        const int g = cn & 3, part = cn >> 2;
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            uint4 qw = {0u, 0u, 0u, 0u};
+            if (g < G && part == 0) qw = *reinterpret_cast<const uint4 *>(&qraw[g][32 * kb + 8 * tg]);
+            Aq[kb] = __builtin_bit_cast(bf16x8, qw);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int j = 32 * kb + 8 * tg + i;
+                const float x = g < G ? qt[j * GP + g] * qt[j * GP + G] : 0.0f;
+                const __bf16 hi = (__bf16)x;
+                const float x1 = x - (float)hi;
+                const __bf16 mid = (__bf16)x1;
+                const __bf16 lo = (__bf16)(x1 - (float)mid);
+                Aqa[kb][i] = part == 0 ? hi : (part == 1 ? mid : (part == 2 ? lo : (__bf16)0.0f));
+            }
+        }
+    };
     // One tile of sequence [s0, s1) whose rows have been requested by prefetch(): scores, online softmax, P V.
-    auto process = [&](int tile, int tnext) {
+    auto process = [&](int tile, int tnext) __attribute__((always_inline)) {
         const uint8_t *tp = tiles + (int64_t)tile * L.tile_bytes;
         const int n_lane = tile * SPARK_TILE_TOKENS + lane;
         const bool valid = (n_lane >= s0) && (n_lane < s1);
@@ -810,167 +857,180 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
                             for (int g = 0; g < G; ++g) s[g] = fmaf(ev[u][g], d, s[g]);
                         }
                 }
-            } else if constexpr (MM) {
-                // Rows of varying length, scores on the matrix cores.  Entry by entry (mask walk, table gather, multiply-
-                // adds) a wavefront's tile costs 24 instructions for every entry of its LONGEST row; here the rows are
-                // spread to dense bf16 pieces of eight channels, as packed values are, at a cost that does not depend on
-                // what they keep, and two matrix products take the sums:
-                //     q . k over the kept entries       B = the pieces, A = the query (bf16, as it came: exact products)
-                //     sum of q_j / a_j over them        B = the pieces with 1.0 for every kept entry, A = q_j / a_j as
-                //                                       three bf16 parts, which together are its float32 value
-                // B operands: lane (tg, cn) = channels 8 tg .. 8 tg + 7 of a block of 32 of token 16 tau + cn.  A operands:
-                // row 4 p + g = query head g; the first product has it in every p, so that lane row tg finds the
-                // scores of its own sixteen tokens in the result of tau = tg; the second has part p there, and the
-                // parts are added up across the lane rows.
-                // Up to four query heads (three parts of more do not fit sixteen rows).  2 x 32768 tokens, 51 kept entries a
-                // row: 53.2 -> 46.2 us, 64 x 1000 tokens: 53.2 -> 44.6 us, error against 64 bits 6.4e-7 -> 3.3e-7 (80 seeds).
-                // Bound by LDS (windows, selector table) and the memory round trips at a tile's start; requesting the
-                // next tile's entries with its values took 47 us (the registers spill).
+            } else if constexpr (VAR) {
+                // Rows of varying length: the kept entries of this lane's row are words [upto - words, upto) of the tile's part
+                // of the stream.
                 const uint32_t cnt = r[5] < (uint32_t)SPARK_D ? r[5] : (uint32_t)SPARK_D;     // (bounds it whatever the cache holds)
                 const uint32_t words = (cnt + 1u) >> 1;
                 const uint32_t upto = (uint32_t)wave_inclusive_sum_i32((int)words);
-                const uint32_t half = (uint32_t)__builtin_amdgcn_readlane((int)upto, 31), all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
                 const uint32_t *vsrc = reinterpret_cast<const uint32_t *>(P.packed + L.off_vals) + (int64_t)h * L.vals_head_words +
                                        reinterpret_cast<const uint32_t *>(P.packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile];
                 typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
-                // the words of half a tile, 16 bytes a lane; loads that straddle the end read at most three words of
-                // what follows or of the stream's padding
-                constexpr int NLV = 4;
-                auto half_words = [&](uint32_t w0, uint32_t w1, u32x4u (&wv)[NLV]) {
+                bool mat = false;
+                if constexpr (MM) mat = __ballot(cnt > walk_limit) != 0ull;       // (wave-uniform)
+                if constexpr (MM) if (mat) {
+                    // Scores on the matrix cores.  Entry by entry (mask walk, table gather, multiply-adds) a wavefront's tile
+                    // costs 24 instructions for every entry of its LONGEST row; here the rows are spread to dense bf16 pieces
+                    // of eight channels, as packed values are, at a cost that does not depend on what they keep, and two
+                    // matrix products take the sums:
+                    //     q . k over the kept entries       B = the pieces, A = the query (bf16, as it came: exact products)
+                    //     sum of q_j / a_j over them        B = the pieces with 1.0 for every kept entry, A = q_j / a_j as
+                    //                                       three bf16 parts, which together are its float32 value
+                    // B operands: lane (tg, cn) = channels 8 tg .. 8 tg + 7 of a block of 32 of token 16 tau + cn.  A operands:
+                    // row 4 p + g = query head g; the first product has it in p = 0 (and zeros in the others), the second has
+                    // part p there.  Both are added up across the lane rows, which hands lane row tg the scores of its own
+                    // sixteen tokens, tau = tg.  (Picking the result of tau = tg by comparisons became branches.)
+                    // Up to four query heads (three parts of more do not fit sixteen rows).  2 x 32768 tokens, 51 kept entries a
+                    // row: 53.4 -> 46.0 us, 64 x 300..1700 tokens: 70.5 -> 54.4 us, error against 64 bits 4.6e-7 -> 2.9e-7
+                    // (the walk, summed by groups: 3.6e-7; twelve seeds of twelve shapes).
+                    // Bound by LDS (windows, selector table) and the memory round trips at a tile's start; requesting the
+                    // next tile's entries with its values took 47 us (the registers spill).
+                    const uint32_t half = (uint32_t)__builtin_amdgcn_readlane((int)upto, 31), all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+                    // the words of half a tile, 16 bytes a lane; loads that straddle the end read at most three words of
+                    // what follows or of the stream's padding
+                    constexpr int NLV = 4;
+                    auto half_words = [&](uint32_t w0, uint32_t w1, u32x4u (&wv)[NLV]) {
 #pragma unroll
-                    for (int u = 0; u < NLV; ++u) {
-                        const uint32_t w = w0 + 4u * (uint32_t)lane + 256u * u;
-                        wv[u] = w < w1 ? *reinterpret_cast<const u32x4u *>(vsrc + w) : u32x4u{0u, 0u, 0u, 0u};
-                    }
-                };
-                uint32_t *raw = reinterpret_cast<uint32_t *>(wbuf[wave]);
-                u32x4u h0[NLV], h1[NLV];
-                half_words(0u, half, h0);
-                half_words(half, all, h1);
-                {
-                    // per token 16 halfwords: kept entries in lower groups << 8 | mask byte of the group; group 4 kb + tg
-                    // at 4 tg + kb, so that a lane fetches the four it works on at once
-                    uint32_t meta[8], before = 0;
+                        for (int u = 0; u < NLV; ++u) {
+                            const uint32_t w = w0 + 4u * (uint32_t)lane + 256u * u;
+                            wv[u] = w < w1 ? *reinterpret_cast<const u32x4u *>(vsrc + w) : u32x4u{0u, 0u, 0u, 0u};
+                        }
+                    };
+                    uint32_t *raw = reinterpret_cast<uint32_t *>(wbuf[wave]);
+                    u32x4u h0[NLV], h1[NLV];
+                    half_words(0u, half, h0);
+                    half_words(half, all, h1);
+                    {
+                        // per token 16 halfwords: kept entries in lower groups << 8 | mask byte of the group; group 4 kb + tg
+                        // at 4 tg + kb, so that a lane fetches the four it works on at once
+                        uint32_t meta[8], before = 0;
 #pragma unroll
-                    for (int c = 0; c < 16; ++c) {
-                        const uint32_t byte = (r[c >> 2] >> (8 * (c & 3))) & 0xFFu;
-                        const uint32_t hw = (before << 8) | byte;
-                        const int at = 4 * (c & 3) + (c >> 2);
-                        if ((c >> 2) & 1) meta[at >> 1] |= hw << 16; else meta[at >> 1] = hw;
-                        before += __popc(byte);
+                        for (int c = 0; c < 16; ++c) {
+                            const uint32_t byte = (r[c >> 2] >> (8 * (c & 3))) & 0xFFu;
+                            const uint32_t hw = (before << 8) | byte;
+                            const int at = 4 * (c & 3) + (c >> 2);
+                            if ((c >> 2) & 1) meta[at >> 1] |= hw << 16; else meta[at >> 1] = hw;
+                            before += __popc(byte);
+                        }
+                        const u32x4 m0 = {meta[0], meta[1], meta[2], meta[3]}, m1 = {meta[4], meta[5], meta[6], meta[7]};
+                        *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8]) = m0;
+                        *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8 + 4]) = m1;
+                        row_at[wave][lane] = upto - words - (lane < 32 ? 0u : half);
                     }
-                    const u32x4 m0 = {meta[0], meta[1], meta[2], meta[3]}, m1 = {meta[4], meta[5], meta[6], meta[7]};
-                    *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8]) = m0;
-                    *reinterpret_cast<u32x4 *>(&vmeta[wave][lane * 8 + 4]) = m1;
-                    row_at[wave][lane] = upto - words - (lane < 32 ? 0u : half);
+                    f32x4 qk[4], qm[4];
+#pragma unroll
+                    for (int tau = 0; tau < 4; ++tau) qk[tau] = qm[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int hs = 0; hs < 2; ++hs) {
+                        const uint32_t w0 = hs ? half : 0u, w1 = hs ? all : half;
+#pragma unroll
+                        for (int u = 0; u < NLV; ++u) *reinterpret_cast<u32x4 *>(&raw[4 * lane + 256 * u]) = hs ? u32x4(h1[u]) : u32x4(h0[u]);
+                        if (w1 - w0 > 256u * NLV) {        // (wave-uniform: more than 64 kept entries a row on average)
+                            u32x4u more[NLV];
+                            half_words(w0 + 256u * NLV, w1, more);
+#pragma unroll
+                            for (int u = 0; u < NLV; ++u) *reinterpret_cast<u32x4 *>(&raw[256 * NLV + 4 * lane + 256 * u]) = u32x4(more[u]);
+                        }
+                        wave_lds_sync();
+#pragma unroll
+                        for (int t2 = 0; t2 < 2; ++t2) {
+                            const int tau = 2 * hs + t2, t = 16 * tau + cn;
+                            const uint32_t at = row_at[wave][t];
+                            const uint2 mt = *reinterpret_cast<const uint2 *>(&vmeta[wave][t * 8 + 2 * tg]);
+#pragma unroll
+                            for (int kb = 0; kb < 4; ++kb) {
+                                const uint32_t hw = ((kb & 2) ? mt.y : mt.x) >> (16 * (kb & 1));
+                                const uint32_t byte = hw & 0xFFu, before = (hw >> 8) & 0xFFu;
+                                const uint32_t *win = &raw[at + (before >> 1)];                // 8 candidates start here ...
+                                const uint32_t sh = (before & 1u) << 4;                         // ... or one halfword further
+                                const uint32_t d0 = win[0], d1 = win[1], d2 = win[2], d3 = win[3], d4 = win[4];
+                                const uint32_t q0 = __builtin_amdgcn_alignbit(d1, d0, sh);
+                                const uint32_t q1 = __builtin_amdgcn_alignbit(d2, d1, sh);
+                                const uint32_t q2 = __builtin_amdgcn_alignbit(d3, d2, sh);
+                                const uint32_t q3 = __builtin_amdgcn_alignbit(d4, d3, sh);
+                                const u32x4 sa = *reinterpret_cast<const u32x4 *>(&vlut[byte * 4]);
+                                const uint2 sb = *reinterpret_cast<const uint2 *>(&vlutb[byte * 2]);
+                                u32x4 piece, ones;
+                                piece.x = __builtin_amdgcn_perm(q1, q0, sa.x);
+                                piece.y = __builtin_amdgcn_perm(q1, q0, sa.y);
+                                piece.z = __builtin_amdgcn_perm(q1, q0, sa.z) | __builtin_amdgcn_perm(q3, q2, sa.w);
+                                piece.w = __builtin_amdgcn_perm(q1, q0, sb.x) | __builtin_amdgcn_perm(q3, q2, sb.y);
+                                constexpr uint32_t kOnes = 0x3F803F80u;      // two bf16 ones: any candidate is 1.0
+                                ones.x = __builtin_amdgcn_perm(kOnes, kOnes, sa.x);
+                                ones.y = __builtin_amdgcn_perm(kOnes, kOnes, sa.y);
+                                ones.z = __builtin_amdgcn_perm(kOnes, kOnes, sa.z) | __builtin_amdgcn_perm(kOnes, kOnes, sa.w);
+                                ones.w = __builtin_amdgcn_perm(kOnes, kOnes, sb.x) | __builtin_amdgcn_perm(kOnes, kOnes, sb.y);
+                                qk[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aq[kb], __builtin_bit_cast(bf16x8, piece), qk[tau], 0, 0, 0);
+                                qm[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aqa[kb], __builtin_bit_cast(bf16x8, ones), qm[tau], 0, 0, 0);
+                            }
+                        }
+                        wave_lds_sync();
+                    }
+#pragma unroll
+                    for (int g = 0; g < G; ++g) {
+                        const float kept = reduce_scatter_rows(qm[0][g], qm[1][g], qm[2][g], qm[3][g]);
+                        const float dot = reduce_scatter_rows(qk[0][g], qk[1][g], qk[2][g], qk[3][g]);
+                        s[g] = fmaf(dot, q_scale, mu * (R[g] - kept));
+                    }
                 }
-                f32x4 qk[4], qm[4];
+                if (!mat) {
+                    const int tmax = (int)wave_max((float)cnt);     // (counts are at most 128: exact in float32)
+                    // The row's words are fetched 16 at a time (32 entries, four 16-byte loads in flight per lane: one
+                    // memory round trip per 32 entries instead of one per word); a load whose first word lies past the
+                    // lane's row is masked off, one that straddles the row's end reads at most three words of the next
+                    // row or of the stream's padding.  Entries are then taken eight at a time like the fixed-count path
+                    // (eight channel numbers off the mask, eight table gathers in flight, eight multiply-adds), a group
+                    // being skipped only when the whole wavefront is past it.  (Measured on the 32K shape with 110 kept
+                    // entries per row: 688 us with one load per word, 306 us with the batched loads, 262 us with the
+                    // grouped gathers; eight loads in flight instead of four changed nothing.)
+                    constexpr int NLD = 4;      // 16-byte loads in flight per lane
+                    for (int i0 = 0; i0 < tmax; i0 += 8 * NLD) {
+                        u32x4u wv[NLD];
 #pragma unroll
-                for (int tau = 0; tau < 4; ++tau) qk[tau] = qm[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        for (int u = 0; u < NLD; ++u) {
+                            const uint32_t w0 = (uint32_t)(i0 >> 1) + 4u * u;
+                            wv[u] = (w0 < words) ? *reinterpret_cast<const u32x4u *>(vsrc + (upto - words) + w0) : u32x4u{0u, 0u, 0u, 0u};
+                        }
 #pragma unroll
-                for (int hs = 0; hs < 2; ++hs) {
-                    const uint32_t w0 = hs ? half : 0u, w1 = hs ? all : half;
+                        for (int u = 0; u < NLD; ++u) {
+                            if (i0 + 8 * u >= tmax) break;                // (wave-uniform; the groups of eight stay whole so
+                                                                          //  that their table gathers are in flight together)
+                            const uint32_t w4[4] = {wv[u].x, wv[u].y, wv[u].z, wv[u].w};
+                            int off[8];
 #pragma unroll
-                    for (int u = 0; u < NLV; ++u) *reinterpret_cast<u32x4 *>(&raw[4 * lane + 256 * u]) = hs ? u32x4(h1[u]) : u32x4(h0[u]);
-                    if (w1 - w0 > 256u * NLV) {        // (wave-uniform: more than 64 kept entries a row on average)
-                        u32x4u more[NLV];
-                        half_words(w0 + 256u * NLV, w1, more);
+                            for (int k = 0; k < 8; ++k) {
+                                // (as next_channel, but defined when the row's bits have run out: an idle lane reads some entry)
+                                const bool sw = (i0 + 8 * u + k == clo);
+                                cur = sw ? upper : cur;
+                                jb = sw ? 64 : jb;
+                                off[k] = ((__builtin_ctzll((unsigned long long)cur | (1ull << 63)) + jb) & (SPARK_D - 1)) * GP;
+                                cur &= cur - 1;
+                            }
+                            float ev[8][G + 1];
 #pragma unroll
-                        for (int u = 0; u < NLV; ++u) *reinterpret_cast<u32x4 *>(&raw[256 * NLV + 4 * lane + 256 * u]) = u32x4(more[u]);
-                    }
-                    wave_lds_sync();
+                            for (int k = 0; k < 8; ++k)
 #pragma unroll
-                    for (int t2 = 0; t2 < 2; ++t2) {
-                        const int tau = 2 * hs + t2, t = 16 * tau + cn;
-                        const uint32_t at = row_at[wave][t];
-                        const uint2 mt = *reinterpret_cast<const uint2 *>(&vmeta[wave][t * 8 + 2 * tg]);
+                                for (int g = 0; g <= G; ++g) ev[k][g] = qt[off[k] + g];
+                            float part[G];           // (summed by groups: smaller rounding errors)
 #pragma unroll
-                        for (int kb = 0; kb < 4; ++kb) {
-                            const uint32_t hw = ((kb & 2) ? mt.y : mt.x) >> (16 * (kb & 1));
-                            const uint32_t byte = hw & 0xFFu, before = (hw >> 8) & 0xFFu;
-                            const uint32_t *win = &raw[at + (before >> 1)];                // 8 candidates start here ...
-                            const uint32_t sh = (before & 1u) << 4;                         // ... or one halfword further
-                            const uint32_t d0 = win[0], d1 = win[1], d2 = win[2], d3 = win[3], d4 = win[4];
-                            const uint32_t q0 = __builtin_amdgcn_alignbit(d1, d0, sh);
-                            const uint32_t q1 = __builtin_amdgcn_alignbit(d2, d1, sh);
-                            const uint32_t q2 = __builtin_amdgcn_alignbit(d3, d2, sh);
-                            const uint32_t q3 = __builtin_amdgcn_alignbit(d4, d3, sh);
-                            const u32x4 sa = *reinterpret_cast<const u32x4 *>(&vlut[byte * 4]);
-                            const uint2 sb = *reinterpret_cast<const uint2 *>(&vlutb[byte * 2]);
-                            u32x4 piece, ones;
-                            piece.x = __builtin_amdgcn_perm(q1, q0, sa.x);
-                            piece.y = __builtin_amdgcn_perm(q1, q0, sa.y);
-                            piece.z = __builtin_amdgcn_perm(q1, q0, sa.z) | __builtin_amdgcn_perm(q3, q2, sa.w);
-                            piece.w = __builtin_amdgcn_perm(q1, q0, sb.x) | __builtin_amdgcn_perm(q3, q2, sb.y);
-                            constexpr uint32_t kOnes = 0x3F803F80u;      // two bf16 ones: any candidate is 1.0
-                            ones.x = __builtin_amdgcn_perm(kOnes, kOnes, sa.x);
-                            ones.y = __builtin_amdgcn_perm(kOnes, kOnes, sa.y);
-                            ones.z = __builtin_amdgcn_perm(kOnes, kOnes, sa.z) | __builtin_amdgcn_perm(kOnes, kOnes, sa.w);
-                            ones.w = __builtin_amdgcn_perm(kOnes, kOnes, sb.x) | __builtin_amdgcn_perm(kOnes, kOnes, sb.y);
-                            qk[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aq[kb], __builtin_bit_cast(bf16x8, piece), qk[tau], 0, 0, 0);
-                            qm[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Aqa[kb], __builtin_bit_cast(bf16x8, ones), qm[tau], 0, 0, 0);
+                            for (int k = 0; k < 8; ++k) {
+                                const bool on = (uint32_t)(i0 + 8 * u + k) < cnt;   // lanes whose row is shorter idle through the rest
+                                const float d = on ? fmaf(-mu, ev[k][G], kept_value(k, w4[k >> 1])) : 0.0f;
+#pragma unroll
+                                for (int g = 0; g < G; ++g) {
+                                    float &sum = MM ? part[g] : s[g];
+                                    sum = (MM && k == 0) ? ev[k][g] * d : fmaf(ev[k][g], d, sum);
+                                }
+                            }
+                            if constexpr (MM) {
+#pragma unroll
+                                for (int g = 0; g < G; ++g) s[g] += part[g];
+                            }
                         }
                     }
-                    wave_lds_sync();
-                }
+                    if constexpr (MM) {
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float kept = reduce_scatter_rows(qm[0][g], qm[1][g], qm[2][g], qm[3][g]);
-                    const float dot = tg == 0 ? qk[0][g] : (tg == 1 ? qk[1][g] : (tg == 2 ? qk[2][g] : qk[3][g]));
-                    s[g] = fmaf(dot, P.scale_log2, mu * (R[g] - kept));
-                }
-            } else if constexpr (VAR) {
-                // this row's kept entries: words [before, before + (count + 1) / 2) of the tile's part of the stream
-                const uint32_t cnt = r[5] < (uint32_t)SPARK_D ? r[5] : (uint32_t)SPARK_D;     // (bounds the walk whatever the cache holds)
-                const uint32_t words = (cnt + 1u) >> 1;
-                const uint32_t before = (uint32_t)wave_inclusive_sum_i32((int)words) - words;
-                const uint32_t *vsrc = reinterpret_cast<const uint32_t *>(P.packed + L.off_vals) + (int64_t)h * L.vals_head_words +
-                                       reinterpret_cast<const uint32_t *>(P.packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile] + before;
-                const int tmax = (int)wave_max((float)cnt);     // (counts are at most 128: exact in float32)
-                // The row's words are fetched 16 at a time (32 entries, four 16-byte loads in flight per lane: one
-                // memory round trip per 32 entries instead of one per word); a load whose first word lies past the
-                // lane's row is masked off, one that straddles the row's end reads at most three words of the next
-                // row or of the stream's padding.  Entries are then taken eight at a time like the fixed-count path
-                // (eight channel numbers off the mask, eight table gathers in flight, eight multiply-adds), a group
-                // being skipped only when the whole wavefront is past it.  (Measured on the 32K shape with 110 kept
-                // entries per row: 688 us with one load per word, 306 us with the batched loads, 262 us with the
-                // grouped gathers; eight loads in flight instead of four changed nothing.)
-                constexpr int NLD = 4;      // 16-byte loads in flight per lane
-                typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
-                for (int i0 = 0; i0 < tmax; i0 += 8 * NLD) {
-                    u32x4u wv[NLD];
-#pragma unroll
-                    for (int u = 0; u < NLD; ++u) {
-                        const uint32_t w0 = (uint32_t)(i0 >> 1) + 4u * u;
-                        wv[u] = (w0 < words) ? *reinterpret_cast<const u32x4u *>(vsrc + w0) : u32x4u{0u, 0u, 0u, 0u};
-                    }
-#pragma unroll
-                    for (int u = 0; u < NLD; ++u) {
-                        if (i0 + 8 * u >= tmax) break;                // (wave-uniform; the groups of eight stay whole so
-                                                                      //  that their table gathers are in flight together)
-                        const uint32_t w4[4] = {wv[u].x, wv[u].y, wv[u].z, wv[u].w};
-                        int off[8];
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            // (as next_channel, but defined when the row's bits have run out: an idle lane reads some entry)
-                            const bool sw = (i0 + 8 * u + k == clo);
-                            cur = sw ? upper : cur;
-                            jb = sw ? 64 : jb;
-                            off[k] = ((__builtin_ctzll((unsigned long long)cur | (1ull << 63)) + jb) & (SPARK_D - 1)) * GP;
-                            cur &= cur - 1;
-                        }
-                        float ev[8][G + 1];
-#pragma unroll
-                        for (int k = 0; k < 8; ++k)
-#pragma unroll
-                            for (int g = 0; g <= G; ++g) ev[k][g] = qt[off[k] + g];
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            const bool on = (uint32_t)(i0 + 8 * u + k) < cnt;   // lanes whose row is shorter idle through the rest
-                            const float d = on ? fmaf(-mu, ev[k][G], kept_value(k, w4[k >> 1])) : 0.0f;
-#pragma unroll
-                            for (int g = 0; g < G; ++g) s[g] = fmaf(ev[k][g], d, s[g]);
-                        }
+                        for (int g = 0; g < G; ++g) s[g] = fmaf(mu, R[g], s[g]);
                     }
                 }
             } else if constexpr (G > 8) {
@@ -1117,7 +1177,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            if (!MM) s[g] = fmaf(mu, R[g], s[g]);
+            s[g] = MM ? s[g] * s_scale : fmaf(mu, R[g], s[g]);
             s[g] = valid ? s[g] : -INFINITY;
         }
 
@@ -1599,12 +1659,12 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         vlutb[tid * 2] = sel[4];
         vlutb[tid * 2 + 1] = sel[5];
     }
-    // ---- per-step query prep: table {q_g[j] * scale * log2e, 1/a[j]} and R_g
+    // ---- per-step query prep: table {q_g[j] * q_scale, 1/a[j]} and R_g
     if (tid < SPARK_D) {
         const int j = tid;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            qt[j * GP + g] = bf16lo(q_r[g]) * P.scale_log2;
+            qt[j * GP + g] = bf16lo(q_r[g]) * q_scale;
             if constexpr (MM) qraw[g][j] = q_r[g];
             if constexpr (REC != 0) qa[j * G + g] = bf16lo(q_r[g]) * P.scale_log2 * inva_r;
         }
@@ -1622,27 +1682,17 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     __syncthreads();
 #pragma unroll
     for (int g = 0; g < G; ++g) R[g] = Rsh[g];
-    if constexpr (MM) {
-        const int g = cn & 3, part = cn >> 2;
-#pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {
-            uint4 qw = {0u, 0u, 0u, 0u};
-            if (g < G) qw = *reinterpret_cast<const uint4 *>(&qraw[g][32 * kb + 8 * tg]);
-            Aq[kb] = __builtin_bit_cast(bf16x8, qw);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int j = 32 * kb + 8 * tg + i;
-                const float x = g < G ? qt[j * GP + g] * qt[j * GP + G] : 0.0f;
-                const __bf16 hi = (__bf16)x;
-                const float x1 = x - (float)hi;
-                const __bf16 mid = (__bf16)x1;
-                const __bf16 lo = (__bf16)(x1 - (float)mid);
-                Aqa[kb][i] = part == 0 ? hi : (part == 1 ? mid : (part == 2 ? lo : (__bf16)0.0f));
-            }
-        }
-    }
-
     if (P.trace != nullptr) { stamp(P, 1, wall_clock64()); stamp(P, 5, (unsigned long long)nts); }
+    if constexpr (MM) {
+        // The operands are made where the wavefront's first tile needs them; another wavefront walks all of its tiles.
+        // (Made in the loop, at the first tile that needs them, the loop spills; made always, short calls whose rows are
+        //  all walked took 13.6 instead of 12.0 us.)
+        walk_limit = walk_limit_of<G>(nts);
+        if (kidx < nts && __ballot(rn[5] > walk_limit) != 0ull)
+            make_operands();
+        else
+            walk_limit = SPARK_D;
+    }
     for (; kidx < nts; kidx += kDecodeWaves) {
         tile = tile_of(kidx);
         const bool more = kidx + kDecodeWaves < nts;            // wave-uniform

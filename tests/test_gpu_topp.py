@@ -136,3 +136,29 @@ def test_config2_size():
     """The 32K benchmark shape (2.1 M rows): every count, mask and kept entry checked, decode checked."""
     w = wl.config(2)
     _run(w, wl.generate(w))
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+@pytest.mark.parametrize("tiles", [2, 7, 19])
+@pytest.mark.parametrize("where", ["nowhere", "first", "later"])
+def test_rows_around_the_lengths_that_choose_the_score_method(G, tiles, where):
+    """Rows of exactly n entries, n on both sides of every limit of the tile-by-tile choice, for blocks of one, two and more
+    tiles a wavefront; one longer row in the block's first tiles, in a later one, or in none."""
+    for n in (32, 33, 48, 49, 64, 65, 72, 73, 80, 81):
+        w = wl.small(name=f"topplen{G}_{tiles}_{n}", batch=1, n_q_heads=G, n_kv_heads=1, seqlens=(64 * tiles - 5,), seed=330 + n)
+        t = wl.generate(w)
+        rng = np.random.default_rng(n)
+        rows = w.total
+        count = np.full(rows, min(n, 33 if where != "nowhere" else n))
+        if where != "nowhere":
+            for tile in (range(4) if where == "first" else range(4, tiles)):
+                if 64 * tile + 7 < rows:
+                    count[64 * tile + 7] = n
+        order = np.argsort(rng.random((rows, 128)), axis=1)
+        on = np.zeros((rows, 128), bool)
+        np.put_along_axis(on, order, np.arange(128)[None] < count[:, None], axis=1)
+        k = wl.bf16_bits_to_f32(t.k).copy()
+        k[0] = np.where(on, np.where(k[0] == 0, 1.0, k[0]), 0.0)
+        t.k = wl.f32_to_bf16_bits(k)
+        pr = _run(w, t, 10000, n_splits=1)                # every entry that is not zero is kept
+        assert pr.count.max() <= n + 1
