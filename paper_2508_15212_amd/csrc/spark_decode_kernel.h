@@ -531,9 +531,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     __shared__ __align__(16) uint32_t vmeta[(PV || MM) ? kDecodeWaves : 1][(PV || MM) ? SPARK_TILE_TOKENS * 8 : 1];
     __shared__ __align__(16) uint32_t vlut[(PV || MM) ? 256 * 4 : 1];
     __shared__ __align__(16) uint32_t vlutb[(PV || MM) ? 256 * 2 : 1];
-    // rows of varying length: first word of every row of the half tile in LDS; the query as it came
+    // rows of varying length: first word of every row of the half tile in LDS
     __shared__ uint32_t row_at[MM ? kDecodeWaves : 1][MM ? SPARK_TILE_TOKENS : 1];
-    __shared__ __align__(16) uint16_t qraw[MM ? G : 1][MM ? SPARK_D : 8];
     __shared__ float red_m[kDecodeWaves][G], red_l[kDecodeWaves][G];
     __shared__ int last_flag;
 
@@ -774,22 +773,22 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     };
     bf16x8 Aq[MM ? 4 : 1], Aqa[MM ? 4 : 1];     // A operands of the scores, one per 32 channels (see the score phase)
     uint32_t walk_limit = 0;                    // (see walk_limit_of; SPARK_D: all tiles are walked)
+    // Operands of the scores on the matrix cores: the query times a power of two, so that the products stay in range where
+    // the scores do, and q / a as the three bf16 numbers of eight bits each that its 24 bits fall into.  Both exact.  (Cut
+    // off, not rounded: the first part of a number just below the largest float32 would round to infinity.)
     auto make_operands = [&]() __attribute__((always_inline)) {
         const int g = cn & 3, part = cn >> 2;
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
-            uint4 qw = {0u, 0u, 0u, 0u};
-            if (g < G && part == 0) qw = *reinterpret_cast<const uint4 *>(&qraw[g][32 * kb + 8 * tg]);
-            Aq[kb] = __builtin_bit_cast(bf16x8, qw);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const int j = 32 * kb + 8 * tg + i;
-                const float x = g < G ? qt[j * GP + g] * qt[j * GP + G] : 0.0f;
-                const __bf16 hi = (__bf16)x;
-                const float x1 = x - (float)hi;
-                const __bf16 mid = (__bf16)x1;
-                const __bf16 lo = (__bf16)(x1 - (float)mid);
-                Aqa[kb][i] = part == 0 ? hi : (part == 1 ? mid : (part == 2 ? lo : (__bf16)0.0f));
+                const float q = g < G ? qt[j * GP + g] : 0.0f;
+                const float x = q * qt[j * GP + G];
+                const float hi = __uint_as_float(__float_as_uint(x) & 0xFFFF0000u), x1 = x - hi;
+                const float mid = __uint_as_float(__float_as_uint(x1) & 0xFFFF0000u);
+                Aq[kb][i] = (__bf16)(part == 0 ? q : 0.0f);
+                Aqa[kb][i] = (__bf16)(part == 0 ? hi : (part == 1 ? mid : (part == 2 ? x1 - mid : 0.0f)));
             }
         }
     };
@@ -873,7 +872,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
                     // costs 24 instructions for every entry of its LONGEST row; here the rows are spread to dense bf16 pieces
                     // of eight channels, as packed values are, at a cost that does not depend on what they keep, and two
                     // matrix products take the sums:
-                    //     q . k over the kept entries       B = the pieces, A = the query (bf16, as it came: exact products)
+                    //     q . k over the kept entries       B = the pieces, A = the query (bf16: exact products)
                     //     sum of q_j / a_j over them        B = the pieces with 1.0 for every kept entry, A = q_j / a_j as
                     //                                       three bf16 parts, which together are its float32 value
                     // B operands: lane (tg, cn) = channels 8 tg .. 8 tg + 7 of a block of 32 of token 16 tau + cn.  A operands:
@@ -970,7 +969,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
                     for (int g = 0; g < G; ++g) {
                         const float kept = reduce_scatter_rows(qm[0][g], qm[1][g], qm[2][g], qm[3][g]);
                         const float dot = reduce_scatter_rows(qk[0][g], qk[1][g], qk[2][g], qk[3][g]);
-                        s[g] = fmaf(dot, q_scale, mu * (R[g] - kept));
+                        s[g] = fmaf(mu, R[g] - kept, dot);
                     }
                 }
                 if (!mat) {
@@ -1665,7 +1664,6 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             qt[j * GP + g] = bf16lo(q_r[g]) * q_scale;
-            if constexpr (MM) qraw[g][j] = q_r[g];
             if constexpr (REC != 0) qa[j * G + g] = bf16lo(q_r[g]) * P.scale_log2 * inva_r;
         }
         qt[j * GP + G] = inva_r;
@@ -1680,8 +1678,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         if (lane == 0) Rsh[g] = r;
     }
     __syncthreads();
+    // (top-p: in scalar registers; with them in vector registers the tile loop spills at four query heads)
 #pragma unroll
-    for (int g = 0; g < G; ++g) R[g] = Rsh[g];
+    for (int g = 0; g < G; ++g) R[g] = MM ? __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(Rsh[g]))) : Rsh[g];
     if (P.trace != nullptr) { stamp(P, 1, wall_clock64()); stamp(P, 5, (unsigned long long)nts); }
     if constexpr (MM) {
         // The operands are made where the wavefront's first tile needs them; another wavefront walks all of its tiles.

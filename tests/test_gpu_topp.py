@@ -162,3 +162,64 @@ def test_rows_around_the_lengths_that_choose_the_score_method(G, tiles, where):
         t.k = wl.f32_to_bf16_bits(k)
         pr = _run(w, t, 10000, n_splits=1)                # every entry that is not zero is kept
         assert pr.count.max() <= n + 1
+
+
+def _decode_scaled(w, t, scale):
+    _, _, a32 = oracle.window_stat(t.qwin, 1)
+    pr = oracle.prune_topp(t.k, t.layout, a32, t.cu, 9900)
+    assert (pr.count > 72).any()                          # (taken on the matrix cores)
+    desc = make_desc(w, "HND")
+    desc.softmax_scale = scale
+    packed = torch.zeros(spark.packed_topp_bytes(desc), dtype=torch.uint8, device="cuda")
+    dcu = torch.from_numpy(np.asarray(t.cu, np.int32)).cuda()
+    spark.prune_topp(desc, to_dev(t.k), to_dev(t.qwin), dcu, 9900, packed)
+    out = torch.empty((1, w.n_q_heads, 128), dtype=torch.float32, device="cuda")
+    spark.decode_attn_topp(desc, to_dev(t.q), packed, to_dev(t.v), dcu, out, spark.new_decode_workspace(desc))
+    err = np.abs(out.cpu().numpy().astype(np.float64) - oracle.decode_literal(t.q, pr, t.v, t.layout, t.cu, scale=scale))
+    print(f"{w.name}: max|err|={err.max():.3e}")
+    assert err.max() <= MAX_ABS
+    return pr, a32
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_query_over_weight_near_the_largest_float(G):
+    """q * scale / a of one channel lies between the largest bf16 and the largest float32 number: the parts that the matrix
+    cores take it in must not round to infinity.  The channel is pruned everywhere, so the scores of that query head are
+    its recovered entry's, and the token with the largest mean takes the softmax."""
+    w = wl.small(name=f"topplarge{G}", batch=1, n_q_heads=G, n_kv_heads=1, window=32, seqlens=(300,), seed=350 + G)
+    t = wl.generate(w)
+    qwin = np.asarray(t.qwin).copy()                      # [1, G, 32, 128], bf16 bits; 32 is 2^-128
+    qwin[..., 5] = 32
+    qwin[0, 0, 0, 5] = 33                                 # 1/a just below 2^128
+    t.qwin = qwin
+    q = np.asarray(t.q).copy()
+    q[..., 5] = 0
+    q[:, 0, 5] = 0x4100                                   # 8.0
+    t.q = q
+    pr, a32 = _decode_scaled(w, t, 1.0001 / 8.0 / 1.4426950408889634)     # scale * log2(e) * q just above 1
+    assert 3.3963e38 < 1.0 / float(a32[0, 0, 5]) < 1.0001 / float(a32[0, 0, 5]) < 3.4028e38
+    assert not (pr.mask[..., 0] >> 5 & 1).any()
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_scores_that_only_the_scale_brings_into_range(G):
+    """The largest q . k is beyond float32, times the softmax scale it is not."""
+    w = wl.small(name=f"toppbig{G}", batch=1, n_q_heads=G, n_kv_heads=1, seqlens=(300,), seed=353 + G)
+    t = wl.generate(w)
+    k = wl.bf16_bits_to_f32(t.k) * np.float32(2.0 ** 116)
+    q = wl.bf16_bits_to_f32(t.q) * np.float32(2.0 ** 12)
+    scale = 2.0 ** -13
+    t.k, t.q = wl.f32_to_bf16_bits(k), wl.f32_to_bf16_bits(q)
+    raw = np.abs(np.einsum("gd,nd->gn", q[0].astype(np.float64), k[0].astype(np.float64))).max()
+    assert raw > 2.0 ** 129 and raw * scale * 1.45 < 2.0 ** 124
+    _decode_scaled(w, t, scale)
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_channel_weights_near_the_largest_float(G):
+    """Window queries scaled by 2^118 and keys by 2^-8: q / a is so small that its lower bf16 parts are subnormal."""
+    w = wl.small(name=f"topptiny{G}", batch=1, n_q_heads=G, n_kv_heads=1, seqlens=(300,), seed=356 + G)
+    t = wl.generate(w)
+    t.qwin = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(t.qwin) * np.float32(2.0 ** 118))
+    t.k = wl.f32_to_bf16_bits(wl.bf16_bits_to_f32(t.k) * np.float32(2.0 ** -8))
+    _decode_scaled(w, t, float(2.0 ** 8 / np.sqrt(128.0)))
