@@ -11,7 +11,8 @@
 //                             step; two steps a group), lane i of sixteen holds channels 8i .. 8i + 7.  A reduction
 //                             over a row is four lane moves that serve four rows, slots and sums are per lane, and
 //                             next to nothing of a row goes through the scalar unit.  Per row:
-//     1. saliencies as float32 bit patterns; their top 15 bits (exponent, seven mantissa bits) are the DIGIT.
+//     1. saliencies as float32 bit patterns; their top 15 bits (exponent, seven mantissa bits; fewer for the
+//        smallest and the largest T) are the DIGIT.
 //     2. one counting pass over 120 LDS bins of one digit each, 0.94 octaves around the place where the T-th largest is
 //        expected: the row's mean digit, i.e. the logarithm of its geometric mean, plus an offset that follows the
 //        rows before.  (Over rows of Gaussian keys the T-th digit stays within 0.44 octaves of that in 98.5 to
@@ -109,6 +110,21 @@ __device__ __forceinline__ uint32_t lds_address(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 __device__ __forceinline__ lds_u32 *lds_word(uint32_t byte_address) { return (lds_u32 *)(uintptr_t)byte_address; }
+
+// Bits of a key below its digit.  The T-th of 128 saliencies strays further from the row's mean the closer T is to either
+// end, and fewer keys are near it.  With 128 digits an octave the window misses it in at most one step of four rows in 30
+// from T = 12 to 99, but in 30 % at 112, 70 % at 120, 93 % at 127, and in 30 to 85 % at 8 and below where some channels are
+// much larger than the others.  Half, a quarter and an eighth of the digits cut that to under 1 % (T = 1: 4 %; 120: under
+// 1 %; 127: 4 %); in the middle they would only leave more keys of the T-th one's bin to be taken off one by one.
+// 131072 tokens x 8 heads, eight large channels, one digit / this (us): T = 4 141 / 78, 8 100 / 80, 104 110 / 105, 112
+// 126 / 109, 120 148 / 110, 127 176 / 116; values at 4 138 / 73, 8 90 / 78, 120 138 / 105.  (Few values of rows without
+// large channels are the worse for it: 4 of 128 78 / 85, 8 80 / 79.)
+__host__ __device__ inline uint32_t digit_shift_of(int T)
+{
+    if (T < 12) return T < 5 ? 18u : 17u;
+    if (T < 100) return 16u;
+    return T < 116 ? 17u : (T < 126 ? 18u : 19u);
+}
 
 // c - 4 a for a below 2^23 (one instruction)
 __device__ __forceinline__ int minus_4x(uint32_t a, int c)
@@ -265,6 +281,7 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
     const int64_t left = L.total_tokens - n0;
     const int nvalid = left < SPARK_TILE_TOKENS ? (int)left : SPARK_TILE_TOKENS;
     const uint32_t T = (uint32_t)L.T;
+    const uint32_t digit_shift = digit_shift_of(L.T);          // (in a scalar register)
     const int row = lane >> 4, sub = lane & 15;          // this lane: channels 8 sub .. 8 sub + 7 of row 4 s + row of the group
     const int sw = spark_stage_words(L);
     uint32_t *const stage = reinterpret_cast<uint32_t *>(smem) + (size_t)wave * (kStageRows * sw + kHistWords);
@@ -366,7 +383,7 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
         uint32_t keep_eq = 0;          // tied: how many of the keys == p are kept
         {
             const bool low = count >= T, inside = bin >= kOverBins;
-            uint32_t hi = low ? (inside ? p + 0x10000u : 0x80000000u) : min(p, 0x80000000u);
+            uint32_t hi = low ? (inside ? p + (1u << digit_shift) : 0x80000000u) : min(p, 0x80000000u);
             bracket(ks, T, p, hi, count, low, !low || inside, 1u, T + kCloseEnough + 1u);
         }
         for (uint32_t it = 0; it <= kCloseEnough; ++it) {
@@ -440,7 +457,7 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
                 uint32_t digit[8], dsum = 0;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) {
-                    digit[c] = key[s][c] >> 16;
+                    digit[c] = key[s][c] >> digit_shift;
                     dsum += digit[c];
                 }
                 mean[s] = (int)(row16_sum(dsum) >> 7);
@@ -450,9 +467,10 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
 #pragma unroll
                     for (int c = 0; c < 8; ++c) wide[c] = key[0][c] >> 20;
                     clear_bins();
-                    add_digits(wide, (mean[0] >> 4) + kTop, 1u);
+                    const uint32_t finer = 20u - digit_shift;
+                    add_digits(wide, (mean[0] >> finer) + kTop, 1u);
                     const int bin = kBins - (int)(bins_reached() & 0xFFFFu);
-                    offset = (((mean[0] >> 4) + kTop - bin) << 4) + 8 - mean[0];
+                    offset = (((mean[0] >> finer) + kTop - bin) << finer) + (1 << (finer - 1u)) - mean[0];
                     have_offset = true;
                     clear_bins();
                 }
@@ -464,7 +482,7 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
             for (int s = 0; s < kSteps; ++s) {
                 const uint32_t (&ks)[8] = key[s];
                 const int bin = kBins - (int)((reached >> (16 * s)) & 0xFFFFu);       // (kBins: below the window)
-                uint32_t p = (uint32_t)(mean[s] + offset + kTop - max(bin, kOverBins - 1)) << 16;
+                uint32_t p = (uint32_t)(mean[s] + offset + kTop - max(bin, kOverBins - 1)) << digit_shift;
                 uint64_t kb[8];
 #pragma unroll
                 for (int c = 0; c < 8; ++c) kb[c] = __ballot(ks[c] >= p);
@@ -499,7 +517,7 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
                         upto = row16_inclusive_sum((uint32_t)__popc(m));
                     }
                 }
-                learned += (int)(p >> 16) - mean[s];
+                learned += (int)(p >> digit_shift) - mean[s];
                 const uint32_t ra = row_a + (uint32_t)(g0 / 4 + s) * step_a;
                 *(lds_u8 *)(uintptr_t)(ra + (uint32_t)sub) = (uint8_t)m;
                 const uint32_t slot = ra + 4u * (uint32_t)L.val0 + 2u * (upto - (uint32_t)__popc(m));

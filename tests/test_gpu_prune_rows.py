@@ -73,3 +73,16 @@ def test_rows_the_counting_window_does_not_fit(kind, T):
     for int8 in (False, True):
         _keys(w, t, int8)
     _values(w, t, T)
+
+
+@pytest.mark.parametrize("T", [4, 5, 11, 12, 99, 100, 115, 116, 125, 126])
+@pytest.mark.parametrize("outliers", [0, 8])
+def test_keep_counts_where_the_digit_changes(T, outliers):
+    w = wl.small(name=f"rowsdigit{T}", keep=T, batch=3, seqlens=(130, 1, 95), n_outlier=outliers, seed=560 + T)
+    t = wl.generate(w)
+    k = wl.bf16_bits_to_f32(t.k).copy()
+    k[:, 40:60] *= np.exp2(np.random.default_rng(T).integers(-60, 60, (1, 20, 1))).astype(np.float32)
+    t.k = wl.f32_to_bf16_bits(k)
+    _keys(w, t)
+    _keys(w, t, int8=True, layout="NHD")
+    _values(w, t, T)
