@@ -146,3 +146,34 @@ def test_int8_storage_with_statistics_rows(kind, G, Hkv, T):
     spark.decode_attn(desc, dq, packed, dv, dcu, out, ws)
     ref0 = oracle.decode_literal(t.q, pq, t.v, t.layout, t.cu)
     assert np.abs(out.cpu().numpy().astype(np.float64) - ref0).max() <= MAX_ABS
+
+
+@pytest.mark.parametrize("kind", [spark.RECOVER_GAUSSIAN, spark.RECOVER_EXPONENTIAL])
+@pytest.mark.parametrize("seed,token,channel,bits", [(452, 55, 26, 0), (800, 30, 58, 0), (2652, 39, 5, 0),                      # smallest
+                                                     (1532, 30, 84, 0x7FFFFF), (3893, 44, 82, 0x7FFFFF), (2756, 59, 57, 0x7FFFFF)])  # largest
+def test_uniforms_at_their_two_ends(kind, seed, token, channel, bits):
+    """The smallest uniform (2^-24) and the largest (1 - 2^-24, whose logarithm is nearly zero) at a pruned channel of head 0,
+    in the place of a radius (even channels) and of an angle (odd ones)."""
+    m32 = 0xFFFFFFFF
+
+    def mix(x):
+        x ^= x >> 16
+        x = x * 0x85EBCA6B & m32
+        x ^= x >> 13
+        x = x * 0xC2B2AE35 & m32
+        return x ^ x >> 16
+
+    assert mix(mix(mix(mix(token) + seed & m32)) + channel * 0x9E3779B9 & m32) >> 9 == bits
+    w = wl.small(name=f"uniform{seed}", batch=1, n_q_heads=4, n_kv_heads=1, keep=26, seqlens=(64,), seed=700 + seed)
+    t = wl.generate(w)
+    k = np.asarray(t.k).copy()
+    k[0, token, channel] = 0                               # pruned there
+    t.k = k
+    t, pr, mu, sigma, desc, packed, dv, dq, dcu = _setup(w, t)
+    assert not pr.mask[token, 0, channel // 32] >> (channel % 32) & 1
+    ref = oracle.decode_sampled(kind, seed, t.q, pr, mu, sigma, t.v, t.layout, t.cu)
+    out = torch.empty((1, 4, 128), dtype=torch.float32, device="cuda")
+    spark.decode_attn_sampled(desc, dq, packed, dv, dcu, out, spark.new_decode_workspace(desc), kind, seed)
+    err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
+    print(f"{w.name}: max|err|={err.max():.3e}")
+    assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
