@@ -326,8 +326,8 @@ __device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h
     // All of the wavefront's rows are requested at once, keys first (lane = row, past the last one the last), then values
     // (lane = channels 2l, 2l+1): the block waits for memory about once.  Fetching four pieces of a key row and eight
     // value rows at a time, a dozen round trips one after the other, made this block the longest of a short batch: four
-    // sequences of 700 to 3900 tokens with up to 256 appended rows took 21.6 us and take 15.6 us, as without appended
-    // rows.
+    // sequences of 700 to 3900 tokens with up to 256 appended rows took 21.7 us and take 17.3 us (medians; the shortest
+    // launches 21.2 and 15.6 us).
     // (Sixteen query heads leave no registers for that and keep the small pieces.)
     constexpr int NK = (G <= 8) ? SPARK_D / 8 : 4, NV = (G <= 8) ? 64 : 8;
     uint4 kx[NK];

@@ -26,7 +26,8 @@
 //   What bounds it: vector issue.  45 vector and 19 scalar instructions a row (with one row at a time, two channels a lane,
 //   41 and 37, and both units were at their limit).  One sequence of 131072 tokens x 8 KV heads, T = 26: 101 -> 87 us
 //   (4.0 TB/s); 64 ragged sequences, T = 64: 66 -> 61 us; 40003 tokens, int8 codes: 46 -> 40 us; values, T_v = 38:
-//   36 -> 34 us; 1024 tokens (one wavefront took a whole tile): 23 -> 10 us.  Four steps a group (fewer instructions,
+//   36 -> 34 us; 1024 tokens (one wavefront took a whole tile): 23 -> 10 us.  (Back to back on one input, of which a part
+//   stays in the memory-side cache.  With inputs that rotate, 8 x 32768 tokens, T = 26: 191 -> 175 us.)  Four steps a group (fewer instructions,
 //   43, but registers for four wavefronts per SIMD only) took 93 us instead of 86.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(8 * SPARK_D) void spark_window_stat_kernel(const ui
 constexpr int kPruneWaves = 4;      // wavefronts per block, each on its own rows
 constexpr int kSteps = 2;           // a GROUP is what a wavefront takes at a time: two STEPS of four rows, sixteen lanes a row
 constexpr int kGroup = 4 * kSteps;
-constexpr int kStageRows = 16;      // rows put together in LDS before they are written out
+constexpr int kStageRows = 16;      // a STAGE: the rows put together in LDS before they are written out
 constexpr int kOverBins = 8;        // bins that collect the keys above the window (lane 0's)
 constexpr int kBins = 128;          // eight a lane; the window is the 120 digits that follow
 constexpr int kBinStride = kBins + 16;      // words per row of a step: the bins, then one spare word per lane
@@ -243,7 +244,8 @@ __device__ __forceinline__ void bracket(const uint32_t (&key)[8], uint32_t T, ui
     }
 }
 
-// 2^lg_per_tile wavefronts (1, 2 or 4) share a tile; each takes its rows sixteen at a time, a GROUP.
+// 2^lg_per_tile wavefronts (1, 2 or 4) share a tile; each takes its rows a group (eight) at a time and writes them
+// out a stage (sixteen, two groups) at a time.
 // MODE: bit 0 = int8 codes + scale instead of bf16 kept entries; bit 1 = the rows also carry the all-channel mean
 // and standard deviation of the row's saliencies (App. "Caching Pruned Channel Statistics", for the sampled recovery).
 // VALUES: the rows are value-cache rows (App. "Pruning Value Cache Channels"): the score of a channel is
@@ -275,7 +277,7 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
     const int h = (int)(gt / (uint32_t)L.n_tiles);
     const int64_t tile = gt - (uint32_t)h * (uint32_t)L.n_tiles;
     const int rows = SPARK_TILE_TOKENS >> lg_per_tile;          // (a multiple of kStageRows)
-    int t0 = (int)(wt & ((1u << lg_per_tile) - 1u)) * rows;     // first row of the group in hand
+    int t0 = (int)(wt & ((1u << lg_per_tile) - 1u)) * rows;     // first row of the stage in hand
     const int t_end = t0 + rows;
     const int64_t n0 = tile * SPARK_TILE_TOKENS;
     const int64_t left = L.total_tokens - n0;
@@ -555,7 +557,7 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
             }
         }
         prune_lds_sync();
-        // ---- the staged rows leave: lane = (row of the group, one of four sections at a time)
+        // ---- the staged rows leave: lane = (row of the stage, one of four sections at a time)
         {
             const int rw = lane & 15, part = lane >> 4;
             uint32_t *const r = stage + rw * sw;
@@ -689,9 +691,11 @@ hipError_t launch_tiles(const uint16_t *x, int64_t tok_stride, int64_t head_stri
     if (tiles == 0) return hipSuccess;
     if (tiles >= ((int64_t)1 << 30)) return hipErrorInvalidValue;
     // Wavefronts per tile.  One has the least set-up, but few tiles then leave the chip idle: with four, up to 1536 tiles
-    // are still resident at once (six wavefronts per SIMD).  Measured with 1 / 2 / 4 at T = 26 (us, the window kernel
-    // included): 128 tiles 20.5 / 15.2 / 13.3, 1536: 26 / 20 / 19, 4096: 34.5 / 32.1 / 32.2, 8192: 53 / 51 / 54,
-    // 12288: 67 / 69 / 74, 16384: 86 / 88 / 97.
+    // are still resident at once (six wavefronts per SIMD).  Measured with 1 / 2 / 4 for bf16 keys at T = 26 (us, the window
+    // kernel included): 128 tiles 20.5 / 15.2 / 13.3, 1536: 26 / 20 / 19, 4096: 34.5 / 32.1 / 32.2, 8192: 53 / 51 / 54,
+    // 12288: 67 / 69 / 74, 16384: 86 / 88 / 97.  Values, int8 rows and rows with statistics follow the same lines; for
+    // them only the result was measured (13 to 16384 tiles, T = 1 to 128, against one wavefront a tile, one row at a
+    // time: 0.2 to 1.0 of its time, values with T_v <= 12 up to 1.2).
     const int lg_per_tile = tiles <= 1536 ? 2 : (tiles <= 10240 ? 1 : 0);
     const int64_t waves = tiles << lg_per_tile;
     auto launch = [&](auto kern) -> hipError_t {
