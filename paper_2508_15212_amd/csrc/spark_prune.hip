@@ -120,7 +120,7 @@ __device__ __forceinline__ lds_u32 *lds_word(uint32_t byte_address) { return (ld
 // 131072 tokens x 8 heads, eight large channels, one digit / this (us): T = 4 141 / 78, 8 100 / 80, 104 110 / 105, 112
 // 126 / 109, 120 148 / 110, 127 176 / 116; values at 4 138 / 73, 8 90 / 78, 120 138 / 105.  (Few values of rows without
 // large channels are the worse for it: 4 of 128 78 / 85, 8 80 / 79.)
-__host__ __device__ inline uint32_t digit_shift_of(int T)
+__host__ inline uint32_t digit_shift_of(int T)
 {
     if (T < 12) return T < 5 ? 18u : 17u;
     if (T < 100) return 16u;
@@ -253,7 +253,7 @@ __device__ __forceinline__ void bracket(const uint32_t (&key)[8], uint32_t T, ui
 template <int MODE, bool VALUES>
 __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
     const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
-    uint8_t *__restrict__ packed, SparkLayout L, int lg_per_tile)
+    uint8_t *__restrict__ packed, SparkLayout L, int lg_per_tile, uint32_t digit_shift)
 {
     constexpr bool INT8 = (MODE & 1) != 0, STATS = (MODE & 2) != 0;
     extern __shared__ __align__(16) uint8_t smem[];
@@ -283,7 +283,6 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
     const int64_t left = L.total_tokens - n0;
     const int nvalid = left < SPARK_TILE_TOKENS ? (int)left : SPARK_TILE_TOKENS;
     const uint32_t T = (uint32_t)L.T;
-    const uint32_t digit_shift = digit_shift_of(L.T);          // (in a scalar register)
     const int row = lane >> 4, sub = lane & 15;          // this lane: channels 8 sub .. 8 sub + 7 of row 4 s + row of the group
     const int sw = spark_stage_words(L);
     uint32_t *const stage = reinterpret_cast<uint32_t *>(smem) + (size_t)wave * (kStageRows * sw + kHistWords);
@@ -700,7 +699,8 @@ hipError_t launch_tiles(const uint16_t *x, int64_t tok_stride, int64_t head_stri
     const int64_t waves = tiles << lg_per_tile;
     auto launch = [&](auto kern) -> hipError_t {
         hipLaunchKernelGGL(kern, dim3((unsigned)((waves + kPruneWaves - 1) / kPruneWaves)), dim3(kPruneWaves * 64),
-                           spark_prune_lds_bytes(L), st, x, tok_stride, head_stride, cu, packed, L, lg_per_tile);
+                           spark_prune_lds_bytes(L), st, x, tok_stride, head_stride, cu, packed, L, lg_per_tile,
+                           digit_shift_of(L.T));
         return hipGetLastError();
     };
     switch (VALUES ? 0 : (L.int8 ? 1 : 0) + (L.stats ? 2 : 0)) {
