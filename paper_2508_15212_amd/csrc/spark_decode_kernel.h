@@ -456,18 +456,20 @@ constexpr int kShortRow = G <= 4 ? 52 : 44;
 // by entry, another one's scores are taken on the matrix cores (see the score phase).  The walk's cost follows the longest
 // row, the other form's does not, and it needs operands prepared and more memory round trips a tile, so the line also
 // depends on the tiles a block has.  Measured, walk / matrix cores (us, every row keeping about the stated number):
-//   G = 4, four tiles a wavefront (64 x 300..1700 tokens):  24: 45.2 / 54.2   31: 49.3 / 54.0   38: 55.1 / 54.6   60: 68.4 / 55.9
-//          two tiles (3 x 8000):    31: 22.3 / 24.9   38: 25.3 / 25.1   60: 28.0 / 25.7
-//          one tile (8 x 500..1500):  31: 13.9 / 16.4   53: 16.0 / 16.2   60: 16.9 / 16.1   68: 17.4 / 18.8   75: 18.2 / 16.9
-//   G = 2, four tiles: 46: 54.3 / 54.5   53: 58.5 / 53.8   two: 60: 25.9 / 26.7   75: 29.0 / 27.1   one: 68: 16.0 / 17.6   75: 16.5 / 15.9
-//   G = 1, four tiles: 46: 52.6 / 51.3   53: 54.9 / 51.3   two: 60: 25.0 / 25.1   68: 26.0 / 25.2   one: 75: 15.3 / 16.2   89: 16.4 / 15.7
+//   G = 4, four tiles a wavefront (64 x 300..1700 tokens):  31: 49.1 / 52.9   38: 55.2 / 53.7   46: 59.3 / 54.7   60: 68.3 / 55.1
+//          two tiles (3 x 8000):      31: 22.5 / 24.5   38: 25.2 / 24.8   60: 28.1 / 25.3
+//          one tile (8 x 500..1500):  31: 14.2 / 16.0   53: 16.3 / 16.2   60: 16.6 / 16.2   68: 17.5 / 19.0   75: 18.2 / 16.8
+//   G = 2, four tiles: 35: 50.5 / 54.1   42: 53.6 / 50.9   53: 58.6 / 51.4
+//          two: 35: 22.6 / 23.9   42: 23.9 / 23.3   53: 25.0 / 23.5   one: 60: 15.2 / 15.0   68: 16.1 / 16.9   75: 16.6 / 15.5
+//   G = 1, four tiles: 35: 47.2 / 50.7   42: 48.8 / 49.0   46: 53.2 / 48.8
+//          two: 42: 21.3 / 22.8   49: 22.8 / 23.0   60: 25.5 / 23.0   one: 60: 14.5 / 14.7   75: 15.6 / 15.9   89: 16.4 / 15.7
 // (Rows of nearly 64 entries each, 68 above, start in few banks; rows whose lengths vary more do not.)
 template <int G>
 __device__ __forceinline__ uint32_t walk_limit_of(int tiles_of_block)
 {
     if (tiles_of_block <= kDecodeWaves) return G == 1 ? 80u : (G == 2 ? 72u : 56u);
-    if (tiles_of_block <= 2 * kDecodeWaves) return G == 1 ? 64u : (G == 2 ? 72u : 32u);
-    return G == 4 ? 32u : 48u;
+    if (tiles_of_block <= 2 * kDecodeWaves) return G == 1 ? 48u : (G == 2 ? 40u : 32u);
+    return G == 4 ? 32u : 40u;
 }
 
 // Timeline of a launch (a measurement aid, off unless a buffer has been given through spark_decode_timeline):

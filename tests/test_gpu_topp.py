@@ -144,7 +144,7 @@ def test_config2_size():
 def test_rows_around_the_lengths_that_choose_the_score_method(G, tiles, where):
     """Rows of exactly n entries, n on both sides of every limit of the tile-by-tile choice, for blocks of one, two and more
     tiles a wavefront; one longer row in the block's first tiles, in a later one, or in none."""
-    for n in (32, 33, 48, 49, 64, 65, 72, 73, 80, 81):
+    for n in (32, 33, 40, 41, 48, 49, 56, 57, 64, 65, 72, 73, 80, 81):
         w = wl.small(name=f"topplen{G}_{tiles}_{n}", batch=1, n_q_heads=G, n_kv_heads=1, seqlens=(64 * tiles - 5,), seed=330 + n)
         t = wl.generate(w)
         rng = np.random.default_rng(n)
