@@ -51,6 +51,11 @@ __global__ __launch_bounds__(8 * SPARK_D) void spark_window_stat_kernel(const ui
 {
     __shared__ double absmean[16][SPARK_D];
     const int bh = blockIdx.x;
+    if (L.topp) {          // the directory of the value streams starts empty (see spark_topp_prune_kernel)
+        uint32_t *const dir = reinterpret_cast<uint32_t *>(packed + L.off_dir);
+        const int64_t n = (int64_t)L.n_kv_heads * (L.n_tiles + 1);
+        for (int64_t i = (int64_t)bh * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) dir[i] = 0u;
+    }
     const int b = bh / Hkv, h = bh % Hkv;
     const int j = threadIdx.x % SPARK_D, g0 = threadIdx.x / SPARK_D;
     const int G = Hq / Hkv, GT = blockDim.x / SPARK_D;      // GT = min(G, 8) head slots
@@ -102,15 +107,6 @@ constexpr int kOverBins = 8;        // bins that collect the keys above the wind
 constexpr int kBins = 128;          // eight a lane; the window is the 120 digits that follow
 constexpr int kBinStride = kBins + 16;      // words per row of a step: the bins, then one spare word per lane
 constexpr int kHistWords = 4 * kBinStride;  // per wavefront
-
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-// LDS byte address of a pointer into shared memory, and back
-__device__ __forceinline__ uint32_t lds_address(const void *p)
-{
-    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
-}
-__device__ __forceinline__ lds_u32 *lds_word(uint32_t byte_address) { return (lds_u32 *)(uintptr_t)byte_address; }
 
 // Bits of a key below its digit.  The T-th of 128 saliencies strays further from the row's mean the closer T is to either
 // end, and fewer keys are near it.  With 128 digits an octave the window misses it in at most one step of four rows in 30
@@ -197,11 +193,6 @@ __device__ __forceinline__ float stage_row(uint32_t slot, const uint4 &x, const 
 #undef SPARK_STAGE_SUM
 #undef SPARK_STAGE
     return (s0 + s1) + (s2 + s3);
-}
-
-__device__ __forceinline__ uint32_t min8(const uint32_t (&x)[8])
-{
-    return min(min(min(x[0], x[1]), min(x[2], x[3])), min(min(x[4], x[5]), min(x[6], x[7])));
 }
 
 // keys >= x of a row (the same in its sixteen lanes)

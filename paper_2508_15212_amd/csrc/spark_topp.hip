@@ -9,25 +9,27 @@
 //     10000 * sum q  >=  p * (total of q),      i.e.   sum q >= need := ceil(p * total / 10000).
 // Exact in any summation order, which is what a parallel reduction needs.  Ties: lower channel first.
 //
-// Kernels (one block per tile of 64 tokens, four wavefronts of sixteen rows each, FOUR ROWS AT A TIME: sixteen lanes a
-// row, eight channels a lane, so that a reduction over a row is four lane moves that serve four rows, and nothing of
-// a row has to be wave-uniform)
-//   spark_topp_select_kernel  per row a selection ON SUMS: every lane adds the q of its channels to 128 LDS bins of an
-//                             eighth of an octave each, from the row's largest key down; a prefix sum over the bins
-//                             gives the bin in which the running sum reaches `need`, and the keys of that bin are
-//                             then taken one by one, largest first (1.4 of them on average, 2.0 for the slowest of four rows;
-//                             with four bins an octave 1.7 and 2.8).  A bin of which four keys or more are needed
-//                             is first cut into 64 finer ones, up to three times.  Writes the rows' fixed part
-//                             (mask, mean saliency of the pruned channels, count) and the tile's length in the
-//                             value stream.
-//   spark_topp_scan_kernel    prefix sum of the tile lengths of every KV head: the directory.
-//   spark_topp_pack_kernel    reads the dense key rows again; every lane finds the slots of its eight channels from
-//                             the row's mask bytes, the kept entries of sixteen rows are put together in LDS and
-//                             leave as whole words of the value stream.
-// What bounds them (one sequence of 65536 tokens x 8 KV heads, 51 kept channels a row): the selection is bound by
-// vector issue, 100 instructions a row, 71 us (150 us with one row at a time, two channels a lane, radix levels
-// of 64 bins and a wave-wide scan for each); the pack kernel by memory, 31 us for 134 MB read and 54 MB written
-// (47 us with one row at a time and 16-bit stores to memory); the scan is one load and one store's latency, 5 us.
+// Everything works on tiles of 64 tokens, four wavefronts of sixteen rows each, FOUR ROWS AT A TIME: sixteen lanes a row,
+// eight channels a lane, so that a reduction over a row is four lane moves that serve four rows, and nothing of a row has
+// to be wave-uniform.
+//   select_tile   per row a selection ON SUMS: every lane adds the q of its channels to 128 LDS bins of an eighth of an
+//                 octave each, from the row's largest key down; a prefix sum over the bins gives the bin in which the
+//                 running sum reaches `need`, and the keys of that bin are then taken one by one, largest first (1.4 of them
+//                 on average, 2.0 for the slowest of four rows; with four bins an octave 1.7 and 2.8).  A bin of which
+//                 four keys or more are needed is first cut into 64 finer ones, up to three times.  Writes the rows'
+//                 fixed part (mask, mean saliency of the pruned channels, count).
+//   write_tile    takes the dense key rows again; every lane finds the slots of its eight channels from the row's mask byte, the
+//                 kept entries of sixteen rows are put together in LDS and leave as whole words of the value stream.
+//   spark_topp_prune_kernel   both, for small and large calls, in one launch: a block selects a tile and then writes one that
+//                 was selected about 2048 tiles (over all heads) earlier, while one more block per head turns the
+//                 tiles' lengths into the directory as they arrive.
+//   spark_topp_select_kernel, spark_topp_scan_kernel, spark_topp_pack_kernel   the same one after the other, for calls in
+//                 between (measurements beside the launch).
+// What bounds them (one sequence of 65536 tokens x 8 KV heads, 51 kept channels a row): the selection by vector issue, 75 to 80
+// instructions a row, 62 us alone; the writing by memory, 31 us alone for 134 MB read and 54 MB written.  In one launch they
+// overlap: 100 -> 85 us for the whole call.  Tried: every block writing its own tile (137 us: it waits for the slowest
+// block in front, holding its place), blocks that stay and write a tile late from LDS (109 us), 8 blocks per compute unit
+// (spills, 109 us), 6 (90 us).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -46,7 +48,7 @@ constexpr int kSteps = kRowsPerWave / 4;      // four rows at a time
 // First counting level: eight bins an octave over the sixteen octaves below the top of the largest key's.
 constexpr int kBins = 128;
 constexpr int kBinsPerLane = kBins / 16;
-constexpr int kBinStride = 256;      // words per row: keys further down count past the bins that are read
+constexpr int kBinStride = kBins + 16;        // words per row: the bins, then one spare word per lane for keys further down
 
 // a saliency (float32 bits, sign clear) in units of 2^(emax - 150), rounded down; emax >= 1 and not below its exponent
 __device__ __forceinline__ uint32_t quantise(uint32_t bits, int emax)
@@ -56,47 +58,137 @@ __device__ __forceinline__ uint32_t quantise(uint32_t bits, int emax)
     return mant >> min(emax - e, 31);
 }
 
-__device__ __forceinline__ uint32_t min8(const uint32_t (&x)[8])
-{
-    return min(min(min(x[0], x[1]), min(x[2], x[3])), min(min(x[4], x[5]), min(x[6], x[7])));
-}
-
 // Where the running sum over the sixteen lanes' bins (NB a lane, in order) reaches `need`: the number of bins in
-// front of that one, and the sum over them.
+// front of that one, and the sum over them.  What is missing to `need`, less one, is followed instead of the sum: its sign
+// says that a bin has reached it (a byte permute makes bytes of all ones of two signs, a dot product of bytes counts
+// them), and its smallest value above -1, taken as unsigned, gives the sum.
 template <int NB>
 __device__ __forceinline__ void find_bin(const uint32_t *bins, uint32_t before, uint32_t need, uint32_t &n, uint32_t &above)
 {
-    uint32_t c = before, cnt = 0, below = 0;
+    uint32_t r = need - 1u - before, least = r;
+    int reached = 0;
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        c += bins[j];
-        const bool low = c < need;
-        cnt += low ? 1u : 0u;
-        below = low ? c : below;
+    for (int j = 0; j < NB; j += 2) {
+        const uint32_t r0 = r - bins[j], r1 = r0 - bins[j + 1];
+        r = r1;
+        least = min(least, min(r0, r1));
+        reached = __builtin_amdgcn_sdot4((int)__builtin_amdgcn_perm(r1, r0, 0x0C0C0B09u), 0x0000FFFF, reached, false);
     }
-    n = row16_sum(cnt);
-    above = row16_max(below);
+    n = 16u * NB - row16_sum((uint32_t)reached);
+    above = need - 1u - row16_min(least);
+}
+
+// Sum of the saliencies (float32 bits in key) that are NOT in the channels' wave masks.  The additions run under the masks'
+// complements; all lanes are active before and after.
+__device__ __forceinline__ float sum_pruned(const uint64_t (&kb)[8], const uint32_t (&key)[8])
+{
+    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;      // (sums by pairs: smaller rounding errors than one running sum's)
+#define SPARK_SUM(C, S) "s_not_b64 exec, %[k" C "]\n\tv_add_f32 %[" S "], %[" S "], %[w" C "]\n\t"
+    asm volatile(SPARK_SUM("0", "s0") SPARK_SUM("1", "s1") SPARK_SUM("2", "s2") SPARK_SUM("3", "s3") SPARK_SUM("4", "s0")
+                 SPARK_SUM("5", "s1") SPARK_SUM("6", "s2") SPARK_SUM("7", "s3") "s_mov_b64 exec, -1"
+                 : [s0] "+v"(s0), [s1] "+v"(s1), [s2] "+v"(s2), [s3] "+v"(s3)
+                 : [k0] "s"(kb[0]), [k1] "s"(kb[1]), [k2] "s"(kb[2]), [k3] "s"(kb[3]), [k4] "s"(kb[4]), [k5] "s"(kb[5]),
+                   [k6] "s"(kb[6]), [k7] "s"(kb[7]), [w0] "v"(key[0]), [w1] "v"(key[1]), [w2] "v"(key[2]), [w3] "v"(key[3]),
+                   [w4] "v"(key[4]), [w5] "v"(key[5]), [w6] "v"(key[6]), [w7] "v"(key[7])
+                 : "scc");
+#undef SPARK_SUM
+    return (s0 + s1) + (s2 + s3);
+}
+
+// What a tile's directory entry holds while the streams are being written: 0 (as cleared), the words of its own tile, or
+// the words of all tiles up to it, which is what it holds in the end.  No tile has more than 64 * 64 words or fewer than
+// one; a stream does not come near 2^32 words.
+constexpr uint32_t kOwnWords = 0xFFFFE000u;
+__device__ __forceinline__ uint32_t dir_load(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void dir_store(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// One wavefront follows a head's directory and turns the entries, as the blocks file them, into running sums.
+__device__ __forceinline__ void sum_directory(uint32_t *dir, int64_t n_tiles, int lane)
+{
+    constexpr int kAhead = 4;                            // entries a lane requests at a time
+    uint32_t sum = 0;
+    for (int64_t next = 1; next <= n_tiles;) {
+        uint32_t v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t i = next + 64 * u + lane;
+            v[u] = i <= n_tiles ? dir_load(dir + i) : 0u;
+        }
+        const int64_t start = next;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (next != start + 64 * u) break;           // (wave-uniform)
+            const uint64_t missing = ~__ballot(v[u] >= kOwnWords);
+            const int there = missing != 0ull ? (int)__builtin_ctzll(missing) : 64;
+            const uint32_t upto = wave_inclusive_sum(lane < there ? v[u] - kOwnWords : 0u);
+            if (lane < there) dir_store(dir + next + lane, sum + upto);
+            sum += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+            next += there;
+        }
+        if (next == start) __builtin_amdgcn_s_sleep(2);
+    }
+}
+
+// The kept ones of a lane's eight channels (x: two channels a word; m: their mask byte) go to the 16-bit places in
+// LDS that end at byte address `end`, in order.  The stores run under the channels' wave masks, taken off the byte
+// from its top bit on; all lanes are active before and after.
+__device__ __forceinline__ void stage_kept(uint32_t m, uint32_t end, const uint4 &x)
+{
+    m <<= 24;
+    asm volatile(
+#define SPARK_STAGE(STORE, X)                  \
+    "v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"   \
+    "s_mov_b64 exec, vcc\n\t"                  \
+    "v_add_u32 %[p], -2, %[p]\n\t"             \
+    STORE " %[p], " X "\n\t"                   \
+    "s_mov_b64 exec, -1\n\t"
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x3]")
+        SPARK_STAGE("ds_write_b16", "%[x3]")
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x2]")
+        SPARK_STAGE("ds_write_b16", "%[x2]")
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x1]")
+        SPARK_STAGE("ds_write_b16", "%[x1]")
+        SPARK_STAGE("ds_write_b16_d16_hi", "%[x0]")
+        SPARK_STAGE("ds_write_b16", "%[x0]")
+#undef SPARK_STAGE
+        : [m] "+v"(m), [p] "+v"(end)
+        : [x0] "v"(x.x), [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w)
+        : "memory", "vcc");
 }
 
 }  // namespace
 
-__global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
-    const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
-    uint8_t *__restrict__ packed, SparkLayout L, int p_bp)
+// header of the cache, by sixteen lanes (the channel weights are written by the window kernel that runs before)
+__device__ __forceinline__ void write_header(uint8_t *packed, const SparkLayout &L, int p_bp)
 {
-    __shared__ __align__(16) uint32_t hist_all[kWaves][4 * kBinStride];
-    __shared__ uint32_t words_of_wave[kWaves];
+    const int lane = threadIdx.x;
+    uint32_t v = 0;
+    if (lane == 0) v = SPARK_MAGIC;
+    if (lane == 3) v = (uint32_t)L.batch;
+    if (lane == 4) v = (uint32_t)L.n_kv_heads;
+    if (lane == 5) v = (uint32_t)L.total_tokens;
+    if (lane == 6) v = (uint32_t)L.ndw;
+    if (lane == 9) v = 1u;   // top-p cache
+    if (lane == 10) v = (uint32_t)p_bp;
+    reinterpret_cast<uint32_t *>(packed)[lane] = v;
+}
+
+// Selects the kept channels of a tile's rows: masks, means and counts; returns the words that the wavefront's rows take in the
+// stream.  Everything that another block reads is stored with device scope.
+__device__ __forceinline__ uint32_t select_tile(const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride,
+                                                const int32_t *__restrict__ cu, uint8_t *__restrict__ packed, const SparkLayout &L,
+                                                int p_bp, int h, int64_t tile, uint32_t *wave_lds)
+{
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane >> 4, sub = lane & 15;          // this lane: channels 8 sub .. 8 sub + 7 of row 4 s + row
-    const int h = (int)(blockIdx.x / (uint32_t)L.n_tiles);
-    const int64_t tile = blockIdx.x % (uint32_t)L.n_tiles;
     const int64_t n0 = tile * SPARK_TILE_TOKENS;
     const int64_t left = L.total_tokens - n0;
     const int nvalid = left < SPARK_TILE_TOKENS ? (int)left : SPARK_TILE_TOKENS;
     const int t0 = wave * kRowsPerWave;
     uint8_t *tile_out = packed + L.off_tiles + ((int64_t)h * L.n_tiles + tile) * L.tile_bytes;
     uint32_t my_mu = 0, my_cnt = 0;      // lane 16 row + s (s < kSteps): mean pruned saliency and count of row t0 + 4 s + row
+    uint32_t masks = 0;                  // mask byte of step s in byte s
 
     if (t0 < nvalid) {
         // all of the wavefront's rows are requested at once; rows past the last token repeat it
@@ -126,7 +218,9 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
             a[4] = hi.x; a[5] = hi.y; a[6] = hi.z; a[7] = hi.w;
         };
         load_a();
-        uint32_t *const hist = hist_all[wave] + row * kBinStride;
+        uint32_t *const hist = wave_lds + row * kBinStride;
+        const uint32_t hist_a = lds_address(hist);
+        const uint32_t below = ((uint32_t)(kBins + sub) << 20) | 0xFFFFFu;      // the lane's spare word, as a distance
 
 #pragma unroll
         for (int s = 0; s < kSteps; ++s) {
@@ -151,16 +245,22 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
             const uint32_t kmax = row16_max(max(max(max(key[0], key[1]), max(key[2], key[3])), max(max(key[4], key[5]), max(key[6], key[7]))));
             const int emax = max((int)(kmax >> 23), 1);
             // Bins are laid out from the top of the largest key's octave down: bin (top - key) >> 20 holds an eighth of
-            // an octave, and an eighth of its number is the distance of the exponents, which is what a saliency is
-            // shifted by.
+            // an octave.
             const uint32_t top = kmax | 0x7FFFFFu;
-            uint32_t q[8], bin[8], total = 0;
+            uint32_t q[8], total = 0;
+            // In units of the largest key's last place, rounded down: a product with a power of two, which is exact, and a
+            // conversion that cuts off.  (Rows whose largest key is too small for that power, and keys that are no numbers, are
+            // taken apart instead.)
+            const bool plain = __ballot(kmax - (24u << 23) >= (255u - 24u) << 23) == 0ull;
+            const float unit = __uint_as_float((uint32_t)(277 - emax) << 23);
+            auto units_of = [&](uint32_t bits) __attribute__((always_inline)) {
+                uint32_t u;
+                if (__builtin_expect(plain, 1)) u = (uint32_t)(__uint_as_float(bits) * unit); else u = quantise(bits, emax);
+                return u;
+            };
+            if (__builtin_expect(plain, 1)) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) bin[c] = min(top - key[c], 255u << 20) >> 20;
-            if (__builtin_expect(__ballot(kmax < (24u << 23)) == 0ull, 1)) {
-                // (no subnormal saliency is worth a unit here, so the implied bit needs no test)
-#pragma unroll
-                for (int c = 0; c < 8; ++c) q[c] = ((key[c] & 0x7FFFFFu) | 0x800000u) >> (bin[c] >> 3);
+                for (int c = 0; c < 8; ++c) q[c] = (uint32_t)(__uint_as_float(key[c]) * unit);
             } else {
 #pragma unroll
                 for (int c = 0; c < 8; ++c) q[c] = quantise(key[c], emax);
@@ -170,7 +270,10 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
             prune_lds_sync();
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                atomicAdd(&hist[bin[c]], q[c]);
+                const uint32_t bin = min(top - key[c], below) >> 20;
+                uint32_t at;
+                asm("v_lshl_add_u32 %0, %1, 2, %2" : "=v"(at) : "v"(bin), "v"(hist_a));     // (written out: the compiler takes one more)
+                __hip_atomic_fetch_add(lds_word(at), q[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
                 total += q[c];
             }
             prune_lds_sync();
@@ -218,7 +321,7 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
 #pragma unroll
                 for (int c = 0; c < 8; ++c) dist[c] = upper - key[c];        // (keys >= hi wrap round)
                 theta = upper - row16_min(min8(dist));
-                q_theta = quantise(theta, emax);
+                q_theta = units_of(theta);
                 n_eq = 0;
 #pragma unroll
                 for (int c = 0; c < 8; ++c) n_eq += __popcll(__ballot(key[c] == theta));
@@ -259,50 +362,179 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
             }
             const uint32_t m = byte_of_masks(kb);
             const uint32_t cnt = row16_sum((uint32_t)__popc(m));
-            float gone[8];           // (summed by pairs: smaller rounding errors than one running sum's)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) gone[c] = __builtin_amdgcn_inverse_ballot_w64(kb[c]) ? 0.0f : __uint_as_float(key[c]);
-            const float psum = row16_sum_f32(((gone[0] + gone[1]) + (gone[2] + gone[3])) + ((gone[4] + gone[5]) + (gone[6] + gone[7])));
-            // mask bytes in channel order (rows past the last token: empty mask)
-            tile_out[t * 16 + sub] = (uint8_t)(t < nvalid ? m : 0u);
+            const uint32_t psum = __float_as_uint(row16_sum_f32(sum_pruned(kb, key)));
+            masks |= (t < nvalid ? m : 0u) << (8 * s);       // (rows past the last token: empty mask)
             if (sub == s) {
-                my_mu = __float_as_uint(psum);
+                my_mu = psum;
                 my_cnt = cnt;
             }
         }
-    } else {
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s) tile_out[(t0 + 4 * s + row) * 16 + sub] = 0;
     }
 
-    // ---- the rest of the rows' fixed part (rows past the last token: mean 0, count 0)
+    // ---- the rows' fixed part (rows past the last token: mean 0, count 0).  The mask bytes are put in order in LDS.
+    prune_lds_sync();
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) reinterpret_cast<uint8_t *>(wave_lds)[64 * s + lane] = (uint8_t)(masks >> (8 * s));
+    prune_lds_sync();
+    __hip_atomic_store(reinterpret_cast<uint32_t *>(tile_out) + t0 * 4 + lane, wave_lds[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    prune_lds_sync();
     const int t = t0 + 4 * sub + row;
     const bool valid = sub < kSteps && t < nvalid;
     if (sub < kSteps) {
         const float mu = my_cnt < SPARK_D ? __uint_as_float(my_mu) / (float)(SPARK_D - my_cnt) : 0.0f;
-        *reinterpret_cast<uint2 *>(tile_out + 1024 + t * 8) = make_uint2(valid ? __float_as_uint(mu) : 0u, valid ? my_cnt : 0u);
+        __hip_atomic_store(reinterpret_cast<uint64_t *>(tile_out + 1024 + t * 8),
+                           valid ? (uint64_t)__float_as_uint(mu) | ((uint64_t)my_cnt << 32) : 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // words this tile takes in the head's value stream (every row rounded up to a whole word)
-    const uint32_t words = wave_inclusive_sum(valid ? (my_cnt + 1u) / 2u : 0u);
-    if (lane == 63) words_of_wave[wave] = words;
+    // (every row rounded up to a whole word)
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(valid ? (my_cnt + 1u) / 2u : 0u), 63);
+}
+
+// The dense rows of a tile that are to be written, requested: sixteen a wavefront, rows past the last token repeat it.
+__device__ __forceinline__ void request_rows(const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const SparkLayout &L,
+                                             int h, int64_t tile, uint4 (&x)[kSteps])
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t n0 = tile * SPARK_TILE_TOKENS;
+    const int64_t left = L.total_tokens - n0;
+    const int nvalid = left < SPARK_TILE_TOKENS ? (int)left : SPARK_TILE_TOKENS;
+    const uint16_t *kbase = k + n0 * k_tok_stride + (int64_t)h * k_head_stride + 8 * (lane & 15);
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        const int t = wave * kRowsPerWave + 4 * s + (lane >> 4);
+        x[s] = *reinterpret_cast<const uint4 *>(kbase + (int64_t)(t < nvalid ? t : nvalid - 1) * k_tok_stride);
+    }
+}
+
+// Writes the kept entries (rows in x) of a tile whose rows have been selected, by any block, to its place in the head's
+// stream: every lane finds the slots of its eight channels from the row's mask byte, the entries of sixteen rows are put
+// together in LDS and leave as whole words.  `sum`: words of all tiles up to it.
+__device__ __forceinline__ void write_tile(const uint4 (&x)[kSteps], uint8_t *__restrict__ packed, const SparkLayout &L, int h, int64_t tile,
+                                           uint32_t sum, uint32_t *wave_lds)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane >> 4, sub = lane & 15;
+    const int t0 = wave * kRowsPerWave;
+    if (t0 >= L.total_tokens - tile * SPARK_TILE_TOKENS) return;       // (no block barrier is used)
+    const uint8_t *tp = packed + L.off_tiles + ((int64_t)h * L.n_tiles + tile) * L.tile_bytes;
+    const uint32_t word_of_mask = dir_load(reinterpret_cast<const uint32_t *>(tp) + t0 * 4 + lane);
+    const uint32_t cnt = dir_load(reinterpret_cast<const uint32_t *>(tp + 1024 + lane * 8 + 4));
+    prune_lds_sync();
+    wave_lds[lane] = word_of_mask;
+    prune_lds_sync();
+    uint32_t m[kSteps];
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) m[s] = reinterpret_cast<const uint8_t *>(wave_lds)[64 * s + lane];   // (past the last token: empty)
+    prune_lds_sync();
+    const uint32_t upto = wave_inclusive_sum((cnt + 1u) / 2u);       // lane = token: words of the tile's rows 0 .. token
+    const uint32_t base = sum - (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    const uint32_t first = t0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, t0 - 1) : 0u;
+    const uint32_t nwords = (uint32_t)__builtin_amdgcn_readlane((int)upto, t0 + kRowsPerWave - 1) - first;
+    const uint32_t stage_a = lds_address(wave_lds);
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+        const int t = t0 + 4 * s + row;
+        const uint32_t last = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * t, (int)upto) - first - 1u;    // the row's last word
+        const uint32_t kept = (uint32_t)__popc(m[s]);
+        const uint32_t kept_upto = row16_inclusive_sum(kept), kept_row = row16_last(kept_upto);
+        // (its upper half stays 0 where the count is odd; the entries are stored after it)
+        if (sub == 0 && kept_row != 0u) *lds_word(stage_a + 4u * last) = 0u;
+        prune_lds_sync();
+        stage_kept(m[s], stage_a + 4u * (last + 1u) - 2u * (kept_row + (kept_row & 1u)) + 2u * kept_upto, x[s]);
+    }
+    prune_lds_sync();
+    uint32_t *dst = reinterpret_cast<uint32_t *>(packed + L.off_vals) + (int64_t)h * L.vals_head_words + base + first;
+    for (uint32_t i = lane; i < nwords; i += 64) dst[i] = wave_lds[i];
+}
+
+// Blocks take tickets of their head in the order in which they start: ticket 0 sums the directory, ticket i selects tile
+// i - 1 and then writes the entries of tile i - 1 - lag, whose place in the stream is known by then as a rule; `lag` more
+// tickets only write.
+__global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_prune_kernel(
+    const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
+    uint8_t *__restrict__ packed, SparkLayout L, int p_bp, int lag)
+{
+    // per wavefront: counting bins of four rows, or the kept entries of sixteen
+    __shared__ __align__(16) uint32_t lds_all[kWaves][kRowsPerWave * SPARK_D / 2];
+    static_assert(4 * kBinStride <= kRowsPerWave * SPARK_D / 2, "one area for both");
+    __shared__ uint32_t words_of_wave[kWaves];
+    __shared__ uint32_t ticket, sum_of_late;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = (int)(blockIdx.x % (uint32_t)L.n_kv_heads);
+    uint32_t *const dir = reinterpret_cast<uint32_t *>(packed + L.off_dir) + (int64_t)h * (L.n_tiles + 1);
+    if (blockIdx.x == 0 && threadIdx.x < 16) write_header(packed, L, p_bp);
+    // The tickets are counted in the directory's first entry, which the last taker sets back to 0.  Every wait ends: who
+    // waits for tile i's place needs words that blocks with smaller tickets file before they wait for anything.
+    if (threadIdx.x == 0) {
+        const uint32_t t = __hip_atomic_fetch_add(dir, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((int64_t)t == L.n_tiles + lag) dir_store(dir, 0u);
+        ticket = t;
+    }
+    __syncthreads();
+    const int64_t mine = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)ticket);
+    if (mine == 0) {
+        if (wave == 0) sum_directory(dir, L.n_tiles, lane);
+        return;
+    }
+    uint32_t *const wave_lds = lds_all[wave];
+    uint32_t words = 0;
+    if (mine <= L.n_tiles) words = select_tile(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, mine - 1, wave_lds);
+    const int64_t late = mine - 1 - lag;                 // the tile to be written
+    uint4 x[kSteps];
+    if (late >= 0) request_rows(k, k_tok_stride, k_head_stride, L, h, late, x);
+    if (mine <= L.n_tiles) {
+        if (lane == 0) words_of_wave[wave] = words;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);         // the rows' fixed part has been acknowledged
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t all = 0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) all += words_of_wave[w];
+            dir_store(dir + mine, kOwnWords + all);
+        }
+    }
+    if (late < 0) return;
+    // A sum that is there says that the tile's own block has filed its words, after its rows' fixed part had reached the
+    // point where all the chip's caches agree.  (The tile's place is this sum less its own words: the entry in front may
+    // still be on its way when this one is there.)  One wavefront asks for all four, and not too often: what many ask for
+    // at a time comes late.
+    if (wave == 0) {
+        uint32_t sum;
+        for (;;) {
+            sum = (uint32_t)__builtin_amdgcn_readfirstlane((int)dir_load(dir + late + 1));
+            if (sum != 0u && sum < kOwnWords) break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+        if (lane == 0) sum_of_late = sum;
+    }
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    write_tile(x, packed, L, h, late, (uint32_t)__builtin_amdgcn_readfirstlane((int)sum_of_late), wave_lds);
+}
+
+// ---- the same in three launches: selection (a block per tile), directory (a block per head), writing (a block per tile)
+
+__global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
+    const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
+    uint8_t *__restrict__ packed, SparkLayout L, int p_bp)
+{
+    __shared__ __align__(16) uint32_t hist_all[kWaves][4 * kBinStride];
+    __shared__ uint32_t words_of_wave[kWaves];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int h = (int)(blockIdx.x / (uint32_t)L.n_tiles);
+    const int64_t tile = blockIdx.x % (uint32_t)L.n_tiles;
+    if (blockIdx.x == 0 && threadIdx.x < 16) write_header(packed, L, p_bp);
+    const uint32_t words = select_tile(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, tile, hist_all[wave]);
+    if ((threadIdx.x & 63) == 0) words_of_wave[wave] = words;
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t sum = 0;
+        uint32_t all = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) sum += words_of_wave[w];
-        reinterpret_cast<uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile + 1] = sum;
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 16) {
-        // header (the channel weights are written by the window kernel that runs before)
-        uint32_t v = 0;
-        if (lane == 0) v = SPARK_MAGIC;
-        if (lane == 3) v = (uint32_t)L.batch;
-        if (lane == 4) v = (uint32_t)L.n_kv_heads;
-        if (lane == 5) v = (uint32_t)L.total_tokens;
-        if (lane == 6) v = (uint32_t)L.ndw;
-        if (lane == 9) v = 1u;   // top-p cache
-        if (lane == 10) v = (uint32_t)p_bp;
-        reinterpret_cast<uint32_t *>(packed)[lane] = v;
+        for (int w = 0; w < kWaves; ++w) all += words_of_wave[w];
+        reinterpret_cast<uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile + 1] = all;
     }
 }
 
@@ -334,83 +566,18 @@ __global__ __launch_bounds__(kScanThreads) void spark_topp_scan_kernel(uint8_t *
     }
 }
 
-// The kept ones of a lane's eight channels (x: two channels a word; m: their mask byte) go to the 16-bit places in
-// LDS that end at byte address `end`, in order.  The stores run under the channels' wave masks, taken off the byte
-// from its top bit on; all lanes are active before and after.
-__device__ __forceinline__ void stage_kept(uint32_t m, uint32_t end, const uint4 &x)
-{
-    m <<= 24;
-    asm volatile(
-#define SPARK_STAGE(STORE, X)                  \
-    "v_add_co_u32 %[m], vcc, %[m], %[m]\n\t"   \
-    "s_mov_b64 exec, vcc\n\t"                  \
-    "v_add_u32 %[p], -2, %[p]\n\t"             \
-    STORE " %[p], " X "\n\t"                   \
-    "s_mov_b64 exec, -1\n\t"
-        SPARK_STAGE("ds_write_b16_d16_hi", "%[x3]")
-        SPARK_STAGE("ds_write_b16", "%[x3]")
-        SPARK_STAGE("ds_write_b16_d16_hi", "%[x2]")
-        SPARK_STAGE("ds_write_b16", "%[x2]")
-        SPARK_STAGE("ds_write_b16_d16_hi", "%[x1]")
-        SPARK_STAGE("ds_write_b16", "%[x1]")
-        SPARK_STAGE("ds_write_b16_d16_hi", "%[x0]")
-        SPARK_STAGE("ds_write_b16", "%[x0]")
-#undef SPARK_STAGE
-        : [m] "+v"(m), [p] "+v"(end)
-        : [x0] "v"(x.x), [x1] "v"(x.y), [x2] "v"(x.z), [x3] "v"(x.w)
-        : "memory", "vcc");
-}
-
-// One block per tile, sixteen rows a wavefront, sixteen lanes a row as in spark_topp_select_kernel.  The rows of a
-// wavefront take consecutive words of the head's stream: their kept entries are put together in LDS and leave as
-// whole words.
 __global__ __launch_bounds__(kWaves * 64) void spark_topp_pack_kernel(const uint16_t *__restrict__ k, int64_t k_tok_stride,
                                                                       int64_t k_head_stride, uint8_t *__restrict__ packed,
                                                                       SparkLayout L)
 {
     __shared__ __align__(16) uint32_t stage_all[kWaves][kRowsPerWave * SPARK_D / 2];
-    const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int row = lane >> 4, sub = lane & 15;
     const int h = (int)(blockIdx.x / (uint32_t)L.n_tiles);
     const int64_t tile = blockIdx.x % (uint32_t)L.n_tiles;
-    const int64_t n0 = tile * SPARK_TILE_TOKENS;
-    const int64_t left = L.total_tokens - n0;
-    const int nvalid = left < SPARK_TILE_TOKENS ? (int)left : SPARK_TILE_TOKENS;
-    const int t0 = wave * kRowsPerWave;
-    if (t0 >= nvalid) return;                            // (no block barrier is used)
-    const uint8_t *tp = packed + L.off_tiles + ((int64_t)h * L.n_tiles + tile) * L.tile_bytes;
-    const uint16_t *kbase = k + n0 * k_tok_stride + (int64_t)h * k_head_stride + 8 * sub;
     uint4 x[kSteps];
-    uint32_t m[kSteps];
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-        const int t = t0 + 4 * s + row;
-        x[s] = *reinterpret_cast<const uint4 *>(kbase + (int64_t)(t < nvalid ? t : nvalid - 1) * k_tok_stride);
-        m[s] = tp[t * 16 + sub];                         // (rows past the last token have an empty mask)
-    }
-    const uint32_t cnt = *reinterpret_cast<const uint32_t *>(tp + 1024 + lane * 8 + 4);
-    const uint32_t base = reinterpret_cast<const uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile];
-    const uint32_t upto = wave_inclusive_sum((cnt + 1u) / 2u);       // lane = token: words of the tile's rows 0 .. token
-    const uint32_t first = t0 ? (uint32_t)__builtin_amdgcn_readlane((int)upto, t0 - 1) : 0u;
-    const uint32_t nwords = (uint32_t)__builtin_amdgcn_readlane((int)upto, t0 + kRowsPerWave - 1) - first;
-    uint32_t *const stage = stage_all[wave];
-    typedef __attribute__((address_space(3))) uint32_t lds_u32;
-    const uint32_t stage_a = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)stage;
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-        const int t = t0 + 4 * s + row;
-        const uint32_t last = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * t, (int)upto) - first - 1u;    // the row's last word
-        const uint32_t kept = (uint32_t)__popc(m[s]);
-        const uint32_t kept_upto = row16_inclusive_sum(kept), kept_row = row16_last(kept_upto);
-        // (its upper half stays 0 where the count is odd; the entries are stored after it)
-        if (sub == 0 && kept_row != 0u) *(lds_u32 *)(uintptr_t)(stage_a + 4u * last) = 0u;
-        prune_lds_sync();
-        stage_kept(m[s], stage_a + 4u * (last + 1u) - 2u * (kept_row + (kept_row & 1u)) + 2u * kept_upto, x[s]);
-    }
-    prune_lds_sync();
-    uint32_t *dst = reinterpret_cast<uint32_t *>(packed + L.off_vals) + (int64_t)h * L.vals_head_words + base + first;
-    for (uint32_t i = lane; i < nwords; i += 64) dst[i] = stage[i];
+    request_rows(k, k_tok_stride, k_head_stride, L, h, tile, x);
+    const uint32_t sum = reinterpret_cast<const uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile + 1];
+    write_tile(x, packed, L, h, tile, sum, stage_all[wave]);
 }
 
 // canonical export, one thread per (token, KV head) row
@@ -449,13 +616,28 @@ hipError_t launch_prune_topp(const uint16_t *k, int64_t k_tok_stride, int64_t k_
                              uint8_t *packed, const SparkLayout &L, int p_bp, hipStream_t st)
 {
     if (L.n_tiles == 0) return hipSuccess;
-    hipLaunchKernelGGL(spark_topp_select_kernel, dim3((unsigned)(L.n_tiles * L.n_kv_heads)), dim3(kWaves * 64), 0, st, k,
-                       k_tok_stride, k_head_stride, cu, packed, L, p_bp);
+    const int64_t tiles = L.n_tiles * L.n_kv_heads;
+    const dim3 threads(kWaves * 64);
+    // One launch or three.  In one, few tiles (lag 0: a block writes its own tile) save two launches, and many tiles (a lag
+    // of about as many as the chip has in flight) hide the writing, which waits for memory, behind the selection, which
+    // is bound by vector issue.  In between, where all blocks select at once and then all write, the way from a tile's words to
+    // its place (three trips through memory) costs more than the launches; and with few heads the count of the tickets
+    // (11.5 ns each) does.  Three launches / one (us, 51 kept channels a row, window kernel included):
+    //   8 heads, tiles:  64 19 / 15   256 19 / 17   512 20 / 20   1024 24 / 27   1504 29 / 33   2048 35 / 33   4096 57 / 48   8192 100 / 85
+    //   1 head:  128 18 / 17   512 19 / 23   1024 24 / 33      2 heads:  2048 36 / 42
+    if (tiles <= 256 || (tiles >= 2048 && L.n_kv_heads >= 4)) {
+        const int lag = tiles <= 256 ? 0 : 2048 / L.n_kv_heads;
+        const int64_t tickets = L.n_tiles + lag + 1;
+        hipLaunchKernelGGL(spark_topp_prune_kernel, dim3((unsigned)(tickets * L.n_kv_heads)), threads, 0, st, k, k_tok_stride,
+                           k_head_stride, cu, packed, L, p_bp, lag);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(spark_topp_select_kernel, dim3((unsigned)tiles), threads, 0, st, k, k_tok_stride, k_head_stride, cu, packed,
+                       L, p_bp);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     hipLaunchKernelGGL(spark_topp_scan_kernel, dim3(L.n_kv_heads), dim3(kScanThreads), 0, st, packed, L);
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    hipLaunchKernelGGL(spark_topp_pack_kernel, dim3((unsigned)(L.n_tiles * L.n_kv_heads)), dim3(kWaves * 64), 0, st, k,
-                       k_tok_stride, k_head_stride, packed, L);
+    hipLaunchKernelGGL(spark_topp_pack_kernel, dim3((unsigned)tiles), threads, 0, st, k, k_tok_stride, k_head_stride, packed, L);
     return hipGetLastError();
 }
 
