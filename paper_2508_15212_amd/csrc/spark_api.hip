@@ -89,6 +89,16 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
         p.nchunk_max = d->batch * p.fixed_splits;
     else   // a sequence of len tokens spans at most len / 64 + 2 tiles, and rounding up costs at most one chunk
         p.nchunk_max = (int)((tiles + 2 * (int64_t)d->batch) / chunk + d->batch + 1);
+    // Rounding up every sequence's share can put a few blocks more on the chip than it holds at once, and they start when
+    // the others are done.  The kernel, which knows the lengths, then takes longer chunks.  (Few sequences only: their
+    // table is one register a lane; 256 pairs and more are cut less finely, see above.)  Llama heads, T = 26, without / with
+    // the limit (us): 8 sequences of 20000 to 45000 tokens 133 / 110, 16 of 2000 to 9000 56 / 48 (T = 64: 76 / 66), 28 of
+    // 500 to 3000 33 / 29, 10 of 8000 49 / 40; 4 of 12001 to 18777 with packed values, which are bound by each block's own
+    // work, 35.1 / 34.9.
+    p.chunk_limit = 0;
+    if (p.fixed_splits == 0 && d->batch <= 64 && (int64_t)d->batch * d->n_kv_heads < 256 &&
+        (int64_t)p.nchunk_max * d->n_kv_heads > 512)
+        p.chunk_limit = 512 / d->n_kv_heads;
     // Many sequences, each too short to be cut: one block per (sequence, KV head) would make the launch last as
     // long as its longest sequence.  Then (or on request, n_splits = -1) the (sequence, tile) items of a KV head
     // are dealt out evenly to as many wavefronts as are resident at once, 2048 over all heads.  The mode holds

@@ -55,6 +55,7 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
     P.fixed_splits = plan.fixed_splits;
     P.chunk_tiles = plan.chunk_tiles;
     P.nchunk_max = plan.nchunk_max;
+    P.chunk_limit = plan.chunk_limit;
     // balanced mode: dense values, degenerate recovery, rows of one length, query groups up to 8 (else chunks)
     P.warm_waves = (!packed_v && rec == 0 && !L.topp && Hq / L.n_kv_heads <= 8) ? plan.warm_waves : 0;
     P.tail_slots = plan.tail_slots;

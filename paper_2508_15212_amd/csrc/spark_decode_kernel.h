@@ -64,7 +64,8 @@ struct DecodeParams {
     // launches nchunk_max >= the true count and blocks past the last chunk leave at once.
     // Slot of (global chunk c, q head) = c * Hq + head; the appended rows' slots follow at tail_base:
     // ((b * Hq + head) * tail_slots + part).
-    int fixed_splits, chunk_tiles, nchunk_max;
+    // With chunk_limit > 0 a chunk is made as much longer as it takes for the whole batch to have at most that many.
+    int fixed_splits, chunk_tiles, nchunk_max, chunk_limit;
     // Balanced mode (warm_waves > 0; ragged batches of many short sequences): the (sequence, tile) items of a KV
     // head, sequences back to back, are dealt out in equal contiguous ranges to warm_waves wavefronts, each of
     // which works on its own and leaves one partial per sequence it touches.  Wavefront w covers items
@@ -182,18 +183,24 @@ __device__ __forceinline__ SeqChunks locate_chunks(const DecodeParams &P, int B,
         if (b < B) { r.b = b; r.first = b * P.fixed_splits; r.n = P.fixed_splits; r.s0 = P.cu[b]; r.s1 = P.cu[b + 1]; }
         return r;
     }
-    int base = 0;
+    int base = 0, chunk = P.chunk_tiles;
     for (int b0 = 0; b0 < B; b0 += 64) {
         const int bb = b0 + lane;
-        int n = 0, s0 = 0, s1 = 0;
+        int s0 = 0, s1 = 0;
         if (bb < B) {
             s0 = P.cu[bb];
             s1 = P.cu[bb + 1];
-            const int ntile = (s1 > s0) ? ((s1 - 1) / SPARK_TILE_TOKENS - s0 / SPARK_TILE_TOKENS + 1) : 0;
-            n = (ntile + P.chunk_tiles - 1) / P.chunk_tiles;
-            n = n < 1 ? 1 : n;     // an empty sequence still gets one block: somebody has to write its zeros
         }
-        const int inc = wave_inclusive_sum_i32(n);
+        const int ntile = (s1 > s0) ? ((s1 - 1) / SPARK_TILE_TOKENS - s0 / SPARK_TILE_TOKENS + 1) : 0;
+        int n, inc;
+        for (;;) {
+            n = (int)((uint32_t)(ntile + chunk - 1) / (uint32_t)chunk);
+            n = (bb < B && n < 1) ? 1 : n;     // an empty sequence still gets one block: somebody has to write its zeros
+            inc = wave_inclusive_sum_i32(n);
+            // (a limit is given for up to 64 sequences and is no smaller than their number, so the chunks get long enough)
+            if (P.chunk_limit == 0 || __builtin_amdgcn_readlane(inc, 63) <= P.chunk_limit) break;
+            chunk += 1 + chunk / 16;
+        }
         uint64_t hit;
         if (want_b >= 0)
             hit = (want_b >= b0 && want_b < b0 + 64) ? (1ull << (want_b - b0)) : 0ull;
