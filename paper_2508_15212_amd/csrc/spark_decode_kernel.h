@@ -1151,36 +1151,41 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
             const float sg = __uint_as_float(*reinterpret_cast<const uint32_t *>(tp + spark_tile_word_offset(L, lane, INT8 ? 7 : 6)));
             constexpr float kLn2 = 0.69314718055994530942f;
             const float neg_mu_ln2 = -mu_a * kLn2;
+            const float sg_root = sg * 1.17741002251547469101f;      // sigma * sqrt(2 ln 2)
 #pragma unroll
             for (int wd = 0; wd < 4; ++wd) {
                 uint32_t pruned = ~r[wd];
-#pragma unroll 4
-                for (int pp = 0; pp < 16; ++pp) {
-                    const int j = 32 * wd + 2 * pp;
-                    const float u1 = unif((uint32_t)j), u2 = unif((uint32_t)j + 1u);
-                    float w0, w1;
-                    if (REC == 1) {   // Box-Muller pair for channels j, j + 1
-                        // root of x = -2 ln u1 (between 2^-23 and 34): reciprocal root and one Newton step, which ends
-                        // within a hair of the correctly rounded root
-                        const float x = -2.0f * kLn2 * __builtin_amdgcn_logf(u1);
-                        const float y = __builtin_amdgcn_rsqf(x), r0 = x * y;
-                        const float rr = fmaf(fmaf(-r0, r0, x), 0.5f * y, r0) * sg;
-                        w0 = fmaf(rr, __builtin_amdgcn_cosf(u2), mu_a);    // v_cos / v_sin take revolutions
-                        w1 = fmaf(rr, __builtin_amdgcn_sinf(u2), mu_a);
-                    } else {          // rate 1 / mu
-                        w0 = neg_mu_ln2 * __builtin_amdgcn_logf(u1);
-                        w1 = neg_mu_ln2 * __builtin_amdgcn_logf(u2);
-                    }
-                    // (a one-bit field with its sign: all bits for a pruned channel, none for a kept one; written out
-                    //  because the compiler makes a test, a compare and a selection of it)
-                    uint32_t m0, m1;
-                    asm("v_bfe_i32 %0, %1, 0, 1" : "=v"(m0) : "v"(pruned));
-                    asm("v_bfe_i32 %0, %1, 1, 1" : "=v"(m1) : "v"(pruned));
-                    const float t0 = __uint_as_float(__float_as_uint(w0) & m0), t1 = __uint_as_float(__float_as_uint(w1) & m1);
-                    pruned >>= 2;
+                float part[G];           // (summed by quarters of the row: smaller rounding errors)
 #pragma unroll
-                    for (int g = 0; g < G; ++g) s[g] = fmaf(qa[(j + 1) * G + g], t1, fmaf(qa[j * G + g], t0, s[g]));
+                for (int g = 0; g < G; ++g) part[g] = 0.0f;
+#pragma unroll 1
+                for (int c0 = 0; c0 < 32; c0 += 8) {
+#pragma unroll
+                    for (int c = 0; c < 8; c += 2) {
+                        const int j = 32 * wd + c0 + c;
+                        const float u1 = unif((uint32_t)j), u2 = unif((uint32_t)j + 1u);
+                        float w0, w1;
+                        if (REC == 1) {   // Box-Muller pair for channels j, j + 1: radius sigma * sqrt(-2 ln u1)
+                            const float rr = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1)) * sg_root;
+                            w0 = fmaf(rr, __builtin_amdgcn_cosf(u2), mu_a);    // v_cos / v_sin take revolutions
+                            w1 = fmaf(rr, __builtin_amdgcn_sinf(u2), mu_a);
+                        } else {          // rate 1 / mu
+                            w0 = neg_mu_ln2 * __builtin_amdgcn_logf(u1);
+                            w1 = neg_mu_ln2 * __builtin_amdgcn_logf(u2);
+                        }
+                        // (a one-bit field with its sign: all bits for a pruned channel, none for a kept one; written out
+                        //  because the compiler makes a test, a compare and a selection of it)
+                        uint32_t m0, m1;
+                        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m0) : "v"(pruned), "n"(c));
+                        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m1) : "v"(pruned), "n"(c + 1));
+                        const float t0 = __uint_as_float(__float_as_uint(w0) & m0), t1 = __uint_as_float(__float_as_uint(w1) & m1);
+#pragma unroll
+                        for (int g = 0; g < G; ++g) part[g] = fmaf(qa[(j + 1) * G + g], t1, fmaf(qa[j * G + g], t0, part[g]));
+                    }
+                    pruned >>= 8;
                 }
+#pragma unroll
+                for (int g = 0; g < G; ++g) s[g] += part[g];
             }
         }
 #pragma unroll
