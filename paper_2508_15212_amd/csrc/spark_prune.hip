@@ -235,8 +235,8 @@ __device__ __forceinline__ void bracket(const uint32_t (&key)[8], uint32_t T, ui
     }
 }
 
-// 2^lg_per_tile wavefronts (1, 2 or 4) share a tile; each takes its rows a group (eight) at a time and writes them
-// out a stage (sixteen, two groups) at a time.
+// The first n_whole tiles (over all heads) take one wavefront each, the next n_half two, the others four; a wavefront takes its
+// rows a group (eight) at a time and writes them out a stage (sixteen, two groups) at a time.
 // MODE: bit 0 = int8 codes + scale instead of bf16 kept entries; bit 1 = the rows also carry the all-channel mean
 // and standard deviation of the row's saliencies (App. "Caching Pruned Channel Statistics", for the sampled recovery).
 // VALUES: the rows are value-cache rows (App. "Pruning Value Cache Channels"): the score of a channel is
@@ -244,7 +244,7 @@ __device__ __forceinline__ void bracket(const uint32_t (&key)[8], uint32_t T, ui
 template <int MODE, bool VALUES>
 __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
     const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
-    uint8_t *__restrict__ packed, SparkLayout L, int lg_per_tile, uint32_t digit_shift)
+    uint8_t *__restrict__ packed, SparkLayout L, uint32_t n_whole, uint32_t n_half, uint32_t digit_shift)
 {
     constexpr bool INT8 = (MODE & 1) != 0, STATS = (MODE & 2) != 0;
     extern __shared__ __align__(16) uint8_t smem[];
@@ -263,12 +263,20 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
         if (lane == 7) v = 1u;   // value cache
         reinterpret_cast<uint32_t *>(packed)[lane] = v;
     }
-    const uint32_t gt = wt >> lg_per_tile;               // tile number over the heads
+    // tile number over the heads, and which share of the tile
+    uint32_t gt = wt, lg_per_tile = 0, share = 0;
+    if (wt >= n_whole) {
+        const uint32_t after_whole = wt - n_whole, after_half = after_whole - 2u * n_half;
+        lg_per_tile = after_whole < 2u * n_half ? 1u : 2u;
+        const uint32_t i = lg_per_tile == 1u ? after_whole : after_half;
+        gt = n_whole + (lg_per_tile == 1u ? 0u : n_half) + (i >> lg_per_tile);
+        share = i & ((1u << lg_per_tile) - 1u);
+    }
     if (gt >= (uint32_t)(L.n_tiles * L.n_kv_heads)) return;     // the whole wavefront leaves; no block barrier is used
     const int h = (int)(gt / (uint32_t)L.n_tiles);
     const int64_t tile = gt - (uint32_t)h * (uint32_t)L.n_tiles;
     const int rows = SPARK_TILE_TOKENS >> lg_per_tile;          // (a multiple of kStageRows)
-    int t0 = (int)(wt & ((1u << lg_per_tile) - 1u)) * rows;     // first row of the stage in hand
+    int t0 = (int)share * rows;                                 // first row of the stage in hand
     const int t_end = t0 + rows;
     const int64_t n0 = tile * SPARK_TILE_TOKENS;
     const int64_t left = L.total_tokens - n0;
@@ -680,17 +688,22 @@ hipError_t launch_tiles(const uint16_t *x, int64_t tok_stride, int64_t head_stri
     const int64_t tiles = L.n_tiles * L.n_kv_heads;
     if (tiles == 0) return hipSuccess;
     if (tiles >= ((int64_t)1 << 30)) return hipErrorInvalidValue;
-    // Wavefronts per tile.  One has the least set-up, but few tiles then leave the chip idle: with four, up to 1536 tiles
-    // are still resident at once (six wavefronts per SIMD).  Measured with 1 / 2 / 4 for bf16 keys at T = 26 (us, the window
-    // kernel included): 128 tiles 20.5 / 15.2 / 13.3, 1536: 26 / 20 / 19, 4096: 34.5 / 32.1 / 32.2, 8192: 53 / 51 / 54,
-    // 12288: 67 / 69 / 74, 16384: 86 / 88 / 97.  Values, int8 rows and rows with statistics follow the same lines; for
-    // them only the result was measured (13 to 16384 tiles, T = 1 to 128, against one wavefront a tile, one row at a
-    // time: 0.2 to 1.0 of its time, values with T_v <= 12 up to 1.2).
-    const int lg_per_tile = tiles <= 1536 ? 2 : (tiles <= 10240 ? 1 : 0);
-    const int64_t waves = tiles << lg_per_tile;
+    // Wavefronts per tile.  One has the least set-up, but a wavefront that starts late and works on 64 rows lasts long
+    // after the others are done (10 us with the chip to itself).  So wavefronts start in the order of their work: whole tiles
+    // first, then halves of 1536 tiles, at the end quarters of 512 (2048 wavefronts, a third of what is resident).  Us, the
+    // window kernel included, one / two / four wavefronts for every tile (the earlier rule took four up to 1536 tiles, two
+    // up to 10240) -> this; keys at T = 26, values at T_v = 38:
+    //   keys: 1000 tiles 24 / 19 / 17 -> 16   2000 27 / 23 / 24 -> 21   5008 (int8) 46 / 42 / 43 -> 39   8000 55 / 52 -> 46
+    //         16384 88 / 90 -> 83   4544 (ragged, T = 64) 64 / 62 -> 59   32768 161 / 167 -> 157
+    //   values: 1000 21 / 15 / 13 -> 14   2000 24 / 19 / 18 -> 18   5008 34 / 33 / 34 -> 31   8000 49 / 47 -> 44   16384 85 / 87 -> 81
+    // Quarters of 256, 384, 768, 1536 and 3072 tiles and halves of 512 to 6144 were tried: 0 to 3 % slower.
+    const int64_t n_quarter = tiles < 512 ? tiles : 512;
+    const int64_t n_half = tiles - n_quarter < 1536 ? tiles - n_quarter : 1536;
+    const int64_t n_whole = tiles - n_quarter - n_half;
+    const int64_t waves = n_whole + 2 * n_half + 4 * (tiles - n_whole - n_half);
     auto launch = [&](auto kern) -> hipError_t {
         hipLaunchKernelGGL(kern, dim3((unsigned)((waves + kPruneWaves - 1) / kPruneWaves)), dim3(kPruneWaves * 64),
-                           spark_prune_lds_bytes(L), st, x, tok_stride, head_stride, cu, packed, L, lg_per_tile,
+                           spark_prune_lds_bytes(L), st, x, tok_stride, head_stride, cu, packed, L, (uint32_t)n_whole, (uint32_t)n_half,
                            digit_shift_of(L.T));
         return hipGetLastError();
     };
