@@ -315,105 +315,153 @@ __device__ __forceinline__ PairInfo warm_pair(const DecodeParams &P, const WarmS
 // ---------------------------------------------------------------- appended (never pruned) rows
 
 // [Sec. "Preliminaries": each decode step concatenates the new token's key and value to the cache; pruning
-//  happens once, at prefill, so these rows stay dense.]  One extra block per (batch, KV head) of the decode
+//  happens once, at prefill, so these rows stay dense.]  One extra block per (batch, KV head) and 256 rows of the decode
 // grid runs plain attention over the sequence's appended rows and leaves the softmax state (m, l,
 // unnormalised output) in the spare partial slot; it then takes part in the arrival count like a sequence
-// split, so whichever block comes last folds it in.  qs [G][128] and Psh [4][G][64] are LDS scratch.
+// split, so whichever block comes last folds it in.
+//
+// A wavefront takes 64 rows, all of them requested at once, and both contractions go to the matrix cores:
+//   scores   B operand: lane (tg, cn) = channels 32 kb + 8 tg .. + 7 of row 16 tau + cn, straight from memory; A operand:
+//            row cn = query head cn, times the power of two of the softmax scale (exact products, in range where the
+//            scores are); the rest of the scale after.
+//   output   probabilities as three bf16 parts, which together are their float32 value, through LDS into A operands;
+//            values as in the main loop (rows 4 i + tg of half a tile, transposed in registers).
+// Bound by the round trips: row count, rows, partial.  Entry by entry in float32 (1500 instructions by a lone wavefront)
+// it was the longest block of a short batch: four sequences of 700 to 3900 tokens with up to 256 appended rows 17.6 -> 16.6 us
+// (entry to partial 13.5 -> 9.3), 100 of 51 to 206 tokens with up to 700, eight query heads, 51 -> 36 us.  Error against 64 bits as
+// before (5.1e-7; where there are only appended rows 3.0e-7 -> 2.7e-7).
 template <int G>
-__device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h, int part, int len, float *qs, float *Psh,
-                                             float (*red_m)[G], float (*red_l)[G], float *red_acc /* [4][G][128] */)
+__device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h, int part, int len, float (*red_m)[G], float (*red_l)[G],
+                                             float *red_acc /* [4][G][128] */)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tg = lane >> 4, cn = lane & 15;
+    // (an exact split of the softmax scale, as for rows of varying length)
+    const uint32_t scale_bits = __float_as_uint(P.scale_log2);
+    const bool normal = (scale_bits & 0x7F800000u) != 0u;
+    const float q_scale = normal ? __uint_as_float(scale_bits & 0x7F800000u) : 1.0f;
+    const float s_scale = normal ? __uint_as_float((scale_bits & 0x807FFFFFu) | 0x3F800000u) : P.scale_log2;
+    uint4 qx[4];
+    {
+        const uint16_t *qrow = P.q + ((int64_t)b * P.Hq + h * G + (cn < G ? cn : G - 1)) * SPARK_D + 8 * tg;
+        if ((reinterpret_cast<uintptr_t>(P.q) & 15u) == 0u) {
+#pragma unroll
+            for (int kb = 0; kb < 4; ++kb) qx[kb] = *reinterpret_cast<const uint4 *>(qrow + 32 * kb);
+        } else {                                                        // (2-byte alignment is all that is asked for)
+#pragma unroll 1
+            for (int kb = 0; kb < 4; ++kb) {
+                const uint16_t *p8 = qrow + 32 * kb;
+                uint32_t w[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[c] = (uint32_t)p8[2 * c] | ((uint32_t)p8[2 * c + 1] << 16);
+                const uint4 x = make_uint4(w[0], w[1], w[2], w[3]);
+                if (kb == 0) qx[0] = x; else if (kb == 1) qx[1] = x; else if (kb == 2) qx[2] = x; else qx[3] = x;
+            }
+        }
+    }
     len = len < 0 ? 0 : (len > P.tail_cap ? P.tail_cap : len);
     // this block's share: rows [256 * part, 256 * part + 256), 64 of them by each wavefront
     const int c0 = part * kDecodeWaves * 64 + wave * 64;
     const int nval = (len - c0 < 64) ? (len - c0) : 64;
-    const int64_t row0 = (int64_t)b * P.tail_cap;
-    // All of the wavefront's rows are requested at once, keys first (lane = row, past the last one the last), then values
-    // (lane = channels 2l, 2l+1): the block waits for memory about once.  Fetching four pieces of a key row and eight
-    // value rows at a time, a dozen round trips one after the other, made this block the longest of a short batch: four
-    // sequences of 700 to 3900 tokens with up to 256 appended rows took 21.7 us and take 17.3 us (medians; the shortest
-    // launches 21.2 and 15.6 us).
-    // (Sixteen query heads leave no registers for that and keep the small pieces.)
-    constexpr int NK = (G <= 8) ? SPARK_D / 8 : 4, NV = (G <= 8) ? 64 : 8;
-    uint4 kx[NK];
-    uint32_t vw[NV];
-    auto request_keys = [&](int k0) __attribute__((always_inline)) {
-        const uint16_t *krow = P.tail_k + ((row0 + c0 + (lane < nval ? lane : nval - 1)) * P.Hkv + h) * SPARK_D + 8 * k0;
+    float m[4], l[4];                                                   // of head 4 tg + r
+    f32x4 acc[8];
 #pragma unroll
-        for (int c = 0; c < NK; ++c) kx[c] = *reinterpret_cast<const uint4 *>(krow + 8 * c);
-    };
-    auto request_values = [&](int v0) __attribute__((always_inline)) {
-        const uint16_t *vbase = P.tail_v + ((row0 + c0) * P.Hkv + h) * SPARK_D + 2 * lane;
-        const int64_t vstep = (int64_t)P.Hkv * SPARK_D;
+    for (int r = 0; r < 4; ++r) { m[r] = -INFINITY; l[r] = 0.0f; }
 #pragma unroll
-        for (int t0 = 0; t0 < NV; t0 += 8) {
-            if (v0 + t0 < nval) {                  // (wave-uniform)
-#pragma unroll
-                for (int t = t0; t < t0 + 8; ++t)
-                    vw[t] = *reinterpret_cast<const uint32_t *>(vbase + (v0 + t < nval ? v0 + t : nval - 1) * vstep);
-            }
-        }
-    };
+    for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    uint16_t *const pw = reinterpret_cast<uint16_t *>(red_acc + wave * G * SPARK_D);       // [3][G][64]
     if (nval > 0) {
-        request_keys(0);
-        if (NV == 64) request_values(0);
-    }
-    for (int idx = tid; idx < G * SPARK_D; idx += kDecodeWaves * 64) {
-        const int g = idx / SPARK_D, j = idx % SPARK_D;
-        qs[g * SPARK_D + j] = bf16lo(P.q[((int64_t)b * P.Hq + h * G + g) * SPARK_D + j]) * P.scale_log2;
-    }
-    __syncthreads();
-    float m[G], l[G], acc[G][2];
+        // rows past the last one: the last one
+        const int64_t row0 = ((int64_t)b * P.tail_cap + c0) * P.Hkv + h, step = P.Hkv;
+        uint4 kx[4][4], vx[2][8];
 #pragma unroll
-    for (int g = 0; g < G; ++g) { m[g] = -INFINITY; l[g] = 0.0f; acc[g][0] = acc[g][1] = 0.0f; }
-    float *pw = Psh + wave * G * 64;
-    if (nval > 0) {
-        // scores, lane = token
-        float s[G];
+        for (int tau = 0; tau < 4; ++tau) {
+            const int n = 16 * tau + cn;
+            const uint16_t *krow = P.tail_k + (row0 + (n < nval ? n : nval - 1) * step) * SPARK_D + 8 * tg;
 #pragma unroll
-        for (int g = 0; g < G; ++g) s[g] = 0.0f;
-#pragma unroll 1
-        for (int k0 = 0; k0 < SPARK_D / 8; k0 += NK) {
-            if (k0 > 0) request_keys(k0);
-#pragma unroll
-            for (int c = 0; c < NK; ++c) {
-                const uint4 x = kx[c];
-                const float kf[8] = {bf16lo(x.x), bf16hi(x.x), bf16lo(x.y), bf16hi(x.y),
-                                     bf16lo(x.z), bf16hi(x.z), bf16lo(x.w), bf16hi(x.w)};
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-#pragma unroll
-                    for (int g = 0; g < G; ++g) s[g] = fmaf(qs[g * SPARK_D + 8 * (k0 + c) + e], kf[e], s[g]);
-            }
+            for (int kb = 0; kb < 4; ++kb) kx[tau][kb] = *reinterpret_cast<const uint4 *>(krow + 32 * kb);
         }
-        // softmax over the wavefront's rows (log2 domain); probabilities to LDS
+        auto request_values = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const float sg = lane < nval ? s[g] : -INFINITY;
-            m[g] = wave_max(sg);                                    // finite: lane 0's row is there
-            l[g] = fast_exp2(sg - m[g]);
-            pw[g * 64 + lane] = l[g];
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int n = 32 * ks + 4 * i + tg;
+                    vx[ks][i] = *reinterpret_cast<const uint4 *>(P.tail_v + (row0 + (n < nval ? n : nval - 1) * step) * SPARK_D + 8 * cn);
+                }
+        };
+        if (G <= 8) request_values();                    // (sixteen query heads: the registers for both are not there)
+        f32x4 s[4];
+#pragma unroll
+        for (int tau = 0; tau < 4; ++tau) s[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) {
+            const uint32_t w[4] = {qx[kb].x, qx[kb].y, qx[kb].z, qx[kb].w};
+            bf16x8 A;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                A[2 * c] = (__bf16)(cn < G ? bf16lo(w[c]) * q_scale : 0.0f);
+                A[2 * c + 1] = (__bf16)(cn < G ? bf16hi(w[c]) * q_scale : 0.0f);
+            }
+#pragma unroll
+            for (int tau = 0; tau < 4; ++tau)
+                s[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, kx[tau][kb]), s[tau], 0, 0, 0);
+        }
+        if (G > 8) request_values();
+        // softmax over the wavefront's rows (log2 domain); lane (tg, cn): heads 4 tg + r, rows 16 tau + cn
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float v[4], top = -INFINITY;
+#pragma unroll
+            for (int tau = 0; tau < 4; ++tau) {
+                v[tau] = 16 * tau + cn < nval ? s[tau][r] * s_scale : -INFINITY;
+                top = fmaxf(top, v[tau]);
+            }
+            top = dpp_max_step<0x128, 0xF>(top);                         // over the sixteen lanes
+            top = dpp_max_step<0x124, 0xF>(top);
+            top = dpp_max_step<0x122, 0xF>(top);
+            top = dpp_max_step<0x121, 0xF>(top);
+            m[r] = top;                                                 // finite: row 0 is there
+#pragma unroll
+            for (int tau = 0; tau < 4; ++tau) {
+                const float p = fast_exp2(v[tau] - top);                // (0 past the last row)
+                l[r] += p;
+                // three parts of eight bits each, cut off: exactly p
+                const float hi = __uint_as_float(__float_as_uint(p) & 0xFFFF0000u), rest = p - hi;
+                const float mid = __uint_as_float(__float_as_uint(rest) & 0xFFFF0000u), lo = rest - mid;
+                const int n = 16 * tau + cn, g = 4 * tg + r;
+                const int at = (n & 32) | ((n & 3) << 3) | ((n & 31) >> 2);      // (the order in which the value rows come)
+                if (g < G) {
+                    pw[(0 * G + g) * 64 + at] = (uint16_t)(__float_as_uint(hi) >> 16);
+                    pw[(1 * G + g) * 64 + at] = (uint16_t)(__float_as_uint(mid) >> 16);
+                    pw[(2 * G + g) * 64 + at] = (uint16_t)(__float_as_uint(lo) >> 16);
+                }
+            }
         }
         wave_lds_sync();
-        // weighted sum, lane = channels 2l, 2l+1
-#pragma unroll 1
-        for (int v0 = 0; v0 < nval; v0 += NV) {
-            if (NV < 64) request_values(v0);
 #pragma unroll
-            for (int t0 = 0; t0 < NV; t0 += 8) {
-                if (v0 + t0 < nval) {
+        for (int ks = 0; ks < 2; ++ks) {
+            bf16x8 A[3];
 #pragma unroll
-                    for (int t = t0; t < t0 + 8; ++t) {
-                        const float x0 = bf16lo(vw[t]), x1 = bf16hi(vw[t]);
+            for (int k = 0; k < 3; ++k) {
+                uint4 a = {0, 0, 0, 0};
+                if (cn < G) a = *reinterpret_cast<const uint4 *>(&pw[(k * G + cn) * 64 + 32 * ks + 8 * tg]);
+                A[k] = __builtin_bit_cast(bf16x8, a);
+            }
 #pragma unroll
-                        for (int g = 0; g < G; ++g) {
-                            const float p = pw[g * 64 + v0 + t];    // (0 past the last row)
-                            acc[g][0] = fmaf(p, x0, acc[g][0]);
-                            acc[g][1] = fmaf(p, x1, acc[g][1]);
-                        }
-                    }
+            for (int cp = 0; cp < 4; ++cp) {
+                u32x4 even, odd;
+#pragma unroll
+                for (int tp2 = 0; tp2 < 4; ++tp2) {
+                    const uint32_t x = u4c(vx[ks][2 * tp2], cp), y = u4c(vx[ks][2 * tp2 + 1], cp);
+                    even[tp2] = __builtin_amdgcn_perm(y, x, 0x05040100u);
+                    odd[tp2] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+                }
+#pragma unroll
+                for (int k = 2; k >= 0; --k) {                           // (small parts first)
+                    acc[2 * cp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[k], __builtin_bit_cast(bf16x8, even), acc[2 * cp], 0, 0, 0);
+                    acc[2 * cp + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[k], __builtin_bit_cast(bf16x8, odd), acc[2 * cp + 1], 0, 0, 0);
                 }
             }
         }
@@ -421,11 +469,18 @@ __device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h
     }
     // merge the wavefronts and write the partial (device-scope stores, as the sequence splits do)
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const float lt = wave_sum(l[g]);
-        if (lane == 0) { red_m[wave][g] = m[g]; red_l[wave][g] = lt; }
-        red_acc[(wave * G + g) * SPARK_D + 2 * lane] = acc[g][0];
-        red_acc[(wave * G + g) * SPARK_D + 2 * lane + 1] = acc[g][1];
+    for (int r = 0; r < 4; ++r) {
+        const int g = 4 * tg + r;
+        float lt = l[r];                                                 // over the sixteen lanes
+        lt += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(lt), 0x128, 0xF, 0xF, true));
+        lt += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(lt), 0x124, 0xF, 0xF, true));
+        lt += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(lt), 0x122, 0xF, 0xF, true));
+        lt += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(lt), 0x121, 0xF, 0xF, true));
+        if (g < G) {
+            if (cn == 0) { red_m[wave][g] = m[r]; red_l[wave][g] = lt; }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) red_acc[(wave * G + g) * SPARK_D + 8 * cn + e] = acc[e][r];
+        }
     }
     __syncthreads();
     for (int idx = tid; idx < G * SPARK_D; idx += kDecodeWaves * 64) {
@@ -575,6 +630,10 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     const int h = is_tail ? (tb / P.ntail) % P.Hkv : (int)(blockIdx.x % P.Hkv);
     // (requested before the sequence table is read: one memory round trip less before the appended rows' own)
     const int tail_rows = is_tail ? P.tail_len[(tb / P.ntail) / P.Hkv] : 0;
+    if (is_tail) {
+        static_assert(WBUF >= G * SPARK_D * 4, "LDS reuse");
+        tail_partial<G>(P, (tb / P.ntail) / P.Hkv, h, tb % P.ntail, tail_rows, red_m, red_l, reinterpret_cast<float *>(&wbuf[0][0]));
+    }
     WarmSeqs W;
     PairInfo pi = {0, 0, 0};
     int s0 = 0, s1 = 0;                                  // token range of the sequence being streamed
@@ -667,11 +726,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     const int b = pi.b;
     const int nsplit = pi.nsplit;
     const int nmerge = nsplit + P.ntail;                 // partial states the last arrival folds
-    if (is_tail) {
-        static_assert(sizeof(qtab) >= G * SPARK_D * 4 && sizeof(Pbuf) >= kDecodeWaves * G * 64 * 4, "LDS reuse");
-        tail_partial<G>(P, b, h, tb % P.ntail, tail_rows, qtab, reinterpret_cast<float *>(&Pbuf[0][0][0][0]), red_m, red_l,
-                        reinterpret_cast<float *>(&wbuf[0][0]));
-    } else {
+    if (!is_tail) {
     float m[G], l[G], R[G];
     f32x4 acc[8];
 #pragma unroll
