@@ -10,6 +10,25 @@ extern template hipError_t launch_g<4>(const DecodeParams &, int, hipStream_t);
 extern template hipError_t launch_g<8>(const DecodeParams &, int, hipStream_t);
 extern template hipError_t launch_g<16>(const DecodeParams &, int, hipStream_t);
 
+// Whether a call's tiles (over all KV heads) are few enough, and not too few, for the blocks of sixteen wavefronts of
+// spark_decode_short.h.  Such a block takes four tiles at a time with four lanes a row, but all in one compute unit, whose LDS then
+// bounds it; blocks of four wavefronts are as fast or faster for the row lengths that have an instantiation, except where
+// eight query heads leave registers for small groups of entries only, and for very small calls of short rows.  One sequence, 8 KV
+// heads, four / sixteen wavefronts a block (us; 1024 tokens are 128 tiles):
+//   G = 4, T = 33:  1024 11.1 / 11.5   4096 13.2 / 12.6   8192 15.5 / 14.8   16384 21.3 / 20.2   32768 26.8 / 28.2
+//          T = 90:  100 12.7 / 8.4   1024 15.6 / 13.5   8192 19.2 / 17.3   16384 24.8 / 26.0     T = 127:  1024 17.7 / 14.5
+//   G = 8, T = 30:  1024 13.2 / 12.8   4096 16.2 / 14.5   16384 26.6 / 22.9    T = 80:  1024 19.1 / 15.6   16384 31.5 / 29.7
+//          T = 26 (instantiated):  1024 11.9 / 12.2   8192 18.1 / 17.2   16384 25.4 / 22.5     T = 64:  8192 20.8 / 20.0
+//   G = 2, T = 30:  2048 10.4 / 11.0   8192 14.1 / 13.4   T = 70:  1024 11.7 / 12.3   T = 127:  1024 15.8 / 14.0
+//   G = 1, T = 30:  1024 8.8 / 9.5   4096 11.0 / 10.6   8192 13.6 / 12.3   T = 70:  1024 11.2 / 10.5   16384 21.0 / 21.2
+static bool short_call_tiles(const SparkLayout &L, int G, int64_t tiles)
+{
+    if (row_length_instantiated(L)) return G == 8 && tiles >= 512 && tiles <= 2048;
+    const bool long_rows = L.T > (G == 2 ? 80 : 64);
+    const int64_t least = long_rows || G == 8 ? 0 : (G == 4 ? 288 : 512);
+    return tiles >= least && tiles <= (long_rows && G <= 4 ? 1024 : 2048);
+}
+
 // Zeroes the arrival counters of a fresh workspace.
 __global__ void spark_zero_kernel(uint32_t *p, int n)
 {
@@ -71,6 +90,21 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
     P.scale_log2 = softmax_scale * 1.44269504088896340736f;
     P.L = L;
     const int G = P.Hq / P.Hkv;
+    // Short calls: all blocks are resident at once, one a compute unit.  Chunks get as much longer as that takes, where blocks of
+    // four wavefronts would have to do the same, or where that is half a pass (of four tiles) on average.  T = 32, four / sixteen
+    // wavefronts a block (us): 6 x 2000 to 3000 tokens 21.6 / 18.6; with 5.5 tiles a place (4 x 700 to 3900 tokens and appended
+    // rows) 15.1 / 14.5, with 6.6 (8 x 800 to 1500 and appended rows) 14.6 / 16.1.
+    P.short_call = 0;
+    if (!packed_v && rec == 0 && !L.topp && G <= 8 && P.warm_waves == 0 && short_call_tiles(L, G, L.n_tiles * P.Hkv)) {
+        const int64_t room = 256 / P.Hkv - (int64_t)L.batch * P.ntail;       // chunks there are places for
+        if (P.nchunk_max <= room) {
+            P.short_call = 1;
+        } else if (P.fixed_splits == 0 && L.batch <= 64 && room >= 2 * L.batch &&
+                   (P.chunk_limit > 0 || L.n_tiles + 2 * L.batch <= 6 * room)) {
+            P.short_call = 1;
+            P.chunk_limit = P.nchunk_max = (int)room;
+        }
+    }
     const int nblocks = P.Hkv * ((P.warm_waves > 0 ? P.warm_waves / kDecodeWaves : P.nchunk_max) + L.batch * P.ntail);
     P.trace = (g_timeline != nullptr && (size_t)nblocks <= g_timeline_blocks) ? g_timeline : nullptr;
     switch (G) {

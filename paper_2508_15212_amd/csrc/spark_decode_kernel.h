@@ -74,6 +74,7 @@ struct DecodeParams {
     // pairs share one); a sequence without tokens has the single id warm_waves + batch + b: warm_waves + 2 * batch
     // ids in all.
     int warm_waves;
+    int short_call;          // 1: blocks of sixteen wavefronts (spark_decode_short.h)
     int ntail;               // blocks per (batch, KV head) for the appended rows, 256 rows each (0: none)
     int tail_slots;          // slots reserved per (batch, q head) for them (>= max(1, ntail))
     int64_t tail_base;       // first of them: the number of chunk ids the workspace provides for, times Hq
@@ -312,6 +313,48 @@ __device__ __forceinline__ PairInfo warm_pair(const DecodeParams &P, const WarmS
     return pi;
 }
 
+// The softmax scale (times log2 e) as its power of two, which a query can take exactly, and the rest, which the scores take.
+__device__ __forceinline__ float split_scale(float scale_log2, float &rest)
+{
+    const uint32_t bits = __float_as_uint(scale_log2);
+    const bool normal = (bits & 0x7F800000u) != 0u;
+    rest = normal ? __uint_as_float((bits & 0x807FFFFFu) | 0x3F800000u) : scale_log2;
+    return normal ? __uint_as_float(bits & 0x7F800000u) : 1.0f;
+}
+
+// Query rows of a KV head as they lie in an A operand: lane (tg, cn) = channels 32 kb + 8 tg .. + 7 of query head cn.
+template <int G>
+__device__ __forceinline__ void tail_query_rows(const DecodeParams &P, int b, int h, int cn, int tg, uint4 (&qx)[4])
+{
+    const uint16_t *qrow = P.q + ((int64_t)b * P.Hq + h * G + (cn < G ? cn : G - 1)) * SPARK_D + 8 * tg;
+    if ((reinterpret_cast<uintptr_t>(P.q) & 15u) == 0u) {
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb) qx[kb] = *reinterpret_cast<const uint4 *>(qrow + 32 * kb);
+    } else {                                                            // (2-byte alignment is all that is asked for)
+#pragma unroll 1
+        for (int kb = 0; kb < 4; ++kb) {
+            const uint16_t *p8 = qrow + 32 * kb;
+            uint32_t w[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) w[c] = (uint32_t)p8[2 * c] | ((uint32_t)p8[2 * c + 1] << 16);
+            const uint4 x = make_uint4(w[0], w[1], w[2], w[3]);
+            if (kb == 0) qx[0] = x; else if (kb == 1) qx[1] = x; else if (kb == 2) qx[2] = x; else qx[3] = x;
+        }
+    }
+}
+
+// 32 channels of them, times a power of two (rows without a query head: 0)
+template <int G>
+__device__ __forceinline__ void tail_query_operand(const uint4 &qx, int cn, float q_scale, bf16x8 &A)
+{
+    const uint32_t w[4] = {qx.x, qx.y, qx.z, qx.w};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        A[2 * c] = (__bf16)(cn < G ? bf16lo(w[c]) * q_scale : 0.0f);
+        A[2 * c + 1] = (__bf16)(cn < G ? bf16hi(w[c]) * q_scale : 0.0f);
+    }
+}
+
 // ---------------------------------------------------------------- appended (never pruned) rows
 
 // [Sec. "Preliminaries": each decode step concatenates the new token's key and value to the cache; pruning
@@ -337,29 +380,10 @@ __device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tg = lane >> 4, cn = lane & 15;
-    // (an exact split of the softmax scale, as for rows of varying length)
-    const uint32_t scale_bits = __float_as_uint(P.scale_log2);
-    const bool normal = (scale_bits & 0x7F800000u) != 0u;
-    const float q_scale = normal ? __uint_as_float(scale_bits & 0x7F800000u) : 1.0f;
-    const float s_scale = normal ? __uint_as_float((scale_bits & 0x807FFFFFu) | 0x3F800000u) : P.scale_log2;
+    float s_scale;
+    const float q_scale = split_scale(P.scale_log2, s_scale);
     uint4 qx[4];
-    {
-        const uint16_t *qrow = P.q + ((int64_t)b * P.Hq + h * G + (cn < G ? cn : G - 1)) * SPARK_D + 8 * tg;
-        if ((reinterpret_cast<uintptr_t>(P.q) & 15u) == 0u) {
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) qx[kb] = *reinterpret_cast<const uint4 *>(qrow + 32 * kb);
-        } else {                                                        // (2-byte alignment is all that is asked for)
-#pragma unroll 1
-            for (int kb = 0; kb < 4; ++kb) {
-                const uint16_t *p8 = qrow + 32 * kb;
-                uint32_t w[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) w[c] = (uint32_t)p8[2 * c] | ((uint32_t)p8[2 * c + 1] << 16);
-                const uint4 x = make_uint4(w[0], w[1], w[2], w[3]);
-                if (kb == 0) qx[0] = x; else if (kb == 1) qx[1] = x; else if (kb == 2) qx[2] = x; else qx[3] = x;
-            }
-        }
-    }
+    tail_query_rows<G>(P, b, h, cn, tg, qx);
     len = len < 0 ? 0 : (len > P.tail_cap ? P.tail_cap : len);
     // this block's share: rows [256 * part, 256 * part + 256), 64 of them by each wavefront
     const int c0 = part * kDecodeWaves * 64 + wave * 64;
@@ -397,13 +421,8 @@ __device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h
         for (int tau = 0; tau < 4; ++tau) s[tau] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
-            const uint32_t w[4] = {qx[kb].x, qx[kb].y, qx[kb].z, qx[kb].w};
             bf16x8 A;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                A[2 * c] = (__bf16)(cn < G ? bf16lo(w[c]) * q_scale : 0.0f);
-                A[2 * c + 1] = (__bf16)(cn < G ? bf16hi(w[c]) * q_scale : 0.0f);
-            }
+            tail_query_operand<G>(qx[kb], cn, q_scale, A);
 #pragma unroll
             for (int tau = 0; tau < 4; ++tau)
                 s[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, __builtin_bit_cast(bf16x8, kx[tau][kb]), s[tau], 0, 0, 0);
@@ -1840,6 +1859,12 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     if (P.trace != nullptr) { stamp(P, 4, wall_clock64()); stamp(P, 7, 1ull); }
 }
 
+}  // namespace spark
+
+#include "spark_decode_short.h"
+
+namespace spark {
+
 // ---------------------------------------------------------------- host-side launch
 
 template <int G, int TCT, int INT8, int TVC, int REC = 0, int VAR = 0, int WARM = 0>
@@ -1876,13 +1901,21 @@ static hipError_t launch_pv(const DecodeParams &P, int nblocks, hipStream_t st)
     return launch_one<G, TCT, INT8, -1>(P, nblocks, st);
 }
 
+// Whether launch_g has an instantiation for the key rows' length (rows that carry the all-channel statistics are longer)
+static inline bool row_length_instantiated(const SparkLayout &L)
+{
+    return !L.stats && (L.T == 26 || L.T == 38 || L.T == 64 || (L.T == 25 && !L.int8));
+}
+
 // One instantiation per query-group size G; each lives in its own translation unit (spark_decode_g*.hip) so
 // that the units compile in parallel.
 template <int G>
 hipError_t launch_g(const DecodeParams &P, int nblocks, hipStream_t st)
 {
-    // rows that carry the all-channel statistics are longer: only the any-length instantiations read them
-    const int T = P.L.stats ? -1 : P.L.T;
+    if constexpr (G <= 8) {
+        if (P.short_call) return launch_short<G>(P, nblocks, st);
+    }
+    const int T = row_length_instantiated(P.L) ? P.L.T : -1;      // (-1: any length)
     if (P.L.topp) return launch_one<G, 0, 0, 0, 0, 1>(P, nblocks, st);
     if (P.rec == 1) return P.L.int8 ? launch_one<G, 0, 1, 0, 1>(P, nblocks, st) : launch_one<G, 0, 0, 0, 1>(P, nblocks, st);
     if (P.rec == 2) return P.L.int8 ? launch_one<G, 0, 1, 0, 2>(P, nblocks, st) : launch_one<G, 0, 0, 0, 2>(P, nblocks, st);
