@@ -6,7 +6,8 @@
 //
 // Kernels
 //   spark_window_stat_kernel  a[b,h,j] = mean_g | mean_t Q_win[b,g,t,j] |  in float64, stored
-//                             as float32 together with 1/a (G*128 threads per (b, h)).
+//                             as float32 together with 1/a (G*128 threads per (b, h)); short calls
+//                             do this in the pruning launch (see one_launch).
 //   spark_prune_kernel        top-T selection and packing, SIXTEEN LANES A ROW: a wavefront takes four rows at a time (a
 //                             step; two steps a group), lane i of sixteen holds channels 8i .. 8i + 7.  A reduction
 //                             over a row is four lane moves that serve four rows, slots and sums are per lane, and
@@ -32,6 +33,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "spark_kernels.h"
 #include "spark_layout.h"
 #include "spark_wave.h"
@@ -39,6 +42,21 @@
 namespace spark {
 
 // ---------------------------------------------------------------- window statistic
+
+// header of a key cache, by 64 threads
+__device__ __forceinline__ void write_key_header(uint8_t *packed, const SparkLayout &L, int j)
+{
+    uint32_t v = 0;
+    if (j == 0) v = SPARK_MAGIC;
+    if (j == 1) v = (uint32_t)L.T;
+    if (j == 2) v = (uint32_t)L.int8;
+    if (j == 3) v = (uint32_t)L.batch;
+    if (j == 4) v = (uint32_t)L.n_kv_heads;
+    if (j == 5) v = (uint32_t)L.total_tokens;
+    if (j == 6) v = (uint32_t)L.ndw;
+    if (j == 8) v = (uint32_t)L.stats;      // (word 7 = 0: a key cache)
+    reinterpret_cast<uint32_t *>(packed)[j] = v;
+}
 
 // grid = batch * Hkv blocks, min(G, 8) * 128 threads: thread (g, j) sums head g's window column j in
 // float64 (t ascending), thread (0, j) then adds the G absolute means in g order -- the same order
@@ -82,19 +100,7 @@ __global__ __launch_bounds__(8 * SPARK_D) void spark_window_stat_kernel(const ui
     float *inva_out = reinterpret_cast<float *>(packed + L.off_inva);
     a_out[(int64_t)bh * SPARK_D + j] = a32;
     inva_out[(int64_t)bh * SPARK_D + j] = (a32 != 0.0f) ? (1.0f / a32) : 0.0f;
-    if (bh == 0 && j < 64) {
-        uint32_t *hdr = reinterpret_cast<uint32_t *>(packed);
-        uint32_t v = 0;
-        if (j == 0) v = SPARK_MAGIC;
-        if (j == 1) v = (uint32_t)L.T;
-        if (j == 2) v = (uint32_t)L.int8;
-        if (j == 3) v = (uint32_t)L.batch;
-        if (j == 4) v = (uint32_t)L.n_kv_heads;
-        if (j == 5) v = (uint32_t)L.total_tokens;
-        if (j == 6) v = (uint32_t)L.ndw;
-        if (j == 8) v = (uint32_t)L.stats;      // (word 7 = 0: a key cache)
-        hdr[j] = v;
-    }
+    if (bh == 0 && j < 64) write_key_header(packed, L, j);
 }
 
 // ---------------------------------------------------------------- top-T selection + pack
@@ -147,7 +153,7 @@ __host__ __device__ inline int spark_stage_words(const SparkLayout &L)
     return 4 * (((w + 3) / 4) | 1);
 }
 
-__host__ inline size_t spark_prune_lds_bytes(const SparkLayout &L)
+__host__ __device__ inline size_t spark_prune_lds_bytes(const SparkLayout &L)
 {
     return (size_t)kPruneWaves * (kStageRows * spark_stage_words(L) + kHistWords) * 4;
 }
@@ -235,17 +241,57 @@ __device__ __forceinline__ void bracket(const uint32_t (&key)[8], uint32_t T, ui
     }
 }
 
+// The channel weights of one (sequence, KV head) by a block of the pruning kernel: the sums of spark_window_stat_kernel in the
+// same order, two channels a thread.  absmean: G * 128 doubles of LDS, a_out: 128 floats of LDS.  Whole block; ends in a barrier.
+__device__ __forceinline__ void block_window_stat(const uint16_t *__restrict__ qwin, int Hq, int G, int W, int b, int h,
+                                                  double *absmean, float *a_out)
+{
+    for (int p = threadIdx.x; p < G * (SPARK_D / 2); p += kPruneWaves * 64) {
+        const int g = p / (SPARK_D / 2), j2 = 2 * (p % (SPARK_D / 2));
+        const char *src = reinterpret_cast<const char *>(qwin + ((int64_t)(b * Hq + h * G + g) * W) * SPARK_D + j2);
+        double s0 = 0.0, s1 = 0.0;
+        auto add_rows = [&](auto n, int t) __attribute__((always_inline)) {
+            uint32_t x[decltype(n)::value];
+#pragma unroll
+            for (int u = 0; u < decltype(n)::value; ++u) x[u] = *reinterpret_cast<const uint32_t *>(src + (t + u) * (2 * SPARK_D));
+#pragma unroll
+            for (int u = 0; u < decltype(n)::value; ++u) {
+                s0 += (double)bf16_bits_to_float(x[u] & 0xFFFFu);
+                s1 += (double)__uint_as_float(x[u] & 0xFFFF0000u);
+            }
+        };
+        int t = 0;
+        for (; t + 32 <= W; t += 32) add_rows(std::integral_constant<int, 32>(), t);
+        for (; t + 8 <= W; t += 8) add_rows(std::integral_constant<int, 8>(), t);
+        for (; t < W; ++t) add_rows(std::integral_constant<int, 1>(), t);
+        absmean[g * SPARK_D + j2] = fabs(s0 / (double)W);
+        absmean[g * SPARK_D + j2 + 1] = fabs(s1 / (double)W);
+    }
+    __syncthreads();
+    if (threadIdx.x < SPARK_D) {
+        double s = 0.0;
+        for (int gg = 0; gg < G; ++gg) s += absmean[gg * SPARK_D + threadIdx.x];
+        a_out[threadIdx.x] = (float)(s / (double)G);
+    }
+    __syncthreads();
+}
+
 // The first n_whole tiles (over all heads) take one wavefront each, the next n_half two, the others four; a wavefront takes its
 // rows a group (eight) at a time and writes them out a stage (sixteen, two groups) at a time.
 // MODE: bit 0 = int8 codes + scale instead of bf16 kept entries; bit 1 = the rows also carry the all-channel mean
 // and standard deviation of the row's saliencies (App. "Caching Pruned Channel Statistics", for the sampled recovery).
 // VALUES: the rows are value-cache rows (App. "Pruning Value Cache Channels"): the score of a channel is
 // |v| itself, there is no channel weight, no sequence bookkeeping and no statistic of the pruned set.
-template <int MODE, bool VALUES>
-__global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
+// WINDOW: short calls (a block is a tile, four wavefronts), where the window statistic's own launch would be a third of
+// the time: a block computes the channel weights of the sequences in its tile itself, in LDS, while its rows are on their way;
+// batch * Hkv further blocks store them for the reader of the cache.
+template <int MODE, bool VALUES, bool WINDOW = false>
+__global__ __launch_bounds__(kPruneWaves * 64, WINDOW ? 4 : 6) void spark_prune_kernel(
     const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
-    uint8_t *__restrict__ packed, SparkLayout L, uint32_t n_whole, uint32_t n_half, uint32_t digit_shift)
+    uint8_t *__restrict__ packed, SparkLayout L, uint32_t n_whole, uint32_t n_half, uint32_t digit_shift,
+    const uint16_t *__restrict__ qwin, int Hq, int W)
 {
+    static_assert(!(VALUES && WINDOW), "values have no channel weights");
     constexpr bool INT8 = (MODE & 1) != 0, STATS = (MODE & 2) != 0;
     extern __shared__ __align__(16) uint8_t smem[];
     const int lane = threadIdx.x & 63;
@@ -262,6 +308,23 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
         if (lane == 6) v = (uint32_t)L.ndw;
         if (lane == 7) v = 1u;   // value cache
         reinterpret_cast<uint32_t *>(packed)[lane] = v;
+    }
+    // (WINDOW: weights of the tile's sequences, in order, and which sequences they are, behind the wavefronts' areas)
+    float *const a_lds = reinterpret_cast<float *>(smem + spark_prune_lds_bytes(L));
+    int *const seq_lds = reinterpret_cast<int *>(a_lds + SPARK_TILE_TOKENS * SPARK_D);
+    const int G = WINDOW ? Hq / L.n_kv_heads : 1;
+    if constexpr (WINDOW) {
+        const int64_t bh = (int64_t)blockIdx.x - L.n_tiles * L.n_kv_heads;
+        if (bh >= 0) {                                   // (block-uniform)
+            block_window_stat(qwin, Hq, G, W, (int)(bh / L.n_kv_heads), (int)(bh % L.n_kv_heads), reinterpret_cast<double *>(smem), a_lds);
+            if (threadIdx.x < SPARK_D) {
+                const float a32 = a_lds[threadIdx.x];
+                reinterpret_cast<float *>(packed + L.off_a)[bh * SPARK_D + threadIdx.x] = a32;
+                reinterpret_cast<float *>(packed + L.off_inva)[bh * SPARK_D + threadIdx.x] = (a32 != 0.0f) ? (1.0f / a32) : 0.0f;
+                if (bh == 0 && threadIdx.x < 64) write_key_header(packed, L, threadIdx.x);
+            }
+            return;
+        }
     }
     // tile number over the heads, and which share of the tile
     uint32_t gt = wt, lg_per_tile = 0, share = 0;
@@ -310,19 +373,42 @@ __global__ __launch_bounds__(kPruneWaves * 64, 6) void spark_prune_kernel(
     int b = 0, seq_end_t = 0x7FFFFFFF;
     float a[8];
     const float *const a_all = reinterpret_cast<const float *>(packed + L.off_a) + (int64_t)h * SPARK_D + 8 * sub;
+    int a_slot = 0;
     auto load_a = [&]() __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(a_all + (int64_t)b * L.n_kv_heads * SPARK_D);
+        if constexpr (WINDOW) {
+            while (seq_lds[a_slot] != b) ++a_slot;       // (every sequence with a token in the tile is there)
+            src = reinterpret_cast<const float4 *>(a_lds + a_slot * SPARK_D + 8 * sub);
+        }
         const float4 lo = src[0], hi = src[1];
         a[0] = lo.x; a[1] = lo.y; a[2] = lo.z; a[3] = lo.w;
         a[4] = hi.x; a[5] = hi.y; a[6] = hi.z; a[7] = hi.w;
     };
-    if constexpr (!VALUES) {
-        const int64_t first = n0 + (t0 < nvalid ? t0 : nvalid - 1);
-        int hi = L.batch;     // invariant: cu[b] <= first < cu[hi]
-        while (hi - b > 1) {
-            const int mid = (b + hi) >> 1;
-            if (cu[mid] <= first) b = mid; else hi = mid;
+    auto sequence_of = [&](int64_t token) __attribute__((always_inline)) {
+        int lo = 0, hi = L.batch;     // invariant: cu[lo] <= token < cu[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (cu[mid] <= token) lo = mid; else hi = mid;
         }
+        return lo;
+    };
+    if constexpr (WINDOW) {
+        // (64 sequences at most: each has a token in the tile)
+        int sb = sequence_of(n0), end = cu[sb + 1];
+        for (int i = 0;; ++i) {
+            block_window_stat(qwin, Hq, G, W, sb, h, reinterpret_cast<double *>(smem), a_lds + i * SPARK_D);
+            if (threadIdx.x == 0) seq_lds[i] = sb;
+            if (end >= n0 + nvalid || i == SPARK_TILE_TOKENS - 1) break;
+            const int from = end;
+            do {
+                ++sb;
+                end = cu[sb + 1];
+            } while (end <= from);
+        }
+        __syncthreads();
+    }
+    if constexpr (!VALUES) {
+        b = sequence_of(n0 + (t0 < nvalid ? t0 : nvalid - 1));
         seq_end_t = (int)((int64_t)cu[b + 1] - n0);   // total < 2^31
         load_a();
     }
@@ -704,7 +790,7 @@ hipError_t launch_tiles(const uint16_t *x, int64_t tok_stride, int64_t head_stri
     auto launch = [&](auto kern) -> hipError_t {
         hipLaunchKernelGGL(kern, dim3((unsigned)((waves + kPruneWaves - 1) / kPruneWaves)), dim3(kPruneWaves * 64),
                            spark_prune_lds_bytes(L), st, x, tok_stride, head_stride, cu, packed, L, (uint32_t)n_whole, (uint32_t)n_half,
-                           digit_shift_of(L.T));
+                           digit_shift_of(L.T), (const uint16_t *)nullptr, 0, 0);
         return hipGetLastError();
     };
     switch (VALUES ? 0 : (L.int8 ? 1 : 0) + (L.stats ? 2 : 0)) {
@@ -725,9 +811,45 @@ hipError_t launch_window_stat(const uint16_t *qwin, uint8_t *packed, const Spark
     return hipGetLastError();
 }
 
+// The window statistic and the pruning in one launch: four wavefronts a tile, then a block per (sequence, KV head).
+static hipError_t launch_window_and_tiles(const uint16_t *k, int64_t tok_stride, int64_t head_stride, const uint16_t *qwin, const int32_t *cu,
+                                          uint8_t *packed, const SparkLayout &L, int Hq, int W, hipStream_t st)
+{
+    static_assert(kPruneWaves == 4, "a block is a tile");
+    const unsigned blocks = (unsigned)((L.n_tiles + L.batch) * L.n_kv_heads);
+    const size_t lds = spark_prune_lds_bytes(L) + SPARK_TILE_TOKENS * (SPARK_D * sizeof(float) + sizeof(int));
+    auto launch = [&](auto kern) -> hipError_t {
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kPruneWaves * 64), lds, st, k, tok_stride, head_stride, cu, packed, L, 0u, 0u,
+                           digit_shift_of(L.T), qwin, Hq, W);
+        return hipGetLastError();
+    };
+    switch ((L.int8 ? 1 : 0) + (L.stats ? 2 : 0)) {
+        case 0: return launch(&spark_prune_kernel<0, false, true>);
+        case 1: return launch(&spark_prune_kernel<1, false, true>);
+        case 2: return launch(&spark_prune_kernel<2, false, true>);
+        default: return launch(&spark_prune_kernel<3, false, true>);
+    }
+}
+
+// Whether the window statistic goes into the pruning launch: calls whose tiles have four wavefronts each, up to 512 of them.  A
+// launch of its own costs 4 us with the gap before the next; in the tile's block it costs 1 to 2 us per sequence that the tile
+// spans (a block's loads, one after the other: therefore 256 tokens a sequence on average) and reads the window once per
+// tile (therefore a bound on that: 16 MB).  One sequence, 8 KV heads, two launches / one (us):
+//   G = 4, W = 32: 100 tokens 11.6 / 10.6   1024 13.2 / 10.5   2048 13.2 / 10.7   4096 14.5 / 12.6
+//   G = 8, W = 64: 1024 15.8 / 13.9   G = 1, W = 16: 2048 13.5 / 11.2   one KV head, 16384 tokens: 12.3 / 10.5
+//   8 sequences of 260 tokens 13.7 / 12.6, of 300 to 700 14.4 / 12.9; prune and first decode step of 1024 tokens 23.3 / 21.2
+static bool one_launch(const uint16_t *qwin, const SparkLayout &L, int Hq, int W)
+{
+    const int64_t tiles = L.n_tiles * L.n_kv_heads;
+    const int G = Hq / L.n_kv_heads;
+    return tiles > 0 && tiles <= 512 && G <= 8 && (reinterpret_cast<uintptr_t>(qwin) & 3u) == 0u &&
+           L.total_tokens >= 256 * (int64_t)L.batch && tiles * G * W <= 65536;
+}
+
 hipError_t launch_prune(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const uint16_t *qwin,
                         const int32_t *cu, uint8_t *packed, const SparkLayout &L, int Hq, int W, hipStream_t st)
 {
+    if (one_launch(qwin, L, Hq, W)) return launch_window_and_tiles(k, k_tok_stride, k_head_stride, qwin, cu, packed, L, Hq, W, st);
     const hipError_t e = launch_window_stat(qwin, packed, L, Hq, W, st);
     if (e != hipSuccess) return e;
     return launch_tiles<false>(k, k_tok_stride, k_head_stride, cu, packed, L, st);
