@@ -174,7 +174,8 @@ __device__ __forceinline__ void write_header(uint8_t *packed, const SparkLayout 
 }
 
 // Selects the kept channels of a tile's rows: masks, means and counts; returns the words that the wavefront's rows take in the
-// stream.  Everything that another block reads is stored with device scope.
+// stream.  SAME_LAUNCH: another block of this launch reads them, so they are stored with device scope.
+template <bool SAME_LAUNCH>
 __device__ __forceinline__ uint32_t select_tile(const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride,
                                                 const int32_t *__restrict__ cu, uint8_t *__restrict__ packed, const SparkLayout &L,
                                                 int p_bp, int h, int64_t tile, uint32_t *wave_lds)
@@ -376,14 +377,16 @@ __device__ __forceinline__ uint32_t select_tile(const uint16_t *__restrict__ k, 
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) reinterpret_cast<uint8_t *>(wave_lds)[64 * s + lane] = (uint8_t)(masks >> (8 * s));
     prune_lds_sync();
-    __hip_atomic_store(reinterpret_cast<uint32_t *>(tile_out) + t0 * 4 + lane, wave_lds[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t *const mask_out = reinterpret_cast<uint32_t *>(tile_out) + t0 * 4 + lane;
+    if constexpr (SAME_LAUNCH) dir_store(mask_out, wave_lds[lane]); else *mask_out = wave_lds[lane];
     prune_lds_sync();
     const int t = t0 + 4 * sub + row;
     const bool valid = sub < kSteps && t < nvalid;
     if (sub < kSteps) {
         const float mu = my_cnt < SPARK_D ? __uint_as_float(my_mu) / (float)(SPARK_D - my_cnt) : 0.0f;
-        __hip_atomic_store(reinterpret_cast<uint64_t *>(tile_out + 1024 + t * 8),
-                           valid ? (uint64_t)__float_as_uint(mu) | ((uint64_t)my_cnt << 32) : 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint64_t *const fixed_out = reinterpret_cast<uint64_t *>(tile_out + 1024 + t * 8);
+        const uint64_t fixed = valid ? (uint64_t)__float_as_uint(mu) | ((uint64_t)my_cnt << 32) : 0ull;
+        if constexpr (SAME_LAUNCH) __hip_atomic_store(fixed_out, fixed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); else *fixed_out = fixed;
     }
     // (every row rounded up to a whole word)
     return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(valid ? (my_cnt + 1u) / 2u : 0u), 63);
@@ -409,6 +412,7 @@ __device__ __forceinline__ void request_rows(const uint16_t *__restrict__ k, int
 // Writes the kept entries (rows in x) of a tile whose rows have been selected, by any block, to its place in the head's
 // stream: every lane finds the slots of its eight channels from the row's mask byte, the entries of sixteen rows are put
 // together in LDS and leave as whole words.  `sum`: words of all tiles up to it.
+template <bool SAME_LAUNCH>
 __device__ __forceinline__ void write_tile(const uint4 (&x)[kSteps], uint8_t *__restrict__ packed, const SparkLayout &L, int h, int64_t tile,
                                            uint32_t sum, uint32_t *wave_lds)
 {
@@ -418,8 +422,9 @@ __device__ __forceinline__ void write_tile(const uint4 (&x)[kSteps], uint8_t *__
     const int t0 = wave * kRowsPerWave;
     if (t0 >= L.total_tokens - tile * SPARK_TILE_TOKENS) return;       // (no block barrier is used)
     const uint8_t *tp = packed + L.off_tiles + ((int64_t)h * L.n_tiles + tile) * L.tile_bytes;
-    const uint32_t word_of_mask = dir_load(reinterpret_cast<const uint32_t *>(tp) + t0 * 4 + lane);
-    const uint32_t cnt = dir_load(reinterpret_cast<const uint32_t *>(tp + 1024 + lane * 8 + 4));
+    const uint32_t *const mask_in = reinterpret_cast<const uint32_t *>(tp) + t0 * 4 + lane;
+    const uint32_t *const cnt_in = reinterpret_cast<const uint32_t *>(tp + 1024 + lane * 8 + 4);
+    const uint32_t word_of_mask = SAME_LAUNCH ? dir_load(mask_in) : *mask_in, cnt = SAME_LAUNCH ? dir_load(cnt_in) : *cnt_in;
     prune_lds_sync();
     wave_lds[lane] = word_of_mask;
     prune_lds_sync();
@@ -480,7 +485,7 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_prune_kernel(
     }
     uint32_t *const wave_lds = lds_all[wave];
     uint32_t words = 0;
-    if (mine <= L.n_tiles) words = select_tile(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, mine - 1, wave_lds);
+    if (mine <= L.n_tiles) words = select_tile<true>(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, mine - 1, wave_lds);
     const int64_t late = mine - 1 - lag;                 // the tile to be written
     uint4 x[kSteps];
     if (late >= 0) request_rows(k, k_tok_stride, k_head_stride, L, h, late, x);
@@ -512,7 +517,7 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_prune_kernel(
     }
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    write_tile(x, packed, L, h, late, (uint32_t)__builtin_amdgcn_readfirstlane((int)sum_of_late), wave_lds);
+    write_tile<true>(x, packed, L, h, late, (uint32_t)__builtin_amdgcn_readfirstlane((int)sum_of_late), wave_lds);
 }
 
 // ---- the same in three launches: selection (a block per tile), directory (a block per head), writing (a block per tile)
@@ -527,7 +532,7 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_select_kernel(
     const int h = (int)(blockIdx.x / (uint32_t)L.n_tiles);
     const int64_t tile = blockIdx.x % (uint32_t)L.n_tiles;
     if (blockIdx.x == 0 && threadIdx.x < 16) write_header(packed, L, p_bp);
-    const uint32_t words = select_tile(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, tile, hist_all[wave]);
+    const uint32_t words = select_tile<false>(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, tile, hist_all[wave]);
     if ((threadIdx.x & 63) == 0) words_of_wave[wave] = words;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -577,7 +582,7 @@ __global__ __launch_bounds__(kWaves * 64) void spark_topp_pack_kernel(const uint
     uint4 x[kSteps];
     request_rows(k, k_tok_stride, k_head_stride, L, h, tile, x);
     const uint32_t sum = reinterpret_cast<const uint32_t *>(packed + L.off_dir)[(int64_t)h * (L.n_tiles + 1) + tile + 1];
-    write_tile(x, packed, L, h, tile, sum, stage_all[wave]);
+    write_tile<false>(x, packed, L, h, tile, sum, stage_all[wave]);
 }
 
 // canonical export, one thread per (token, KV head) row
