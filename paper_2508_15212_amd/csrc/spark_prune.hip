@@ -158,6 +158,13 @@ __host__ __device__ inline size_t spark_prune_lds_bytes(const SparkLayout &L)
     return (size_t)kPruneWaves * (kStageRows * spark_stage_words(L) + kHistWords) * 4;
 }
 
+// WINDOW: sequences that can have a token in one tile, and the LDS for their channel weights besides
+__host__ __device__ inline int spark_window_slots(const SparkLayout &L) { return L.batch < SPARK_TILE_TOKENS ? L.batch : SPARK_TILE_TOKENS; }
+__host__ inline size_t spark_window_lds_bytes(const SparkLayout &L)
+{
+    return spark_prune_lds_bytes(L) + (size_t)spark_window_slots(L) * (SPARK_D * sizeof(float) + sizeof(int));
+}
+
 // The kept ones of a lane's eight channels (x: two a word; kb: the channels' wave masks) go to the 16-bit places in LDS
 // from byte address `slot` on; returns the sum of the other ones' saliencies (their float32 bits in key).  Stores run
 // under the masks and additions under their complements; all lanes are active before and after.
@@ -311,7 +318,8 @@ __global__ __launch_bounds__(kPruneWaves * 64, WINDOW ? 4 : 6) void spark_prune_
     }
     // (WINDOW: weights of the tile's sequences, in order, and which sequences they are, behind the wavefronts' areas)
     float *const a_lds = reinterpret_cast<float *>(smem + spark_prune_lds_bytes(L));
-    int *const seq_lds = reinterpret_cast<int *>(a_lds + SPARK_TILE_TOKENS * SPARK_D);
+    const int a_slots = spark_window_slots(L);
+    int *const seq_lds = reinterpret_cast<int *>(a_lds + a_slots * SPARK_D);
     const int G = WINDOW ? Hq / L.n_kv_heads : 1;
     if constexpr (WINDOW) {
         const int64_t bh = (int64_t)blockIdx.x - L.n_tiles * L.n_kv_heads;
@@ -393,12 +401,11 @@ __global__ __launch_bounds__(kPruneWaves * 64, WINDOW ? 4 : 6) void spark_prune_
         return lo;
     };
     if constexpr (WINDOW) {
-        // (64 sequences at most: each has a token in the tile)
         int sb = sequence_of(n0), end = cu[sb + 1];
         for (int i = 0;; ++i) {
             block_window_stat(qwin, Hq, G, W, sb, h, reinterpret_cast<double *>(smem), a_lds + i * SPARK_D);
             if (threadIdx.x == 0) seq_lds[i] = sb;
-            if (end >= n0 + nvalid || i == SPARK_TILE_TOKENS - 1) break;
+            if (end >= n0 + nvalid || i == a_slots - 1) break;
             const int from = end;
             do {
                 ++sb;
@@ -819,9 +826,8 @@ static hipError_t launch_window_and_tiles(const uint16_t *k, int64_t tok_stride,
 {
     static_assert(kPruneWaves == 4, "a block is a tile");
     const unsigned blocks = (unsigned)((L.n_tiles + L.batch) * L.n_kv_heads);
-    const size_t lds = spark_prune_lds_bytes(L) + SPARK_TILE_TOKENS * (SPARK_D * sizeof(float) + sizeof(int));
     auto launch = [&](auto kern) -> hipError_t {
-        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kPruneWaves * 64), lds, st, k, tok_stride, head_stride, cu, packed, L, 0u, 0u,
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(kPruneWaves * 64), spark_window_lds_bytes(L), st, k, tok_stride, head_stride, cu, packed, L, 0u, 0u,
                            digit_shift_of(L.T), qwin, Hq, W);
         return hipGetLastError();
     };
@@ -833,19 +839,23 @@ static hipError_t launch_window_and_tiles(const uint16_t *k, int64_t tok_stride,
     }
 }
 
-// Whether the window statistic goes into the pruning launch: calls whose tiles have four wavefronts each, up to 512 of them.  A
-// launch of its own costs 4 us with the gap before the next; in the tile's block it costs 1 to 2 us per sequence that the tile
-// spans (a block's loads, one after the other: therefore 256 tokens a sequence on average) and reads the window once per
-// tile (therefore a bound on that: 16 MB).  One sequence, 8 KV heads, two launches / one (us):
-//   G = 4, W = 32: 100 tokens 11.6 / 10.6   1024 13.2 / 10.5   2048 13.2 / 10.7   4096 14.5 / 12.6
+// Whether the window statistic goes into the pruning launch: calls whose blocks, one a tile, are all resident at once (three a
+// compute unit, four would fit their registers; fewer where they take more LDS).  A launch of its own costs 4 us with the gap before the
+// next; in the tile's block it costs 1 to 2 us per sequence that the tile spans (a block's loads, one after the other:
+// therefore 256 tokens a sequence on average) and reads the window once per tile (therefore a bound on that: 32 MB).  One
+// sequence, 8 KV heads, two launches / one (us):
+//   G = 4, W = 32: 100 tokens 11.6 / 10.6   1024 13.2 / 10.5   2048 13.2 / 10.7   4096 14.6 / 12.5   5000 15.3 / 14.0
 //   G = 8, W = 64: 1024 15.8 / 13.9   G = 1, W = 16: 2048 13.5 / 11.2   one KV head, 16384 tokens: 12.3 / 10.5
 //   8 sequences of 260 tokens 13.7 / 12.6, of 300 to 700 14.4 / 12.9; prune and first decode step of 1024 tokens 23.3 / 21.2
+// The line: 6000 tokens (760 blocks) 15.2 / 14.8, five of 1000 to 2000 (980 blocks) 16.5 / 17.1; with more blocks than are
+// resident, 8192 tokens where there was room for 768, 17.1 / 19.9.
 static bool one_launch(const uint16_t *qwin, const SparkLayout &L, int Hq, int W)
 {
-    const int64_t tiles = L.n_tiles * L.n_kv_heads;
+    const int64_t tiles = L.n_tiles * L.n_kv_heads, blocks = tiles + (int64_t)L.batch * L.n_kv_heads;
     const int G = Hq / L.n_kv_heads;
-    return tiles > 0 && tiles <= 512 && G <= 8 && (reinterpret_cast<uintptr_t>(qwin) & 3u) == 0u &&
-           L.total_tokens >= 256 * (int64_t)L.batch && tiles * G * W <= 65536;
+    const int64_t by_lds = (int64_t)(160 * 1024 / spark_window_lds_bytes(L));
+    return tiles > 0 && blocks <= 256 * (by_lds < 3 ? by_lds : 3) && G <= 8 && (reinterpret_cast<uintptr_t>(qwin) & 3u) == 0u &&
+           L.total_tokens >= 256 * (int64_t)L.batch && tiles * G * W <= 131072;
 }
 
 hipError_t launch_prune(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const uint16_t *qwin,
