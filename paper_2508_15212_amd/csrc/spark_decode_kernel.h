@@ -575,7 +575,9 @@ __device__ __forceinline__ void stamp(const DecodeParams &P, int word, unsigned 
 // its own query table, on a contiguous range of (sequence, tile) items; nothing in a block waits for another
 // wavefront, and a sequence boundary inside a range costs one partial store and one table rebuild while the
 // next tile is already in flight.
-template <int G, int TCT, int INT8, int TVC, int REC = 0, int VAR = 0, int WARM = 0>
+// TAIL: 0 leaves out the appended rows' blocks.  The balanced mode has an instantiation without them: their code, which such a call
+// never runs, costs its tile loop 1 % (64 ragged sequences, T = 64: 56.0 -> 55.3 us).
+template <int G, int TCT, int INT8, int TVC, int REC = 0, int VAR = 0, int WARM = 0, int TAIL = 1>
 __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void spark_decode_kernel(DecodeParams P)
 {
     static_assert(!VAR || (TCT == 0 && INT8 == 0 && TVC == 0 && REC == 0), "variable-length rows: any-length bf16 path only");
@@ -643,7 +645,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     // wavefronts, KV head); when rows have been appended after prefill, B * Hkv * ntail more blocks follow, each
     // taking 256 of a (batch, KV head)'s appended rows
     const int nmain = (WARM ? P.warm_waves / kDecodeWaves : P.nchunk_max) * P.Hkv;
-    const bool is_tail = (int)blockIdx.x >= nmain;      // block-uniform
+    const bool is_tail = TAIL && (int)blockIdx.x >= nmain;      // block-uniform
     const int tb = (int)blockIdx.x - nmain;
     const int gid = is_tail ? -1 : (int)(blockIdx.x / P.Hkv);
     const int h = is_tail ? (tb / P.ntail) % P.Hkv : (int)(blockIdx.x % P.Hkv);
@@ -673,7 +675,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     }
     // partial slot of (q head index within the batch element's heads, i-th partial of a (batch, KV head))
     auto slot_of = [&](const PairInfo &pr, int qh, int i) -> int64_t {
-        return (i < pr.nsplit) ? (int64_t)(pr.first + i) * P.Hq + qh
+        return (!TAIL || i < pr.nsplit) ? (int64_t)(pr.first + i) * P.Hq + qh
                                : P.tail_base + ((int64_t)pr.b * P.Hq + qh) * P.tail_slots + (i - pr.nsplit);
     };
     // Folds the nmerge partial states of pair pr for query head h * G + g and writes the output (one wavefront;
@@ -744,7 +746,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     };
     const int b = pi.b;
     const int nsplit = pi.nsplit;
-    const int nmerge = nsplit + P.ntail;                 // partial states the last arrival folds
+    const int nmerge = nsplit + (TAIL ? P.ntail : 0);    // partial states the last arrival folds
     if (!is_tail) {
     float m[G], l[G], R[G];
     f32x4 acc[8];
@@ -1867,10 +1869,10 @@ namespace spark {
 
 // ---------------------------------------------------------------- host-side launch
 
-template <int G, int TCT, int INT8, int TVC, int REC = 0, int VAR = 0, int WARM = 0>
+template <int G, int TCT, int INT8, int TVC, int REC = 0, int VAR = 0, int WARM = 0, int TAIL = 1>
 static hipError_t launch_one(const DecodeParams &P, int nblocks, hipStream_t st)
 {
-    hipLaunchKernelGGL((spark_decode_kernel<G, TCT, INT8, TVC, REC, VAR, WARM>), dim3(nblocks), dim3(kDecodeWaves * 64), 0, st, P);
+    hipLaunchKernelGGL((spark_decode_kernel<G, TCT, INT8, TVC, REC, VAR, WARM, TAIL>), dim3(nblocks), dim3(kDecodeWaves * 64), 0, st, P);
     return hipGetLastError();
 }
 
@@ -1879,6 +1881,7 @@ template <int G, int TCT, int INT8>
 static hipError_t launch_plain(const DecodeParams &P, int nblocks, hipStream_t st)
 {
     if constexpr (G <= 8) {
+        if (P.warm_waves > 0 && P.ntail == 0) return launch_one<G, TCT, INT8, 0, 0, 0, 1, 0>(P, nblocks, st);
         if (P.warm_waves > 0) return launch_one<G, TCT, INT8, 0, 0, 0, 1>(P, nblocks, st);
     }
     return launch_one<G, TCT, INT8, 0>(P, nblocks, st);
