@@ -21,13 +21,13 @@
 //   write_tile    takes the dense key rows again; every lane finds the slots of its eight channels from the row's mask byte, the
 //                 kept entries of sixteen rows are put together in LDS and leave as whole words of the value stream.
 //   spark_topp_prune_kernel   both, for small and large calls, in one launch: a block selects a tile and then writes one that
-//                 was selected about 2048 tiles (over all heads) earlier, while one more block per head turns the
-//                 tiles' lengths into the directory as they arrive.
+//                 was selected about 2048 tiles (over all heads) earlier; one block in up to 32 turns the lengths
+//                 that the blocks before it have filed into the directory's sums.
 //   spark_topp_select_kernel, spark_topp_scan_kernel, spark_topp_pack_kernel   the same one after the other, for calls in
 //                 between (measurements beside the launch).
 // What bounds them (one sequence of 65536 tokens x 8 KV heads, 51 kept channels a row): the selection by vector issue, 75 to 80
 // instructions a row, 62 us alone; the writing by memory, 31 us alone for 134 MB read and 54 MB written.  In one launch they
-// overlap: 100 -> 85 us for the whole call.  Tried: every block writing its own tile (137 us: it waits for the slowest
+// overlap: 96 -> 84 us for the whole call (calls back to back).  Tried: every block writing its own tile (137 us: it waits for the slowest
 // block in front, holding its place), blocks that stay and write a tile late from LDS (109 us), 8 blocks per compute unit
 // (spills, 109 us), 6 (90 us).
 #include <hip/hip_runtime.h>
@@ -102,30 +102,28 @@ constexpr uint32_t kOwnWords = 0xFFFFE000u;
 __device__ __forceinline__ uint32_t dir_load(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void dir_store(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// One wavefront follows a head's directory and turns the entries, as the blocks file them, into running sums.
-__device__ __forceinline__ void sum_directory(uint32_t *dir, int64_t n_tiles, int lane)
+// Words of all tiles up to the one whose entry is dir[last], by one wavefront: from that entry back, own words are added until
+// an entry holds a sum or there are no more.  Waits for entries that have not been filed.  after: words of the `lane` entries
+// behind dir[last - lane].
+__device__ __forceinline__ uint32_t words_up_to(const uint32_t *dir, int64_t last, int lane, uint32_t &after)
 {
-    constexpr int kAhead = 4;                            // entries a lane requests at a time
+    const int64_t end = last;
     uint32_t sum = 0;
-    for (int64_t next = 1; next <= n_tiles;) {
-        uint32_t v[kAhead];
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            const int64_t i = next + 64 * u + lane;
-            v[u] = i <= n_tiles ? dir_load(dir + i) : 0u;
+    for (;;) {
+        const int64_t i = last - lane;                   // lane 0: the nearest
+        const uint32_t v = i > 0 ? dir_load(dir + i) : 0u;
+        const uint64_t sums = __ballot(i <= 0 || (v != 0u && v < kOwnWords));
+        const int n = sums != 0ull ? (int)__builtin_ctzll(sums) : 64;           // own words to be added, then a sum
+        if (__ballot(lane < n && v == 0u) != 0ull) {
+            __builtin_amdgcn_s_sleep(8);                 // (what many ask for at a time comes late)
+            continue;
         }
-        const int64_t start = next;
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            if (next != start + 64 * u) break;           // (wave-uniform)
-            const uint64_t missing = ~__ballot(v[u] >= kOwnWords);
-            const int there = missing != 0ull ? (int)__builtin_ctzll(missing) : 64;
-            const uint32_t upto = wave_inclusive_sum(lane < there ? v[u] - kOwnWords : 0u);
-            if (lane < there) dir_store(dir + next + lane, sum + upto);
-            sum += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-            next += there;
-        }
-        if (next == start) __builtin_amdgcn_s_sleep(2);
+        const uint32_t add = lane < n ? v - kOwnWords : (lane == n ? v : 0u);
+        const uint32_t upto = wave_inclusive_sum(add);
+        if (last == end) after = upto - add;
+        sum += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+        if (n < 64) return sum;
+        last -= 64;
     }
 }
 
@@ -453,12 +451,17 @@ __device__ __forceinline__ void write_tile(const uint4 (&x)[kSteps], uint8_t *__
     for (uint32_t i = lane; i < nwords; i += 64) dst[i] = wave_lds[i];
 }
 
-// Blocks take tickets of their head in the order in which they start: ticket 0 sums the directory, ticket i selects tile
-// i - 1 and then writes the entries of tile i - 1 - lag, whose place in the stream is known by then as a rule; `lag` more
-// tickets only write.
+// Blocks take tickets of their head in the order in which they start: ticket i selects tile i, files its words in the
+// directory, and then writes the entries of tile i - lag, whose place in the stream is known by then as a rule; `lag` more
+// tickets only write.  Every group-th ticket turns the words of the last `group` tiles into sums.
+// Every wait ends, however few blocks are resident, because nobody waits for a block that may not have started: who makes sums
+// waits for words that smaller tickets file before they wait for anything; who writes tile i - lag waits for a sum that a
+// smaller ticket makes (group <= lag, or lag = 0 and group = 1: its own).
+// (A directory entry is read by few: a line that many ask for is handed out about every 10 ns.  Every block adding up its own
+// place from the entries before it: 133 us instead of the 87 us of 65536 tokens x 8 heads.)
 __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_prune_kernel(
     const uint16_t *__restrict__ k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *__restrict__ cu,
-    uint8_t *__restrict__ packed, SparkLayout L, int p_bp, int lag)
+    uint8_t *__restrict__ packed, SparkLayout L, int p_bp, int lag, int group)
 {
     // per wavefront: counting bins of four rows, or the kept entries of sixteen
     __shared__ __align__(16) uint32_t lds_all[kWaves][kRowsPerWave * SPARK_D / 2];
@@ -470,26 +473,22 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_prune_kernel(
     const int h = (int)(blockIdx.x % (uint32_t)L.n_kv_heads);
     uint32_t *const dir = reinterpret_cast<uint32_t *>(packed + L.off_dir) + (int64_t)h * (L.n_tiles + 1);
     if (blockIdx.x == 0 && threadIdx.x < 16) write_header(packed, L, p_bp);
-    // The tickets are counted in the directory's first entry, which the last taker sets back to 0.  Every wait ends: who
-    // waits for tile i's place needs words that blocks with smaller tickets file before they wait for anything.
+    // The tickets are counted in the directory's first entry, which the last taker sets back to 0.
     if (threadIdx.x == 0) {
         const uint32_t t = __hip_atomic_fetch_add(dir, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((int64_t)t == L.n_tiles + lag) dir_store(dir, 0u);
+        if ((int64_t)t == L.n_tiles + lag - 1) dir_store(dir, 0u);
         ticket = t;
     }
     __syncthreads();
     const int64_t mine = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)ticket);
-    if (mine == 0) {
-        if (wave == 0) sum_directory(dir, L.n_tiles, lane);
-        return;
-    }
     uint32_t *const wave_lds = lds_all[wave];
     uint32_t words = 0;
-    if (mine <= L.n_tiles) words = select_tile<true>(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, mine - 1, wave_lds);
-    const int64_t late = mine - 1 - lag;                 // the tile to be written
+    if (mine < L.n_tiles) words = select_tile<true>(k, k_tok_stride, k_head_stride, cu, packed, L, p_bp, h, mine, wave_lds);
+    const int64_t late = mine - lag;                     // the tile to be written
     uint4 x[kSteps];
     if (late >= 0) request_rows(k, k_tok_stride, k_head_stride, L, h, late, x);
-    if (mine <= L.n_tiles) {
+    uint32_t sum = 0;                                    // (wavefront 0: words of all tiles up to `late`)
+    if (mine < L.n_tiles) {
         if (lane == 0) words_of_wave[wave] = words;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);         // the rows' fixed part has been acknowledged
@@ -498,7 +497,13 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_prune_kernel(
             uint32_t all = 0;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) all += words_of_wave[w];
-            dir_store(dir + mine, kOwnWords + all);
+            dir_store(dir + mine + 1, kOwnWords + all);
+        }
+        const int in_group = (int)(mine % group);
+        if (wave == 0 && (in_group == group - 1 || mine == L.n_tiles - 1)) {
+            uint32_t after;
+            sum = words_up_to(dir, mine + 1, lane, after);
+            if (lane <= in_group) dir_store(dir + mine + 1 - lane, sum - after);
         }
     }
     if (late < 0) return;
@@ -507,11 +512,12 @@ __global__ __launch_bounds__(kWaves * 64, 7) void spark_topp_prune_kernel(
     // still be on its way when this one is there.)  One wavefront asks for all four, and not too often: what many ask for
     // at a time comes late.
     if (wave == 0) {
-        uint32_t sum;
-        for (;;) {
-            sum = (uint32_t)__builtin_amdgcn_readfirstlane((int)dir_load(dir + late + 1));
-            if (sum != 0u && sum < kOwnWords) break;
-            __builtin_amdgcn_s_sleep(8);
+        if (late != mine) {
+            for (;;) {
+                sum = (uint32_t)__builtin_amdgcn_readfirstlane((int)dir_load(dir + late + 1));
+                if (sum != 0u && sum < kOwnWords) break;
+                __builtin_amdgcn_s_sleep(8);
+            }
         }
         if (lane == 0) sum_of_late = sum;
     }
@@ -626,15 +632,18 @@ hipError_t launch_prune_topp(const uint16_t *k, int64_t k_tok_stride, int64_t k_
     // One launch or three.  In one, few tiles (lag 0: a block writes its own tile) save two launches, and many tiles (a lag
     // of about as many as the chip has in flight) hide the writing, which waits for memory, behind the selection, which
     // is bound by vector issue.  In between, where all blocks select at once and then all write, the way from a tile's words to
-    // its place (three trips through memory) costs more than the launches; and with few heads the count of the tickets
-    // (11.5 ns each) does.  Three launches / one (us, 51 kept channels a row, window kernel included):
-    //   8 heads, tiles:  64 19 / 15   256 19 / 17   512 20 / 20   1024 24 / 27   1504 29 / 33   2048 35 / 33   4096 57 / 48   8192 100 / 85
-    //   1 head:  128 18 / 17   512 19 / 23   1024 24 / 33      2 heads:  2048 36 / 42
-    if (tiles <= 256 || (tiles >= 2048 && L.n_kv_heads >= 4)) {
-        const int lag = tiles <= 256 ? 0 : 2048 / L.n_kv_heads;
-        const int64_t tickets = L.n_tiles + lag + 1;
+    // its place (two trips through memory, or one for every 64 tiles of a head) costs more than the launches; and with few heads
+    // the count of the tickets (11.5 ns each) does.  Three launches / one (us, 51 kept channels a row, window kernel included):
+    //   8 heads, tiles:  64 17.8 / 15.3   256 18.0 / 17.1   512 20.2 / 27   1024 23.9 / 39   2048 35.6 / 34.3   4096 56.5 / 49.7   8192 96.3 / 84.2
+    //   1 head:  64 17.5 / 15.8   128 16.7 / 17.4   256 17.0 / 19.3   1024 24 / 63      2 heads:  128 17.2 / 16.3   256 17.2 / 18.1   2048 37 / 57
+    //   4 heads:  256 18.3 / 17.2   2048 35.8 / 35.6   4096 57.0 / 52.8   8192 98 / 87      16 heads:  4096 56.7 / 49.3
+    //   64 heads:  2048 36.0 / 32.8      1024 heads:  2048 41.0 / 34.5      4096 heads:  8192 129 / 111
+    if ((tiles <= 256 && L.n_tiles <= 64) || (tiles >= 2048 && L.n_kv_heads >= 4)) {
+        const int lag = tiles <= 256 ? 0 : (L.n_kv_heads < 2048 ? 2048 / L.n_kv_heads : 1);
+        const int group = lag < 4 ? 1 : (lag < 64 ? lag / 2 : 32);
+        const int64_t tickets = L.n_tiles + lag;
         hipLaunchKernelGGL(spark_topp_prune_kernel, dim3((unsigned)(tickets * L.n_kv_heads)), threads, 0, st, k, k_tok_stride,
-                           k_head_stride, cu, packed, L, p_bp, lag);
+                           k_head_stride, cu, packed, L, p_bp, lag, group);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(spark_topp_select_kernel, dim3((unsigned)tiles), threads, 0, st, k, k_tok_stride, k_head_stride, cu, packed,

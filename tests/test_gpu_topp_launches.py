@@ -12,11 +12,18 @@ from tests.test_gpu_topp import _run
 pytestmark = pytest.mark.gpu
 
 
-# (KV heads, tokens): one launch up to 256 tiles over all heads, and from 2048 on with four heads or more
-@pytest.mark.parametrize("hkv,tokens", [(1, 1), (1, 256 * 64), (1, 256 * 64 + 1), (8, 32 * 64 - 5), (8, 33 * 64), (4, 511 * 64), (4, 512 * 64 - 1),
+# (KV heads, tokens): one launch up to 256 tiles over all heads, 64 of each, and from 2048 on with four heads or more
+@pytest.mark.parametrize("hkv,tokens", [(1, 1), (1, 64 * 64), (1, 65 * 64), (4, 64 * 64 - 9), (1, 256 * 64), (1, 256 * 64 + 1), (8, 32 * 64 - 5), (8, 33 * 64), (4, 511 * 64), (4, 512 * 64 - 1),
                                         (3, 683 * 64), (5, 410 * 64 + 17)])
 def test_both_sides_of_the_rule(hkv, tokens):
     w = wl.small(name=f"topp{hkv}x{tokens}", batch=2, n_q_heads=hkv, n_kv_heads=hkv, seqlens=(tokens - tokens // 3, tokens // 3), seed=351 + hkv)
+    _run(w, wl.generate(w), p_bp=9500, decode=False)
+
+
+@pytest.mark.parametrize("hkv,tokens", [(2560, 64), (4100, 40), (700, 200)])
+def test_more_heads_than_the_chip_holds_blocks(hkv, tokens):
+    """No block may wait for one that has not started: 2304 blocks or fewer are resident at once."""
+    w = wl.small(name=f"toppheads{hkv}", batch=1, n_q_heads=hkv, n_kv_heads=hkv, seqlens=(tokens,), seed=371)
     _run(w, wl.generate(w), p_bp=9500, decode=False)
 
 
