@@ -322,7 +322,9 @@ spark_status spark_unpack_values(const spark_desc *desc, const void *packed_v, u
  *   p_basis_points  1 .. 10000 (9900 = the paper's 99 %)
  *   packed_out      spark_packed_topp_bytes(desc) bytes, 256-byte aligned: sized for the worst case (every row
  *                   keeps all 128 channels); rows are 24 bytes (mask, mu, count) plus two bytes per kept entry
- *                   in a value stream, and only the used part of the stream is written or ever read
+ *                   in a value stream per KV head, and only the used part of the stream is written or ever read
+ *                   (it is addressed with 32 bits: fewer than 2^32 words, two entries each, every row rounded up;
+ *                   67.1 million tokens that keep all their channels)
  * Uses batch, head counts, window, total_tokens and the k strides of `desc`; desc->keep is not used;
  * bf16 storage only (SPARK_ERR_UNSUPPORTED for SPARK_PACK_INT8 or stats).  Other arguments as spark_prune.
  */

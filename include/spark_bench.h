@@ -36,6 +36,14 @@ spark_status spark_probe_read(const void *src, size_t bytes, void *sink, int32_t
  */
 spark_status spark_decode_timeline(void *device_buffer, size_t bytes);
 
+/*
+ * Which of its forms a call with this description takes (for tests and timings of the forms; launches nothing):
+ *   SPARK_CALL_PRUNE_TOPP   1: selection and writing in one launch   3: in three
+ * 0 for an invalid description, another call, or a call that launches nothing.
+ */
+#define SPARK_CALL_PRUNE_TOPP 1
+int32_t spark_call_form(const spark_desc *desc, int32_t call);
+
 #ifdef __cplusplus
 }
 #endif

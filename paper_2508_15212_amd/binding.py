@@ -24,7 +24,8 @@ EXPORTS = ["spark_packed_bytes", "spark_prune_workspace", "spark_decode_workspac
            "spark_packed_values_bytes", "spark_prune_values", "spark_unpack_values", "spark_decode_attn_values", "spark_decode_attn_tail",
            "spark_decode_attn_values_tail", "spark_decode_attn_sampled", "spark_unpack_stats", "spark_check_packed",
            "spark_decode_attn_static", "spark_packed_topp_bytes", "spark_prune_topp", "spark_decode_attn_topp",
-           "spark_unpack_topp", "spark_decode_timeline"]
+           "spark_unpack_topp", "spark_decode_timeline", "spark_call_form"]
+CALL_PRUNE_TOPP = 1
 
 
 class SparkError(RuntimeError):
@@ -113,6 +114,8 @@ def load() -> ctypes.CDLL:
     lib.spark_probe_read.argtypes = [vp, ctypes.c_size_t, vp, ctypes.c_int32, vp]
     lib.spark_decode_timeline.restype = ctypes.c_int
     lib.spark_decode_timeline.argtypes = [vp, ctypes.c_size_t]
+    lib.spark_call_form.restype = ctypes.c_int32
+    lib.spark_call_form.argtypes = [dp, ctypes.c_int32]
     lib.spark_status_string.restype = ctypes.c_char_p
     lib.spark_status_string.argtypes = [ctypes.c_int]
     _lib = lib
@@ -285,6 +288,11 @@ def decode_timeline(buffer) -> None:
     else:
         rc = load().spark_decode_timeline(_ptr(buffer), buffer.numel() * buffer.element_size())
     _check(rc, "spark_decode_timeline")
+
+
+def call_form(desc: SparkDesc, call: int) -> int:
+    """spark_call_form (include/spark_bench.h): which of its forms a call (CALL_*) takes with this description."""
+    return int(load().spark_call_form(ctypes.byref(desc), int(call)))
 
 
 def probe_read(src: torch.Tensor, sink: torch.Tensor, n_blocks: int) -> None:

@@ -7,6 +7,7 @@
 #include <mutex>
 
 #include "../../include/spark.h"
+#include "../../include/spark_bench.h"
 #include "spark_kernels.h"
 #include "spark_layout.h"
 
@@ -439,6 +440,14 @@ spark_status spark_decode_attn_topp(const spark_desc *desc, const void *q_bf16, 
     if (desc && (desc->pack_dtype != SPARK_PACK_BF16 || desc->stats)) return SPARK_ERR_UNSUPPORTED;
     return decode_common(desc, q_bf16, packed, v_bf16, nullptr, cu_seqlens, out, workspace, workspace_bytes, hip_stream,
                          nullptr, nullptr, nullptr, 0, 0, true);
+}
+
+int32_t spark_call_form(const spark_desc *desc, int32_t call)
+{
+    spark_status why;
+    if (!desc_ok(desc, &why)) return 0;
+    if (call == SPARK_CALL_PRUNE_TOPP) return spark::topp_prune_launches(topp_layout_of(desc));
+    return 0;
 }
 
 spark_status spark_unpack_topp(const spark_desc *desc, const void *packed, uint32_t *mask_out, int32_t *count_out,

@@ -62,6 +62,7 @@ hipError_t launch_window_stat(const uint16_t *qwin, uint8_t *packed, const Spark
 // top-p variant (L from spark_make_topp_layout; launch_window_stat must have run before, for every call anew)
 hipError_t launch_prune_topp(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *cu,
                              uint8_t *packed, const SparkLayout &L, int p_bp, hipStream_t st);
+int topp_prune_launches(const SparkLayout &L);     // how many launches launch_prune_topp takes
 hipError_t launch_unpack_topp(const uint8_t *packed, const SparkLayout &L, uint32_t *mask_out, int32_t *count_out,
                               uint16_t *vals_out, float *mu_out, float *a_out, hipStream_t st);
 

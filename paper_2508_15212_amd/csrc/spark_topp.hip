@@ -97,7 +97,8 @@ __device__ __forceinline__ float sum_pruned(const uint64_t (&kb)[8], const uint3
 
 // What a tile's directory entry holds while the streams are being written: 0 (as cleared), the words of its own tile, or
 // the words of all tiles up to it, which is what it holds in the end.  No tile has more than 64 * 64 words or fewer than
-// one; a stream does not come near 2^32 words.
+// one.  (A sum of kOwnWords or more would be taken for the words of a tile, and waited for without end: calls whose streams have
+// room for that many do not come here, see topp_prune_launches.)
 constexpr uint32_t kOwnWords = 0xFFFFE000u;
 __device__ __forceinline__ uint32_t dir_load(const uint32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void dir_store(uint32_t *p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -623,22 +624,32 @@ __global__ void spark_topp_unpack_kernel(const uint8_t *__restrict__ packed, Spa
 
 // ---------------------------------------------------------------- host-side launch
 
+// One launch or three.  In one, few tiles (lag 0: a block writes its own tile) save two launches, and many tiles (a lag of
+// about as many as the chip has in flight) hide the writing, which waits for memory, behind the selection, which is bound
+// by vector issue.  In between, where all blocks select at once and then all write, the way from a tile's words to its place
+// (two trips through memory, or one for every 64 tiles of a head) costs more than the launches; and with few heads the count of
+// the tickets (11.5 ns each) does.  Three launches / one (us, 51 kept channels a row, window kernel included):
+//   8 heads, tiles:  64 17.8 / 15.3   256 18.0 / 17.1   512 20.2 / 27   1024 23.9 / 39   2048 35.6 / 34.3   4096 56.5 / 49.7   8192 96.3 / 84.2
+//   1 head:  64 17.5 / 15.8   128 16.7 / 17.4   256 17.0 / 19.3   1024 24 / 63      2 heads:  128 17.2 / 16.3   256 17.2 / 18.1   2048 37 / 57
+//   4 heads:  256 18.3 / 17.2   2048 35.8 / 35.6   4096 57.0 / 52.8   8192 98 / 87      16 heads:  4096 56.7 / 49.3
+//   64 heads:  2048 36.0 / 32.8      1024 heads:  2048 41.0 / 34.5      4096 heads:  8192 129 / 111
+// Heads of 67.1 million tokens and more, whose streams have room for kOwnWords words, take three: there the directory's words are
+// sums only.
+int topp_prune_launches(const SparkLayout &L)
+{
+    const int64_t tiles = L.n_tiles * L.n_kv_heads;
+    if (tiles == 0) return 0;
+    if (L.vals_head_words >= (int64_t)kOwnWords) return 3;
+    return (tiles <= 256 && L.n_tiles <= 64) || (tiles >= 2048 && L.n_kv_heads >= 4) ? 1 : 3;
+}
+
 hipError_t launch_prune_topp(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *cu,
                              uint8_t *packed, const SparkLayout &L, int p_bp, hipStream_t st)
 {
     if (L.n_tiles == 0) return hipSuccess;
     const int64_t tiles = L.n_tiles * L.n_kv_heads;
     const dim3 threads(kWaves * 64);
-    // One launch or three.  In one, few tiles (lag 0: a block writes its own tile) save two launches, and many tiles (a lag
-    // of about as many as the chip has in flight) hide the writing, which waits for memory, behind the selection, which
-    // is bound by vector issue.  In between, where all blocks select at once and then all write, the way from a tile's words to
-    // its place (two trips through memory, or one for every 64 tiles of a head) costs more than the launches; and with few heads
-    // the count of the tickets (11.5 ns each) does.  Three launches / one (us, 51 kept channels a row, window kernel included):
-    //   8 heads, tiles:  64 17.8 / 15.3   256 18.0 / 17.1   512 20.2 / 27   1024 23.9 / 39   2048 35.6 / 34.3   4096 56.5 / 49.7   8192 96.3 / 84.2
-    //   1 head:  64 17.5 / 15.8   128 16.7 / 17.4   256 17.0 / 19.3   1024 24 / 63      2 heads:  128 17.2 / 16.3   256 17.2 / 18.1   2048 37 / 57
-    //   4 heads:  256 18.3 / 17.2   2048 35.8 / 35.6   4096 57.0 / 52.8   8192 98 / 87      16 heads:  4096 56.7 / 49.3
-    //   64 heads:  2048 36.0 / 32.8      1024 heads:  2048 41.0 / 34.5      4096 heads:  8192 129 / 111
-    if ((tiles <= 256 && L.n_tiles <= 64) || (tiles >= 2048 && L.n_kv_heads >= 4)) {
+    if (topp_prune_launches(L) == 1) {
         const int lag = tiles <= 256 ? 0 : (L.n_kv_heads < 2048 ? 2048 / L.n_kv_heads : 1);
         const int group = lag < 4 ? 1 : (lag < 64 ? lag / 2 : 32);
         const int64_t tickets = L.n_tiles + lag;

@@ -218,3 +218,20 @@ def test_timeline_aid_checks_its_buffer_on_the_host():
     assert lib.spark_decode_timeline(0x7F0000000004, 4096) == 1          # misaligned
     assert lib.spark_decode_timeline(0x7F0000000000, 32) == 1            # no room for one block
     assert lib.spark_decode_timeline(None, 0) == 0
+
+
+def test_one_launch_of_the_top_p_prune_only_where_words_and_sums_can_be_told_apart():
+    """The one launch files a tile's own words as 2^32 - 8192 and up: a stream must not have room for that many words."""
+    form = lambda **kw: spark.call_form(_desc(**kw), spark.CALL_PRUNE_TOPP)
+    fits = ((1 << 32) - 8192) // 4096 - 1                  # tiles of 64 rows of 64 words
+    assert form(n_kv_heads=4, batch=1, total_tokens=64 * fits) == 1
+    assert form(n_kv_heads=4, batch=1, total_tokens=64 * fits + 1) == 3
+    assert form(n_kv_heads=8, batch=1, total_tokens=(1 << 31) - 256) == 3
+    # few tiles, or many of four heads or more
+    assert form(n_q_heads=1, n_kv_heads=1, batch=1, total_tokens=64 * 64) == 1
+    assert form(n_q_heads=1, n_kv_heads=1, batch=1, total_tokens=64 * 64 + 1) == 3
+    assert form(batch=1, total_tokens=2048) == 1 and form(batch=1, total_tokens=2049) == 3
+    assert form(batch=1, total_tokens=256 * 64) == 1 and form(batch=1, total_tokens=255 * 64) == 3
+    assert form(n_q_heads=2, n_kv_heads=2, batch=1, total_tokens=1 << 20) == 3
+    assert form(total_tokens=0) == 0 and form(head_dim=64) == 0
+    assert spark.call_form(_desc(), 0) == 0
