@@ -357,6 +357,32 @@ __device__ __forceinline__ void tail_query_operand(const uint4 &qx, int cn, floa
 
 // ---------------------------------------------------------------- appended (never pruned) rows
 
+// A probability goes to the matrix cores in parts, and a part that is 0 times an infinite value is NaN although the
+// probability times that value is infinite.  Where an output came out NaN, the sums are taken again in float32, row by row:
+// lane (tg, cn) = heads 4 tg + r, channels 8 cn + e; vcol: the lane's channels of row 0; prob(n): the four heads' probabilities of row n.
+template <typename Prob>
+__device__ __forceinline__ void tail_infinite_values(const uint16_t *vcol, int64_t step, int nval, const Prob &prob, f32x4 (&acc)[8])
+{
+    bool nan = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) nan = nan || __builtin_isunordered(acc[e][0], acc[e][1]) || __builtin_isunordered(acc[e][2], acc[e][3]);
+    if (__builtin_expect(__ballot(nan) == 0ull, 1)) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int n = 0; n < nval; ++n) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(vcol + n * step);
+        const f32x4 p = prob(n);
+#pragma unroll
+        for (int cp = 0; cp < 4; ++cp)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                acc[2 * cp][r] = fmaf(p[r], bf16lo(u4c(x, cp)), acc[2 * cp][r]);
+                acc[2 * cp + 1][r] = fmaf(p[r], bf16hi(u4c(x, cp)), acc[2 * cp + 1][r]);
+            }
+    }
+}
+
 // [Sec. "Preliminaries": each decode step concatenates the new token's key and value to the cache; pruning
 //  happens once, at prefill, so these rows stay dense.]  One extra block per (batch, KV head) and 256 rows of the decode
 // grid runs plain attention over the sequence's appended rows and leaves the softmax state (m, l,
@@ -484,6 +510,18 @@ __device__ __forceinline__ void tail_partial(const DecodeParams &P, int b, int h
                 }
             }
         }
+        tail_infinite_values(P.tail_v + row0 * SPARK_D + 8 * cn, step * SPARK_D, nval,
+                             [&](int n) __attribute__((always_inline)) {
+                                 const int at = (n & 32) | ((n & 3) << 3) | ((n & 31) >> 2);
+                                 f32x4 p = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                                 for (int r = 0; r < 4; ++r)
+                                     if (4 * tg + r < G) {
+#pragma unroll
+                                         for (int k = 0; k < 3; ++k) p[r] += bf16lo(pw[(k * G + 4 * tg + r) * 64 + at]);
+                                     }
+                                 return p;
+                             }, acc);
         wave_lds_sync();
     }
     // merge the wavefronts and write the partial (device-scope stores, as the sequence splits do)

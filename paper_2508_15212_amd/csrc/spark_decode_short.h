@@ -307,6 +307,19 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
             }
             const bf16x8 A2 = __builtin_bit_cast(bf16x8, third);
             add_output(__builtin_bit_cast(bf16x8, a), &A2);
+            tail_infinite_values(P.tail_v + row0 * SPARK_D + 8 * cn, step * SPARK_D, nval,
+                                 [&](int n) __attribute__((always_inline)) {
+                                     const int at = 8 * (n & 3) + (n >> 2);
+                                     f32x4 p = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                                     for (int r = 0; r < 4; ++r) {
+                                         const int g = 4 * tg + r;
+                                         if (g < G)
+                                             p[r] = (bf16lo(pbuf[wave][g][at]) + bf16lo(pbuf[wave][g][at + 4])) +
+                                                    bf16lo(pthird[wave][g][4 * (n & 3) + (n >> 2)]);
+                                     }
+                                     return p;
+                                 }, acc);
         }
         if (P.trace != nullptr) stamp(P, 2, wall_clock64());
 #pragma unroll

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import workloads as wl
 import paper_2508_15212_amd as spark
 from tests.gpu_util import make_desc, to_dev
@@ -48,3 +49,48 @@ def test_alignment_and_range(G, shift):
     assert torch.isfinite(base).all()
     assert torch.equal(base, run(0, 1))
     assert torch.equal(base, run(shift, 0))
+
+
+# (26: the appended rows' blocks of the four-wavefront kernel, 90: those of the sixteen-wavefront kernel, except at G = 16)
+@pytest.mark.parametrize("keep", [26, 90])
+@pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
+def test_infinite_values(G, keep):
+    """+-inf in an appended value gives +-inf in the outputs of its channel and nothing elsewhere: the probabilities go to the
+    matrix cores in parts, of which some are 0.  In the row that takes the softmax of every query head, in rows in the
+    middle, and in the last one."""
+    lens = (90, 37, 250, 1)
+    w = wl.small(name=f"tailinf{G}", batch=4, n_q_heads=G, n_kv_heads=1, keep=keep, seqlens=(0, 100, 70, 0), seed=470 + G)
+    t = wl.generate(w)
+    # (no score so high that an appended row's probability is 0 in float32: 0 times infinity is NaN by rights)
+    t.k = wl.f32_to_bf16_bits((wl.bf16_bits_to_f32(t.k) * 0.02).astype(np.float32))
+    rng = np.random.default_rng(G)
+    cap = 300
+    tk, tv = (rng.standard_normal((4, cap, 1, 128)).astype(np.float32) for _ in range(2))
+    q = wl.bf16_bits_to_f32(t.q)
+    for b in range(4):
+        tk[b, 0, 0] = 0.5 * q[b].sum(0)                  # (a high score: its probability is 1, or close to it)
+    finite = tv.copy()
+    place = {0: 3, 20: 17, 36: 64, 89: 90, 200: 100, 249: 127}
+    for row, ch in place.items():
+        tv[:, row, 0, ch] = np.inf if row % 2 == 0 else -np.inf
+        finite[:, row, 0, ch] = 0.0
+    desc = make_desc(w)
+    desc.tail_capacity = cap
+    packed = torch.empty(spark.packed_bytes(desc), dtype=torch.uint8, device="cuda")
+    cu = torch.from_numpy(np.asarray(t.cu, np.int32)).cuda()
+    spark.prune(desc, to_dev(t.k), to_dev(t.qwin), cu, packed)
+    out = torch.empty((4, G, 128), dtype=torch.float32, device="cuda")
+    bits = lambda x: to_dev(wl.f32_to_bf16_bits(x))
+    tl = np.asarray(lens, np.int32)
+    spark.decode_attn_tail(desc, to_dev(t.q), packed, to_dev(t.v), cu, bits(tk), bits(tv), torch.from_numpy(tl).cuda(), out,
+                           spark.new_decode_workspace(desc))
+    got = out.cpu().numpy()
+    _, _, a32 = oracle.window_stat(t.qwin, 1)
+    ref = oracle.decode_literal_tail(t.q, oracle.prune(t.k, t.layout, a32, t.cu, keep), t.v, t.layout, t.cu,
+                                     wl.f32_to_bf16_bits(tk), wl.f32_to_bf16_bits(finite), tl)
+    for row, ch in place.items():
+        for b in range(4):
+            if row < lens[b]:
+                assert np.all(got[b, :, ch] == (np.inf if row % 2 == 0 else -np.inf)), (b, row, ch)
+                got[b, :, ch] = ref[b, :, ch]
+    assert np.abs(got - ref).max() <= 1e-2
