@@ -105,6 +105,7 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
     // are dealt out evenly to as many wavefronts as are resident at once, 2048 over all heads.  The mode holds
     // the batch's sequence table in registers (at most 256 sequences) and numbers items in 32 bits.
     p.warm_waves = 0;
+    p.short_call = 0;
     p.chunk_ids = p.nchunk_max;
     const int64_t pairs = (int64_t)d->batch * d->n_kv_heads;
     // (a batch that its caller knows to be near-uniform is balanced with one block per sequence already)
@@ -128,12 +129,15 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 // chunks an average-length sequence is cut into; 0 for the balanced cut (what spark_decode_splits reports)
 int pick_splits(const spark_desc *d)
 {
-    const spark::DecodePlan p = plan_of(d);
+    const spark::DecodePlan p = spark::decode_form(plan_of(d), layout_of(d), d->n_q_heads, true, 0);
     if (p.warm_waves > 0) return 0;
     if (p.fixed_splits > 0) return p.fixed_splits;
+    // (as the kernel numbers them, for a batch of sequences of that length)
     const int64_t avg_tiles = (d->total_tokens / d->batch + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS;
-    const int64_t n = (avg_tiles + p.chunk_tiles - 1) / p.chunk_tiles;
-    return (int)(n < 1 ? 1 : n);
+    for (int64_t chunk = p.chunk_tiles;; chunk += 1 + chunk / 16) {
+        const int64_t n = avg_tiles > chunk ? (avg_tiles + chunk - 1) / chunk : 1;
+        if (p.chunk_limit == 0 || n * d->batch <= p.chunk_limit) return (int)n;
+    }
 }
 
 // partial slots in the workspace: one per (chunk, q head), then the appended rows' (one per 256 rows of
@@ -446,6 +450,11 @@ int32_t spark_call_form(const spark_desc *desc, int32_t call)
 {
     spark_status why;
     if (!desc_ok(desc, &why)) return 0;
+    if (call == SPARK_CALL_DECODE || call == SPARK_CALL_DECODE_TAIL) {
+        const spark::DecodePlan cut = plan_of(desc);
+        const spark::DecodePlan p = spark::decode_form(cut, layout_of(desc), desc->n_q_heads, true, call == SPARK_CALL_DECODE ? 0 : cut.tail_slots);
+        return p.warm_waves > 0 ? 3 : (p.short_call ? 2 : 1);
+    }
     if (call == SPARK_CALL_PRUNE_TOPP) return spark::topp_prune_launches(topp_layout_of(desc));
     return 0;
 }

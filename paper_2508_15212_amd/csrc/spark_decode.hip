@@ -29,6 +29,29 @@ static bool short_call_tiles(const SparkLayout &L, int G, int64_t tiles)
     return tiles >= least && tiles <= (long_rows && G <= 4 ? 1024 : 2048);
 }
 
+// The balanced mode and the blocks of sixteen wavefronts: dense values, degenerate recovery, rows of one length (`plain`),
+// query groups up to 8 (else chunks by blocks of four).
+// Short calls: all blocks are resident at once, one a compute unit.  Chunks get as much longer as that takes, where blocks of
+// four wavefronts would have to do the same, or where that is half a pass (of four tiles) on average.  T = 32, four / sixteen
+// wavefronts a block (us): 6 x 2000 to 3000 tokens 21.6 / 18.6; with 5.5 tiles a place (4 x 700 to 3900 tokens and appended
+// rows) 15.1 / 14.5, with 6.6 (8 x 800 to 1500 and appended rows) 14.6 / 16.1.
+DecodePlan decode_form(DecodePlan plan, const SparkLayout &L, int Hq, bool plain, int ntail)
+{
+    const int G = Hq / L.n_kv_heads;
+    if (!plain || G > 8) plan.warm_waves = 0;
+    plan.short_call = 0;
+    if (!plain || G > 8 || plan.warm_waves > 0 || !short_call_tiles(L, G, L.n_tiles * L.n_kv_heads)) return plan;
+    const int64_t room = 256 / L.n_kv_heads - (int64_t)L.batch * ntail;      // chunks there are places for
+    if (plan.nchunk_max <= room) {
+        plan.short_call = 1;
+    } else if (plan.fixed_splits == 0 && L.batch <= 64 && room >= 2 * L.batch &&
+               (plan.chunk_limit > 0 || L.n_tiles + 2 * L.batch <= 6 * room)) {
+        plan.short_call = 1;
+        plan.chunk_limit = plan.nchunk_max = (int)room;
+    }
+    return plan;
+}
+
 // Zeroes the arrival counters of a fresh workspace.
 __global__ void spark_zero_kernel(uint32_t *p, int n)
 {
@@ -51,7 +74,7 @@ void set_decode_timeline(unsigned long long *device_words, size_t blocks)
 hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const uint16_t *v, int64_t v_tok_stride,
                               int64_t v_head_stride, const uint8_t *packed_v, const SparkLayout *Lv,
                               const int32_t *cu, float *part_acc, float *part_ml,
-                              uint32_t *counters, int Hq, const DecodePlan &plan, float softmax_scale, const SparkLayout &L,
+                              uint32_t *counters, int Hq, const DecodePlan &cut, float softmax_scale, const SparkLayout &L,
                               void *out, int out_f32, const uint16_t *tail_k, const uint16_t *tail_v,
                               const int32_t *tail_len, int tail_cap, int rec, uint64_t seed, hipStream_t st)
 {
@@ -71,12 +94,14 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
     P.out_f32 = out_f32;
     P.Hq = Hq;
     P.Hkv = L.n_kv_heads;
+    const bool plain = !packed_v && rec == 0 && !L.topp;
+    const DecodePlan plan = decode_form(cut, L, Hq, plain, tail_k ? cut.tail_slots : 0);
     P.fixed_splits = plan.fixed_splits;
     P.chunk_tiles = plan.chunk_tiles;
     P.nchunk_max = plan.nchunk_max;
     P.chunk_limit = plan.chunk_limit;
-    // balanced mode: dense values, degenerate recovery, rows of one length, query groups up to 8 (else chunks)
-    P.warm_waves = (!packed_v && rec == 0 && !L.topp && Hq / L.n_kv_heads <= 8) ? plan.warm_waves : 0;
+    P.short_call = plan.short_call;
+    P.warm_waves = plan.warm_waves;
     P.tail_slots = plan.tail_slots;
     P.ntail = tail_k ? plan.tail_slots : 0;
     P.tail_base = (int64_t)plan.chunk_ids * Hq;
@@ -90,21 +115,6 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
     P.scale_log2 = softmax_scale * 1.44269504088896340736f;
     P.L = L;
     const int G = P.Hq / P.Hkv;
-    // Short calls: all blocks are resident at once, one a compute unit.  Chunks get as much longer as that takes, where blocks of
-    // four wavefronts would have to do the same, or where that is half a pass (of four tiles) on average.  T = 32, four / sixteen
-    // wavefronts a block (us): 6 x 2000 to 3000 tokens 21.6 / 18.6; with 5.5 tiles a place (4 x 700 to 3900 tokens and appended
-    // rows) 15.1 / 14.5, with 6.6 (8 x 800 to 1500 and appended rows) 14.6 / 16.1.
-    P.short_call = 0;
-    if (!packed_v && rec == 0 && !L.topp && G <= 8 && P.warm_waves == 0 && short_call_tiles(L, G, L.n_tiles * P.Hkv)) {
-        const int64_t room = 256 / P.Hkv - (int64_t)L.batch * P.ntail;       // chunks there are places for
-        if (P.nchunk_max <= room) {
-            P.short_call = 1;
-        } else if (P.fixed_splits == 0 && L.batch <= 64 && room >= 2 * L.batch &&
-                   (P.chunk_limit > 0 || L.n_tiles + 2 * L.batch <= 6 * room)) {
-            P.short_call = 1;
-            P.chunk_limit = P.nchunk_max = (int)room;
-        }
-    }
     const int nblocks = P.Hkv * ((P.warm_waves > 0 ? P.warm_waves / kDecodeWaves : P.nchunk_max) + L.batch * P.ntail);
     P.trace = (g_timeline != nullptr && (size_t)nblocks <= g_timeline_blocks) ? g_timeline : nullptr;
     switch (G) {

@@ -22,8 +22,9 @@ struct DecodePlan {
     int chunk_limit;    // > 0: chunks are made longer until the batch has at most this many (up to 64 sequences, and not fewer)
     int nchunk_max;     // upper bound on the number of chunks in the batch (grid = nchunk_max * Hkv + tail blocks)
     int tail_slots;     // partial slots reserved per (batch, q head) for appended rows
-    int warm_waves;     // > 0: the balanced mode may be used, with this many wavefronts per KV head; the launch
+    int warm_waves;     // > 0: the balanced mode may be used, with this many wavefronts per KV head; decode_form
                         // falls back to the chunked cut for the kernel variants that have no balanced form
+    int short_call;     // 1: blocks of sixteen wavefronts (spark_decode_short.h); chosen by decode_form
     int chunk_ids;      // chunk ids the workspace has partial slots for: >= nchunk_max, and >= the balanced
                         // mode's warm_waves + 2 * batch; the appended rows' slots follow at chunk_ids * Hq
 };
@@ -43,14 +44,18 @@ hipError_t launch_unpack(const uint8_t *packed, const SparkLayout &L, uint32_t *
                          float *mu_out, float *scale_out, float *a_out, float *mu_all_out, float *sigma_out,
                          hipStream_t st);
 
+// The form that a decode call takes: which kernel, and the chunks it is launched with.  plain: dense values, degenerate recovery,
+// a fixed-count cache; ntail: blocks of appended rows per (batch, KV head).
+DecodePlan decode_form(DecodePlan cut, const SparkLayout &L, int Hq, bool plain, int ntail);
+
 // q [B,Hq,128] bf16; the caller splits the workspace into part_acc / part_ml / counters.
 // Values are either dense (v, strides; packed_v = NULL) or a packed value cache (packed_v, Lv; v = NULL).
-// Partial slots: plan.chunk_ids * Hq, then batch * Hq * plan.tail_slots; tail_k != NULL adds the appended rows
+// Partial slots: cut.chunk_ids * Hq, then batch * Hq * cut.tail_slots; tail_k != NULL adds the appended rows
 // [B, tail_cap, Hkv, 128].
 hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const uint16_t *v, int64_t v_tok_stride,
                               int64_t v_head_stride, const uint8_t *packed_v, const SparkLayout *Lv,
                               const int32_t *cu, float *part_acc, float *part_ml,
-                              uint32_t *counters, int Hq, const DecodePlan &plan, float softmax_scale, const SparkLayout &L,
+                              uint32_t *counters, int Hq, const DecodePlan &cut, float softmax_scale, const SparkLayout &L,
                               void *out, int out_f32, const uint16_t *tail_k, const uint16_t *tail_v,
                               const int32_t *tail_len, int tail_cap, int rec, uint64_t seed, hipStream_t st);
 

@@ -235,3 +235,24 @@ def test_one_launch_of_the_top_p_prune_only_where_words_and_sums_can_be_told_apa
     assert form(n_q_heads=2, n_kv_heads=2, batch=1, total_tokens=1 << 20) == 3
     assert form(total_tokens=0) == 0 and form(head_dim=64) == 0
     assert spark.call_form(_desc(), 0) == 0
+
+
+def test_reported_splits_follow_the_limits_on_the_chunks():
+    """A few sequences are cut into no more chunks than the chip holds blocks, a short call into no more than it has
+    compute units."""
+    six = dict(batch=6, total_tokens=6 * 2500, keep=32)            # 40 tiles each, eight KV heads
+    assert spark.call_form(_desc(**six), spark.CALL_DECODE) == 2
+    assert spark.decode_splits(_desc(**six)) == 5                  # 32 places: 8 tiles a chunk (4 would be 60 chunks)
+    assert spark.call_form(_desc(**six, n_splits=9), spark.CALL_DECODE) == 1
+    assert spark.decode_splits(_desc(**six, n_splits=9)) == 9
+    ten = dict(batch=10, total_tokens=10 * 8000)                   # 125 tiles each; 64 places
+    assert spark.call_form(_desc(**ten), spark.CALL_DECODE) == 1
+    assert spark.decode_splits(_desc(**ten)) == 6                  # (20 tiles a chunk would be 70)
+    # no limit: 256 pairs and more
+    assert spark.decode_splits(_desc(batch=40, total_tokens=40 * 1000, max_seqlen=1000)) == 1
+    # appended rows take places of their own
+    tail = dict(batch=4, total_tokens=4 * 2500, keep=33, tail_capacity=256)
+    assert spark.call_form(_desc(**tail), spark.CALL_DECODE) == 2 and spark.call_form(_desc(**tail), spark.CALL_DECODE_TAIL) == 2
+    tail["tail_capacity"] = 2048
+    assert spark.call_form(_desc(**tail), spark.CALL_DECODE) == 2 and spark.call_form(_desc(**tail), spark.CALL_DECODE_TAIL) == 1
+    assert spark.call_form(_desc(batch=64, total_tokens=64 * 1300), spark.CALL_DECODE) == 3
