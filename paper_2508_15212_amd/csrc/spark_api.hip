@@ -450,6 +450,7 @@ int32_t spark_call_form(const spark_desc *desc, int32_t call)
 {
     spark_status why;
     if (!desc_ok(desc, &why)) return 0;
+    if (call == SPARK_CALL_PRUNE) return spark::prune_launches(layout_of(desc), desc->n_q_heads, desc->window);
     if (call == SPARK_CALL_DECODE || call == SPARK_CALL_DECODE_TAIL) {
         const spark::DecodePlan cut = plan_of(desc);
         const spark::DecodePlan p = spark::decode_form(cut, layout_of(desc), desc->n_q_heads, true, call == SPARK_CALL_DECODE ? 0 : cut.tail_slots);

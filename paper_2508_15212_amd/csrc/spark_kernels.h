@@ -33,6 +33,7 @@ struct DecodePlan {
 // (room for `blocks` blocks; launches with more blocks file nothing); NULL switches it off
 void set_decode_timeline(unsigned long long *device_words, size_t blocks);
 
+int prune_launches(const SparkLayout &L, int Hq, int W);     // how many launches launch_prune takes (with a 4-byte aligned window)
 hipError_t launch_prune(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const uint16_t *qwin,
                         const int32_t *cu, uint8_t *packed, const SparkLayout &L, int Hq, int W, hipStream_t st);
 

@@ -7,7 +7,7 @@
 // Kernels
 //   spark_window_stat_kernel  a[b,h,j] = mean_g | mean_t Q_win[b,g,t,j] |  in float64, stored
 //                             as float32 together with 1/a (G*128 threads per (b, h)); short calls
-//                             do this in the pruning launch (see one_launch).
+//                             do this in the pruning launch (see prune_launches).
 //   spark_prune_kernel        top-T selection and packing, SIXTEEN LANES A ROW: a wavefront takes four rows at a time (a
 //                             step; two steps a group), lane i of sixteen holds channels 8i .. 8i + 7.  A reduction
 //                             over a row is four lane moves that serve four rows, slots and sums are per lane, and
@@ -849,19 +849,21 @@ static hipError_t launch_window_and_tiles(const uint16_t *k, int64_t tok_stride,
 //   8 sequences of 260 tokens 13.7 / 12.6, of 300 to 700 14.4 / 12.9; prune and first decode step of 1024 tokens 23.3 / 21.2
 // The line: 6000 tokens (760 blocks) 15.2 / 14.8, five of 1000 to 2000 (980 blocks) 16.5 / 17.1; with more blocks than are
 // resident, 8192 tokens where there was room for 768, 17.1 / 19.9.
-static bool one_launch(const uint16_t *qwin, const SparkLayout &L, int Hq, int W)
+int prune_launches(const SparkLayout &L, int Hq, int W)
 {
     const int64_t tiles = L.n_tiles * L.n_kv_heads, blocks = tiles + (int64_t)L.batch * L.n_kv_heads;
     const int G = Hq / L.n_kv_heads;
     const int64_t by_lds = (int64_t)(160 * 1024 / spark_window_lds_bytes(L));
-    return tiles > 0 && blocks <= 256 * (by_lds < 3 ? by_lds : 3) && G <= 8 && (reinterpret_cast<uintptr_t>(qwin) & 3u) == 0u &&
-           L.total_tokens >= 256 * (int64_t)L.batch && tiles * G * W <= 131072;
+    const bool one = tiles > 0 && blocks <= 256 * (by_lds < 3 ? by_lds : 3) && G <= 8 && L.total_tokens >= 256 * (int64_t)L.batch &&
+                     tiles * G * W <= 131072;
+    return one ? 1 : 2;
 }
 
 hipError_t launch_prune(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const uint16_t *qwin,
                         const int32_t *cu, uint8_t *packed, const SparkLayout &L, int Hq, int W, hipStream_t st)
 {
-    if (one_launch(qwin, L, Hq, W)) return launch_window_and_tiles(k, k_tok_stride, k_head_stride, qwin, cu, packed, L, Hq, W, st);
+    // (a block reads two window columns at a time)
+    if (prune_launches(L, Hq, W) == 1 && (reinterpret_cast<uintptr_t>(qwin) & 3u) == 0u) return launch_window_and_tiles(k, k_tok_stride, k_head_stride, qwin, cu, packed, L, Hq, W, st);
     const hipError_t e = launch_window_stat(qwin, packed, L, Hq, W, st);
     if (e != hipSuccess) return e;
     return launch_tiles<false>(k, k_tok_stride, k_head_stride, cu, packed, L, st);

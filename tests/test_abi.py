@@ -234,7 +234,7 @@ def test_one_launch_of_the_top_p_prune_only_where_words_and_sums_can_be_told_apa
     assert form(batch=1, total_tokens=256 * 64) == 1 and form(batch=1, total_tokens=255 * 64) == 3
     assert form(n_q_heads=2, n_kv_heads=2, batch=1, total_tokens=1 << 20) == 3
     assert form(total_tokens=0) == 0 and form(head_dim=64) == 0
-    assert spark.call_form(_desc(), 0) == 0
+    assert spark.call_form(_desc(), -1) == 0
 
 
 def test_reported_splits_follow_the_limits_on_the_chunks():

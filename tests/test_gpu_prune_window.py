@@ -33,12 +33,30 @@ def test_weights_in_the_pruning_launch(seqlens, G, window, pack, stats):
     t = wl.generate(w)
     desc = make_desc(w, pack=pack)
     desc.stats = stats
+    assert spark.call_form(desc, spark.CALL_PRUNE) == 1
     got, ref = _packed(desc, t, 0), _packed(desc, t, 1)
     assert torch.equal(got, ref)
     if pack == spark.PACK_BF16 and not stats:
-        mask = torch.empty((w.total, hkv, 4), dtype=torch.int32, device="cuda")
-        a = torch.empty((w.batch, hkv, 128), dtype=torch.float32, device="cuda")
-        spark.unpack(desc, got, mask, None, None, None, a)
-        _, _, a32 = oracle.window_stat(t.qwin, hkv)
-        assert np.array_equal(a.cpu().numpy().view(np.uint32), np.asarray(a32, np.float32).reshape(w.batch, hkv, 128).view(np.uint32))
-        assert np.array_equal(mask.cpu().numpy().view(np.uint32), oracle.prune(t.k, t.layout, a32, t.cu, w.keep).mask)
+        _against_oracle(w, t, desc, got)
+
+
+def _against_oracle(w, t, desc, packed):
+    hkv = w.n_kv_heads
+    mask = torch.empty((w.total, hkv, 4), dtype=torch.int32, device="cuda")
+    a = torch.empty((w.batch, hkv, 128), dtype=torch.float32, device="cuda")
+    spark.unpack(desc, packed, mask, None, None, None, a)
+    _, _, a32 = oracle.window_stat(t.qwin, hkv)
+    assert np.array_equal(a.cpu().numpy().view(np.uint32), np.asarray(a32, np.float32).reshape(w.batch, hkv, 128).view(np.uint32))
+    assert np.array_equal(mask.cpu().numpy().view(np.uint32), oracle.prune(t.k, t.layout, a32, t.cu, w.keep).mask)
+
+
+# (a block per tile and one per sequence, over the heads: up to 768)
+@pytest.mark.parametrize("hkv,tokens,launches", [(1, 767 * 64, 1), (1, 767 * 64 + 1, 2), (8, 95 * 64 - 3, 1), (8, 95 * 64 + 1, 2)])
+def test_both_sides_of_the_rule(hkv, tokens, launches):
+    w = wl.small(name=f"winrule{hkv}x{tokens}", batch=1, n_q_heads=hkv, n_kv_heads=hkv, keep=30, seqlens=(tokens,), seed=620 + hkv)
+    t = wl.generate(w)
+    desc = make_desc(w)
+    assert spark.call_form(desc, spark.CALL_PRUNE) == launches
+    got = _packed(desc, t, 0)
+    assert torch.equal(got, _packed(desc, t, 1))
+    _against_oracle(w, t, desc, got)

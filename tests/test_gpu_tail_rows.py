@@ -76,6 +76,7 @@ def test_infinite_values(G, keep):
         finite[:, row, 0, ch] = 0.0
     desc = make_desc(w)
     desc.tail_capacity = cap
+    assert spark.call_form(desc, spark.CALL_DECODE_TAIL) == (1 if keep == 26 or G == 16 else 2)
     packed = torch.empty(spark.packed_bytes(desc), dtype=torch.uint8, device="cuda")
     cu = torch.from_numpy(np.asarray(t.cu, np.int32)).cuda()
     spark.prune(desc, to_dev(t.k), to_dev(t.qwin), cu, packed)

@@ -16,7 +16,10 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("hkv,tokens", [(1, 1), (1, 64 * 64), (1, 65 * 64), (4, 64 * 64 - 9), (1, 256 * 64), (1, 256 * 64 + 1), (8, 32 * 64 - 5), (8, 33 * 64), (4, 511 * 64), (4, 512 * 64 - 1),
                                         (3, 683 * 64), (5, 410 * 64 + 17)])
 def test_both_sides_of_the_rule(hkv, tokens):
+    tiles = (tokens + 63) // 64
+    one = hkv * tiles <= 256 and tiles <= 64 or hkv * tiles >= 2048 and hkv >= 4
     w = wl.small(name=f"topp{hkv}x{tokens}", batch=2, n_q_heads=hkv, n_kv_heads=hkv, seqlens=(tokens - tokens // 3, tokens // 3), seed=351 + hkv)
+    assert spark.call_form(make_desc(w), spark.CALL_PRUNE_TOPP) == (1 if one else 3)
     _run(w, wl.generate(w), p_bp=9500, decode=False)
 
 
@@ -24,6 +27,7 @@ def test_both_sides_of_the_rule(hkv, tokens):
 def test_more_heads_than_the_chip_holds_blocks(hkv, tokens):
     """No block may wait for one that has not started: 2304 blocks or fewer are resident at once."""
     w = wl.small(name=f"toppheads{hkv}", batch=1, n_q_heads=hkv, n_kv_heads=hkv, seqlens=(tokens,), seed=371)
+    assert spark.call_form(make_desc(w), spark.CALL_PRUNE_TOPP) == 1
     _run(w, wl.generate(w), p_bp=9500, decode=False)
 
 
