@@ -10,42 +10,60 @@ extern template hipError_t launch_g<4>(const DecodeParams &, int, hipStream_t);
 extern template hipError_t launch_g<8>(const DecodeParams &, int, hipStream_t);
 extern template hipError_t launch_g<16>(const DecodeParams &, int, hipStream_t);
 
-// Whether a call's tiles (over all KV heads) are few enough, and not too few, for the blocks of sixteen wavefronts of
-// spark_decode_short.h.  Such a block takes four tiles at a time with four lanes a row, but all in one compute unit, whose LDS then
-// bounds it; blocks of four wavefronts are as fast or faster for the row lengths that have an instantiation, except where
-// eight query heads leave registers for small groups of entries only, and for very small calls of short rows.  One sequence, 8 KV
-// heads, four / sixteen wavefronts a block (us; 1024 tokens are 128 tiles):
-//   G = 4, T = 33:  1024 11.1 / 11.5   4096 13.2 / 12.6   8192 15.5 / 14.8   16384 21.3 / 20.2   32768 26.8 / 28.2
-//          T = 90:  100 12.7 / 8.4   1024 15.6 / 13.5   8192 19.2 / 17.3   16384 24.8 / 26.0     T = 127:  1024 17.7 / 14.5
-//   G = 8, T = 30:  1024 13.2 / 12.8   4096 16.2 / 14.5   16384 26.6 / 22.9    T = 80:  1024 19.1 / 15.6   16384 31.5 / 29.7
-//          T = 26 (instantiated):  1024 11.9 / 12.2   8192 18.1 / 17.2   16384 25.4 / 22.5     T = 64:  8192 20.8 / 20.0
-//   G = 2, T = 30:  2048 10.4 / 11.0   8192 14.1 / 13.4   T = 70:  1024 11.7 / 12.3   T = 127:  1024 15.8 / 14.0
-//   G = 1, T = 30:  1024 8.8 / 9.5   4096 11.0 / 10.6   8192 13.6 / 12.3   T = 70:  1024 11.2 / 10.5   16384 21.0 / 21.2
-static bool short_call_tiles(const SparkLayout &L, int G, int64_t tiles)
+// Whether a call gains by the blocks of sixteen wavefronts of spark_decode_short.h.  Such a block takes four tiles at a time, four
+// lanes a row, all in one compute unit, whose LDS then bounds it; 256 of them, a pass, take 1024 tiles (over all KV heads).  It gains
+//   - by the walk, with long rows and with eight query heads, whose walk by one lane has few gathers in flight (not where the
+//     row length has an instantiation): up to a pass, or a quarter more;
+//   - by the merge, where a (sequence, KV head) pair has many partials, half as many here, folded by sixteen wavefronts: that is
+//     with many tiles a sequence.
+// It loses where a second pass is begun for little.  Time against blocks of four wavefronts (outlier channels, jittered rows; KV
+// heads, lengths, tiles a sequence, passes):
+//                                            G = 1, T = 32 / 48 / 60   G = 2, 32 / 48 / 75   G = 4, 32 / 48 / 60   G = 8, 32 / 48 / 75   G = 8, 26 / 38 / 64
+//   8 heads  1 x 4096              64   0.5    1.00 / 0.96 / 0.95        1.06 / 1.02 / 1.00    1.02 / 1.00 / 0.98    0.95 / 0.93 / 0.93    1.04 / 1.04 / 1.05
+//            1 x 6500             102   0.8    0.95 / 0.92 / 0.90        0.99 / 0.97 / 0.95    0.97 / 0.96 / 0.96    0.91 / 0.91 / 0.90    0.99 / 1.00 / 1.00
+//            1 x 10000            157   1.2    0.91 / 0.90 / 0.90        0.96 / 0.96 / 0.95    0.98 / 0.98 / 0.97    0.92 / 0.92 / 0.90    0.98 / 0.99 / 0.99
+//            1 x 16384            256   2.0    0.97 / 0.97 / 0.99        0.97 / 1.00 / 1.05    1.00 / 1.02 / 1.04    0.90 / 0.92 / 0.95    0.93 / 0.95 / 1.02
+//            2 x 6000 to 10000    125   2.0    1.04 / 1.03 / 1.05        1.03 / 1.07 / 1.11    1.04 / 1.07 / 1.08    0.94 / 0.97 / 1.00    0.98 / 1.00 / 1.09
+//            4 x 700 to 3900       36   1.1    1.03 / 0.98 / 0.95        1.05 / 1.04 / 0.98    1.06 / 1.02 / 0.99    0.97 / 0.95 / 0.90    1.06 / 1.05 / 1.00
+//            6 x 2000 to 3000      39   1.8    1.15 / 1.11 / 1.12        1.19 / 1.19 / 1.20    1.16 / 1.15 / 1.15    1.11 / 1.09 / 1.09    1.15 / 1.18 / 1.19
+//            8 x 300 to 800         8   0.5    1.01 / 0.98 / 0.96        1.04 / 1.04 / 1.00    1.04 / 1.00 / 0.99    0.96 / 0.95 / 0.93    1.07 / 1.08 / 1.08
+//   4 heads  1 x 32768            512   2.0    0.79 / 0.80 / 0.82        0.81 / 0.84 / 0.89    0.86 / 0.88 / 0.90    0.75 / 0.77 / 0.80    0.76 / 0.78 / 0.85
+//   2 heads  8 x 3000 to 6000      70   1.1    0.94 / 0.86 / 0.90        0.97 / 0.96 / 0.93    0.96 / 0.95 / 0.94    0.91 / 0.89 / 0.86    0.97 / 0.97 / 0.95
+//            1 x 65536           1024   2.0    0.57 / 0.58 / 0.59        0.63 / 0.65 / 0.68    0.70 / 0.72 / 0.75    0.59 / 0.61 / 0.64    0.60 / 0.62 / 0.66
+// Long rows, 8 heads, four / sixteen (us): 1 x 1024: G = 4, T = 90 15.6 / 13.5, T = 127 17.1 / 14.3, G = 2, T = 127 15.2 / 13.7, G = 1,
+// T = 70 11.2 / 10.5; 1 x 16384: G = 4, T = 90 24.8 / 26.0, G = 1, T = 70 21.0 / 21.2.
+static bool short_call_pays(const SparkLayout &L, int G)
 {
-    if (row_length_instantiated(L)) return G == 8 && tiles >= 512 && tiles <= 2048;
-    const bool long_rows = L.T > (G == 2 ? 80 : 64);
-    const int64_t least = long_rows || G == 8 ? 0 : (G == 4 ? 288 : 512);
-    return tiles >= least && tiles <= (long_rows && G <= 4 ? 1024 : 2048);
+    const bool instantiated = row_length_instantiated(L), long_rows = L.T > (G == 2 ? 80 : 64);
+    const int64_t pass = 256 * 4, tiles = L.n_tiles * L.n_kv_heads, per_sequence = L.n_tiles / L.batch;
+    if (G <= 4 && instantiated) return false;
+    if (G <= 4 && long_rows) return tiles <= pass;
+    if (tiles > 2 * pass) return false;
+    if (G == 8 && !instantiated) return tiles <= pass * 5 / 4 || per_sequence > 64;
+    if (tiles < (G == 4 ? 288 : 512)) return false;
+    if (tiles > pass * 3 / 2) return per_sequence >= (G == 1 || L.T <= 40 ? 256 : 512);
+    if (per_sequence >= 96) return true;
+    if (tiles > pass * 5 / 4) return false;
+    if (tiles > pass && per_sequence > 64) return true;
+    return (G == 1 && (L.T >= 44 || per_sequence >= 64)) || (G == 4 && L.T >= 44);
 }
 
 // The balanced mode and the blocks of sixteen wavefronts: dense values, degenerate recovery, rows of one length (`plain`),
 // query groups up to 8 (else chunks by blocks of four).
 // Short calls: all blocks are resident at once, one a compute unit.  Chunks get as much longer as that takes, where blocks of
-// four wavefronts would have to do the same, or where that is half a pass (of four tiles) on average.  T = 32, four / sixteen
-// wavefronts a block (us): 6 x 2000 to 3000 tokens 21.6 / 18.6; with 5.5 tiles a place (4 x 700 to 3900 tokens and appended
-// rows) 15.1 / 14.5, with 6.6 (8 x 800 to 1500 and appended rows) 14.6 / 16.1.
+// four wavefronts would have to do the same, or where that is half a pass (of four tiles a place) on average; with more (8 x 800 to
+// 1500 tokens and appended rows, T = 32, 6.6 tiles a place) four / sixteen wavefronts a block took 14.6 / 16.1 us.
 DecodePlan decode_form(DecodePlan plan, const SparkLayout &L, int Hq, bool plain, int ntail)
 {
     const int G = Hq / L.n_kv_heads;
     if (!plain || G > 8) plan.warm_waves = 0;
     plan.short_call = 0;
-    if (!plain || G > 8 || plan.warm_waves > 0 || !short_call_tiles(L, G, L.n_tiles * L.n_kv_heads)) return plan;
+    if (!plain || G > 8 || plan.warm_waves > 0 || !short_call_pays(L, G)) return plan;
     const int64_t room = 256 / L.n_kv_heads - (int64_t)L.batch * ntail;      // chunks there are places for
     if (plan.nchunk_max <= room) {
         plan.short_call = 1;
     } else if (plan.fixed_splits == 0 && L.batch <= 64 && room >= 2 * L.batch &&
-               (plan.chunk_limit > 0 || L.n_tiles + 2 * L.batch <= 6 * room)) {
+               (plan.chunk_limit > 0 || L.n_tiles + 2 * L.batch <= 4 * room * 3 / 2)) {
         plan.short_call = 1;
         plan.chunk_limit = plan.nchunk_max = (int)room;
     }

@@ -240,9 +240,9 @@ def test_one_launch_of_the_top_p_prune_only_where_words_and_sums_can_be_told_apa
 def test_reported_splits_follow_the_limits_on_the_chunks():
     """A few sequences are cut into no more chunks than the chip holds blocks, a short call into no more than it has
     compute units."""
-    six = dict(batch=6, total_tokens=6 * 2500, keep=32)            # 40 tiles each, eight KV heads
+    six = dict(batch=6, total_tokens=6 * 1300, keep=32, n_q_heads=64)      # 21 tiles each, eight KV heads
     assert spark.call_form(_desc(**six), spark.CALL_DECODE) == 2
-    assert spark.decode_splits(_desc(**six)) == 5                  # 32 places: 8 tiles a chunk (4 would be 60 chunks)
+    assert spark.decode_splits(_desc(**six)) == 5                  # 32 places: 5 tiles a chunk (4 would be 36 chunks)
     assert spark.call_form(_desc(**six, n_splits=9), spark.CALL_DECODE) == 1
     assert spark.decode_splits(_desc(**six, n_splits=9)) == 9
     ten = dict(batch=10, total_tokens=10 * 8000)                   # 125 tiles each; 64 places
@@ -251,8 +251,25 @@ def test_reported_splits_follow_the_limits_on_the_chunks():
     # no limit: 256 pairs and more
     assert spark.decode_splits(_desc(batch=40, total_tokens=40 * 1000, max_seqlen=1000)) == 1
     # appended rows take places of their own
-    tail = dict(batch=4, total_tokens=4 * 2500, keep=33, tail_capacity=256)
+    tail = dict(batch=4, total_tokens=4 * 2400, keep=33, n_q_heads=64, tail_capacity=256)
     assert spark.call_form(_desc(**tail), spark.CALL_DECODE) == 2 and spark.call_form(_desc(**tail), spark.CALL_DECODE_TAIL) == 2
     tail["tail_capacity"] = 2048
     assert spark.call_form(_desc(**tail), spark.CALL_DECODE) == 2 and spark.call_form(_desc(**tail), spark.CALL_DECODE_TAIL) == 1
     assert spark.call_form(_desc(batch=64, total_tokens=64 * 1300), spark.CALL_DECODE) == 3
+
+
+def test_blocks_of_sixteen_wavefronts_only_where_they_were_measured_faster():
+    form = lambda G, keep, lens, hkv=8: spark.call_form(_desc(n_q_heads=G * hkv, n_kv_heads=hkv, keep=keep, batch=len(lens), total_tokens=sum(lens)),
+                                                        spark.CALL_DECODE)
+    # a second pass for little, few tiles a sequence
+    for G in (1, 2, 4):
+        for keep in (30, 48):
+            assert form(G, keep, (2000, 2200, 2400, 2600, 2800, 3000)) == 1
+            assert form(G, keep, (6000, 10000)) == 1
+    assert form(8, 30, (2000, 2200, 2400, 2600, 2800, 3000)) == 1 and form(8, 26, (2000, 2200, 2400, 2600, 2800, 3000)) == 1
+    assert form(2, 48, (300,) * 8) == 1 and form(8, 64, (300,) * 8) == 1 and form(4, 30, (300,) * 8) == 1
+    # many tiles a sequence; long rows; eight query heads
+    for G in (1, 2, 4):
+        assert form(G, 30, (8192,)) == 2 and form(G, 30, (65536,), 2) == 2 and form(G, 90, (1024,)) == 2 and form(G, 90, (16384,)) == 1
+        assert form(G, 26, (8192,)) == 1
+    assert form(8, 30, (100,)) == 2 and form(8, 26, (8192,)) == 2 and form(8, 64, (16384,)) == 1 and form(8, 26, (16384,)) == 2

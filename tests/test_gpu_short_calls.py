@@ -42,19 +42,24 @@ def _check(w, t, pack=spark.PACK_BF16, n_splits=0, layout="HND", form=2):
     assert np.abs(res["out_bf16"] - res["out_f32"]).max() <= 2.0 ** -8 * np.abs(res["out_f32"]).max()
 
 
-# (enough KV heads that the call is not too short for its query-group size: 66 tiles each)
+# Short rows take these blocks with many tiles a sequence only: one long sequence among short ones
+FEW_LONG = dict(batch=3, seqlens=(15, 18433, 0))
+
+
 @pytest.mark.parametrize("pack", [spark.PACK_BF16, spark.PACK_INT8])
 @pytest.mark.parametrize("G,Hkv", [(1, 8), (2, 8), (4, 8), (8, 1)])
 @pytest.mark.parametrize("keep", [1, 27, 66, 67, 126, 128])
 def test_row_lengths(keep, G, Hkv, pack):
-    w = wl.small(name=f"short{keep}_{G}", batch=6, n_q_heads=G * Hkv, n_kv_heads=Hkv, keep=keep,
-                 seqlens=(1, 1700, 0, 15, 2033, 451), seed=500 + keep + G)
+    batch = dict(batch=6, seqlens=(1, 1700, 0, 15, 2033, 451))
+    if G < 8 and keep <= (80 if G == 2 else 64):
+        batch, Hkv = FEW_LONG, 2
+    w = wl.small(name=f"short{keep}_{G}", n_q_heads=G * Hkv, n_kv_heads=Hkv, keep=keep, seed=500 + keep + G, **batch)
     _check(w, wl.generate(w), pack)
 
 
 @pytest.mark.parametrize("keep", [26, 64, 38])
 def test_eight_query_heads_instantiated_lengths(keep):
-    w = wl.small(name=f"short8_{keep}", batch=3, n_q_heads=64, n_kv_heads=8, keep=keep, seqlens=(2000, 17, 2500), seed=510 + keep)
+    w = wl.small(name=f"short8_{keep}", n_q_heads=16, n_kv_heads=2, keep=keep, seed=510 + keep, **FEW_LONG)
     _check(w, wl.generate(w), layout="NHD")
 
 
@@ -76,10 +81,10 @@ def test_split_counts(n_splits):
     _check(w, wl.generate(w), n_splits=n_splits)
 
 
-# (32 places for blocks of eight KV heads; up to 192 tiles, two more for every sequence, are one and a half passes)
-@pytest.mark.parametrize("seqlens,form", [((2900,) * 4, 2), ((3000,) * 4, 1), ((700, 3000, 5, 1300, 2400, 0), 2)])
+# (eight KV heads: 32 places, of four tiles a pass; up to 160 tiles in all, or more than 64 a sequence)
+@pytest.mark.parametrize("seqlens,form", [((2500,) * 4, 2), ((2600,) * 4, 1), ((700, 3000, 5, 1300, 2400, 0), 2), ((9000, 7000), 2), ((16384,), 2), ((16385,), 1)])
 def test_chunks_of_more_than_one_pass(seqlens, form):
-    w = wl.small(name=f"shortpass{len(seqlens)}", batch=len(seqlens), n_q_heads=32, n_kv_heads=8, keep=33, seqlens=seqlens, seed=540)
+    w = wl.small(name=f"shortpass{len(seqlens)}", batch=len(seqlens), n_q_heads=64, n_kv_heads=8, keep=33, seqlens=seqlens, seed=540)
     _check(w, wl.generate(w), form=form)
 
 
