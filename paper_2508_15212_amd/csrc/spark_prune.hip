@@ -783,17 +783,21 @@ hipError_t launch_tiles(const uint16_t *x, int64_t tok_stride, int64_t head_stri
     if (tiles >= ((int64_t)1 << 30)) return hipErrorInvalidValue;
     // Wavefronts per tile.  One has the least set-up, but a wavefront that starts late and works on 64 rows lasts long
     // after the others are done (10 us with the chip to itself).  So wavefronts start in the order of their work: whole tiles
-    // first, then halves of 1536 tiles, at the end quarters of 512 (2048 wavefronts, a third of what is resident).  Where quarters of
-    // all tiles are resident at once (6144 wavefronts and fewer) they are the faster ones.  Us, the window kernel included, one / two /
-    // four wavefronts for every tile (the earlier rule took four up to 1536 tiles, two up to 10240) -> whole tiles, halves, quarters:
+    // first, then halves of 1536 tiles, at the end quarters of 512 (2048 wavefronts, a third of what is resident).  No whole tiles
+    // where the halves and quarters are resident together, or nearly (3072 tiles, 7168 wavefronts), and quarters only where tiles
+    // are few (1408, 5632 wavefronts; values 1280).  Us, the window kernel included, one / two / four wavefronts for every tile (the
+    // rule before took four up to 1536 tiles, two up to 10240) -> whole tiles, halves, quarters:
     //   keys: 2000 27 / 23 / 24 -> 21   5008 (int8) 46 / 42 / 43 -> 39   8000 55 / 52 -> 46   16384 88 / 90 -> 83
     //         4544 (ragged, T = 64) 64 / 62 -> 59   32768 161 / 167 -> 157
     //   values: 2000 24 / 19 / 18 -> 18   5008 34 / 33 / 34 -> 31   8000 49 / 47 -> 44   16384 85 / 87 -> 81
-    //   keys, four -> halves and quarters: 625 15.3 -> 17.2   750 15.3 -> 17.2   1024 17.3 -> 18.0   1250 17.9 -> 18.6   1536 19.0 -> 18.7
-    //   the same, int8 codes: 625 16.5 -> 18.8   1024 18.8 -> 19.6   1250 19.8 -> 20.2   1536 21.3 -> 20.1
+    //   keys, four -> halves and quarters: 625 15.3 -> 17.2   1024 17.3 -> 18.0   1250 17.9 -> 18.6; int8 codes: 625 16.5 -> 18.8   1250 19.8 -> 20.2
+    //   the same as a ratio, mean of fifteen T from 24 to 96 (each 0.92 to 1.15): 1290 1.02   1340 1.02   1400 1.01   1460 1.01   1530 1.00;
+    //   int8 codes 1.04, 1.03, 1.01, 1.02, 1.00; values (T_v = 26 / 64 / 100) 1281 1.01 / 1.00 / 1.04   1400 0.95 / 0.95 / 1.02
+    //   two -> with whole tiles -> without: 2150 (T = 26) 22.6 -> 23.8 -> 20.8   2400 (T = 64, int8) 28.5 -> 28.4 -> 25.8   2560 (T = 96) 26.1 -> 27.4 -> 24.8
+    //         3072 (T = 26 / 64 / 96) 26.3 / 26.2 / 29.0 -> 25.1 / 25.5 / 27.8 -> 25.4 / 24.5 / 27.1   values 2200 (T_v = 64) 18.9 -> 20.2 -> 18.8
     // Quarters of 256, 384, 768, 1536 and 3072 tiles and halves of 512 to 6144 were tried: 0 to 3 % slower.
-    const int64_t n_quarter = tiles <= 1280 ? tiles : 512;
-    const int64_t n_half = tiles - n_quarter < 1536 ? tiles - n_quarter : 1536;
+    const int64_t n_quarter = tiles <= (VALUES ? 1280 : 1408) ? tiles : 512;
+    const int64_t n_half = tiles <= 3072 || tiles - n_quarter < 1536 ? tiles - n_quarter : 1536;
     const int64_t n_whole = tiles - n_quarter - n_half;
     const int64_t waves = n_whole + 2 * n_half + 4 * (tiles - n_whole - n_half);
     auto launch = [&](auto kern) -> hipError_t {
