@@ -630,7 +630,8 @@ __global__ void spark_topp_unpack_kernel(const uint8_t *__restrict__ packed, Spa
 // (two trips through memory, or one for every 64 tiles of a head) costs more than the launches; and with few heads the count of
 // the tickets (11.5 ns each) does.  Three launches / one (us, 51 kept channels a row, window kernel included):
 //   8 heads, tiles:  64 17.8 / 15.3   256 18.0 / 17.1   512 20.2 / 27   1024 23.9 / 39   2048 35.6 / 34.3   4096 56.5 / 49.7   8192 96.3 / 84.2
-//   1 head:  64 17.5 / 15.8   128 16.7 / 17.4   256 17.0 / 19.3   1024 24 / 63      2 heads:  128 17.2 / 16.3   256 17.2 / 18.1   2048 37 / 57
+//   1 head:  64 16.3 / 15.1   96 16.7 / 15.8   127 16.8 / 16.6   256 17.0 / 19.3   1024 24 / 63
+//   2 heads:  128 16.5 / 15.8   192 16.9 / 16.4   224 17.1 / 17.2   254 16.8 / 17.4   2048 37 / 57
 //   4 heads:  256 18.3 / 17.2   2048 35.8 / 35.6   4096 57.0 / 52.8   8192 98 / 87      16 heads:  4096 56.7 / 49.3
 //   64 heads:  2048 36.0 / 32.8      1024 heads:  2048 41.0 / 34.5      4096 heads:  8192 129 / 111
 // Heads of 67.1 million tokens and more, whose streams have room for kOwnWords words, take three: there the directory's words are
@@ -640,7 +641,7 @@ int topp_prune_launches(const SparkLayout &L)
     const int64_t tiles = L.n_tiles * L.n_kv_heads;
     if (tiles == 0) return 0;
     if (L.vals_head_words >= (int64_t)kOwnWords) return 3;
-    return (tiles <= 256 && L.n_tiles <= 64) || (tiles >= 2048 && L.n_kv_heads >= 4) ? 1 : 3;
+    return (tiles <= 256 && L.n_tiles <= 112) || (tiles >= 2048 && L.n_kv_heads >= 4) ? 1 : 3;
 }
 
 hipError_t launch_prune_topp(const uint16_t *k, int64_t k_tok_stride, int64_t k_head_stride, const int32_t *cu,

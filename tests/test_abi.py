@@ -228,8 +228,8 @@ def test_one_launch_of_the_top_p_prune_only_where_words_and_sums_can_be_told_apa
     assert form(n_kv_heads=4, batch=1, total_tokens=64 * fits + 1) == 3
     assert form(n_kv_heads=8, batch=1, total_tokens=(1 << 31) - 256) == 3
     # few tiles, or many of four heads or more
-    assert form(n_q_heads=1, n_kv_heads=1, batch=1, total_tokens=64 * 64) == 1
-    assert form(n_q_heads=1, n_kv_heads=1, batch=1, total_tokens=64 * 64 + 1) == 3
+    assert form(n_q_heads=1, n_kv_heads=1, batch=1, total_tokens=112 * 64) == 1
+    assert form(n_q_heads=1, n_kv_heads=1, batch=1, total_tokens=112 * 64 + 1) == 3
     assert form(batch=1, total_tokens=2048) == 1 and form(batch=1, total_tokens=2049) == 3
     assert form(batch=1, total_tokens=256 * 64) == 1 and form(batch=1, total_tokens=255 * 64) == 3
     assert form(n_q_heads=2, n_kv_heads=2, batch=1, total_tokens=1 << 20) == 3

@@ -12,12 +12,12 @@ from tests.test_gpu_topp import _run
 pytestmark = pytest.mark.gpu
 
 
-# (KV heads, tokens): one launch up to 256 tiles over all heads, 64 of each, and from 2048 on with four heads or more
-@pytest.mark.parametrize("hkv,tokens", [(1, 1), (1, 64 * 64), (1, 65 * 64), (4, 64 * 64 - 9), (1, 256 * 64), (1, 256 * 64 + 1), (8, 32 * 64 - 5), (8, 33 * 64), (4, 511 * 64), (4, 512 * 64 - 1),
+# (KV heads, tokens): one launch up to 256 tiles over all heads, 112 of each, and from 2048 on with four heads or more
+@pytest.mark.parametrize("hkv,tokens", [(1, 1), (1, 112 * 64), (1, 113 * 64), (4, 64 * 64 - 9), (1, 256 * 64), (1, 256 * 64 + 1), (8, 32 * 64 - 5), (8, 33 * 64), (4, 511 * 64), (4, 512 * 64 - 1),
                                         (3, 683 * 64), (5, 410 * 64 + 17)])
 def test_both_sides_of_the_rule(hkv, tokens):
     tiles = (tokens + 63) // 64
-    one = hkv * tiles <= 256 and tiles <= 64 or hkv * tiles >= 2048 and hkv >= 4
+    one = hkv * tiles <= 256 and tiles <= 112 or hkv * tiles >= 2048 and hkv >= 4
     w = wl.small(name=f"topp{hkv}x{tokens}", batch=2, n_q_heads=hkv, n_kv_heads=hkv, seqlens=(tokens - tokens // 3, tokens // 3), seed=351 + hkv)
     assert spark.call_form(make_desc(w), spark.CALL_PRUNE_TOPP) == (1 if one else 3)
     _run(w, wl.generate(w), p_bp=9500, decode=False)
