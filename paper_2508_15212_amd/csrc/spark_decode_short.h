@@ -9,8 +9,9 @@
 //   output   both bf16 parts of the probabilities side by side in one 16x16x32 product (K = 2 x 16 tokens);
 //   merge    all sixteen wavefronts share the partials of the block that counts in last.
 // Bound by the round trips (sequence table, rows, partial, count, merge) and, in blocks with all four tiles, by the table
-// gathers in the compute unit's LDS (24 to 36 cycles each).  Measured beside the rule in spark_decode.hip; four sequences of
-// 700 to 3900 tokens with appended rows, T = 32: 15.1 -> 14.5 us, eight query heads and T = 60: 21.2 -> 19.4 us.
+// gathers in the compute unit's LDS (24 to 36 cycles each).  What it takes and what it measured stand beside the rule in
+// spark_decode.hip (short_call_pays); 4 sequences of 700 to 3900 tokens with 256 appended rows each, eight query heads: T = 30
+// 18.0 -> 17.0 us, T = 127 29.2 -> 24.9 us.  (128 registers; four query heads spill 4 of them, eight spill 8.)
 #pragma once
 
 namespace spark {
