@@ -108,8 +108,8 @@ size_t spark_decode_workspace(const spark_desc *desc);
 
 /*
  * Prepares a decode workspace: zeroes the per-(batch, KV head) arrival counters, which sit at its
- * start (batch * n_kv_heads 32-bit words, at a position that does not depend on token counts,
- * split counts or tail capacity; the partial softmax states follow).  Call once after allocating
+ * start (a 32-bit word per (batch, KV head), up to 128 bytes apart, at places that depend on batch and n_kv_heads only, not
+ * on token counts, split counts or tail capacity; the partial softmax states follow).  Call once after allocating
  * (or overwriting) the workspace and whenever batch or n_kv_heads change; spark_decode_attn leaves
  * the counters zeroed, so one workspace that is large enough serves any number of successive calls
  * on one stream, also for descriptions that differ in total_tokens, n_splits or tail_capacity.

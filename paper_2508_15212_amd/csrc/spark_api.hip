@@ -106,7 +106,10 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
     // the batch's sequence table in registers (at most 256 sequences) and numbers items in 32 bits.
     p.warm_waves = 0;
     p.short_call = 0;
-    p.chunk_ids = p.nchunk_max;
+    p.counter_stride = spark::counter_stride((int64_t)d->batch * d->n_kv_heads);
+    // (neighbours share a tile at most, so sequences cut by length span tiles + batch - 1 of them, in no more than
+    //  (tiles - 1) / chunk + batch chunks: one fewer than nchunk_max)
+    p.chunk_ids = p.fixed_splits > 0 ? p.nchunk_max : p.nchunk_max - 1;
     const int64_t pairs = (int64_t)d->batch * d->n_kv_heads;
     // (a batch that its caller knows to be near-uniform is balanced with one block per sequence already)
     const bool even = d->max_seqlen > 0 && (int64_t)d->max_seqlen * d->batch * 8 <= d->total_tokens * 9;
@@ -119,7 +122,7 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
         const bool enough = d->n_splits == -1 || tiles >= 2 * nw;
         if (enough && (tiles + 2 * (int64_t)d->batch + 1) * nw < ((int64_t)1 << 32)) {
             p.warm_waves = (int)nw;
-            const int ids = (int)nw + 2 * d->batch;
+            const int ids = (int)nw + 2 * d->batch - 1;
             if (p.chunk_ids < ids) p.chunk_ids = ids;
         }
     }
@@ -142,17 +145,30 @@ int pick_splits(const spark_desc *d)
 
 // partial slots in the workspace: one per (chunk, q head), then the appended rows' (one per 256 rows of
 // capacity, at least one, per (batch, q head), so a workspace serves calls with and without appended rows)
-size_t partial_slots(const spark_desc *d, bool allow_balanced = true)
+size_t partial_slots(const spark_desc *d, const spark::DecodePlan &p)
 {
-    const spark::DecodePlan p = plan_of(d, allow_balanced);
     return (size_t)p.chunk_ids * d->n_q_heads + (size_t)d->batch * d->n_q_heads * p.tail_slots;
 }
 
 // The arrival counters sit at the START of the workspace, so their position depends on batch and n_kv_heads
 // only and not on how a call cuts its sequences into blocks; the partial states follow at a 256-byte boundary.
-size_t counter_bytes(const spark_desc *d)
+size_t counter_bytes(const spark_desc *d, int stride)
 {
-    return (((size_t)d->batch * d->n_kv_heads * sizeof(uint32_t)) + 255) & ~(size_t)255;
+    return (((size_t)d->batch * d->n_kv_heads * stride * sizeof(uint32_t)) + 255) & ~(size_t)255;
+}
+
+size_t bytes_of(const spark_desc *d, const spark::DecodePlan &p)
+{
+    return partial_slots(d, p) * (SPARK_D + 2) * sizeof(float) + counter_bytes(d, p.counter_stride);
+}
+
+// What a call asks for: never less than it took with the counters side by side and slots for a chunk more.
+size_t workspace_bytes_of(const spark_desc *d, const spark::DecodePlan &p)
+{
+    spark::DecodePlan dense = p;
+    dense.counter_stride = 1;
+    dense.chunk_ids += p.fixed_splits > 0 && p.warm_waves == 0 ? 0 : 1;
+    return bytes_of(d, p) > bytes_of(d, dense) ? bytes_of(d, p) : bytes_of(d, dense);
 }
 
 }  // namespace
@@ -196,8 +212,7 @@ size_t spark_decode_workspace(const spark_desc *desc)
 {
     spark_status why;
     if (!desc_ok(desc, &why)) return 0;
-    const size_t slots = partial_slots(desc);
-    return slots * (SPARK_D + 2) * sizeof(float) + counter_bytes(desc);
+    return workspace_bytes_of(desc, plan_of(desc));
 }
 
 spark_status spark_decode_workspace_init(const spark_desc *desc, void *workspace, size_t workspace_bytes,
@@ -208,7 +223,7 @@ spark_status spark_decode_workspace_init(const spark_desc *desc, void *workspace
     if (!workspace || !aligned(workspace, 16)) return SPARK_ERR_INVALID_ARG;
     if (workspace_bytes < spark_decode_workspace(desc)) return SPARK_ERR_WORKSPACE_TOO_SMALL;
     uint32_t *counters = static_cast<uint32_t *>(workspace);
-    const hipError_t e = spark::launch_zero_counters(counters, desc->batch * desc->n_kv_heads,
+    const hipError_t e = spark::launch_zero_counters(counters, (int)(counter_bytes(desc, plan_of(desc).counter_stride) / sizeof(uint32_t)),
                                                      static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? SPARK_OK : SPARK_ERR_HIP;
 }
@@ -273,7 +288,7 @@ spark_status decode_common(const spark_desc *desc, const void *q_bf16, const voi
                            const void *packed_v, const int32_t *cu_seqlens, void *out, void *workspace,
                            size_t workspace_bytes, void *hip_stream, const void *tail_k = nullptr,
                            const void *tail_v = nullptr, const int32_t *tail_len = nullptr, int rec = 0,
-                           uint64_t seed = 0, bool topp = false, bool allow_balanced = true)
+                           uint64_t seed = 0, bool topp = false, const spark::DecodePlan *given = nullptr)
 {
     spark_status why;
     if (!desc_ok(desc, &why)) return why;
@@ -292,14 +307,14 @@ spark_status decode_common(const spark_desc *desc, const void *q_bf16, const voi
         if (!tail_v || !tail_len || desc->tail_capacity < 1) return SPARK_ERR_INVALID_ARG;
         if (!aligned(tail_k, 16) || !aligned(tail_v, 16) || !aligned(tail_len, 4)) return SPARK_ERR_INVALID_ARG;
     }
-    const size_t slots = partial_slots(desc, allow_balanced);
-    if (workspace_bytes < slots * (SPARK_D + 2) * sizeof(float) + counter_bytes(desc)) return SPARK_ERR_WORKSPACE_TOO_SMALL;
+    const spark::DecodePlan plan = given ? *given : plan_of(desc);
+    const size_t slots = partial_slots(desc, plan);
+    if (workspace_bytes < workspace_bytes_of(desc, plan)) return SPARK_ERR_WORKSPACE_TOO_SMALL;
     const SparkLayout L = topp ? topp_layout_of(desc) : layout_of(desc);
     SparkLayout Lv = L;
     if (packed_v) Lv = values_layout_of(desc);
-    const spark::DecodePlan plan = plan_of(desc, allow_balanced);
     uint32_t *counters = static_cast<uint32_t *>(workspace);
-    float *part_acc = reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + counter_bytes(desc));
+    float *part_acc = reinterpret_cast<float *>(static_cast<uint8_t *>(workspace) + counter_bytes(desc, plan.counter_stride));
     float *part_ml = part_acc + slots * SPARK_D;
     const float scale = desc->softmax_scale != 0.0f ? desc->softmax_scale : 1.0f / sqrtf((float)SPARK_D);
     const hipError_t e = spark::launch_decode_attn(
@@ -506,23 +521,20 @@ spark_status spark_decode_attn_static(const spark_desc *desc, const void *q_bf16
     if (!v_bf16) return SPARK_ERR_INVALID_ARG;
     // the balanced cut of a ragged batch needs more partial slots than the chunked one: where only the chunked
     // one fits the array, that one is used
-    bool balanced = true;
-    size_t need = spark_decode_workspace(desc);
-    if (need > (size_t)SPARK_STATIC_WORKSPACE_BYTES) {
-        balanced = false;
-        need = partial_slots(desc, false) * (SPARK_D + 2) * sizeof(float) + counter_bytes(desc);
-    }
-    if (need > (size_t)SPARK_STATIC_WORKSPACE_BYTES) return SPARK_ERR_WORKSPACE_TOO_SMALL;
+    spark::DecodePlan plan = plan_of(desc);
+    if (workspace_bytes_of(desc, plan) > (size_t)SPARK_STATIC_WORKSPACE_BYTES) plan = plan_of(desc, false);
+    if (workspace_bytes_of(desc, plan) > (size_t)SPARK_STATIC_WORKSPACE_BYTES) plan.counter_stride = 1;
+    if (workspace_bytes_of(desc, plan) > (size_t)SPARK_STATIC_WORKSPACE_BYTES) return SPARK_ERR_WORKSPACE_TOO_SMALL;
     void *ws = scratch_address();
     if (!ws) return SPARK_ERR_HIP;
     // the array keeps whatever the last call on this GPU left: the counters must start at zero (a small fill
     // kernel, not a memset node, so the call can be captured into a graph); partial states are written before
     // they are read
-    if (spark::launch_zero_counters(static_cast<uint32_t *>(ws), desc->batch * desc->n_kv_heads,
+    if (spark::launch_zero_counters(static_cast<uint32_t *>(ws), (int)(counter_bytes(desc, plan.counter_stride) / sizeof(uint32_t)),
                                     static_cast<hipStream_t>(hip_stream)) != hipSuccess)
         return SPARK_ERR_HIP;
     return decode_common(desc, q_bf16, packed, v_bf16, nullptr, cu_seqlens, out, ws, SPARK_STATIC_WORKSPACE_BYTES,
-                         hip_stream, nullptr, nullptr, nullptr, 0, 0, false, balanced);
+                         hip_stream, nullptr, nullptr, nullptr, 0, 0, false, &plan);
 }
 
 }  // extern "C"

@@ -120,6 +120,7 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
     P.chunk_limit = plan.chunk_limit;
     P.short_call = plan.short_call;
     P.warm_waves = plan.warm_waves;
+    P.counter_stride = plan.counter_stride;
     P.tail_slots = plan.tail_slots;
     P.ntail = tail_k ? plan.tail_slots : 0;
     P.tail_base = (int64_t)plan.chunk_ids * Hq;
@@ -145,9 +146,9 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
     }
 }
 
-hipError_t launch_zero_counters(uint32_t *counters, int n, hipStream_t st)
+hipError_t launch_zero_counters(uint32_t *counters, int n_words, hipStream_t st)
 {
-    hipLaunchKernelGGL(spark_zero_kernel, dim3((n + 255) / 256), dim3(256), 0, st, counters, n);
+    hipLaunchKernelGGL(spark_zero_kernel, dim3((n_words + 255) / 256), dim3(256), 0, st, counters, n_words);
     return hipGetLastError();
 }
 

@@ -52,7 +52,8 @@ struct DecodeParams {
     const int32_t *cu;       // [B+1]
     float *part_acc;         // [slots][128]   partial softmax states, see slot numbering below
     float *part_ml;          // [slots][2]     (m in log2 units, l)
-    uint32_t *counters;      // [B*Hkv] arrival counters, zero between calls
+    uint32_t *counters;      // [B*Hkv] arrival counters, counter_stride words apart, zero between calls
+    int counter_stride;
     unsigned long long *trace;   // NULL, or eight 64-bit words per block of the grid for the timeline (see stamp())
     void *out;               // [B, Hq, 128] bf16 or float32
     int out_f32;
@@ -71,7 +72,7 @@ struct DecodeParams {
     // which works on its own and leaves one partial per sequence it touches.  Wavefront w covers items
     // [w * I / warm_waves, (w + 1) * I / warm_waves) of the I items; the partial of (wavefront w, sequence b) has
     // chunk id w + b (both grow along the item list, so the ids of one sequence are consecutive and no two
-    // pairs share one); a sequence without tokens has the single id warm_waves + batch + b: warm_waves + 2 * batch
+    // pairs share one); a sequence without tokens has the single id warm_waves + batch - 1 + b: warm_waves + 2 * batch - 1
     // ids in all.
     int warm_waves;
     int short_call;          // 1: blocks of sixteen wavefronts (spark_decode_short.h)
@@ -307,7 +308,7 @@ __device__ __forceinline__ PairInfo warm_pair(const DecodeParams &P, const WarmS
         pi.first = wf + q.b;
         pi.nsplit = wl - wf + 1;
     } else {
-        pi.first = P.warm_waves + B + q.b;
+        pi.first = P.warm_waves + B - 1 + q.b;
         pi.nsplit = 1;
     }
     return pi;
@@ -1569,7 +1570,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // this wavefront's stores have been acknowledged
             uint32_t old = 0u;
-            if (lane == 0) old = atomicInc(&P.counters[pend.b * P.Hkv + h], (uint32_t)(pend_n - 1));
+            if (lane == 0) old = atomicInc(&P.counters[(pend.b * P.Hkv + h) * P.counter_stride], (uint32_t)(pend_n - 1));
             old = (uint32_t)__builtin_amdgcn_readfirstlane((int)old);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             if (old == (uint32_t)(pend_n - 1)) {
@@ -1888,7 +1889,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);   // this thread's stores have been acknowledged
     __syncthreads();
     if (tid == 0) {
-        const uint32_t old = atomicInc(&P.counters[b * P.Hkv + h], (uint32_t)(nmerge - 1));
+        const uint32_t old = atomicInc(&P.counters[(b * P.Hkv + h) * P.counter_stride], (uint32_t)(nmerge - 1));
         last_flag = (old == (uint32_t)(nmerge - 1));
     }
     __syncthreads();

@@ -384,7 +384,7 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
     if (tid == 0) {
-        const uint32_t old = atomicInc(&P.counters[b * P.Hkv + h], (uint32_t)(nmerge - 1));
+        const uint32_t old = atomicInc(&P.counters[(b * P.Hkv + h) * P.counter_stride], (uint32_t)(nmerge - 1));
         last_flag = (old == (uint32_t)(nmerge - 1));
     }
     __syncthreads();

@@ -15,6 +15,18 @@ constexpr int kWaitVmcnt0 = (0 << 0) | (0 << 14) | (7 << 4) | (15 << 8);      //
 
 struct DecodeParams;
 
+// Words between the arrival counters of two (batch, KV head) pairs.  Device-scope atomics on one 64-byte block are served one
+// after the other, 11.5 ns each, so the counters are spread over 2 KB, at most 128 bytes apart.  Blocks that only count in, all at
+// once, on eight counters side by side / 128 bytes apart (us; 2.4 without counting): 512 blocks 7.2 / 2.4, 1024 13.0 / 3.1; on 64 counters
+// side by side / 32 bytes apart: 512 4.1 / 2.3, 1024 6.2 / 2.6.  Decode, T = 26, eight heads, G = 1 / 4: 8192 tokens 12.1 / 14.0 ->
+// 10.1 / 12.0, 16384 17.9 / 19.5 -> 15.6 / 17.8, 4 x 4096 14.6 / 16.6 -> 13.1 / 15.2; 2 x 8000 with packed values 18.5 -> 16.4.
+inline int counter_stride(int64_t pairs)
+{
+    int stride = 32;
+    while (stride > 1 && pairs * stride > 512) stride /= 2;
+    return stride;
+}
+
 // How the decode grid cuts sequences into blocks (chosen on the host from the description alone).
 struct DecodePlan {
     int fixed_splits;   // > 0: every sequence is cut into this many chunks
@@ -24,9 +36,10 @@ struct DecodePlan {
     int tail_slots;     // partial slots reserved per (batch, q head) for appended rows
     int warm_waves;     // > 0: the balanced mode may be used, with this many wavefronts per KV head; decode_form
                         // falls back to the chunked cut for the kernel variants that have no balanced form
+    int counter_stride; // words between the arrival counters of two pairs
     int short_call;     // 1: blocks of sixteen wavefronts (spark_decode_short.h); chosen by decode_form
-    int chunk_ids;      // chunk ids the workspace has partial slots for: >= nchunk_max, and >= the balanced
-                        // mode's warm_waves + 2 * batch; the appended rows' slots follow at chunk_ids * Hq
+    int chunk_ids;      // chunk ids the workspace has partial slots for: all of a cut by length, and of the balanced
+                        // mode, warm_waves + 2 * batch - 1; the appended rows' slots follow at chunk_ids * Hq
 };
 
 // measurement aid: later decode launches of this process file eight 64-bit words per block into `device_words`
@@ -60,7 +73,7 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
                               void *out, int out_f32, const uint16_t *tail_k, const uint16_t *tail_v,
                               const int32_t *tail_len, int tail_cap, int rec, uint64_t seed, hipStream_t st);
 
-hipError_t launch_zero_counters(uint32_t *counters, int n, hipStream_t st);
+hipError_t launch_zero_counters(uint32_t *counters, int n_words, hipStream_t st);
 
 // channel weights a, 1/a (and the key cache's header) alone; for a top-p cache also its directory, cleared
 hipError_t launch_window_stat(const uint16_t *qwin, uint8_t *packed, const SparkLayout &L, int Hq, int W, hipStream_t st);
