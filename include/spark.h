@@ -102,7 +102,8 @@ typedef struct spark_desc {
  * keep, pack_dtype, total_tokens).  0 if the description is invalid. */
 size_t spark_packed_bytes(const spark_desc *desc);
 
-/* Scratch sizes in bytes (0 is possible; then NULL may be passed as the workspace). */
+/* Scratch sizes in bytes (0 is possible; then NULL may be passed as the workspace).  Of a short call's decode workspace about a
+ * quarter would do (spark_decode_workspace_init and the call accept it): with the whole, a block can take a single tile. */
 size_t spark_prune_workspace(const spark_desc *desc);
 size_t spark_decode_workspace(const spark_desc *desc);
 

@@ -41,8 +41,8 @@ spark_status spark_decode_timeline(void *device_buffer, size_t bytes);
  *   SPARK_CALL_PRUNE        spark_prune:  1: the window statistic in the pruning launch   2: in a launch of its own (which a
  *                           window that is only 2-byte aligned takes always)
  *   SPARK_CALL_PRUNE_TOPP   1: selection and writing in one launch   3: in three
- *   SPARK_CALL_DECODE       spark_decode_attn:  1: chunks, blocks of four wavefronts   2: chunks, blocks of sixteen
- *                           3: the balanced cut
+ *   SPARK_CALL_DECODE       spark_decode_attn:  1: chunks, blocks of four wavefronts (of four tiles or more, or, in short calls
+ *                           whose workspace has room, of one)   2: chunks, blocks of sixteen   3: the balanced cut
  *   SPARK_CALL_DECODE_TAIL  spark_decode_attn_tail, the same
  * 0 for an invalid description, another call, or a call that launches nothing.
  */

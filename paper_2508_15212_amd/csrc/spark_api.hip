@@ -129,10 +129,50 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
     return p;
 }
 
+// A block of four wavefronts for every tile, four lanes a row (plan.short_call = 2, spark_decode_short.h): short calls whose
+// workspace has room for a partial per tile.  Four tiles in a block keep to a quarter of the compute units, each bound by the
+// table gathers in its LDS; a tile a block spreads them, for four times the partials, which the last block of a pair merges.  So it
+// gains until that merge is the longer: the more query heads, the fewer tiles a sequence.  Only where blocks of four wavefronts
+// would take four tiles each.  Time against those, eight KV heads (tiles a sequence, tiles over all heads):
+//                                  G = 1, T = 26 / 32 / 64    G = 2                 G = 4                 G = 8, T = 26 / 64
+//   1 x 500              8    62     0.98 / 0.81 / 0.83      0.98 / 0.80 / 0.83    0.99 / 0.81 / 0.80    1.02 / 0.85
+//   1 x 1024            16   128     0.97 / 0.76 / 0.81      0.96 / 0.79 / 0.84    0.97 / 0.78 / 0.85    0.99 / 0.87
+//   1 x 1500            23   188     1.01 / 0.80 / 0.84      0.99 / 0.82 / 0.85    1.01 / 0.85 / 0.87    1.07 / 0.92
+//   1 x 2048            32   256     0.94 / 0.77 / 0.83      0.95 / 0.79 / 0.84    0.99 / 0.83 / 0.88    1.08 / 0.97
+//   1 x 3000            47   375     0.97 / 0.83 / 0.86      1.01 / 0.88 / 0.93    1.16 / 1.00 / 1.04    1.31 / 1.16
+//   1 x 4096            64   512     0.94 / 0.87 / 0.86                            1.20 / 1.03 / 1.11    1.38 / 1.25
+//   2 x 500 to 1500     15   237     0.92 / 0.79 / 0.80      0.92 / 0.79 / 0.82    0.92 / 0.80 / 0.82    1.01 / 0.87
+//   4 x 300 to 800       9   276     0.95 / 0.82 / 0.84      0.96 / 0.83 / 0.87    0.99 / 0.83 / 0.86    1.00 / 0.89
+//   the same, 256 appended rows      0.98 / 0.84 / 0.86      0.98 / 0.84 / 0.88    0.99 / 0.86 / 0.90    1.04 / 0.93
+//   8 x 300 to 800      10   635     0.99 / 0.85 / 0.89      1.02 / 0.90 / 0.95    1.06 / 0.93 / 0.98    1.14 / 1.06
+//   16 x 100 to 300      3   426     1.05 / 0.88 / 0.93      1.07 / 0.90 / 0.99    1.09 / 0.94 / 1.00    1.14 / 1.04
+//   32 x 100 to 300      3   814     1.24 / 1.03 / 1.08                            1.24 / 1.11 / 1.09    1.27 / 1.15
+// 1024 tokens, G = 4, T = 64: 11.4 -> 9.7 us; T = 32: 11.6 -> 9.1; int8 codes the same within 2 %.
+bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
+{
+    const int G = d->n_q_heads / d->n_kv_heads;
+    const int64_t tiles = (d->total_tokens + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS, per_sequence = tiles / d->batch;
+    const int tail_slots = d->tail_capacity > 0 ? (d->tail_capacity + spark::kFineTailRows - 1) / spark::kFineTailRows : 1;
+    const int64_t blocks = (tiles + d->batch * (1 + (with_tail ? (int64_t)tail_slots : 0))) * d->n_kv_heads;
+    if (tiles == 0 || d->batch > 64 || d->n_splits != 0 || p.warm_waves > 0 || G > 8) return false;
+    const bool short_rows = d->keep < 30;
+    const int64_t longest = short_rows ? (G <= 2 ? 32 : (G == 4 ? 20 : 0)) : (G == 1 ? 64 : (G == 2 ? 48 : (G == 4 ? 32 : 24)));
+    if (per_sequence > longest || blocks > (short_rows || G == 8 ? 320 : 720) + (with_tail ? 128 : 0)) return false;
+    if (spark::decode_form(p, layout_of(d), d->n_q_heads, true, with_tail ? p.tail_slots : 0).short_call != 0) return false;
+    p.short_call = 2;
+    p.chunk_tiles = 1;
+    p.chunk_limit = 0;
+    p.nchunk_max = p.chunk_ids = (int)(tiles + d->batch - 1);      // (see plan_of)
+    p.tail_slots = tail_slots;
+    return true;
+}
+
 // chunks an average-length sequence is cut into; 0 for the balanced cut (what spark_decode_splits reports)
 int pick_splits(const spark_desc *d)
 {
-    const spark::DecodePlan p = spark::decode_form(plan_of(d), layout_of(d), d->n_q_heads, true, 0);
+    spark::DecodePlan p = plan_of(d);
+    fine_plan(d, p, false);
+    p = spark::decode_form(p, layout_of(d), d->n_q_heads, true, 0);
     if (p.warm_waves > 0) return 0;
     if (p.fixed_splits > 0) return p.fixed_splits;
     // (as the kernel numbers them, for a batch of sequences of that length)
@@ -212,7 +252,13 @@ size_t spark_decode_workspace(const spark_desc *desc)
 {
     spark_status why;
     if (!desc_ok(desc, &why)) return 0;
-    return workspace_bytes_of(desc, plan_of(desc));
+    // (what the calls need; short ones are faster with more)
+    size_t bytes = workspace_bytes_of(desc, plan_of(desc));
+    for (const bool with_tail : {false, true}) {
+        spark::DecodePlan fine = plan_of(desc);
+        if (fine_plan(desc, fine, with_tail) && workspace_bytes_of(desc, fine) > bytes) bytes = workspace_bytes_of(desc, fine);
+    }
+    return bytes;
 }
 
 spark_status spark_decode_workspace_init(const spark_desc *desc, void *workspace, size_t workspace_bytes,
@@ -221,7 +267,7 @@ spark_status spark_decode_workspace_init(const spark_desc *desc, void *workspace
     spark_status why;
     if (!desc_ok(desc, &why)) return why;
     if (!workspace || !aligned(workspace, 16)) return SPARK_ERR_INVALID_ARG;
-    if (workspace_bytes < spark_decode_workspace(desc)) return SPARK_ERR_WORKSPACE_TOO_SMALL;
+    if (workspace_bytes < workspace_bytes_of(desc, plan_of(desc))) return SPARK_ERR_WORKSPACE_TOO_SMALL;
     uint32_t *counters = static_cast<uint32_t *>(workspace);
     const hipError_t e = spark::launch_zero_counters(counters, (int)(counter_bytes(desc, plan_of(desc).counter_stride) / sizeof(uint32_t)),
                                                      static_cast<hipStream_t>(hip_stream));
@@ -307,9 +353,13 @@ spark_status decode_common(const spark_desc *desc, const void *q_bf16, const voi
         if (!tail_v || !tail_len || desc->tail_capacity < 1) return SPARK_ERR_INVALID_ARG;
         if (!aligned(tail_k, 16) || !aligned(tail_v, 16) || !aligned(tail_len, 4)) return SPARK_ERR_INVALID_ARG;
     }
-    const spark::DecodePlan plan = given ? *given : plan_of(desc);
-    const size_t slots = partial_slots(desc, plan);
+    spark::DecodePlan plan = given ? *given : plan_of(desc);
     if (workspace_bytes < workspace_bytes_of(desc, plan)) return SPARK_ERR_WORKSPACE_TOO_SMALL;
+    if (!packed_v && rec == 0 && !topp) {
+        spark::DecodePlan fine = plan;
+        if (fine_plan(desc, fine, tail_k != nullptr) && workspace_bytes >= workspace_bytes_of(desc, fine)) plan = fine;
+    }
+    const size_t slots = partial_slots(desc, plan);
     const SparkLayout L = topp ? topp_layout_of(desc) : layout_of(desc);
     SparkLayout Lv = L;
     if (packed_v) Lv = values_layout_of(desc);
@@ -467,9 +517,10 @@ int32_t spark_call_form(const spark_desc *desc, int32_t call)
     if (!desc_ok(desc, &why)) return 0;
     if (call == SPARK_CALL_PRUNE) return spark::prune_launches(layout_of(desc), desc->n_q_heads, desc->window);
     if (call == SPARK_CALL_DECODE || call == SPARK_CALL_DECODE_TAIL) {
-        const spark::DecodePlan cut = plan_of(desc);
+        spark::DecodePlan cut = plan_of(desc);
+        fine_plan(desc, cut, call == SPARK_CALL_DECODE_TAIL);
         const spark::DecodePlan p = spark::decode_form(cut, layout_of(desc), desc->n_q_heads, true, call == SPARK_CALL_DECODE ? 0 : cut.tail_slots);
-        return p.warm_waves > 0 ? 3 : (p.short_call ? 2 : 1);
+        return p.warm_waves > 0 ? 3 : (p.short_call == 1 ? 2 : 1);      // (a block per tile: blocks of four wavefronts)
     }
     if (call == SPARK_CALL_PRUNE_TOPP) return spark::topp_prune_launches(topp_layout_of(desc));
     return 0;

@@ -56,6 +56,7 @@ static bool short_call_pays(const SparkLayout &L, int G)
 DecodePlan decode_form(DecodePlan plan, const SparkLayout &L, int Hq, bool plain, int ntail)
 {
     const int G = Hq / L.n_kv_heads;
+    if (plan.short_call == 2) return plan;
     if (!plain || G > 8) plan.warm_waves = 0;
     plan.short_call = 0;
     if (!plain || G > 8 || plan.warm_waves > 0 || !short_call_pays(L, G)) return plan;

@@ -75,8 +75,8 @@ struct DecodeParams {
     // pairs share one); a sequence without tokens has the single id warm_waves + batch - 1 + b: warm_waves + 2 * batch - 1
     // ids in all.
     int warm_waves;
-    int short_call;          // 1: blocks of sixteen wavefronts (spark_decode_short.h)
-    int ntail;               // blocks per (batch, KV head) for the appended rows, 256 rows each (0: none)
+    int short_call;          // blocks of 1: sixteen 2: four wavefronts of spark_decode_short.h
+    int ntail;               // blocks per (batch, KV head) for the appended rows, 256 rows each (short_call 2: 64; 0: none)
     int tail_slots;          // slots reserved per (batch, q head) for them (>= max(1, ntail))
     int64_t tail_base;       // first of them: the number of chunk ids the workspace provides for, times Hq
     const uint16_t *tail_k, *tail_v;   // appended never-pruned rows [B, tail_cap, Hkv, 128] bf16, or NULL
@@ -1955,7 +1955,8 @@ template <int G>
 hipError_t launch_g(const DecodeParams &P, int nblocks, hipStream_t st)
 {
     if constexpr (G <= 8) {
-        if (P.short_call) return launch_short<G>(P, nblocks, st);
+        if (P.short_call == 1) return launch_short<G, 16>(P, nblocks, st);
+        if (P.short_call == 2) return launch_short<G, 4>(P, nblocks, st);
     }
     const int T = row_length_instantiated(P.L) ? P.L.T : -1;      // (-1: any length)
     if (P.L.topp) return launch_one<G, 0, 0, 0, 0, 1>(P, nblocks, st);

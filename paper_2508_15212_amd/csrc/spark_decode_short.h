@@ -1,4 +1,5 @@
-// Decode attention for short calls on gfx950: one block of SIXTEEN wavefronts per compute unit, sixteen tokens a wavefront.
+// Decode attention for short calls on gfx950: sixteen tokens a wavefront, in blocks of SIXTEEN wavefronts, one per compute unit, or
+// of FOUR, one per tile.
 // (Included by spark_decode_kernel.h, whose parameter block, chunk numbering and partial slots it shares.)
 //
 // A short call is a chain of latencies; the longest was the walk of a lane over all kept entries of its row, one of 64 a
@@ -7,23 +8,24 @@
 //   scores   FOUR lanes a row, one mask word each: lane (tg, cn) walks word tg of row cn, a few entries at a time, and a
 //            lane-swap reduction hands lane row tg the scores of query heads tg, 4 + tg.  Softmax: a row of sixteen lanes;
 //   output   both bf16 parts of the probabilities side by side in one 16x16x32 product (K = 2 x 16 tokens);
-//   merge    all sixteen wavefronts share the partials of the block that counts in last.
-// Bound by the round trips (sequence table, rows, partial, count, merge) and, in blocks with all four tiles, by the table
-// gathers in the compute unit's LDS (24 to 36 cycles each).  What it takes and what it measured stand beside the rule in
-// spark_decode.hip (short_call_pays); 4 sequences of 700 to 3900 tokens with 256 appended rows each, eight query heads: T = 30
-// 18.0 -> 17.0 us, T = 127 29.2 -> 24.9 us.  (128 registers; four query heads spill 4 of them, eight spill 8.)
+//   merge    all wavefronts share the partials of the block that counts in last.
+// Bound by the round trips (sequence table, rows, partial, count, merge) and, in blocks with four tiles, by the table
+// gathers in the compute unit's LDS (24 to 36 cycles each), which a block per tile spreads over four times as many compute
+// units.  What each takes and what it measured stand beside the rules: short_call_pays in spark_decode.hip (sixteen), fine_plan in
+// spark_api.hip (four); 4 sequences of 700 to 3900 tokens with 256 appended rows each, eight query heads, by sixteen wavefronts: T = 30
+// 18.0 -> 17.0 us, T = 127 29.2 -> 24.9 us; 1024 tokens, four query heads, T = 64, by a block per tile: 11.4 -> 9.7 us.  (128
+// registers; four query heads spill 4 of them, eight spill 8.)
 #pragma once
 
 namespace spark {
 
-constexpr int kShortWaves = 16;
 constexpr int kShortRows = 16;          // tokens a wavefront takes at a time
 
-template <int G, int INT8>
-__global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel(DecodeParams P)
+template <int G, int INT8, int BW>
+__global__ __launch_bounds__(BW * 64, 4) void spark_decode_short_kernel(DecodeParams P)
 {
     static_assert(G <= 8, "eight query heads at most");
-    static_assert(kShortWaves * kShortRows == 256, "a block of appended rows is one pass");
+    static_assert(BW * kShortRows == (BW == 4 ? kFineTailRows : 256), "a block of appended rows is one pass");
     constexpr int GP = 8 * ((G + 1 + 3) / 8) + 4;                // floats per table entry (as in spark_decode_kernel)
     constexpr int NH = (G + 3) / 4;                              // query heads per lane row: tg, 4 + tg
     constexpr int kMaxSections = 18;                             // 16-byte sections of the longest row (128 entries, statistics)
@@ -34,10 +36,10 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
     static_assert(kRowWords >= G * SPARK_D && kRowWords % 4 == 0, "accumulators fit, 16-byte aligned");
 
     __shared__ __align__(16) float qt[SPARK_D * GP];
-    __shared__ __align__(16) uint32_t area[kShortWaves][kRowWords];       // rows, then the accumulators
-    __shared__ __align__(16) uint16_t pbuf[kShortWaves][G][32];           // two parts of the probabilities
-    __shared__ __align__(16) uint16_t pthird[kShortWaves][G][16];         // the third one (appended rows)
-    __shared__ float red_m[kShortWaves][G], red_l[kShortWaves][G];
+    __shared__ __align__(16) uint32_t area[BW][kRowWords];       // rows, then the accumulators
+    __shared__ __align__(16) uint16_t pbuf[BW][G][32];           // two parts of the probabilities
+    __shared__ __align__(16) uint16_t pthird[BW][G][16];         // the third one (appended rows)
+    __shared__ float red_m[BW][G], red_l[BW][G];
     __shared__ int last_flag;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -166,12 +168,12 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
         if (P.trace != nullptr) { stamp(P, 1, wall_clock64()); stamp(P, 5, (unsigned long long)((p_end - p_begin + 3) / 4)); }
         uint32_t *const rows = area[wave];
         const uint32_t *const row = rows + cn * sw;
-        for (; part < p_end; part += kShortWaves) {
+        for (; part < p_end; part += BW) {
 #pragma unroll
             for (int u = 0; u < kLoads; ++u)
                 if (4 * u + tg < nsec) *reinterpret_cast<u32x4 *>(&rows[cn * sw + 4 * (4 * u + tg)]) = x[u];
-            const bool more = part + kShortWaves < p_end;        // (wave-uniform)
-            if (more) load_row(part + kShortWaves);
+            const bool more = part + BW < p_end;        // (wave-uniform)
+            if (more) load_row(part + BW);
             wave_lds_sync();
             // ---- scores: this lane's mask word of its row, a few entries at a time
             const u32x4 mk = *reinterpret_cast<const u32x4 *>(row);
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
             uint4 a = {0, 0, 0, 0};
             if (cn < G) a = *reinterpret_cast<const uint4 *>(&pbuf[wave][cn][8 * tg]);
             add_output(__builtin_bit_cast(bf16x8, a), nullptr);
-            if (more) load_v(part + kShortWaves);
+            if (more) load_v(part + BW);
             wave_lds_sync();             // rows and probabilities are rewritten by the next pass
         }
         if (P.trace != nullptr) stamp(P, 2, wall_clock64());
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
         tail_query_rows<G>(P, b, h, cn, tg, qx);
         const float q_scale = split_scale(P.scale_log2, s_scale);
         tail_rows = tail_rows < 0 ? 0 : (tail_rows > P.tail_cap ? P.tail_cap : tail_rows);
-        const int c0 = (tb % P.ntail) * (kShortWaves * kShortRows) + wave * kShortRows;
+        const int c0 = (tb % P.ntail) * (BW * kShortRows) + wave * kShortRows;
         const int nval = min(tail_rows - c0, kShortRows);
         float m[4], l[4];                // of head 4 tg + r
 #pragma unroll
@@ -355,15 +357,15 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
         return i < sc.n ? (int64_t)(sc.first + i) * P.Hq + h * G + g
                         : P.tail_base + ((int64_t)b * P.Hq + h * G + g) * P.tail_slots + (i - sc.n);
     };
-    if (tid < G * SPARK_D) {
-        const int g = tid / SPARK_D, ch = tid % SPARK_D;
+    for (int idx = tid; idx < G * SPARK_D; idx += BW * 64) {
+        const int g = idx / SPARK_D, ch = idx % SPARK_D;
         float M = -INFINITY;
 #pragma unroll
-        for (int w = 0; w < kShortWaves; ++w) M = fmaxf(M, red_m[w][g]);
+        for (int w = 0; w < BW; ++w) M = fmaxf(M, red_m[w][g]);
         const float Ms = (M == -INFINITY) ? 0.0f : M;
         float Lsum = 0.0f, A = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kShortWaves; ++w) {
+        for (int w = 0; w < BW; ++w) {
             const float f = fast_exp2(red_m[w][g] - Ms);
             Lsum = fmaf(red_l[w][g], f, Lsum);
             A = fmaf(reinterpret_cast<const float *>(area[w])[g * SPARK_D + ch], f, A);
@@ -380,7 +382,7 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
     if (nmerge == 1) return;             // (block-uniform)
 
     // ---- the last block of this (batch, KV head) to get here merges: stores acknowledged, then counted (see
-    // spark_decode_kernel).  A wavefront folds every (sixteen / G)-th partial of one query head.
+    // spark_decode_kernel).  A wavefront folds every (BW / G)-th partial of one query head, or all partials of some heads.
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
     if (tid == 0) {
@@ -391,55 +393,59 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
     if (P.trace != nullptr) stamp(P, 4, wall_clock64());
     if (!last_flag) return;
     {
-        constexpr int kShare = kShortWaves / G, RN = 16;         // wavefronts per query head, partials in flight
-        const int g = wave % G, first = wave / G;
-        const uint64_t *pa = reinterpret_cast<const uint64_t *>(P.part_acc + 2 * lane);
-        const uint64_t *pm = reinterpret_cast<const uint64_t *>(P.part_ml);
-        float M = -INFINITY, Lsum = 0.0f, A0 = 0.0f, A1 = 0.0f;
-        for (int i0 = first; i0 < nmerge; i0 += RN * kShare) {
-            const int left = (nmerge - i0 + kShare - 1) / kShare, nn = left < RN ? left : RN;
-            float mi = -INFINITY, li = 0.0f;
-            if (lane < nn) {
-                const uint64_t ml = __hip_atomic_load(pm + slot_of(g, i0 + kShare * lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                mi = __uint_as_float((uint32_t)ml);
-                li = __uint_as_float((uint32_t)(ml >> 32));
-            }
-            uint64_t av[RN];
+        constexpr int kShare = BW > G ? BW / G : 1, kHeads = BW < G ? G / BW : 1;       // wavefronts per query head, heads per wavefront
+        constexpr int RN = BW == 4 ? 32 : 16;                    // partials in flight
+#pragma unroll 1
+        for (int hd = 0; hd < kHeads; ++hd) {
+            const int g = (wave + BW * hd) % G, first = wave / G;
+            const uint64_t *pa = reinterpret_cast<const uint64_t *>(P.part_acc + 2 * lane);
+            const uint64_t *pm = reinterpret_cast<const uint64_t *>(P.part_ml);
+            float M = -INFINITY, Lsum = 0.0f, A0 = 0.0f, A1 = 0.0f;
+            for (int i0 = first; i0 < nmerge; i0 += RN * kShare) {
+                const int left = (nmerge - i0 + kShare - 1) / kShare, nn = left < RN ? left : RN;
+                float mi = -INFINITY, li = 0.0f;
+                if (lane < nn) {
+                    const uint64_t ml = __hip_atomic_load(pm + slot_of(g, i0 + kShare * lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    mi = __uint_as_float((uint32_t)ml);
+                    li = __uint_as_float((uint32_t)(ml >> 32));
+                }
+                uint64_t av[RN];
 #pragma unroll
-            for (int k = 0; k < RN; ++k) {                       // (past the end: the last one, its factor is 0)
-                const int i = i0 + kShare * (k < nn ? k : nn - 1);
-                av[k] = k < nn ? __hip_atomic_load(pa + slot_of(g, i) * (SPARK_D / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
-            }
-            const float Mn = fmaxf(M, wave_max(mi));
-            const float Ms = (Mn == -INFINITY) ? 0.0f : Mn;
-            const float fo = fast_exp2(M - Ms), fi = fast_exp2(mi - Ms);
-            M = Mn;
-            Lsum = fmaf(Lsum, fo, wave_sum(li * fi));
-            A0 *= fo;
-            A1 *= fo;
+                for (int k = 0; k < RN; ++k) {                       // (past the end: the last one, its factor is 0)
+                    const int i = i0 + kShare * (k < nn ? k : nn - 1);
+                    av[k] = k < nn ? __hip_atomic_load(pa + slot_of(g, i) * (SPARK_D / 2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+                }
+                const float Mn = fmaxf(M, wave_max(mi));
+                const float Ms = (Mn == -INFINITY) ? 0.0f : Mn;
+                const float fo = fast_exp2(M - Ms), fi = fast_exp2(mi - Ms);
+                M = Mn;
+                Lsum = fmaf(Lsum, fo, wave_sum(li * fi));
+                A0 *= fo;
+                A1 *= fo;
 #pragma unroll
-            for (int k = 0; k < RN; ++k) {
-                const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fi), k));
-                A0 = fmaf(__uint_as_float((uint32_t)av[k]), f, A0);
-                A1 = fmaf(__uint_as_float((uint32_t)(av[k] >> 32)), f, A1);
+                for (int k = 0; k < RN; ++k) {
+                    const float f = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(fi), k));
+                    A0 = fmaf(__uint_as_float((uint32_t)av[k]), f, A0);
+                    A1 = fmaf(__uint_as_float((uint32_t)(av[k] >> 32)), f, A1);
+                }
             }
+            // (accumulators of the block's own wavefronts have been read by all: two barriers ago)
+            reinterpret_cast<float2 *>(area[wave])[hd * (SPARK_D / 2) + lane] = make_float2(A0, A1);
+            if (lane == 0) { red_m[wave][hd] = M; red_l[wave][hd] = Lsum; }
         }
-        // (accumulators of the block's own wavefronts have been read by all: two barriers ago)
-        reinterpret_cast<float2 *>(area[wave])[lane] = make_float2(A0, A1);
-        if (lane == 0) { red_m[wave][0] = M; red_l[wave][0] = Lsum; }
         __syncthreads();
-        if (tid < G * SPARK_D) {
-            const int gg = tid / SPARK_D, ch = tid % SPARK_D;
+        for (int idx = tid; idx < G * SPARK_D; idx += BW * 64) {
+            const int gg = idx / SPARK_D, ch = idx % SPARK_D, w0 = gg % BW, hd = gg / BW;
             float Mx = -INFINITY;
 #pragma unroll
-            for (int k = 0; k < kShare; ++k) Mx = fmaxf(Mx, red_m[gg + G * k][0]);
+            for (int k = 0; k < kShare; ++k) Mx = fmaxf(Mx, red_m[w0 + G * k][hd]);
             const float Ms = (Mx == -INFINITY) ? 0.0f : Mx;
             float Ls = 0.0f, A = 0.0f;
 #pragma unroll
             for (int k = 0; k < kShare; ++k) {
-                const float f = fast_exp2(red_m[gg + G * k][0] - Ms);
-                Ls = fmaf(red_l[gg + G * k][0], f, Ls);
-                A = fmaf(reinterpret_cast<const float *>(area[gg + G * k])[ch], f, A);
+                const float f = fast_exp2(red_m[w0 + G * k][hd] - Ms);
+                Ls = fmaf(red_l[w0 + G * k][hd], f, Ls);
+                A = fmaf(reinterpret_cast<const float *>(area[w0 + G * k])[hd * SPARK_D + ch], f, A);
             }
             store_out(gg, ch, A, Ls);
         }
@@ -447,13 +453,13 @@ __global__ __launch_bounds__(kShortWaves * 64, 4) void spark_decode_short_kernel
     if (P.trace != nullptr) { stamp(P, 4, wall_clock64()); stamp(P, 7, 1ull); }
 }
 
-template <int G>
+template <int G, int BW>
 static hipError_t launch_short(const DecodeParams &P, int nblocks, hipStream_t st)
 {
     if (P.L.int8)
-        hipLaunchKernelGGL((spark_decode_short_kernel<G, 1>), dim3(nblocks), dim3(kShortWaves * 64), 0, st, P);
+        hipLaunchKernelGGL((spark_decode_short_kernel<G, 1, BW>), dim3(nblocks), dim3(BW * 64), 0, st, P);
     else
-        hipLaunchKernelGGL((spark_decode_short_kernel<G, 0>), dim3(nblocks), dim3(kShortWaves * 64), 0, st, P);
+        hipLaunchKernelGGL((spark_decode_short_kernel<G, 0, BW>), dim3(nblocks), dim3(BW * 64), 0, st, P);
     return hipGetLastError();
 }
 

@@ -28,6 +28,8 @@ inline int counter_stride(int64_t pairs)
 }
 
 // How the decode grid cuts sequences into blocks (chosen on the host from the description alone).
+constexpr int kFineTailRows = 64;      // appended rows per block of DecodePlan::short_call = 2
+
 struct DecodePlan {
     int fixed_splits;   // > 0: every sequence is cut into this many chunks
     int chunk_tiles;    // else: a sequence spanning ntile tiles gets max(1, ceil(ntile / chunk_tiles)) chunks
@@ -37,7 +39,8 @@ struct DecodePlan {
     int warm_waves;     // > 0: the balanced mode may be used, with this many wavefronts per KV head; decode_form
                         // falls back to the chunked cut for the kernel variants that have no balanced form
     int counter_stride; // words between the arrival counters of two pairs
-    int short_call;     // 1: blocks of sixteen wavefronts (spark_decode_short.h); chosen by decode_form
+    int short_call;     // blocks of 1: sixteen 2: four wavefronts of spark_decode_short.h; 1 is chosen by decode_form, 2 is the
+                        // plan of a call whose workspace has room for a partial per tile
     int chunk_ids;      // chunk ids the workspace has partial slots for: all of a cut by length, and of the balanced
                         // mode, warm_waves + 2 * batch - 1; the appended rows' slots follow at chunk_ids * Hq
 };
