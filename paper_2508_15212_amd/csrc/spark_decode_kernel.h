@@ -174,6 +174,22 @@ __device__ __forceinline__ int wave_inclusive_sum_i32(int v)
 struct SeqChunks { int b, first, n, s0, s1; };   // sequence, global id of its first chunk, number of its chunks
                                                   // (0: none), its token range
 
+// A wavefront's priority follows what it still has to do: `left` of the `all` items of a full share.  Of the two wavefronts of a
+// SIMD the older one is served first, so that of two blocks on a compute unit with equal shares one was done early and the other
+// then ran alone, at half the rate (one wavefront gets an instruction in about 6.5 cycles): half of the blocks of 2 x 16001 tokens,
+// sampled, ended at 27 us and half at 37 us; with this, at 32 to 36.  Llama heads: 12001 to 18777 tokens, packed values 34.7 -> 31.9 us,
+// 2 x 16001 sampled 40.9 -> 38.6, 2 x 32768 top-p 45.9 -> 45.3, 8 x 32768 110.2 -> 109.1, 64 of 512 to 2048 54.2 -> 52.4, 4 x 131072, G = 8,
+// int8 codes 213.2 -> 207.7.  Tried: two levels instead of four (values 33.5), a change in the middle of a tile (sampled 40.5 instead of
+// 39.4), high for the products and low for the scores instead (values 33.0).
+__device__ __forceinline__ void set_priority(int left, int all)
+{
+    const int level = (4 * left - 1) / all;      // (wave-uniform)
+    if (level >= 3) __builtin_amdgcn_s_setprio(3);
+    else if (level == 2) __builtin_amdgcn_s_setprio(2);
+    else if (level == 1) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
 // Finds the sequence that owns global chunk `gid` (want_b < 0) or describes sequence `want_b`.  Every lane of
 // the wavefront calls it with the same arguments and gets the same answer: 64 sequences are sized per step
 // (lane = sequence) and a wave prefix sum numbers their chunks.
@@ -691,6 +707,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     // (requested before the sequence table is read: one memory round trip less before the appended rows' own)
     const int tail_rows = is_tail ? P.tail_len[(tb / P.ntail) / P.Hkv] : 0;
     if (is_tail) {
+        __builtin_amdgcn_s_setprio(3);           // (they wait for memory about once: ahead of the blocks that stream)
         static_assert(WBUF >= G * SPARK_D * 4, "LDS reuse");
         tail_partial<G>(P, (tb / P.ntail) / P.Hkv, h, tb % P.ntail, tail_rows, red_m, red_l, reinterpret_cast<float *>(&wbuf[0][0]));
     }
@@ -1458,6 +1475,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
             item = (int)(((uint32_t)wid * (uint32_t)total) / (uint32_t)nwe);
             item_end = (int)((((uint32_t)wid + 1u) * (uint32_t)total) / (uint32_t)nwe);
         }
+        const int n_items = max(item_end - item, 1);
         float *const red = reinterpret_cast<float *>(wbuf[wave]);              // [G][128] staging of the accumulators
 
         // query table {q_g[j] * scale * log2e, 1/a[j]} and R_g of a sequence, built by this wavefront alone.  The
@@ -1645,6 +1663,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
                 WarmSeq nxt = cur;
                 if (newseq) nxt = warm_find(W, item);
                 const int tnext = newseq ? nxt.s0 / SPARK_TILE_TOKENS : tile + 1;
+                set_priority(item_end - item + 1, n_items);      // (item: the next one)
                 process(tile, -1);
                 if (!more) break;
                 s0 = nxt.s0;
@@ -1821,7 +1840,9 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         else
             walk_limit = SPARK_D;
     }
+    const int full_share = max(nts, P.chunk_tiles);
     for (; kidx < nts; kidx += kDecodeWaves) {
+        if (nts > kDecodeWaves) set_priority(nts - (kidx - wave), full_share);
         tile = tile_of(kidx);
         const bool more = kidx + kDecodeWaves < nts;            // wave-uniform
         const int tnext = tile_of(more ? kidx + kDecodeWaves : kidx);
