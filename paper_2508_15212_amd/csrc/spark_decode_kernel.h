@@ -33,6 +33,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 #include "spark_kernels.h"
 #include "spark_layout.h"
 
@@ -173,6 +176,13 @@ __device__ __forceinline__ int wave_inclusive_sum_i32(int v)
 
 struct SeqChunks { int b, first, n, s0, s1; };   // sequence, global id of its first chunk, number of its chunks
                                                   // (0: none), its token range
+
+// f(0), f(2), f(4), ..: the arguments as types
+template <typename F, int... I>
+__device__ __forceinline__ void for_pairs(F f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, 2 * I>()), ...);
+}
 
 // A wavefront's priority follows what it still has to do: `left` of the `all` items of a full share.  Of the two wavefronts of a
 // SIMD the older one is served first, so that of two blocks on a compute unit with equal shares one was done early and the other
@@ -657,7 +667,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     constexpr int NQ_CT = NDW_CT / 4;
 
     __shared__ __align__(16) float qtab[(WARM ? kDecodeWaves : 1) * SPARK_D * GP];   // (balanced mode: one per wavefront)
-    __shared__ __align__(16) float qa[REC ? SPARK_D * G : 1];      // sampled recovery: q_g[j] * scale * log2e / a[j]
+    constexpr int GQ = G < 4 ? G : 4;
+    __shared__ __align__(16) float qa[REC ? SPARK_D * G : 1];      // sampled recovery: q_g[j] * scale * log2e / a[j], [heads by GQ][j][GQ]
     __shared__ float Rsh[16];
     __shared__ __align__(16) uint16_t Pbuf[kDecodeWaves][2][G][64];
     // per wavefront: the accumulators at the end; with packed values, before that, the parked value rows
@@ -1289,13 +1300,36 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
 #pragma unroll
             for (int wd = 0; wd < 4; ++wd) {
                 uint32_t pruned = ~r[wd];
-                float part[G];           // (summed by quarters of the row: smaller rounding errors)
+                // (summed by quarters of the row: smaller rounding errors)
+                typedef float part_t __attribute__((ext_vector_type(GQ)));
+                part_t part[G / GQ];
 #pragma unroll
-                for (int g = 0; g < G; ++g) part[g] = 0.0f;
+                for (int i = 0; i < G / GQ; ++i) part[i] = part_t(0.0f);
 #pragma unroll 1
-                for (int c0 = 0; c0 < 32; c0 += 8) {
+                for (int c0 = 0; c0 < 32; c0 += 16) {
+                    // Four query heads and more: the products with q / a and their sums go through the matrix unit's float32
+                    // product of 4 x 4 blocks, one row a query head, one column a token, one channel at a time (an exact
+                    // multiply-add): a quarter of the instructions, and a lane holds the factors of a channel and a query head
+                    // where the table would be read for every pair.  2 x 16001 tokens, G = 4 / 8 / 16: 38.4 / 51.2 / 82.4 -> 38.1 /
+                    // 47.0 / 66.3 us; 1000 tokens, G = 4: 16.8 -> 16.0; G = 1 / 2: 32.9 / 34.8 -> 34.9 / 36.0, which therefore multiply.
+                    float A[G / GQ];         // lane 4 c + g: query head g of four, channel c of these sixteen
+                    if constexpr (G >= 4) {
 #pragma unroll
-                    for (int c = 0; c < 8; c += 2) {
+                        for (int i = 0; i < G / GQ; ++i) A[i] = qa[(i * SPARK_D + 32 * wd + c0) * GQ + lane];
+                    }
+                    auto add = [&](auto c, float t) __attribute__((always_inline)) {
+#pragma unroll
+                        for (int i = 0; i < G / GQ; ++i) {
+                            if constexpr (G >= 4) {
+                                part[i] = __builtin_amdgcn_mfma_f32_4x4x1f32(A[i], t, part[i], 4, decltype(c)::value, 0);
+                            } else {
+#pragma unroll
+                                for (int g = 0; g < G; ++g) part[0][g] = fmaf(qa[(32 * wd + c0 + decltype(c)::value) * G + g], t, part[0][g]);
+                            }
+                        }
+                    };
+                    for_pairs([&](auto c_) __attribute__((always_inline)) {
+                        constexpr int c = decltype(c_)::value;
                         const int j = 32 * wd + c0 + c;
                         const float u1 = unif((uint32_t)j), u2 = unif((uint32_t)j + 1u);
                         float w0, w1;
@@ -1313,13 +1347,13 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
                         asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m0) : "v"(pruned), "n"(c));
                         asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m1) : "v"(pruned), "n"(c + 1));
                         const float t0 = __uint_as_float(__float_as_uint(w0) & m0), t1 = __uint_as_float(__float_as_uint(w1) & m1);
-#pragma unroll
-                        for (int g = 0; g < G; ++g) part[g] = fmaf(qa[(j + 1) * G + g], t1, fmaf(qa[j * G + g], t0, part[g]));
-                    }
-                    pruned >>= 8;
+                        add(std::integral_constant<int, c>(), t0);
+                        add(std::integral_constant<int, c + 1>(), t1);
+                    }, std::make_integer_sequence<int, 8>());
+                    pruned >>= 16;
                 }
 #pragma unroll
-                for (int g = 0; g < G; ++g) s[g] += part[g];
+                for (int g = 0; g < G; ++g) s[g] += part[g / GQ][g % GQ];
             }
         }
 #pragma unroll
@@ -1814,7 +1848,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             qt[j * GP + g] = bf16lo(q_r[g]) * q_scale;
-            if constexpr (REC != 0) qa[j * G + g] = bf16lo(q_r[g]) * P.scale_log2 * inva_r;
+            if constexpr (REC != 0) qa[((g / GQ) * SPARK_D + j) * GQ + g % GQ] = bf16lo(q_r[g]) * P.scale_log2 * inva_r;
         }
         qt[j * GP + G] = inva_r;
 #pragma unroll
