@@ -193,10 +193,9 @@ __device__ __forceinline__ void for_pairs(F f, std::integer_sequence<int, I...>)
 // 39.4), high for the products and low for the scores instead (values 33.0).
 __device__ __forceinline__ void set_priority(int left, int all)
 {
-    const int level = (4 * left - 1) / all;      // (wave-uniform)
-    if (level >= 3) __builtin_amdgcn_s_setprio(3);
-    else if (level == 2) __builtin_amdgcn_s_setprio(2);
-    else if (level == 1) __builtin_amdgcn_s_setprio(1);
+    if (4 * left > 3 * all) __builtin_amdgcn_s_setprio(3);      // (wave-uniform)
+    else if (4 * left > 2 * all) __builtin_amdgcn_s_setprio(2);
+    else if (4 * left > all) __builtin_amdgcn_s_setprio(1);
     else __builtin_amdgcn_s_setprio(0);
 }
 
@@ -1803,6 +1802,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     int tile = tile_of(kidx);
     // The query and 1/a are requested before the first tile: loads return in order, so the table can be built
     // while the tile is still on its way.
+    if (nts > kDecodeWaves) set_priority(nts, max(nts, P.chunk_tiles));
     float inva_r = 0.0f;
     uint16_t q_r[G];
     if (tid < SPARK_D) {
@@ -1876,14 +1876,15 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         else
             walk_limit = SPARK_D;
     }
-    const int full_share = max(nts, P.chunk_tiles);
     for (; kidx < nts; kidx += kDecodeWaves) {
-        if (nts > kDecodeWaves) set_priority(nts - (kidx - wave), full_share);
         tile = tile_of(kidx);
         const bool more = kidx + kDecodeWaves < nts;            // wave-uniform
         const int tnext = tile_of(more ? kidx + kDecodeWaves : kidx);
         process(tile, more ? tnext : -1);
-        if (more && !PV) prefetch(tnext);   // request the next tile; its latency is covered by the other resident wavefronts
+        if (more) {
+            if (!PV) prefetch(tnext);   // request the next tile; its latency is covered by the other resident wavefronts
+            set_priority(nts - (kidx + kDecodeWaves - wave), max(nts, P.chunk_tiles));
+        }
     }
 
     if (P.trace != nullptr) stamp(P, 2, wall_clock64());
