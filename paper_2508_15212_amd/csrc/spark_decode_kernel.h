@@ -1272,11 +1272,12 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
         if constexpr (REC != 0) {
             // ---- sampled recovery: every pruned entry j adds q_gj * w~_j / a_j
-            // Bound by vector issue: a Gaussian pair of channels is 39 instructions, eight of them at a quarter of the
-            // rate (four 32-bit products of the generator, logarithm, root, sine, cosine), and kept channels'
+            // Bound by vector issue: a Gaussian pair of channels takes 126 cycles of its SIMD at G = 4 (42 in two-cycle, 50 in
+            // four-cycle instructions, 34 in logarithm, root, sine and cosine at eight), and kept channels'
             // variates are drawn and masked off.  2 x 16001 tokens, Llama heads, T = 26: 58.7 us with the library's
             // square root, integer conversions, a branch per channel and four table reads a pair; 44.0 us with a
-            // reciprocal root and a Newton step instead of the root and a shift of the mask per pair; 41.6 us like this.
+            // reciprocal root and a Newton step instead of the root and a shift of the mask per pair; 41.6 us like this, 38.4
+            // with counters apart and priorities by what is left.
             constexpr uint32_t kGold = 0x9E3779B9u;
             auto mix = [](uint32_t x) {
                 x ^= x >> 16; x *= 0x85EBCA6Bu; x ^= x >> 13; x *= 0xC2B2AE35u; x ^= x >> 16;
