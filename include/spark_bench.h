@@ -44,12 +44,17 @@ spark_status spark_decode_timeline(void *device_buffer, size_t bytes);
  *   SPARK_CALL_DECODE       spark_decode_attn:  1: chunks, blocks of four wavefronts (of four tiles or more, or, in short calls
  *                           whose workspace has room, of one)   2: chunks, blocks of sixteen   3: the balanced cut
  *   SPARK_CALL_DECODE_TAIL  spark_decode_attn_tail, the same
+ *   SPARK_CALL_DECODE_TILES, SPARK_CALL_DECODE_TAIL_TILES  of the same two calls with the whole workspace, the tiles of a block where
+ *                           sequences are cut by their length (more where that would make too many blocks): 1 is a block per
+ *                           tile, four or more the other two forms; 0 with a given number of splits and in the balanced cut
  * 0 for an invalid description, another call, or a call that launches nothing.
  */
 #define SPARK_CALL_PRUNE 0
 #define SPARK_CALL_PRUNE_TOPP 1
 #define SPARK_CALL_DECODE 2
 #define SPARK_CALL_DECODE_TAIL 3
+#define SPARK_CALL_DECODE_TILES 4
+#define SPARK_CALL_DECODE_TAIL_TILES 5
 int32_t spark_call_form(const spark_desc *desc, int32_t call);
 
 #ifdef __cplusplus

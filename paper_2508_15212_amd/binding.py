@@ -25,7 +25,7 @@ EXPORTS = ["spark_packed_bytes", "spark_prune_workspace", "spark_decode_workspac
            "spark_decode_attn_values_tail", "spark_decode_attn_sampled", "spark_unpack_stats", "spark_check_packed",
            "spark_decode_attn_static", "spark_packed_topp_bytes", "spark_prune_topp", "spark_decode_attn_topp",
            "spark_unpack_topp", "spark_decode_timeline", "spark_call_form"]
-CALL_PRUNE, CALL_PRUNE_TOPP, CALL_DECODE, CALL_DECODE_TAIL = 0, 1, 2, 3
+CALL_PRUNE, CALL_PRUNE_TOPP, CALL_DECODE, CALL_DECODE_TAIL, CALL_DECODE_TILES, CALL_DECODE_TAIL_TILES = 0, 1, 2, 3, 4, 5
 
 
 class SparkError(RuntimeError):

@@ -516,10 +516,13 @@ int32_t spark_call_form(const spark_desc *desc, int32_t call)
     spark_status why;
     if (!desc_ok(desc, &why)) return 0;
     if (call == SPARK_CALL_PRUNE) return spark::prune_launches(layout_of(desc), desc->n_q_heads, desc->window);
-    if (call == SPARK_CALL_DECODE || call == SPARK_CALL_DECODE_TAIL) {
+    const bool tiles = call == SPARK_CALL_DECODE_TILES || call == SPARK_CALL_DECODE_TAIL_TILES;
+    if (call == SPARK_CALL_DECODE || call == SPARK_CALL_DECODE_TAIL || tiles) {
+        const bool with_tail = call == SPARK_CALL_DECODE_TAIL || call == SPARK_CALL_DECODE_TAIL_TILES;
         spark::DecodePlan cut = plan_of(desc);
-        fine_plan(desc, cut, call == SPARK_CALL_DECODE_TAIL);
-        const spark::DecodePlan p = spark::decode_form(cut, layout_of(desc), desc->n_q_heads, true, call == SPARK_CALL_DECODE ? 0 : cut.tail_slots);
+        fine_plan(desc, cut, with_tail);
+        const spark::DecodePlan p = spark::decode_form(cut, layout_of(desc), desc->n_q_heads, true, with_tail ? cut.tail_slots : 0);
+        if (tiles) return p.warm_waves > 0 || p.fixed_splits > 0 ? 0 : p.chunk_tiles;
         return p.warm_waves > 0 ? 3 : (p.short_call == 1 ? 2 : 1);      // (a block per tile: blocks of four wavefronts)
     }
     if (call == SPARK_CALL_PRUNE_TOPP) return spark::topp_prune_launches(topp_layout_of(desc));

@@ -273,3 +273,16 @@ def test_blocks_of_sixteen_wavefronts_only_where_they_were_measured_faster():
         assert form(G, 30, (8192,)) == 2 and form(G, 30, (65536,), 2) == 2 and form(G, 90, (1024,)) == 2 and form(G, 90, (16384,)) == 1
         assert form(G, 26, (8192,)) == 1
     assert form(8, 30, (100,)) == 2 and form(8, 26, (8192,)) == 2 and form(8, 64, (16384,)) == 1 and form(8, 26, (16384,)) == 2
+
+
+def _tiles(lens, tail=False, G=4, hkv=8, **kw):
+    """Tiles of a block of the decode call: 1 is a block per tile."""
+    d = _desc(n_q_heads=G * hkv, n_kv_heads=hkv, batch=len(lens), total_tokens=sum(lens), **kw)
+    return spark.call_form(d, spark.CALL_DECODE_TAIL_TILES if tail else spark.CALL_DECODE_TILES)
+
+
+def test_the_block_per_tile_can_be_told_from_blocks_of_four():
+    assert _tiles((1024,), keep=64) == 1 and _tiles((1024,), keep=64, tail=True, tail_capacity=64) == 1
+    assert _tiles((1024,), keep=64, tail=True, tail_capacity=1 << 14) == 4      # (256 blocks of appended rows a KV head)
+    assert _tiles((1024,), keep=64, G=16) == 4
+    assert _tiles((32768,) * 8) == 64 and _tiles((1024,), keep=64, n_splits=2) == 0 and _tiles((1300,) * 64) == 0
