@@ -157,7 +157,7 @@ bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
     if (tiles == 0 || d->batch > 64 || d->n_splits != 0 || p.warm_waves > 0 || G > 8) return false;
     const bool short_rows = d->keep < 30;
     const int64_t longest = short_rows ? (G <= 2 ? 32 : (G == 4 ? 20 : 0)) : (G == 1 ? 64 : (G == 2 ? 48 : (G == 4 ? 32 : 24)));
-    if (per_sequence > longest || blocks > (short_rows || G == 8 ? 320 : 720) + (with_tail ? 128 : 0)) return false;
+    if (longest == 0 || per_sequence > longest || blocks > (short_rows || G == 8 ? 320 : 720) + (with_tail ? 128 : 0)) return false;
     if (spark::decode_form(p, layout_of(d), d->n_q_heads, true, with_tail ? p.tail_slots : 0).short_call != 0) return false;
     p.short_call = 2;
     p.chunk_tiles = 1;

@@ -285,4 +285,6 @@ def test_the_block_per_tile_can_be_told_from_blocks_of_four():
     assert _tiles((1024,), keep=64) == 1 and _tiles((1024,), keep=64, tail=True, tail_capacity=64) == 1
     assert _tiles((1024,), keep=64, tail=True, tail_capacity=1 << 14) == 4      # (256 blocks of appended rows a KV head)
     assert _tiles((1024,), keep=64, G=16) == 4
+    # (eight query heads with short rows never: also where there are fewer tiles than sequences)
+    assert _tiles((3,) * 11 + (1, 1, 0), keep=26, G=8) == 4 and _tiles((1024,), keep=26, G=8) == 4
     assert _tiles((32768,) * 8) == 64 and _tiles((1024,), keep=64, n_splits=2) == 0 and _tiles((1300,) * 64) == 0
