@@ -163,7 +163,7 @@ bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
     p.chunk_tiles = 1;
     p.chunk_limit = 0;
     p.nchunk_max = p.chunk_ids = (int)(tiles + d->batch - 1);      // (see plan_of)
-    p.tail_slots = tail_slots;
+    p.tail_slots = with_tail ? tail_slots : 0;
     return true;
 }
 
@@ -183,8 +183,8 @@ int pick_splits(const spark_desc *d)
     }
 }
 
-// partial slots in the workspace: one per (chunk, q head), then the appended rows' (one per 256 rows of
-// capacity, at least one, per (batch, q head), so a workspace serves calls with and without appended rows)
+// partial slots in the workspace: one per (chunk, q head), then the appended rows' (per (batch, q head): one per 256 rows of
+// capacity, at least one, so a workspace serves calls with and without appended rows; with a block per tile one per 64 rows, or none)
 size_t partial_slots(const spark_desc *d, const spark::DecodePlan &p)
 {
     return (size_t)p.chunk_ids * d->n_q_heads + (size_t)d->batch * d->n_q_heads * p.tail_slots;

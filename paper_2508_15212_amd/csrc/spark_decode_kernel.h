@@ -80,7 +80,7 @@ struct DecodeParams {
     int warm_waves;
     int short_call;          // blocks of 1: sixteen 2: four wavefronts of spark_decode_short.h
     int ntail;               // blocks per (batch, KV head) for the appended rows, 256 rows each (short_call 2: 64; 0: none)
-    int tail_slots;          // slots reserved per (batch, q head) for them (>= max(1, ntail))
+    int tail_slots;          // slots reserved per (batch, q head) for them (>= ntail)
     int64_t tail_base;       // first of them: the number of chunk ids the workspace provides for, times Hq
     const uint16_t *tail_k, *tail_v;   // appended never-pruned rows [B, tail_cap, Hkv, 128] bf16, or NULL
     const int32_t *tail_len;           // [B]

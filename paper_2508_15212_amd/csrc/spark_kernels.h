@@ -35,7 +35,7 @@ struct DecodePlan {
     int chunk_tiles;    // else: a sequence spanning ntile tiles gets max(1, ceil(ntile / chunk_tiles)) chunks
     int chunk_limit;    // > 0: chunks are made longer until the batch has at most this many (up to 64 sequences, and not fewer)
     int nchunk_max;     // upper bound on the number of chunks in the batch (grid = nchunk_max * Hkv + tail blocks)
-    int tail_slots;     // partial slots reserved per (batch, q head) for appended rows
+    int tail_slots;     // partial slots reserved per (batch, q head) for appended rows (none in a block-per-tile plan without them)
     int warm_waves;     // > 0: the balanced mode may be used, with this many wavefronts per KV head; decode_form
                         // falls back to the chunked cut for the kernel variants that have no balanced form
     int counter_stride; // words between the arrival counters of two pairs

@@ -288,3 +288,18 @@ def test_the_block_per_tile_can_be_told_from_blocks_of_four():
     # (eight query heads with short rows never: also where there are fewer tiles than sequences)
     assert _tiles((3,) * 11 + (1, 1, 0), keep=26, G=8) == 4 and _tiles((1024,), keep=26, G=8) == 4
     assert _tiles((32768,) * 8) == 64 and _tiles((1024,), keep=64, n_splits=2) == 0 and _tiles((1300,) * 64) == 0
+
+
+def test_room_for_appended_rows_is_what_calls_with_appended_rows_use():
+    """Sixteen sequences of 256 tokens take a block per tile without appended rows, and blocks of four with many: their workspace
+    has slots for 256 appended rows each, as those blocks take them, not for 64."""
+    slot = 130 * 4
+    for capacity in (4096, 32768):
+        kw = dict(batch=16, total_tokens=16 * 256, keep=64, tail_capacity=capacity)
+        assert spark.call_form(_desc(**kw), spark.CALL_DECODE_TAIL_TILES) == 4
+        # (chunks: at most (64 tiles + 2 * 16) // 4 + 16 + 1)
+        assert spark.decode_workspace_bytes(_desc(**kw)) == (41 * 32 + 16 * 32 * (capacity // 256)) * slot + 16 * 8 * 4
+    # with few: slots for 64 rows each, and as many chunks as tiles that two sequences can span, and one
+    kw = dict(batch=2, total_tokens=2 * 1024, keep=64, tail_capacity=256)
+    assert spark.call_form(_desc(**kw), spark.CALL_DECODE_TAIL_TILES) == 1
+    assert spark.decode_workspace_bytes(_desc(**kw)) == ((32 + 2) * 32 + 2 * 32 * 4) * slot + 256
