@@ -94,8 +94,10 @@ typedef struct spark_desc {
                                  knows it (the lengths themselves are on the device), 0 where not.  With
                                  n_splits = 0 a batch whose longest sequence is within 9/8 of the average is
                                  balanced as it is and keeps one block per sequence, which is 3 to 5 %
-                                 cheaper there than the balanced cut.  Never affects results; enters the
-                                 workspace size like n_splits. */
+                                 cheaper there than the balanced cut; and a short call takes a block per tile
+                                 (up to a quarter faster) while no sequence has too many to merge, for
+                                 which without the hint one sequence may have all tokens.  Affects results in
+                                 their last bits at most; enters the workspace size like n_splits. */
 } spark_desc;
 
 /* Size in bytes of the packed key cache for this description (depends on batch, n_kv_heads,

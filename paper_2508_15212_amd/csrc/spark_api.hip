@@ -4,6 +4,7 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "../../include/spark.h"
@@ -132,38 +133,64 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 // A block of four wavefronts for every tile, four lanes a row (plan.short_call = 2, spark_decode_short.h): short calls whose
 // workspace has room for a partial per tile.  Four tiles in a block keep to a quarter of the compute units, each bound by the
 // table gathers in its LDS; a tile a block spreads them, for four times the partials, which the last block of a pair merges.  So it
-// gains until that merge is the longer: the more query heads, the fewer tiles a sequence.  Only where blocks of four wavefronts
-// would take four tiles each.  Time against those, eight KV heads (tiles a sequence, tiles over all heads):
-//                                  G = 1, T = 26 / 32 / 64    G = 2                 G = 4                 G = 8, T = 26 / 64
-//   1 x 500              8    62     0.98 / 0.81 / 0.83      0.98 / 0.80 / 0.83    0.99 / 0.81 / 0.80    1.02 / 0.85
-//   1 x 1024            16   128     0.97 / 0.76 / 0.81      0.96 / 0.79 / 0.84    0.97 / 0.78 / 0.85    0.99 / 0.87
-//   1 x 1500            23   188     1.01 / 0.80 / 0.84      0.99 / 0.82 / 0.85    1.01 / 0.85 / 0.87    1.07 / 0.92
-//   1 x 2048            32   256     0.94 / 0.77 / 0.83      0.95 / 0.79 / 0.84    0.99 / 0.83 / 0.88    1.08 / 0.97
-//   1 x 3000            47   375     0.97 / 0.83 / 0.86      1.01 / 0.88 / 0.93    1.16 / 1.00 / 1.04    1.31 / 1.16
-//   1 x 4096            64   512     0.94 / 0.87 / 0.86                            1.20 / 1.03 / 1.11    1.38 / 1.25
-//   2 x 500 to 1500     15   237     0.92 / 0.79 / 0.80      0.92 / 0.79 / 0.82    0.92 / 0.80 / 0.82    1.01 / 0.87
-//   4 x 300 to 800       9   276     0.95 / 0.82 / 0.84      0.96 / 0.83 / 0.87    0.99 / 0.83 / 0.86    1.00 / 0.89
-//   the same, 256 appended rows      0.98 / 0.84 / 0.86      0.98 / 0.84 / 0.88    0.99 / 0.86 / 0.90    1.04 / 0.93
-//   8 x 300 to 800      10   635     0.99 / 0.85 / 0.89      1.02 / 0.90 / 0.95    1.06 / 0.93 / 0.98    1.14 / 1.06
-//   16 x 100 to 300      3   426     1.05 / 0.88 / 0.93      1.07 / 0.90 / 0.99    1.09 / 0.94 / 1.00    1.14 / 1.04
-//   32 x 100 to 300      3   814     1.24 / 1.03 / 1.08                            1.24 / 1.11 / 1.09    1.27 / 1.15
-// 1024 tokens, G = 4, T = 64: 11.4 -> 9.7 us; T = 32: 11.6 -> 9.1; int8 codes the same within 2 %.
+// gains where blocks of four wavefronts would take four tiles each, and
+//   - until the merge of ONE sequence's partials is the longer: the more query heads, the fewer tiles.  The lengths are on the device:
+//     the longest sequence can have all tiles of the batch unless max_seqlen says less.  (5000 and three times 100 tokens, G = 4,
+//     T = 64: 1.42; one KV head, 40000 and 21 times 200 tokens: 58.9 instead of 22.2 us);
+//   - from sequences of 240 tokens on average: up to four tiles are one block of the other form, and nothing is merged there (with
+//     appended rows both merge);
+//   - while there are few blocks: rows of a length that has a kernel of its own are walked fast enough there that a second block on a
+//     compute unit costs the gain, rows of any length are not (up to 512 or 704 blocks).
+// Rows of 25, 26 (bf16) and 38 kept channels (one or eight query heads) gain nothing anywhere; eight query heads with rows of any
+// length are taken by blocks of sixteen wavefronts.  Time against blocks of four tiles (graphs of 40 to 160 calls; the larger of the
+// ratios with caches in the L2 and with ones that rotate through 400 MB), tiles of the batch, sequences (s: the first has 80 % of them):
+//   KV heads     G = 1, T = 26 / 32 / 38 / 48 / 64    G = 2                              G = 4                              G = 8, T = 26 / 38 / 64
+//   8   3 in 1   1.42 / 1.07 / 1.35 / 0.97 / 1.19   1.37 / 1.06 / 1.31 / 0.95 / 1.13   1.26 / 1.01 / 1.21 / 0.93 / 1.08   1.32 / 1.28 / 1.13
+//   8   8 in 4   1.40 / 1.07 / 1.33 / 0.97 / 1.18   1.35 / 1.04 / 1.29 / 0.93 / 1.13   1.25 / 0.99 / 1.19 / 0.91 / 1.06   1.30 / 1.26 / 1.12
+//   8   8 in 1   1.03 / 0.85 / 1.04 / 0.78 / 0.93   0.99 / 0.81 / 0.97 / 0.75 / 0.87   1.01 / 0.82 / 0.95 / 0.77 / 0.88   1.00 / 0.99 / 0.89
+//   8  20 in 1   1.01 / 0.85 / 1.03 / 0.78 / 0.92   1.01 / 0.84 / 0.98 / 0.78 / 0.89   1.04 / 0.88 / 1.01 / 0.81 / 0.93   1.08 / 1.08 / 0.98
+//   8  32 in 1   1.04 / 0.86 / 1.05 / 0.80 / 0.94   1.04 / 0.86 / 1.01 / 0.80 / 0.93   1.11 / 0.93 / 1.08 / 0.87 / 0.98   1.20 / 1.20 / 1.09
+//   8  40 in 1   1.07 / 0.91 / 1.10 / 0.85 / 1.00   1.08 / 0.92 / 1.07 / 0.87 / 1.00   1.25 / 1.07 / 1.22 / 1.00 / 1.12   1.38 / 1.36 / 1.24
+//   8  64 in 1   1.09 / 1.00 / 1.10 / 1.01 / 1.01   1.14 / 0.97 / 1.13 / 0.91 / 1.05   1.39 / 1.18 / 1.33 / 1.00 / 1.24   1.54 / 1.51 / 1.39
+//   8  32 in 4   1.08 / 0.91 / 1.11 / 0.86 / 1.02   1.06 / 0.87 / 1.04 / 0.83 / 0.97   1.07 / 0.90 / 1.04 / 0.84 / 0.97   1.09 / 1.09 / 0.99
+//   8  64 in 8   1.15 / 0.97 / 1.15 / 1.00 / 1.07   1.14 / 0.97 / 1.14 / 0.95 / 1.08   1.18 / 1.02 / 1.17 / 1.00 / 1.11   1.26 / 1.27 / 1.19
+//   8  64 in 4s  1.09 / 0.92 / 1.11 / 1.00 / 1.03   1.11 / 0.94 / 1.10 / 0.93 / 1.07   1.29 / 1.10 / 1.24 / 1.00 / 1.20   1.42 / 1.40 / 1.31
+//   16 32 in 4   1.13 / 0.96 / 1.14 / 1.00 / 1.04   1.10 / 0.94 / 1.09 / 0.90 / 1.07   1.16 / 0.99 / 1.12 / 1.00 / 1.09   1.22 / 1.20 / 1.14
+//   2  32 in 1   1.02 / 0.85 / 1.05 / 0.80 / 0.95   1.02 / 0.83 / 1.00 / 0.79 / 0.91   1.08 / 0.89 / 1.05 / 0.83 / 0.97   1.15 / 1.12 / 1.02
+//   2  64 in 1   1.00 / 0.82 / 0.99 / 0.79 / 0.93   1.03 / 0.84 / 1.00 / 0.80 / 0.94   1.23 / 1.03 / 1.20 / 0.96 / 1.10   1.37 / 1.35 / 1.25
+//   2  90 in 1   1.01 / 0.84 / 1.01 / 0.79 / 0.95   1.15 / 0.95 / 1.13 / 0.90 / 1.06   1.38 / 1.16 / 1.33 / 1.08 / 1.24   1.58 / 1.55 / 1.43
+//   2  64 in 8   0.97 / 0.81 / 0.99 / 0.76 / 0.91   0.95 / 0.77 / 0.92 / 0.73 / 0.86   0.95 / 0.80 / 0.93 / 0.74 / 0.86   0.97 / 0.97 / 0.88
+// Of 2680 such measurements that the rule takes without max_seqlen (1, 2, 4, 8 and 16 KV heads, T = 20 to 64) the worst is 1.015 and the
+// mean 0.86, with max_seqlen 1.03 (two sequences of 32 tiles, four KV heads, G = 4) and 0.86; with 200 appended rows 0.88, int8 codes 0.88.
 bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
-    const int64_t tiles = (d->total_tokens + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS, per_sequence = tiles / d->batch;
-    const int tail_slots = d->tail_capacity > 0 ? (d->tail_capacity + spark::kFineTailRows - 1) / spark::kFineTailRows : 1;
-    const int64_t blocks = (tiles + d->batch * (1 + (with_tail ? (int64_t)tail_slots : 0))) * d->n_kv_heads;
+    const int64_t tiles = (d->total_tokens + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS;
     if (tiles == 0 || d->batch > 64 || d->n_splits != 0 || p.warm_waves > 0 || G > 8) return false;
-    const bool short_rows = d->keep < 30;
-    const int64_t longest = short_rows ? (G <= 2 ? 32 : (G == 4 ? 20 : 0)) : (G == 1 ? 64 : (G == 2 ? 48 : (G == 4 ? 32 : 24)));
-    if (longest == 0 || per_sequence > longest || blocks > (short_rows || G == 8 ? 320 : 720) + (with_tail ? 128 : 0)) return false;
-    if (spark::decode_form(p, layout_of(d), d->n_q_heads, true, with_tail ? p.tail_slots : 0).short_call != 0) return false;
+    const SparkLayout L = layout_of(d);
+    int longest = 0, blocks = 0;         // tiles of one sequence, blocks of the cache
+    if (!spark::row_length_instantiated(L)) {
+        longest = G == 1 ? 96 : (G == 2 ? 64 : (G == 4 ? 36 : 0));
+        blocks = G <= 2 ? 704 : 512;
+    } else if (L.T == 64) {
+        longest = G == 1 ? 96 : (G == 2 ? 56 : (G == 4 ? 28 : 20));
+        blocks = G <= 2 ? 264 : 256;
+    } else if (L.T == 38) {
+        longest = G == 2 ? 48 : (G == 4 ? 20 : 0);
+        blocks = 256;
+    }
+    if (longest == 0 || (!with_tail && d->total_tokens < 240 * (int64_t)d->batch)) return false;
+    const int tail_slots = !with_tail ? 0 : (d->tail_capacity > 0 ? (d->tail_capacity + spark::kFineTailRows - 1) / spark::kFineTailRows : 1);
+    int64_t most = tiles;                // (a sequence can begin and end inside a tile)
+    if (d->max_seqlen > 0) most = std::min(most, ((int64_t)d->max_seqlen + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS + 1);
+    if (most + tail_slots > longest || (tiles + d->batch) * d->n_kv_heads > blocks) return false;
+    if ((tiles + d->batch * (1 + (int64_t)tail_slots)) * d->n_kv_heads > 848) return false;
+    if (spark::decode_form(p, L, d->n_q_heads, true, with_tail ? p.tail_slots : 0).short_call != 0) return false;
     p.short_call = 2;
     p.chunk_tiles = 1;
     p.chunk_limit = 0;
     p.nchunk_max = p.chunk_ids = (int)(tiles + d->batch - 1);      // (see plan_of)
-    p.tail_slots = with_tail ? tail_slots : 0;
+    p.tail_slots = tail_slots;
     return true;
 }
 

@@ -2004,12 +2004,6 @@ static hipError_t launch_pv(const DecodeParams &P, int nblocks, hipStream_t st)
     return launch_one<G, TCT, INT8, -1>(P, nblocks, st);
 }
 
-// Whether launch_g has an instantiation for the key rows' length (rows that carry the all-channel statistics are longer)
-static inline bool row_length_instantiated(const SparkLayout &L)
-{
-    return !L.stats && (L.T == 26 || L.T == 38 || L.T == 64 || (L.T == 25 && !L.int8));
-}
-
 // One instantiation per query-group size G; each lives in its own translation unit (spark_decode_g*.hip) so
 // that the units compile in parallel.
 template <int G>

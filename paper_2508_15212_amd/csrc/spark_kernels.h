@@ -27,9 +27,15 @@ inline int counter_stride(int64_t pairs)
     return stride;
 }
 
-// How the decode grid cuts sequences into blocks (chosen on the host from the description alone).
 constexpr int kFineTailRows = 64;      // appended rows per block of DecodePlan::short_call = 2
 
+// Whether the decode kernels have an instantiation for the key rows' length (rows that carry the all-channel statistics are longer)
+inline bool row_length_instantiated(const SparkLayout &L)
+{
+    return !L.stats && (L.T == 26 || L.T == 38 || L.T == 64 || (L.T == 25 && !L.int8));
+}
+
+// How the decode grid cuts sequences into blocks (chosen on the host from the description alone).
 struct DecodePlan {
     int fixed_splits;   // > 0: every sequence is cut into this many chunks
     int chunk_tiles;    // else: a sequence spanning ntile tiles gets max(1, ceil(ntile / chunk_tiles)) chunks

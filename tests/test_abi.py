@@ -291,15 +291,44 @@ def test_the_block_per_tile_can_be_told_from_blocks_of_four():
 
 
 def test_room_for_appended_rows_is_what_calls_with_appended_rows_use():
-    """Sixteen sequences of 256 tokens take a block per tile without appended rows, and blocks of four with many: their workspace
+    """Four sequences of 400 tokens take a block per tile without appended rows, and blocks of four with many: their workspace
     has slots for 256 appended rows each, as those blocks take them, not for 64."""
     slot = 130 * 4
     for capacity in (4096, 32768):
-        kw = dict(batch=16, total_tokens=16 * 256, keep=64, tail_capacity=capacity)
-        assert spark.call_form(_desc(**kw), spark.CALL_DECODE_TAIL_TILES) == 4
-        # (chunks: at most (64 tiles + 2 * 16) // 4 + 16 + 1)
-        assert spark.decode_workspace_bytes(_desc(**kw)) == (41 * 32 + 16 * 32 * (capacity // 256)) * slot + 16 * 8 * 4
-    # with few: slots for 64 rows each, and as many chunks as tiles that two sequences can span, and one
-    kw = dict(batch=2, total_tokens=2 * 1024, keep=64, tail_capacity=256)
+        kw = dict(batch=4, total_tokens=4 * 400, keep=64, tail_capacity=capacity)
+        assert spark.call_form(_desc(**kw), spark.CALL_DECODE_TILES) == 1 and spark.call_form(_desc(**kw), spark.CALL_DECODE_TAIL_TILES) == 4
+        # (chunks: at most (25 tiles + 2 * 4) // 4 + 4 + 1)
+        assert spark.decode_workspace_bytes(_desc(**kw)) == (13 * 32 + 4 * 32 * (capacity // 256)) * slot + 256
+    # with few: slots for 64 rows each, and as many chunks as tiles that four sequences can span, and one
+    kw = dict(batch=4, total_tokens=4 * 400, keep=64, tail_capacity=128)
     assert spark.call_form(_desc(**kw), spark.CALL_DECODE_TAIL_TILES) == 1
-    assert spark.decode_workspace_bytes(_desc(**kw)) == ((32 + 2) * 32 + 2 * 32 * 4) * slot + 256
+    assert spark.decode_workspace_bytes(_desc(**kw)) == ((25 + 4) * 32 + 4 * 32 * 2) * slot + 256
+
+
+def test_a_block_per_tile_only_where_it_was_measured_faster():
+    """Both sides of every limit: tiles that one sequence can have, blocks, tokens a sequence, row lengths."""
+    n = lambda tiles: (64 * tiles,)
+    for G, keep, most, hkv in ((1, 64, 96, 2), (2, 64, 56, 4), (4, 64, 28, 8), (8, 64, 20, 8), (2, 38, 48, 4), (4, 38, 20, 8), (1, 33, 96, 4), (2, 33, 64, 8), (4, 33, 36, 8),
+                               (1, 20, 96, 4), (4, 28, 36, 8)):
+        assert _tiles(n(most), keep=keep, G=G, hkv=hkv) == 1 and _tiles(n(most + 1), keep=keep, G=G, hkv=hkv) > 1, (G, keep)
+        # without a longest length one sequence of several can have all tiles; with one, it has those and one more at a seam
+        pair = (64 * most, 240, 240)
+        for max_seqlen, tiles in ((0, 4), (64 * (most - 1), 1), (64 * (most - 1) + 1, 4)):
+            assert _tiles(pair, keep=keep, G=G, hkv=2, max_seqlen=max_seqlen) == tiles, (G, keep, max_seqlen)
+        # appended rows are merged too: 64 a block
+        assert _tiles(n(most - 3), True, keep=keep, G=G, hkv=2, tail_capacity=192) == 1 and _tiles(n(most - 2), True, keep=keep, G=G, hkv=2, tail_capacity=192) == 4
+    # blocks of the cache: 264 or 256 for rows with a kernel of their own, 704 or 512 for rows of any length
+    assert _tiles((2048,), keep=64, G=1) == 1 and _tiles((2049,), keep=64, G=1) == 4
+    assert _tiles((1920,) * 2, keep=64, G=4, max_seqlen=1000, hkv=4) == 1 and _tiles((1984,) * 2, keep=64, G=4, max_seqlen=1000, hkv=4) == 1
+    assert _tiles((1984, 2048), keep=64, G=4, max_seqlen=1000, hkv=4) == 4
+    assert _tiles((64 * 50, 64 * 36), keep=33, G=1, hkv=8) == 1 and _tiles((64 * 50, 64 * 37), keep=33, G=1, hkv=8) == 4
+    assert _tiles((64 * 30, 64 * 32), keep=33, G=4, hkv=8, max_seqlen=2048) == 1 and _tiles((64 * 30, 64 * 33), keep=33, G=4, hkv=8, max_seqlen=2048) == 4
+    # short sequences are one block of four tiles, with appended rows two
+    assert _tiles((239,), keep=64) == 4 and _tiles((240,), keep=64) == 1 and _tiles((239,), True, keep=64, tail_capacity=64) == 1
+    assert _tiles((0, 479), keep=33) == 4 and _tiles((0, 480), keep=33) == 1
+    # rows of 25 and 26, rows of 38 with one and eight query heads, eight query heads with rows of any length: never
+    for keep, G in ((25, 1), (25, 4), (26, 1), (26, 2), (26, 4), (26, 8), (38, 1), (38, 8), (33, 8), (64, 16)):
+        assert _tiles((512,), keep=keep, G=G) == 4 and _tiles((512,), True, keep=keep, G=G, tail_capacity=64) == 4, (keep, G)
+    assert _tiles((512,), keep=25, G=1, pack_dtype=spark.PACK_INT8) == 1       # (no kernel of its own)
+    # one long conversation among short ones
+    assert _tiles((5000, 100, 100, 100), keep=64) == 4 and _tiles((40000,) + (200,) * 21, keep=64, hkv=1) == 4
