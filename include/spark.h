@@ -104,8 +104,10 @@ typedef struct spark_desc {
  * keep, pack_dtype, total_tokens).  0 if the description is invalid. */
 size_t spark_packed_bytes(const spark_desc *desc);
 
-/* Scratch sizes in bytes (0 is possible; then NULL may be passed as the workspace).  Of a short call's decode workspace about a
- * quarter would do (spark_decode_workspace_init and the call accept it): with the whole, a block can take a single tile. */
+/* Scratch sizes in bytes (0 is possible; then NULL may be passed as the workspace).  spark_decode_workspace_init and the decode calls
+ * accept less where a call can do with less: a short call then takes four tiles a block instead of one, and counters without room to
+ * lie apart (2 KB at most) lie side by side, behind which the call clears their places.  Four tiles a block or one sum in different
+ * orders: outputs of workspaces of different sizes can differ in their last bits. */
 size_t spark_prune_workspace(const spark_desc *desc);
 size_t spark_decode_workspace(const spark_desc *desc);
 

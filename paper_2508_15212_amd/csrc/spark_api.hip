@@ -238,6 +238,14 @@ size_t workspace_bytes_of(const spark_desc *d, const spark::DecodePlan &p)
     return bytes_of(d, p) > bytes_of(d, dense) ? bytes_of(d, p) : bytes_of(d, dense);
 }
 
+// What a call gets by with: its counters side by side.  (A call that has no more clears the places of counters further apart behind
+// itself, which its partial states lie on: the next call finds zeros there.)
+size_t least_workspace_of(const spark_desc *d, spark::DecodePlan p)
+{
+    p.counter_stride = 1;
+    return workspace_bytes_of(d, p);
+}
+
 }  // namespace
 
 extern "C" {
@@ -294,7 +302,8 @@ spark_status spark_decode_workspace_init(const spark_desc *desc, void *workspace
     spark_status why;
     if (!desc_ok(desc, &why)) return why;
     if (!workspace || !aligned(workspace, 16)) return SPARK_ERR_INVALID_ARG;
-    if (workspace_bytes < workspace_bytes_of(desc, plan_of(desc))) return SPARK_ERR_WORKSPACE_TOO_SMALL;
+    if (workspace_bytes < least_workspace_of(desc, plan_of(desc))) return SPARK_ERR_WORKSPACE_TOO_SMALL;
+    // (a workspace has two slots of 520 bytes a pair at least, counters take 128 bytes a pair at most)
     uint32_t *counters = static_cast<uint32_t *>(workspace);
     const hipError_t e = spark::launch_zero_counters(counters, (int)(counter_bytes(desc, plan_of(desc).counter_stride) / sizeof(uint32_t)),
                                                      static_cast<hipStream_t>(hip_stream));
@@ -381,6 +390,11 @@ spark_status decode_common(const spark_desc *desc, const void *q_bf16, const voi
         if (!aligned(tail_k, 16) || !aligned(tail_v, 16) || !aligned(tail_len, 4)) return SPARK_ERR_INVALID_ARG;
     }
     spark::DecodePlan plan = given ? *given : plan_of(desc);
+    size_t clear = 0;                    // bytes at the start to clear behind the call
+    if (!given && workspace_bytes < workspace_bytes_of(desc, plan)) {
+        clear = counter_bytes(desc, plan.counter_stride);
+        plan.counter_stride = 1;
+    }
     if (workspace_bytes < workspace_bytes_of(desc, plan)) return SPARK_ERR_WORKSPACE_TOO_SMALL;
     if (!packed_v && rec == 0 && !topp) {
         spark::DecodePlan fine = plan;
@@ -401,7 +415,10 @@ spark_status decode_common(const spark_desc *desc, const void *q_bf16, const voi
         desc->n_q_heads, plan, scale, L, out, desc->out_dtype == SPARK_OUT_F32,
         static_cast<const uint16_t *>(tail_k), static_cast<const uint16_t *>(tail_v), tail_len,
         desc->tail_capacity, rec, seed, static_cast<hipStream_t>(hip_stream));
-    return e == hipSuccess ? SPARK_OK : SPARK_ERR_HIP;
+    if (e != hipSuccess) return SPARK_ERR_HIP;
+    if (clear > 0 && spark::launch_zero_counters(counters, (int)(clear / sizeof(uint32_t)), static_cast<hipStream_t>(hip_stream)) != hipSuccess)
+        return SPARK_ERR_HIP;
+    return SPARK_OK;
 }
 
 }  // namespace
