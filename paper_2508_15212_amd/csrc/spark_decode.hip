@@ -71,6 +71,24 @@ DecodePlan decode_form(DecodePlan plan, const SparkLayout &L, int Hq, bool plain
     return plan;
 }
 
+// Whether the blocks of a call with appended rows set priorities (set_priority).  The appended rows' blocks come last in the grid.  With
+// more blocks than the 512 that are resident at once they start as others end, which happens early without priorities and at the very
+// end with them.  That costs more than priorities gain while a block has seven tiles or fewer.  Time with / without priorities against the
+// same without either and with counters side by side, mean (largest) of 2 to 31 sequences of 300 to 16000 tokens, 64 to 1024 rows of room,
+// G = 1 to 16, two to eight KV heads, T = 26 / 48 / 64, by tiles of a block:
+//   5          1.017 / 1.006   1.012 / 1.003   1.020 / 1.006   (1.07 / 1.04)
+//   7          1.010 / 1.003   1.012 / 0.999   1.006 / 1.005   (1.08 / 1.03)
+//   8 and 9    1.011 / 1.004   1.003 / 1.003   0.987 / 1.000   (1.07 / 1.03)
+//   10 to 12   0.995 / 1.005   0.988 / 1.005   0.959 / 1.002   (1.08 / 1.03)
+//   13 to 16   1.021 / 1.008   0.999 / 1.002   0.979 / 1.004   (1.08 / 1.07)
+//   17 to 39   1.002 / 1.003   0.981 / 1.002   0.975 / 1.000   (1.07 / 1.05)
+// 12 of 500 to 3000 tokens, 256 rows, G = 4, T = 64 / 26: with 26.6 / 22.8 us, without 23.8 / 20.7; 8 of 1500 to 7000 tokens, T = 64: with
+// 29.1, without 32.9.  Tried: the appended rows' blocks first in the grid (1.02 to 1.05 of last), the others' levels below theirs (no change).
+static bool priorities_pay(int chunk_tiles, int64_t nblocks)
+{
+    return nblocks <= 544 || chunk_tiles >= 8;
+}
+
 // Zeroes the arrival counters of a fresh workspace.
 __global__ void spark_zero_kernel(uint32_t *p, int n)
 {
@@ -136,6 +154,9 @@ hipError_t launch_decode_attn(const uint16_t *q, const uint8_t *packed, const ui
     P.L = L;
     const int G = P.Hq / P.Hkv;
     const int nblocks = P.Hkv * ((P.warm_waves > 0 ? P.warm_waves / kDecodeWaves : P.nchunk_max) + L.batch * P.ntail);
+    const int chunks = P.chunk_limit > 0 && P.chunk_limit < P.nchunk_max ? P.chunk_limit : P.nchunk_max;
+    const bool prior = !tail_k || !plain || priorities_pay(P.chunk_tiles, (int64_t)P.Hkv * (chunks + (int64_t)L.batch * P.ntail));
+    P.full_share = prior ? P.chunk_tiles : kNoPriority;
     P.trace = (g_timeline != nullptr && (size_t)nblocks <= g_timeline_blocks) ? g_timeline : nullptr;
     switch (G) {
         case 1: return launch_g<1>(P, nblocks, st);

@@ -70,6 +70,7 @@ struct DecodeParams {
     // ((b * Hq + head) * tail_slots + part).
     // With chunk_limit > 0 a chunk is made as much longer as it takes for the whole batch to have at most that many.
     int fixed_splits, chunk_tiles, nchunk_max, chunk_limit;
+    int full_share;          // tiles that a block's priority is measured by (set_priority), or kNoPriority
     // Balanced mode (warm_waves > 0; ragged batches of many short sequences): the (sequence, tile) items of a KV
     // head, sequences back to back, are dealt out in equal contiguous ranges to warm_waves wavefronts, each of
     // which works on its own and leaves one partial per sequence it touches.  Wavefront w covers items
@@ -188,8 +189,13 @@ __device__ __forceinline__ void for_pairs(F f, std::integer_sequence<int, I...>)
 // SIMD the older one is served first, so that of two blocks on a compute unit with equal shares one was done early and the other
 // then ran alone, at half the rate (one wavefront gets an instruction in about 6.5 cycles): half of the blocks of 2 x 16001 tokens,
 // sampled, ended at 27 us and half at 37 us; with this, at 32 to 36.  Llama heads: 12001 to 18777 tokens, packed values 34.7 -> 31.9 us,
-// 2 x 16001 sampled 40.9 -> 38.6, 2 x 32768 top-p 45.9 -> 45.3, 8 x 32768 110.2 -> 109.1, 64 of 512 to 2048 54.2 -> 52.4, 4 x 131072, G = 8,
-// int8 codes 213.2 -> 207.7.  Tried: two levels instead of four (values 33.5), a change in the middle of a tile (sampled 40.5 instead of
+// 2 x 16001 sampled 40.9 -> 38.6, 8 x 32768 110.2 -> 109.1, 64 of 512 to 2048 54.2 -> 52.4, 4 x 131072, G = 8,
+// int8 codes 213.2 -> 207.7; 2 x 32768 top-p the same within the spread of its runs.
+// The full share is the plan's chunk, or all that a block has where that is more (a limit on the chunks makes them longer, and
+// then each block starts at level 3; measured by the length that the chunks do get, 7 batches under a limit took the same within 2 %;
+// given splits have no chunk: what equal lengths would be cut into).
+// Where blocks of appended rows find no place beside the others, that all of these end together makes them wait: see
+// priorities_pay in spark_decode.hip.  Tried: two levels instead of four (values 33.5), a change in the middle of a tile (sampled 40.5 instead of
 // 39.4), high for the products and low for the scores instead (values 33.0).
 __device__ __forceinline__ void set_priority(int left, int all)
 {
@@ -719,7 +725,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     if (is_tail) {
         // (they wait for memory about once: not behind the blocks that stream; ahead of ones that set no priority, 8 x 500 to 900
         //  tokens with 256 appended rows took 13.0 instead of 12.5 us)
-        if (WARM || P.chunk_tiles > kDecodeWaves) __builtin_amdgcn_s_setprio(3);
+        if (WARM || (P.full_share > kDecodeWaves && P.full_share < kNoPriority)) __builtin_amdgcn_s_setprio(3);
         static_assert(WBUF >= G * SPARK_D * 4, "LDS reuse");
         tail_partial<G>(P, (tb / P.ntail) / P.Hkv, h, tb % P.ntail, tail_rows, red_m, red_l, reinterpret_cast<float *>(&wbuf[0][0]));
     }
@@ -1805,7 +1811,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
     int tile = tile_of(kidx);
     // The query and 1/a are requested before the first tile: loads return in order, so the table can be built
     // while the tile is still on its way.
-    if (nts > kDecodeWaves) set_priority(nts, max(nts, P.chunk_tiles));
+    if (nts > kDecodeWaves) set_priority(nts, max(nts, P.full_share));
     float inva_r = 0.0f;
     uint16_t q_r[G];
     if (tid < SPARK_D) {
@@ -1886,7 +1892,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         process(tile, more ? tnext : -1);
         if (more) {
             if (!PV) prefetch(tnext);   // request the next tile; its latency is covered by the other resident wavefronts
-            set_priority(nts - (kidx + kDecodeWaves - wave), max(nts, P.chunk_tiles));
+            set_priority(nts - (kidx + kDecodeWaves - wave), max(nts, P.full_share));
         }
     }
 

@@ -27,6 +27,7 @@ inline int counter_stride(int64_t pairs)
     return stride;
 }
 
+constexpr int kNoPriority = 1 << 28;   // (more than four times the tiles of a cache: every block stays at the lowest level)
 constexpr int kFineTailRows = 64;      // appended rows per block of DecodePlan::short_call = 2
 
 // Whether the decode kernels have an instantiation for the key rows' length (rows that carry the all-channel statistics are longer)
