@@ -96,7 +96,7 @@ typedef struct spark_desc {
                                  balanced as it is and keeps one block per sequence, which is 3 to 5 %
                                  cheaper there than the balanced cut; and a short call takes a block per tile
                                  (up to a quarter faster) while no sequence has too many to merge, for
-                                 which without the hint one sequence may have all tokens.  Affects results in
+                                 which without the hint one may have four fifths of all tokens.  Affects results in
                                  their last bits at most; enters the workspace size like n_splits. */
 } spark_desc;
 

@@ -135,12 +135,13 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 // table gathers in its LDS; a tile a block spreads them, for four times the partials, which the last block of a pair merges.  So it
 // gains where blocks of four wavefronts would take four tiles each, and
 //   - until the merge of ONE sequence's partials is the longer: the more query heads, the fewer tiles.  The lengths are on the device:
-//     the longest sequence can have all tiles of the batch unless max_seqlen says less.  (5000 and three times 100 tokens, G = 4,
-//     T = 64: 1.42; one KV head, 40000 and 21 times 200 tokens: 58.9 instead of 22.2 us);
+//     the longest of several sequences is taken to have four fifths of the batch's tiles, or what max_seqlen says.
+//     (5000 and three times 100 tokens, G = 4, T = 64: 1.42; one KV head, 40000 and 21 times 200 tokens: 58.9 instead of 22.2 us.  One of
+//     several with more than four fifths, at the limit: up to 1.09.)
 //   - from sequences of 240 tokens on average: up to four tiles are one block of the other form, and nothing is merged there (with
 //     appended rows both merge);
-//   - while there are few blocks: rows of a length that has a kernel of its own are walked fast enough there that a second block on a
-//     compute unit costs the gain, rows of any length are not (up to 512 or 704 blocks).
+//   - while the blocks are resident at once, 512 of them (rows of any length, which gain more, up to 704; eight query heads, which
+//     need more LDS, 256).  T = 64, 256 to 512 / 512 to 640 blocks: G = 1 0.96 / 1.02, G = 2 0.96 / 1.05, G = 4 0.97 / 1.10.
 // Rows of 25, 26 (bf16) and 38 kept channels (one or eight query heads) gain nothing anywhere; eight query heads with rows of any
 // length are taken by blocks of sixteen wavefronts.  Time against blocks of four tiles (graphs of 40 to 160 calls; the larger of the
 // ratios with caches in the L2 and with ones that rotate through 400 MB), tiles of the batch, sequences (s: the first has 80 % of them):
@@ -160,8 +161,8 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 //   2  64 in 1   1.00 / 0.82 / 0.99 / 0.79 / 0.93   1.03 / 0.84 / 1.00 / 0.80 / 0.94   1.23 / 1.03 / 1.20 / 0.96 / 1.10   1.37 / 1.35 / 1.25
 //   2  90 in 1   1.01 / 0.84 / 1.01 / 0.79 / 0.95   1.15 / 0.95 / 1.13 / 0.90 / 1.06   1.38 / 1.16 / 1.33 / 1.08 / 1.24   1.58 / 1.55 / 1.43
 //   2  64 in 8   0.97 / 0.81 / 0.99 / 0.76 / 0.91   0.95 / 0.77 / 0.92 / 0.73 / 0.86   0.95 / 0.80 / 0.93 / 0.74 / 0.86   0.97 / 0.97 / 0.88
-// Of 2680 such measurements that the rule takes without max_seqlen (1, 2, 4, 8 and 16 KV heads, T = 20 to 64) the worst is 1.015 and the
-// mean 0.86, with max_seqlen 1.03 (two sequences of 32 tiles, four KV heads, G = 4) and 0.86; with 200 appended rows 0.88, int8 codes 0.88.
+// Of 2935 such measurements that the rule takes without max_seqlen (1, 2, 4, 8 and 16 KV heads, T = 20 to 64) the worst is 1.05 (G = 1, T = 64,
+// from memory; 0.96 from the L2) and the mean 0.86, with max_seqlen the same; with 200 appended rows 0.89 and 1.06, int8 codes 0.89 and 1.06.
 bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
@@ -173,16 +174,16 @@ bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
         longest = G == 1 ? 96 : (G == 2 ? 64 : (G == 4 ? 36 : 0));
         blocks = G <= 2 ? 704 : 512;
     } else if (L.T == 64) {
-        longest = G == 1 ? 96 : (G == 2 ? 56 : (G == 4 ? 28 : 20));
-        blocks = G <= 2 ? 264 : 256;
+        longest = G == 1 ? 96 : (G == 2 ? 64 : (G == 4 ? 32 : 24));
+        blocks = G <= 4 ? 512 : 256;
     } else if (L.T == 38) {
         longest = G == 2 ? 48 : (G == 4 ? 20 : 0);
         blocks = 256;
     }
     if (longest == 0 || (!with_tail && d->total_tokens < 240 * (int64_t)d->batch)) return false;
     const int tail_slots = !with_tail ? 0 : (d->tail_capacity > 0 ? (d->tail_capacity + spark::kFineTailRows - 1) / spark::kFineTailRows : 1);
-    int64_t most = tiles;                // (a sequence can begin and end inside a tile)
-    if (d->max_seqlen > 0) most = std::min(most, ((int64_t)d->max_seqlen + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS + 1);
+    int64_t most = d->batch > 1 ? (4 * tiles + 4) / 5 : tiles;
+    if (d->max_seqlen > 0) most = std::min(tiles, ((int64_t)d->max_seqlen + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS + 1);      // (it can begin and end in a tile)
     if (most + tail_slots > longest || (tiles + d->batch) * d->n_kv_heads > blocks) return false;
     if ((tiles + d->batch * (1 + (int64_t)tail_slots)) * d->n_kv_heads > 848) return false;
     if (spark::decode_form(p, L, d->n_q_heads, true, with_tail ? p.tail_slots : 0).short_call != 0) return false;

@@ -308,19 +308,20 @@ def test_room_for_appended_rows_is_what_calls_with_appended_rows_use():
 def test_a_block_per_tile_only_where_it_was_measured_faster():
     """Both sides of every limit: tiles that one sequence can have, blocks, tokens a sequence, row lengths."""
     n = lambda tiles: (64 * tiles,)
-    for G, keep, most, hkv in ((1, 64, 96, 2), (2, 64, 56, 4), (4, 64, 28, 8), (8, 64, 20, 8), (2, 38, 48, 4), (4, 38, 20, 8), (1, 33, 96, 4), (2, 33, 64, 8), (4, 33, 36, 8),
+    for G, keep, most, hkv in ((1, 64, 96, 2), (2, 64, 64, 4), (4, 64, 32, 8), (8, 64, 24, 8), (2, 38, 48, 4), (4, 38, 20, 8), (1, 33, 96, 4), (2, 33, 64, 8), (4, 33, 36, 8),
                                (1, 20, 96, 4), (4, 28, 36, 8)):
         assert _tiles(n(most), keep=keep, G=G, hkv=hkv) == 1 and _tiles(n(most + 1), keep=keep, G=G, hkv=hkv) > 1, (G, keep)
-        # without a longest length one sequence of several can have all tiles; with one, it has those and one more at a seam
-        pair = (64 * most, 240, 240)
-        for max_seqlen, tiles in ((0, 4), (64 * (most - 1), 1), (64 * (most - 1) + 1, 4)):
-            assert _tiles(pair, keep=keep, G=G, hkv=2, max_seqlen=max_seqlen) == tiles, (G, keep, max_seqlen)
+        # without a longest length one sequence of several has four fifths of the tiles; with one, it has those and one more at a seam
+        several = lambda tiles: (64 * tiles - 2 * 240, 240, 240)
+        assert _tiles(several(most * 5 // 4), keep=keep, G=G, hkv=2) == 1 and _tiles(several(most * 5 // 4 + 1), keep=keep, G=G, hkv=2) == 4, (G, keep)
+        for max_seqlen, tiles in ((64 * (most - 1), 1), (64 * (most - 1) + 1, 4)):
+            assert _tiles(several(most * 5 // 4 + 1), keep=keep, G=G, hkv=2, max_seqlen=max_seqlen) == tiles, (G, keep, max_seqlen)
         # appended rows are merged too: 64 a block
         assert _tiles(n(most - 3), True, keep=keep, G=G, hkv=2, tail_capacity=192) == 1 and _tiles(n(most - 2), True, keep=keep, G=G, hkv=2, tail_capacity=192) == 4
-    # blocks of the cache: 264 or 256 for rows with a kernel of their own, 704 or 512 for rows of any length
-    assert _tiles((2048,), keep=64, G=1) == 1 and _tiles((2049,), keep=64, G=1) == 4
-    assert _tiles((1920,) * 2, keep=64, G=4, max_seqlen=1000, hkv=4) == 1 and _tiles((1984,) * 2, keep=64, G=4, max_seqlen=1000, hkv=4) == 1
-    assert _tiles((1984, 2048), keep=64, G=4, max_seqlen=1000, hkv=4) == 4
+    # blocks of the cache: 512, 256 with eight query heads, 704 for one and two with rows of any length
+    assert _tiles((64 * 63,), keep=64, G=1) == 1 and _tiles((64 * 64,), keep=64, G=1) == 4
+    for hkv, G, n in ((16, 4, 30), (8, 8, 30)):
+        assert _tiles((64 * n - 900, 900), keep=64, G=G, max_seqlen=1020, hkv=hkv) == 1 and _tiles((64 * n - 836, 900), keep=64, G=G, max_seqlen=1020, hkv=hkv) == 4
     assert _tiles((64 * 50, 64 * 36), keep=33, G=1, hkv=8) == 1 and _tiles((64 * 50, 64 * 37), keep=33, G=1, hkv=8) == 4
     assert _tiles((64 * 30, 64 * 32), keep=33, G=4, hkv=8, max_seqlen=2048) == 1 and _tiles((64 * 30, 64 * 33), keep=33, G=4, hkv=8, max_seqlen=2048) == 4
     # short sequences are one block of four tiles, with appended rows two

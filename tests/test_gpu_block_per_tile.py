@@ -69,8 +69,8 @@ def test_eight_query_heads(pack):
 
 
 # (from 240 tokens a sequence on average; the most tiles, and the most blocks, that each group takes)
-@pytest.mark.parametrize("G,hkv,keep,seqlens", [(1, 8, 64, (2048,)), (1, 2, 64, (6144,)), (2, 8, 64, (2048,)), (2, 4, 64, (3584,)), (4, 8, 64, (1792,)), (4, 1, 64, (240,)),
-                                                (4, 8, 33, (2304,)), (2, 8, 33, (3000, 1060)), (1, 11, 33, (64 * 53, 576)), (8, 8, 64, (1279,)), (2, 3, 64, (241,)),
+@pytest.mark.parametrize("G,hkv,keep,seqlens", [(1, 8, 64, (2048,)), (1, 2, 64, (6144,)), (2, 8, 64, (2048,)), (2, 4, 64, (4096,)), (4, 8, 64, (2048,)), (4, 1, 64, (240,)),
+                                                (4, 8, 33, (2304,)), (2, 8, 33, (3000, 1060)), (1, 11, 33, (64 * 53, 576)), (8, 8, 64, (1535,)), (2, 3, 64, (241,)),
                                                 (4, 2, 64, (65, 0, 0, 927)), (1, 2, 33, (1,) * 15 + (0,) * 3 + (16, 17, 48, 5300))])
 def test_sequence_lengths(G, hkv, keep, seqlens):
     _check(wl.small(name=f"tilelen{len(seqlens)}_{G}", batch=len(seqlens), n_q_heads=G * hkv, n_kv_heads=hkv, keep=keep, seqlens=seqlens, seed=820 + G))
