@@ -63,7 +63,7 @@ def test_size_queries_follow_the_layout():
 
 def test_balanced_cut_sizes_its_partial_slots_on_the_host():
     """n_splits = -1 asks for the balanced cut: 4 * (512 / KV heads) wavefronts per KV head, chunk ids
-    wavefronts + 2 * batch.  Batches of 32 to 256 sequences with 256 or more (batch, KV head) pairs and two
+    wavefronts + 2 * batch - 1 (the size holds one more).  Batches of 32 to 256 sequences with 256 or more (batch, KV head) pairs and two
     tiles or more per wavefront get it unasked; more than 256 sequences, or 16 query heads per KV head, never do."""
     slot = 130 * 4
     small = _desc(batch=4, total_tokens=4 * 1000)

@@ -1,5 +1,5 @@
 """Appended rows on the matrix cores: row counts around the sixteen rows of an operand, the 64 of a wavefront and the 256 of
-a block, all query-group sizes, a query that is only 2-byte aligned, and scores whose query and softmax scale are far from
+a block (16 and 64 where a block takes a tile), all query-group sizes, a query that is only 2-byte aligned, and scores whose query and softmax scale are far from
 one (a power of two moved from one to the other changes nothing)."""
 import numpy as np
 import pytest
@@ -14,11 +14,12 @@ from tests.test_gpu_tail import _tail_case
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("keep", [26, 64])
 @pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
-def test_row_counts(G):
+def test_row_counts(G, keep):
     lens = (1, 15, 16, 17, 32, 33, 63, 64, 65, 128, 255, 256, 257, 300)
-    w = wl.small(name=f"tailrows{G}", batch=len(lens), n_q_heads=2 * G, n_kv_heads=2, keep=26, seqlens=(0, 5) * 7, seed=440 + G)
-    _tail_case(w, cap=300, tail_len=lens, seed=441 + G)
+    w = wl.small(name=f"tailrows{G}", batch=len(lens), n_q_heads=2 * G, n_kv_heads=2, keep=keep, seqlens=(0, 5) * 7, seed=440 + G)
+    _tail_case(w, cap=300, tail_len=lens, seed=441 + G, tiles=1 if keep == 64 and G <= 8 else 4)
 
 
 @pytest.mark.parametrize("shift", [-60, 60])
@@ -51,8 +52,8 @@ def test_alignment_and_range(G, shift):
     assert torch.equal(base, run(shift, 0))
 
 
-# (26: the appended rows' blocks of the four-wavefront kernel, 90: those of the sixteen-wavefront kernel, except at G = 16)
-@pytest.mark.parametrize("keep", [26, 90])
+# (26: the appended rows' blocks of 256 rows by four wavefronts, 90: by sixteen, 64: blocks of 64 rows; G = 16 has the first only)
+@pytest.mark.parametrize("keep", [26, 90, 64])
 @pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
 def test_infinite_values(G, keep):
     """+-inf in an appended value gives +-inf in the outputs of its channel and nothing elsewhere: the probabilities go to the
@@ -76,7 +77,8 @@ def test_infinite_values(G, keep):
         finite[:, row, 0, ch] = 0.0
     desc = make_desc(w)
     desc.tail_capacity = cap
-    assert spark.call_form(desc, spark.CALL_DECODE_TAIL) == (1 if keep == 26 or G == 16 else 2)
+    assert spark.call_form(desc, spark.CALL_DECODE_TAIL) == (1 if keep != 90 or G == 16 else 2)
+    assert spark.call_form(desc, spark.CALL_DECODE_TAIL_TILES) == (1 if keep == 64 and G <= 8 else 4)
     packed = torch.empty(spark.packed_bytes(desc), dtype=torch.uint8, device="cuda")
     cu = torch.from_numpy(np.asarray(t.cu, np.int32)).cuda()
     spark.prune(desc, to_dev(t.k), to_dev(t.qwin), cu, packed)
