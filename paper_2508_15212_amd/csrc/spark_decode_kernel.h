@@ -1278,8 +1278,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64, decode_min_blocks(G, TCT)) void 
         }
         if constexpr (REC != 0) {
             // ---- sampled recovery: every pruned entry j adds q_gj * w~_j / a_j
-            // Bound by vector issue: a Gaussian pair of channels takes 126 cycles of its SIMD at G = 4 (42 in two-cycle, 50 in
-            // four-cycle instructions, 34 in logarithm, root, sine and cosine at eight), and kept channels'
+            // Bound by vector issue: a Gaussian pair of channels takes 123 cycles of its SIMD at G = 4 (13.5 instructions of two
+            // cycles, 12 of four, and of eight cycles logarithm, root, sine, cosine and two matrix products), and kept channels'
             // variates are drawn and masked off.  2 x 16001 tokens, Llama heads, T = 26: 58.7 us with the library's
             // square root, integer conversions, a branch per channel and four table reads a pair; 44.0 us with a
             // reciprocal root and a Newton step instead of the root and a shift of the mask per pair; 41.6 us like this, 38.4
