@@ -142,8 +142,8 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 //     appended rows both merge);
 //   - while the blocks are resident at once, 512 of them (rows of any length, which gain more, up to 704; eight query heads, which
 //     need more LDS, 256).  T = 64, 256 to 512 / 512 to 640 blocks: G = 1 0.96 / 1.02, G = 2 0.96 / 1.05, G = 4 0.97 / 1.10.
-// Rows of 25, 26 (bf16) and 38 kept channels (one or eight query heads) gain nothing anywhere; eight query heads with rows of any
-// length are taken by blocks of sixteen wavefronts.  Time against blocks of four tiles (graphs of 40 to 160 calls; the larger of the
+// Rows of 25 (bf16), 26 and 38 kept channels gain nothing with one query head, nor those of 26 with eight; eight query heads with rows of
+// any length are taken by blocks of sixteen wavefronts.  Time against blocks of four tiles (graphs of 40 to 160 calls; the larger of the
 // ratios with caches in the L2 and with ones that rotate through 400 MB), tiles of the batch, sequences (s: the first has 80 % of them):
 //   KV heads     G = 1, T = 26 / 32 / 38 / 48 / 64    G = 2                              G = 4                              G = 8, T = 26 / 38 / 64
 //   8   3 in 1   1.42 / 1.07 / 1.35 / 0.97 / 1.19   1.37 / 1.06 / 1.31 / 0.95 / 1.13   1.26 / 1.01 / 1.21 / 0.93 / 1.08   1.32 / 1.28 / 1.13
@@ -161,8 +161,8 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 //   2  64 in 1   1.00 / 0.82 / 0.99 / 0.79 / 0.93   1.03 / 0.84 / 1.00 / 0.80 / 0.94   1.23 / 1.03 / 1.20 / 0.96 / 1.10   1.37 / 1.35 / 1.25
 //   2  90 in 1   1.01 / 0.84 / 1.01 / 0.79 / 0.95   1.15 / 0.95 / 1.13 / 0.90 / 1.06   1.38 / 1.16 / 1.33 / 1.08 / 1.24   1.58 / 1.55 / 1.43
 //   2  64 in 8   0.97 / 0.81 / 0.99 / 0.76 / 0.91   0.95 / 0.77 / 0.92 / 0.73 / 0.86   0.95 / 0.80 / 0.93 / 0.74 / 0.86   0.97 / 0.97 / 0.88
-// Of 2935 such measurements that the rule takes without max_seqlen (1, 2, 4, 8 and 16 KV heads, T = 20 to 64) the worst is 1.05 (G = 1, T = 64,
-// from memory; 0.96 from the L2) and the mean 0.86, with max_seqlen the same; with 200 appended rows 0.89 and 1.06, int8 codes 0.89 and 1.06.
+// Of 3135 such measurements that the rule takes without max_seqlen (1, 2, 4, 8 and 16 KV heads, T = 20 to 64) the worst is 1.05 (G = 1, T = 64,
+// from memory; 0.96 from the L2) and the mean 0.87, with max_seqlen the same; with 200 appended rows 0.90 and 1.06, int8 codes 0.90 and 1.05.
 bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
@@ -176,8 +176,8 @@ bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
     } else if (L.T == 64) {
         longest = G == 1 ? 96 : (G == 2 ? 64 : (G == 4 ? 32 : 24));
         blocks = G <= 4 ? 512 : 256;
-    } else if (L.T == 38) {
-        longest = G == 2 ? 48 : (G == 4 ? 20 : 0);
+    } else {
+        longest = G == 2 ? (L.T == 38 ? 48 : 32) : (G == 4 ? 20 : (G == 8 && L.T == 38 ? 12 : 0));
         blocks = 256;
     }
     if (longest == 0 || (!with_tail && d->total_tokens < 240 * (int64_t)d->batch)) return false;

@@ -14,7 +14,7 @@ MAX_ABS, MEAN_ABS = 1e-2, 1e-3
 
 
 def _tail_case(w, cap, tail_len, seed, n_splits=0, scale_k=1.0, tiles=None):
-    """tiles: asserted tiles of a block of the call (1: a block per tile, which takes appended rows by 64; 4: blocks that take 256)."""
+    """tiles: asserted tiles of a block of the call (1: a block per tile, which takes appended rows by 64; 4, or 0 with given splits: blocks that take 256)."""
     t = wl.generate(w)
     rng = np.random.default_rng(seed)
     shape = (w.batch, cap, w.n_kv_heads, w.head_dim)
@@ -61,11 +61,11 @@ def test_tail_longer_than_one_chunk_and_many_splits():
     _tail_case(w, cap=600, tail_len=(600, 257), seed=410, n_splits=7)
 
 
-@pytest.mark.parametrize("keep,tiles", [(64, 1), (26, 4)])
-def test_tail_dominates_the_softmax(keep, tiles):
+@pytest.mark.parametrize("n_splits,tiles", [(0, 1), (2, 0)])
+def test_tail_dominates_the_softmax(n_splits, tiles):
     """Appended keys ten times larger: nearly all probability mass sits on the appended rows."""
-    w = wl.small(name="tail_peaked", batch=2, seqlens=(300, 141), keep=keep, seed=420)
-    _tail_case(w, cap=16, tail_len=(16, 3), seed=420, scale_k=10.0, tiles=tiles)
+    w = wl.small(name="tail_peaked", batch=2, seqlens=(300, 141), keep=64, seed=420)
+    _tail_case(w, cap=16, tail_len=(16, 3), seed=420, n_splits=n_splits, scale_k=10.0, tiles=tiles)
 
 
 def test_tail_with_empty_prefix_and_empty_tail():
@@ -109,4 +109,5 @@ def test_tail_together_with_pruned_values():
 def test_tail_lengths_around_the_pieces_it_is_read_in(keep, rows, G, Hkv):
     """Groups of eight value rows, a wavefront's 64 rows, a block's 256 (64 kept channels, up to eight query heads: 16 and 64)."""
     w = wl.small(name=f"tail_rows{G}", n_q_heads=G * Hkv, n_kv_heads=Hkv, keep=keep, seqlens=(70, 1, 64, 33), batch=4, seed=460 + G)
-    _tail_case(w, cap=260, tail_len=rows, seed=460 + sum(rows), tiles=1 if keep == 64 and G <= 8 else 4)
+    n_splits = 1 if keep == 26 else 0
+    _tail_case(w, cap=260, tail_len=rows, seed=460 + sum(rows), n_splits=n_splits, tiles=0 if n_splits else 1 if G <= 8 else 4)

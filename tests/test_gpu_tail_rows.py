@@ -19,7 +19,8 @@ pytestmark = pytest.mark.gpu
 def test_row_counts(G, keep):
     lens = (1, 15, 16, 17, 32, 33, 63, 64, 65, 128, 255, 256, 257, 300)
     w = wl.small(name=f"tailrows{G}", batch=len(lens), n_q_heads=2 * G, n_kv_heads=2, keep=keep, seqlens=(0, 5) * 7, seed=440 + G)
-    _tail_case(w, cap=300, tail_len=lens, seed=441 + G, tiles=1 if keep == 64 and G <= 8 else 4)
+    n_splits = 1 if keep == 26 else 0
+    _tail_case(w, cap=300, tail_len=lens, seed=441 + G, n_splits=n_splits, tiles=0 if n_splits else 1 if G <= 8 else 4)
 
 
 @pytest.mark.parametrize("shift", [-60, 60])
@@ -52,7 +53,7 @@ def test_alignment_and_range(G, shift):
     assert torch.equal(base, run(shift, 0))
 
 
-# (26: the appended rows' blocks of 256 rows by four wavefronts, 90: by sixteen, 64: blocks of 64 rows; G = 16 has the first only)
+# (26, with a split: the appended rows' blocks of 256 rows by four wavefronts, 90: by sixteen, 64: blocks of 64 rows; G = 16 has the first only)
 @pytest.mark.parametrize("keep", [26, 90, 64])
 @pytest.mark.parametrize("G", [1, 2, 4, 8, 16])
 def test_infinite_values(G, keep):
@@ -75,10 +76,10 @@ def test_infinite_values(G, keep):
     for row, ch in place.items():
         tv[:, row, 0, ch] = np.inf if row % 2 == 0 else -np.inf
         finite[:, row, 0, ch] = 0.0
-    desc = make_desc(w)
+    desc = make_desc(w, n_splits=1 if keep == 26 else 0)
     desc.tail_capacity = cap
     assert spark.call_form(desc, spark.CALL_DECODE_TAIL) == (1 if keep != 90 or G == 16 else 2)
-    assert spark.call_form(desc, spark.CALL_DECODE_TAIL_TILES) == (1 if keep == 64 and G <= 8 else 4)
+    assert spark.call_form(desc, spark.CALL_DECODE_TAIL_TILES) == (0 if keep == 26 else 1 if keep == 64 and G <= 8 else 4)
     packed = torch.empty(spark.packed_bytes(desc), dtype=torch.uint8, device="cuda")
     cu = torch.from_numpy(np.asarray(t.cu, np.int32)).cuda()
     spark.prune(desc, to_dev(t.k), to_dev(t.qwin), cu, packed)
