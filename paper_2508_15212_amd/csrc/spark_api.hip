@@ -138,12 +138,14 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 //     the longest of several sequences is taken to have four fifths of the batch's tiles, or what max_seqlen says.
 //     (5000 and three times 100 tokens, G = 4, T = 64: 1.42; one KV head, 40000 and 21 times 200 tokens: 58.9 instead of 22.2 us.  One of
 //     several with more than four fifths, at the limit: up to 1.09.)
-//   - from sequences of 240 tokens on average: up to four tiles are one block of the other form, and nothing is merged there (with
-//     appended rows both merge);
+//   - from sequences of 200 or 240 tokens on average: up to four tiles are one block of the other form, and nothing is merged there (with
+//     appended rows both merge).  Sequences of 128 / 192 / 256 tokens, G = 2, up to 512 blocks: T = 26 1.30 / 1.23 / 0.99, T = 64 1.11 / 1.06 / 0.91,
+//     T = 28 1.02 / 0.99 / 0.83; long rows of any length gain there as well: T = 48 0.91 / 0.88 / 0.77;
 //   - while the blocks are resident at once, 512 of them (rows of any length, which gain more, up to 704; eight query heads, which
 //     need more LDS, 256).  T = 64, 256 to 512 / 512 to 640 blocks: G = 1 0.96 / 1.02, G = 2 0.96 / 1.05, G = 4 0.97 / 1.10.
-// Rows of 25 (bf16), 26 and 38 kept channels gain nothing with one query head, nor those of 26 with eight; eight query heads with rows of
-// any length are taken by blocks of sixteen wavefronts.  Time against blocks of four tiles (graphs of 40 to 160 calls; the larger of the
+// Rows of 25 (bf16), 26 and 38 kept channels are the same either way with one query head (int8 codes of 26 lose 6 %) and lose with eight
+// (38: from 16 tiles, up to 8 % at 20); this form has the smaller error against 64 bits.  Eight query heads with rows of any length are taken by blocks of
+// sixteen wavefronts.  Time against blocks of four tiles (graphs of 40 to 160 calls; the larger of the
 // ratios with caches in the L2 and with ones that rotate through 400 MB), tiles of the batch, sequences (s: the first has 80 % of them):
 //   KV heads     G = 1, T = 26 / 32 / 38 / 48 / 64    G = 2                              G = 4                              G = 8, T = 26 / 38 / 64
 //   8   3 in 1   1.42 / 1.07 / 1.35 / 0.97 / 1.19   1.37 / 1.06 / 1.31 / 0.95 / 1.13   1.26 / 1.01 / 1.21 / 0.93 / 1.08   1.32 / 1.28 / 1.13
@@ -161,30 +163,34 @@ spark::DecodePlan plan_of(const spark_desc *d, bool allow_balanced = true)
 //   2  64 in 1   1.00 / 0.82 / 0.99 / 0.79 / 0.93   1.03 / 0.84 / 1.00 / 0.80 / 0.94   1.23 / 1.03 / 1.20 / 0.96 / 1.10   1.37 / 1.35 / 1.25
 //   2  90 in 1   1.01 / 0.84 / 1.01 / 0.79 / 0.95   1.15 / 0.95 / 1.13 / 0.90 / 1.06   1.38 / 1.16 / 1.33 / 1.08 / 1.24   1.58 / 1.55 / 1.43
 //   2  64 in 8   0.97 / 0.81 / 0.99 / 0.76 / 0.91   0.95 / 0.77 / 0.92 / 0.73 / 0.86   0.95 / 0.80 / 0.93 / 0.74 / 0.86   0.97 / 0.97 / 0.88
-// Of 3135 such measurements that the rule takes without max_seqlen (1, 2, 4, 8 and 16 KV heads, T = 20 to 64) the worst is 1.05 (G = 1, T = 64,
-// from memory; 0.96 from the L2) and the mean 0.87, with max_seqlen the same; with 200 appended rows 0.90 and 1.06, int8 codes 0.90 and 1.05.
+// Of 3564 such measurements that the rule takes without max_seqlen (1, 2, 4, 8 and 16 KV heads, T = 20 to 64) the worst is 1.07 (G = 1, T = 38,
+// from memory; 0.96 from the L2) and the mean 0.88, with max_seqlen the same; with 200 appended rows 0.91 and 1.07, int8 codes 0.90 and 1.05.
 bool fine_plan(const spark_desc *d, spark::DecodePlan &p, bool with_tail)
 {
     const int G = d->n_q_heads / d->n_kv_heads;
     const int64_t tiles = (d->total_tokens + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS;
     if (tiles == 0 || d->batch > 64 || d->n_splits != 0 || p.warm_waves > 0 || G > 8) return false;
     const SparkLayout L = layout_of(d);
-    int longest = 0, blocks = 0;         // tiles of one sequence, blocks of the cache
+    const int64_t cache_blocks = (tiles + d->batch) * d->n_kv_heads;
+    int longest, blocks, tokens;         // tiles of one sequence, blocks of the cache at most; tokens a sequence at least
     if (!spark::row_length_instantiated(L)) {
         longest = G == 1 ? 96 : (G == 2 ? 64 : (G == 4 ? 36 : 0));
         blocks = G <= 2 ? 704 : 512;
+        tokens = cache_blocks > 256 ? 240 : (L.T < 40 ? 200 : 0);
     } else if (L.T == 64) {
         longest = G == 1 ? 96 : (G == 2 ? 64 : (G == 4 ? 32 : 24));
         blocks = G <= 4 ? 512 : 256;
+        tokens = G == 1 ? 240 : 200;
     } else {
-        longest = G == 2 ? (L.T == 38 ? 48 : 32) : (G == 4 ? 20 : (G == 8 && L.T == 38 ? 12 : 0));
+        longest = G == 1 ? (L.int8 && L.T == 26 ? 0 : 32) : (G == 2 ? (L.T == 38 ? 48 : 32) : (G == 4 ? 20 : (L.T == 38 ? 20 : 0)));
         blocks = 256;
+        tokens = 240;
     }
-    if (longest == 0 || (!with_tail && d->total_tokens < 240 * (int64_t)d->batch)) return false;
+    if (longest == 0 || (!with_tail && d->total_tokens < tokens * (int64_t)d->batch)) return false;
     const int tail_slots = !with_tail ? 0 : (d->tail_capacity > 0 ? (d->tail_capacity + spark::kFineTailRows - 1) / spark::kFineTailRows : 1);
     int64_t most = d->batch > 1 ? (4 * tiles + 4) / 5 : tiles;
     if (d->max_seqlen > 0) most = std::min(tiles, ((int64_t)d->max_seqlen + SPARK_TILE_TOKENS - 1) / SPARK_TILE_TOKENS + 1);      // (it can begin and end in a tile)
-    if (most + tail_slots > longest || (tiles + d->batch) * d->n_kv_heads > blocks) return false;
+    if (most + tail_slots > longest || cache_blocks > blocks) return false;
     if ((tiles + d->batch * (1 + (int64_t)tail_slots)) * d->n_kv_heads > 848) return false;
     if (spark::decode_form(p, L, d->n_q_heads, true, with_tail ? p.tail_slots : 0).short_call != 0) return false;
     p.short_call = 2;

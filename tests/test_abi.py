@@ -308,7 +308,7 @@ def test_room_for_appended_rows_is_what_calls_with_appended_rows_use():
 def test_a_block_per_tile_only_where_it_was_measured_faster():
     """Both sides of every limit: tiles that one sequence can have, blocks, tokens a sequence, row lengths."""
     n = lambda tiles: (64 * tiles,)
-    for G, keep, most, hkv in ((1, 64, 96, 2), (2, 64, 64, 4), (4, 64, 32, 8), (8, 64, 24, 8), (2, 38, 48, 4), (4, 38, 20, 8), (8, 38, 12, 8), (2, 26, 32, 4), (4, 26, 20, 8), (4, 25, 20, 8), (1, 33, 96, 4), (2, 33, 64, 8), (4, 33, 36, 8),
+    for G, keep, most, hkv in ((1, 64, 96, 2), (2, 64, 64, 4), (4, 64, 32, 8), (8, 64, 24, 8), (2, 38, 48, 4), (4, 38, 20, 8), (8, 38, 20, 8), (2, 26, 32, 4), (4, 26, 20, 8), (4, 25, 20, 8), (1, 26, 32, 4), (1, 38, 32, 4), (1, 33, 96, 4), (2, 33, 64, 8), (4, 33, 36, 8),
                                (1, 20, 96, 4), (4, 28, 36, 8)):
         assert _tiles(n(most), keep=keep, G=G, hkv=hkv) == 1 and _tiles(n(most + 1), keep=keep, G=G, hkv=hkv) > 1, (G, keep)
         # without a longest length one sequence of several has four fifths of the tiles; with one, it has those and one more at a seam
@@ -325,11 +325,14 @@ def test_a_block_per_tile_only_where_it_was_measured_faster():
     assert _tiles((64 * 50, 64 * 36), keep=33, G=1, hkv=8) == 1 and _tiles((64 * 50, 64 * 37), keep=33, G=1, hkv=8) == 4
     assert _tiles((64 * 30, 64 * 32), keep=33, G=4, hkv=8, max_seqlen=2048) == 1 and _tiles((64 * 30, 64 * 33), keep=33, G=4, hkv=8, max_seqlen=2048) == 4
     # short sequences are one block of four tiles, with appended rows two
-    assert _tiles((239,), keep=64) == 4 and _tiles((240,), keep=64) == 1 and _tiles((239,), True, keep=64, tail_capacity=64) == 1
-    assert _tiles((0, 479), keep=33) == 4 and _tiles((0, 480), keep=33) == 1
-    # short rows with kernels of their own and one query head, those of 26 with eight, eight query heads with rows of any length: never
-    for keep, G in ((25, 1), (26, 1), (38, 1), (25, 8), (26, 8), (33, 8), (64, 16)):
-        assert _tiles((512,), keep=keep, G=G) == 4 and _tiles((512,), True, keep=keep, G=G, tail_capacity=64) == 4, (keep, G)
+    for keep, G, tokens in ((64, 1, 240), (64, 2, 200), (64, 4, 200), (64, 8, 200), (33, 4, 200), (39, 1, 200), (26, 2, 240), (38, 4, 240)):
+        assert _tiles((tokens - 1,), keep=keep, G=G) == 4 and _tiles((tokens,), keep=keep, G=G) == 1, (keep, G)
+        assert _tiles((0, 2 * tokens - 1), keep=keep, G=G) == 4 and _tiles((0, 2 * tokens), keep=keep, G=G) == 1, (keep, G)
+        assert _tiles((tokens - 1,), True, keep=keep, G=G, tail_capacity=64) == 1, (keep, G)
+    assert _tiles((1,), keep=40, G=1) == 1 and _tiles((190,) * 9, keep=40, G=1) == 4 and _tiles((240,) * 9, keep=40, G=1) == 1      # (256 blocks)
+    # short rows with kernels of their own and eight query heads, one with int8 codes of 26, eight with rows of any length: never
+    for keep, G, pack in ((25, 8, 0), (26, 8, 0), (26, 1, spark.PACK_INT8), (33, 8, 0), (64, 16, 0)):
+        assert _tiles((512,), keep=keep, G=G, pack_dtype=pack) == 4 and _tiles((512,), True, keep=keep, G=G, pack_dtype=pack, tail_capacity=64) == 4, (keep, G)
     assert _tiles((512,), keep=25, G=1, pack_dtype=spark.PACK_INT8) == 1       # (no kernel of its own)
     # one long conversation among short ones
     assert _tiles((5000, 100, 100, 100), keep=64) == 4 and _tiles((40000,) + (200,) * 21, keep=64, hkv=1) == 4

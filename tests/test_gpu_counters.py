@@ -69,7 +69,8 @@ def test_a_workspace_with_room_for_counters_side_by_side_only(batch, hkv, G, n_s
     for i, out in enumerate(outs):
         err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
         assert err.max() <= 1e-2 and err.mean() <= 1e-3, (i, err.max())
-        if i % 4 < 3:
+        # (with all the room a short call takes a block per tile: other last bits)
+        if i % 4 < (2 if spark.call_form(desc, spark.CALL_DECODE_TILES) == 1 else 3):
             assert torch.equal(out, outs[0]), i
     with pytest.raises(spark.SparkError):
         run(desc, narrow // 4 - 1)
